@@ -1,0 +1,607 @@
+// Attention over the selected rows where nothing is applied to the reconstructed rows (no rotation), bf16 products:
+//   out_h = softmax(scale K^_g q_h)^T V^_g,  K^_g = A^K[I_g,:] B^K_{l,g},  V^_g = A^V[I_g,:] B^V_{l,g}   (Sec. 3.2, Eq. 3)
+// regrouped so that B_l meets one vector per query head instead of every selected row:
+//   z_h = scale A^K[I_g,:] (B^K_{l,g} q_h),   U_h = w_h^T A^V[I_g,:],   out_h = U_h B^V_{l,g}.
+//
+// What bounds it: the gather of the rows.  Multiplying every row with B^K and B^V (the form that rows which are rotated
+// still need, gather_attend_mfma.hip) takes 272 matrix instructions of 32 x 32 x 16 per 32 rows at ranks 512 and streams
+// both B through LDS behind a barrier per 128 ranks; regrouped it is 32 + 16 of that size, no operand is shared by the
+// wavefronts but the 32 KiB of projected queries, and the main loop has no barrier.
+//
+// A wavefront owns 32 rows of a tile from the first load to its own sums U.  Rows arrive line-wise (16 lanes x 16 B of
+// four rows per request, 128 ranks of the 32 rows = one group = 8 requests), RG groups ahead in registers, and turn into
+// operands in a wavefront-private 8 KiB LDS tile:
+//   logits  v_mfma_f32_32x32x16_bf16, rows of A^K x projected queries; the 32 columns are 16 head slots twice, the high
+//           part of the projected query and its remainder, so that the logits carry single-precision accuracy;
+//   sums    v_mfma_f32_16x16x32_bf16, softmax weights [16 slots x 32 rows] x rows of A^V; the rows are the summed index
+//           here, so the operand comes out of the tile through the transposing LDS read (4 rows x 16 ranks a time).
+// The 16 result lanes of a logit tile hold, slot by slot, exactly the rows that the weights operand wants in that lane, so
+// logits become weights without leaving the registers (online softmax, U rescaled once per tile).  At the end the wavefronts' U are added in LDS,
+// split into a bf16 high part and remainder (again 16 + 16 rows of one operand) and multiplied with B^V.
+#include "xkv_common.h"
+
+#include "prepass.h"
+
+namespace xkv {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4_t;
+typedef __attribute__((ext_vector_type(8))) float f32x8_t;
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((ext_vector_type(8))) short s16x8_t;
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+// Projected queries of the heads of one KV head as operand fragments (see project_z_block), 4 wavefronts per block, then
+// B^V_l and, for the rotated form, B^K_l and the query fragments: what the selected-row kernels need of q and B_l.
+__global__ __launch_bounds__(256) void gather_prepare_kernel(PackArgs a) { gather_prepare_block(a, (int)blockIdx.x); }
+
+hipError_t launch_gather_prepare(const PackArgs &a, hipStream_t st)
+{
+    const int blocks = a.blocks();
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(gather_prepare_kernel, dim3(blocks), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+constexpr int kOutPitch = 132;  // floats per row of the last product's result
+// The wavefronts' sums U are merged PG groups of 128 ranks at a time, [wavefront][rank][head slots, whole quads] floats: a
+// lane of U holds a quad of slots of one rank.
+__host__ __device__ inline int slab_quads(int n_rep) { return (n_rep + 3) / 4; }
+__host__ __device__ inline int slab_bytes(int waves, int n_rep, int pg) { return waves * pg * 128 * slab_quads(n_rep) * 16; }
+__host__ __device__ inline int slab_groups(int waves, int n_rep, int ngv, int occ)  // (two workgroups share the LDS at occ 2)
+{
+    int pg = ngv;
+    while (pg > 1 && slab_bytes(waves, n_rep, pg) > (occ == 2 ? 44 : 100) * 1024) --pg;
+    return pg;
+}
+
+// A group of quantised rows: 128 ranks = 4 quantisation groups of 32 rows, lane = (row lane / 4, group lane % 4) of 16 rows
+// a request; 4-bit rows bring the group's (step, lo) word along, 3-bit pieces hold it.
+template <int QB> struct RowGroup {
+    static constexpr int N = QB == 0 ? 8 : 2;  // 16-byte requests per group and lane
+    u32x4_t piece[N];
+    uint32_t param[QB == 4 ? 2 : 1];
+};
+
+// 16 bytes of codes (32 ranks) and the group's (step, lo) -> 32 bf16 values, four 16-byte pieces in rank order.  A code c
+// or-ed onto 0x4300 is the bf16 number 128 + c, so x^ = step (128 + c) + (lo - 128 step) is one multiply-add per element.
+template <int QB> __device__ __forceinline__ u32x4_t dequant_word(uint32_t codes, float step, float lo2)
+{
+    constexpr uint32_t kMask = QB == 4 ? 0x000F000Fu : 0x00070007u;
+    f32x8_t x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t pr = ((codes >> (QB * i)) & kMask) | 0x43004300u;
+        x[2 * i] = fmaf(step, __uint_as_float(pr << 16), lo2);
+        x[2 * i + 1] = fmaf(step, __uint_as_float(pr & 0xFFFF0000u), lo2);
+    }
+    return __builtin_bit_cast(u32x4_t, __builtin_convertvector(x, bf16x8_t));
+}
+
+// The group into the wavefront's tile.  For the logits row t sits at 272 t (a lane reads 16 bytes of its own row: 16 rows
+// then cover every bank once).  For the sums a transposing read takes 32 bytes of the four rows 4 q + i of each of the
+// quarters q of the wavefront; row t = 16 a + 8 b + 4 c + d goes to place 16 b + 8 c + 4 a + d at a pitch of 288, which
+// puts the rows of a read next to each other and their pieces on different banks.  Every access is one lane register
+// plus a constant.
+constexpr int kTileK = 272, kTileV = 288, kTileBytes = 32 * kTileV;
+template <int QB, bool IS_K>
+__device__ __forceinline__ void group_to_tile(const RowGroup<QB> &g, unsigned char *At, int lane)
+{
+    constexpr int PITCH = IS_K ? kTileK : kTileV;
+    if constexpr (QB == 0) {
+        unsigned char *dst = At + (lane >> 4) * PITCH + 16 * (lane & 15);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int place = IS_K ? 4 * j : 16 * ((j >> 1) & 1) + 8 * (j & 1) + 4 * (j >> 2);
+            *reinterpret_cast<u32x4_t *>(dst + place * PITCH) = g.piece[j];
+        }
+    } else {
+        const int r = lane >> 2, place = IS_K ? r : 16 * (r >> 3) + 8 * ((r >> 2) & 1) + (r & 3);
+        unsigned char *dst = At + place * PITCH + 64 * (lane & 3);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const u32x4_t w = g.piece[i];
+            uint32_t codes[4], par;
+            if constexpr (QB == 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) codes[u] = w[u];
+                par = g.param[i];
+            } else {  // 96 bits of codes, four units of 24, then (step, lo)
+                const uint32_t u4[4] = {w[0], (w[0] >> 24) | (w[1] << 8), (w[1] >> 16) | (w[2] << 16), w[2] >> 8};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) codes[u] = (u4[u] & 0xFFFu) | ((u4[u] << 4) & 0x0FFF0000u);
+                par = w[3];
+            }
+            const float step = __uint_as_float(par << 16), lo = __uint_as_float(par & 0xFFFF0000u);
+            const float lo2 = fmaf(-128.0f, step, lo);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                *reinterpret_cast<u32x4_t *>(dst + (IS_K ? 16 : 4) * i * PITCH + 16 * u) = dequant_word<QB>(codes[u], step, lo2);
+        }
+    }
+}
+
+// Row (16 lanes) and half-wavefront exchanges on the vector ALU.  permlane16_swap(x, y) trades the odd rows of x for the
+// even rows of y: x' = (x0, y0, x2, y2), y' = (x1, y1, x3, y3); permlane32_swap does the same with the two halves.
+__device__ __forceinline__ float add_row_pairs(float x, float y)  // lanes of row 0: x0 + x1, of row 1: y0 + y1, ...
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float max_over_rows(float x)  // over the four lanes with the same number in their row
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float a = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+
+// WAVES wavefronts of 32 rows each; NGV groups of 128 ranks of A^V (U has NGV * 32 registers); RG groups in flight (a
+// divisor of NGV).  QB: 0 = rows of A in bf16, 4 or 3 = quantised rows.
+template <int WAVES, int NGV, int RG, int QB, int OCC>
+__global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
+    const void *__restrict__ A_k, const void *__restrict__ A_v, const u32x4_t *__restrict__ Pz, size_t pz_head_stride,
+    const u32x4_t *__restrict__ pack_v, size_t pack_seq_stride, size_t pack_head_stride, const int32_t *__restrict__ idx,
+    const int32_t *__restrict__ counts, float *__restrict__ part_o, float *__restrict__ part_ml, int L, int r_k, int r_v,
+    int H_kv, int H_q, int k, int splits, int chunk, int FZ, float scale)
+{
+    static_assert(NGV % RG == 0, "a tile's groups of A^V start at ring entry 0");
+    constexpr int TILE = WAVES * 32;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    // workgroup id -> (KV head fastest: the heads of a sequence gather from the same rows' lines), split, sequence
+    const int g = blockIdx.x % H_kv, split = (blockIdx.x / H_kv) % splits, b = blockIdx.x / (H_kv * splits);
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int n = lane & 31, hf = lane >> 5, l16 = lane & 15, q4 = lane >> 4;
+    const int n_rep = H_q / H_kv;
+
+    const int NGK = FZ / 8, nkp = (NGK + RG - 1) / RG * RG;  // groups of A^K, and padded to whole rings
+    u32x4_t *Pl = reinterpret_cast<u32x4_t *>(smem_raw);     // [nkp][512], zero for the padding
+    unsigned char *At = smem_raw + (size_t)nkp * 8192 + w * kTileBytes;
+    int *toks = reinterpret_cast<int *>(smem_raw + (size_t)nkp * 8192 + WAVES * kTileBytes) + w * (chunk / WAVES + 32);  // this wavefront's ids, tile by tile, then 32 times the first
+
+    int k_eff = k;  // with `counts`, only the first counts[sequence][head] ids of a row are attended over
+    if (counts) {
+        const int cn = counts[b * H_kv + g];
+        k_eff = cn < k ? (cn > 0 ? cn : 0) : k;
+    }
+    const int m_begin = split * chunk;
+    const int m_end_raw = m_begin + chunk < k_eff ? m_begin + chunk : k_eff;
+    const int m_end = m_end_raw > m_begin ? m_end_raw : m_begin;
+    const int n_tiles = __builtin_amdgcn_readfirstlane((m_end - m_begin + TILE - 1) / TILE);
+
+    // ids of this wavefront's rows (clamped into [0, L); rows past the end repeat the last one), then the projected
+    // queries: requested before the ids are waited for
+    const int32_t *ids = idx + ((size_t)b * H_kv + g) * k;
+    const int n_ids = n_tiles * 32;
+    int first_id[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + 64 * u;
+        int m = m_begin + (i >> 5) * TILE + w * 32 + (i & 31);
+        m = m < m_end ? m : (m_end > m_begin ? m_end - 1 : 0);
+        first_id[u] = ids[m];
+    }
+    const u32x4_t *psrc = Pz + ((size_t)b * H_kv + g) * pz_head_stride;
+    const int p_total = FZ * 64;  // a multiple of 512
+    constexpr int PN = 8;
+    u32x4_t ptmp[PN];
+#pragma unroll
+    for (int j = 0; j < PN; ++j) {
+        const int e = tid + j * WAVES * 64;
+        ptmp[j] = psrc[e < p_total ? e : 0];
+    }
+    asm volatile("" : "+v"(first_id[0]), "+v"(first_id[1]));  // (keeps both loads ahead of the others, outside the branches)
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = lane + 64 * u, t = first_id[u];
+        const int tc = t < 0 ? 0 : (t >= L ? L - 1 : t);
+        if (i < n_ids) toks[i] = tc;
+        if (u == 0 && lane < 32) toks[chunk / WAVES + lane] = __builtin_amdgcn_readfirstlane(tc);
+    }
+    for (int i = lane + 128; i < n_ids; i += 64) {
+        int m = m_begin + (i >> 5) * TILE + w * 32 + (i & 31);
+        m = m < m_end ? m : m_end - 1;
+        const int t = ids[m];
+        toks[i] = t < 0 ? 0 : (t >= L ? L - 1 : t);
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- the sequence of groups of this wavefront: per tile all groups of A^K (padded to whole rings), then those of A^V.
+    // (it_*) walks RG groups ahead of the group being multiplied; groups that do not exist (padding, past the end) are
+    // requested from one row, a cache hit.
+    // (a sequence has fewer than 2^24 rows and less than 4 GiB of them: byte offsets are 32-bit)
+    const uint32_t pitch_k = QB == 0 ? (uint32_t)r_k * 2 : (uint32_t)quant_row_bytes(r_k, QB);
+    const uint32_t pitch_v = QB == 0 ? (uint32_t)r_v * 2 : (uint32_t)quant_row_bytes(r_v, QB);
+    const unsigned char *Ak = reinterpret_cast<const unsigned char *>(A_k) + (size_t)b * L * pitch_k;
+    const unsigned char *Av = reinterpret_cast<const unsigned char *>(A_v) + (size_t)b * L * pitch_v;
+    int it_i = 0, it_tile = 0;
+    auto advance = [&]() __attribute__((always_inline)) {
+        if (++it_i == nkp + NGV) {
+            it_i = 0;
+            ++it_tile;
+        }
+    };
+    // what a group's requests need: the row base, the row pitch, the byte within the row (lane's piece, and its (step, lo)
+    // word for 4-bit rows; pieces beyond the row are replaced by the first: they meet zero operands) and the row ids
+    struct Request {
+        const unsigned char *base;
+        uint32_t pitch, off, par;
+        const int *rows;  // this lane's first row id in LDS
+    };
+    auto request_of = [&]() __attribute__((always_inline)) {
+        Request q;
+        const bool is_k = it_i < nkp, real = it_tile < n_tiles && (it_i < NGK || it_i >= nkp);
+        const int r = is_k ? r_k : r_v, it_g = is_k ? it_i : it_i - nkp;
+        q.base = is_k ? Ak : Av;
+        q.pitch = is_k ? pitch_k : pitch_v;
+        if constexpr (QB == 0) {
+            const int pc = 16 * it_g + (lane & 15);
+            q.off = 16 * (pc < (r >> 3) ? pc : 0);
+            q.par = 0;
+        } else {
+            const int gq = 4 * it_g + (lane & 3);
+            const int gc = gq < (r >> 5) ? gq : 0;
+            q.off = 16 * gc;
+            q.par = (r >> 1) + 4 * gc;
+        }
+        q.rows = toks + (real ? it_tile * 32 : chunk / WAVES) + (QB == 0 ? lane >> 4 : lane >> 2);
+        return q;
+    };
+    constexpr int NF = RowGroup<QB>::N, HS = OCC == 2 ? 2 : 4;  // requests per group; steps whose operands are read together
+    RowGroup<QB> ring[RG];
+    // the rows of the requests [J0, J0 + N) of a group (read together, ahead of the requests), and request j
+    auto rows_of = [&](const Request &q, int (&tk)[NF], int j0, int jn) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j)
+            if (j >= j0 && j < jn) tk[j] = q.rows[(QB == 0 ? 4 : 16) * j];
+    };
+    auto fetch = [&](RowGroup<QB> &e, const Request &q, const int (&tk)[NF], int j) __attribute__((always_inline)) {
+        const uint32_t row = __umul24((uint32_t)tk[j], q.pitch);
+        e.piece[j] = *reinterpret_cast<const u32x4_t *>(q.base + (row + q.off));
+        if constexpr (QB == 4) e.param[j] = *reinterpret_cast<const uint32_t *>(q.base + (row + q.par));
+    };
+#pragma unroll
+    for (int s = 0; s < RG; ++s) {
+        const Request q = request_of();
+        advance();
+        int tk[NF];
+        rows_of(q, tk, 0, NF);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) fetch(ring[s], q, tk, j);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // projected queries into LDS
+#pragma unroll
+    for (int j = 0; j < PN; ++j) {
+        const int e = tid + j * WAVES * 64;
+        if (e < nkp * 512) Pl[e] = e < p_total ? ptmp[j] : u32x4_t{0u, 0u, 0u, 0u};
+    }
+    for (int e = tid + PN * WAVES * 64; e < nkp * 512; e += WAVES * 64)
+        Pl[e] = e < p_total ? psrc[e] : u32x4_t{0u, 0u, 0u, 0u};
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+
+    f32x4_t U[NGV * 8];
+#pragma unroll
+    for (int i = 0; i < NGV * 8; ++i) U[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float m_run = -INFINITY, l_run = 0.0f;  // of slot lane % 16 (the sum: this lane's share)
+    const unsigned char *krd = At + n * kTileK + 16 * hf, *vrd = At + (4 * q4 + (l16 >> 2)) * kTileV + 8 * (l16 & 3);
+
+    for (int tile = 0; tile < n_tiles; ++tile) {
+        // ---- logits
+        f32x16_t Z;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) Z[v] = 0.0f;
+        for (int i = 0; i < nkp; i += RG) {
+#pragma unroll
+            for (int s = 0; s < RG; ++s) {
+                const Request q = request_of();
+                advance();
+                int tk[NF];
+                if constexpr (OCC == 1) rows_of(q, tk, 0, NF);  // (two wavefronts per SIMD: registers are short instead)
+                group_to_tile<QB, true>(ring[s], At, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                const u32x4_t *pf = Pl + (i + s) * 512 + lane;
+                // operands of HS steps are read together, the requests go out between the reads and the products
+#pragma unroll
+                for (int h4 = 0; h4 < 8; h4 += HS) {
+                    u32x4_t a4[HS], p4[HS];
+                    if constexpr (OCC == 2) rows_of(q, tk, h4, h4 + HS);
+#pragma unroll
+                    for (int fl = 0; fl < HS; ++fl) {
+                        a4[fl] = *reinterpret_cast<const u32x4_t *>(krd + 32 * (h4 + fl));
+                        p4[fl] = pf[(h4 + fl) * 64];
+                    }
+#pragma unroll
+                    for (int fl = h4; fl < h4 + HS; ++fl)
+                        if (fl < NF) fetch(ring[s], q, tk, fl);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int fl = 0; fl < HS; ++fl)
+                        Z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a4[fl]),
+                                                                    __builtin_bit_cast(bf16x8_t, p4[fl]), Z, 0, 0, 0);
+                    if (OCC == 2 || h4 + HS == 8) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        // lane (slot column n, hf), register v = row 8 (v / 4) + 4 hf + v % 4; columns 16 .. 31 are the remainders of the
+        // projected queries.  Of the two lanes of a slot, the first keeps registers 0 .. 7, the second 8 .. 15.
+        const int base = m_begin + tile * TILE + w * 32;
+        float z8[8], m_loc = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float z = add_row_pairs(Z[e], Z[8 + e]);
+            const int t = base + (n & 16) + 4 * hf + 8 * (e / 4) + e % 4;
+            z8[e] = t < m_end ? scale * z : -INFINITY;
+            m_loc = fmaxf(m_loc, z8[e]);
+        }
+        // ---- logits -> weights (bf16, as the operand); rescaling of U and of the running sum
+        const float m_new = fmaxf(m_run, max_over_rows(m_loc));
+        const float alpha = (m_new == -INFINITY) ? 1.0f : __expf(m_run - m_new);
+        f32x8_t wv;
+        float l_add = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            wv[e] = z8[e] == -INFINITY ? 0.0f : __expf(z8[e] - m_new);
+            l_add += wv[e];
+        }
+        const bf16x8_t wf = __builtin_convertvector(wv, bf16x8_t);
+        l_run = l_run * alpha + l_add;
+        m_run = m_new;
+        if (tile > 0) {  // rows of U are slots 4 (lane / 16) + v
+            if (lane < 16) reinterpret_cast<float *>(At)[lane] = alpha;  // (the tile is between two groups)
+            const f32x4_t a = reinterpret_cast<const f32x4_t *>(At)[q4];
+#pragma unroll
+            for (int i = 0; i < NGV * 8; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) U[i][v] *= a[v];
+        }
+        // ---- U += W A^V[rows]
+#pragma unroll
+        for (int gv = 0; gv < NGV; ++gv) {
+            const Request q = request_of();
+            advance();
+            int tk[NF];
+            if constexpr (OCC == 1) rows_of(q, tk, 0, NF);
+            group_to_tile<QB, false>(ring[gv % RG], At, lane);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h4 = 0; h4 < 8; h4 += HS) {
+                s16x4_t v4[HS][2];
+                if constexpr (OCC == 2) rows_of(q, tk, h4, h4 + HS);
+#pragma unroll
+                for (int j = 0; j < HS; ++j) {
+                    const unsigned char *p = vrd + 32 * (h4 + j);
+                    v4[j][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)p);
+                    v4[j][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(p + 16 * kTileV));
+                }
+#pragma unroll
+                for (int j = h4; j < h4 + HS; ++j)
+                    if (j < NF) fetch(ring[gv % RG], q, tk, j);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < HS; ++j) {
+                    const s16x8_t v8 = __builtin_shufflevector(v4[j][0], v4[j][1], 0, 1, 2, 3, 4, 5, 6, 7);
+                    U[gv * 8 + h4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(bf16x8_t, v8),
+                                                                                U[gv * 8 + h4 + j], 0, 0, 0);
+                }
+                if (OCC == 2 || h4 + HS == 8) __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+
+    // ---- merge of the wavefronts and the product with B^V.  The rows of B^V that this wavefront multiplies are requested
+    // first: fragments of 16 ranks x its 32 channels.
+    constexpr int KH = WAVES == 8 ? 2 : 1, NDB = WAVES >= 4 ? 1 : 4 / WAVES, NFB = NGV * 8 / KH;
+    const u32x4_t *pv = pack_v + (size_t)b * pack_seq_stride + (size_t)g * pack_head_stride + lane;
+    const int db0 = WAVES >= 4 ? (w & 3) : w * NDB, kh = WAVES == 8 ? w >> 2 : 0;
+    constexpr int NPF = NFB < 16 ? NFB : NGV == 6 || OCC == 2 ? 16 : NFB < 32 ? NFB : 32;  // fragments requested ahead of the merge
+    u32x4_t bv[NPF];
+#pragma unroll
+    for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)((kh * NFB + f) * 4 + db0) * 64];
+
+    const float l_a = l_run + __shfl_xor(l_run, 16, kWave), l_tot = l_a + __shfl_xor(l_a, 32, kWave);
+    const int PG = slab_groups(WAVES, n_rep, NGV, OCC), NQ = slab_quads(n_rep);
+    uint16_t *Uf = reinterpret_cast<uint16_t *>(smem_raw);                         // [NGV * 8][64][8]
+    float *ml = reinterpret_cast<float *>(smem_raw + NGV * 8 * 1024);               // [2][WAVES][16]
+    float *slab = ml + 2 * WAVES * 16;
+    __syncthreads();  // everybody is done with the operands
+    if (lane < 16) {
+        ml[w * 16 + lane] = m_run;
+        ml[(WAVES + w) * 16 + lane] = l_tot;
+    }
+    __syncthreads();
+    f32x4_t f4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int hh = 4 * q4 + v;
+        float M = -INFINITY;
+#pragma unroll
+        for (int ww = 0; ww < WAVES; ++ww) M = fmaxf(M, ml[ww * 16 + hh]);
+        const float mw = ml[w * 16 + hh];
+        f4[v] = mw == -INFINITY ? 0.0f : __expf(mw - M);
+    }
+    for (int g0 = 0; g0 < NGV; g0 += PG) {
+#pragma unroll
+        for (int gv = 0; gv < NGV; ++gv)
+            if (gv >= g0 && gv < g0 + PG && q4 < NQ) {
+                f32x4_t *dst = reinterpret_cast<f32x4_t *>(slab) + ((w * PG + gv - g0) * 128 + l16) * NQ + q4;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) dst[16 * j * NQ] = f4 * U[gv * 8 + j];
+            }
+        __syncthreads();
+        const int ng = NGV - g0 < PG ? NGV - g0 : PG;
+        for (int item = tid; item < NQ * ng * 32; item += WAVES * 64) {  // four ranks of four slots
+            const int hq = item % NQ, c = 4 * (item / NQ);
+            const f32x4_t *src = reinterpret_cast<const f32x4_t *>(slab) + c * NQ + hq;
+            f32x4_t sum[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = src[e * NQ];
+#pragma unroll
+            for (int ww = 1; ww < WAVES; ++ww)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] += src[(ww * PG * 128 + e) * NQ];
+            uint16_t *dst = Uf + (((g0 * 8 + (c >> 4)) * 64 + ((c >> 3) & 1) * 32 + 4 * hq) * 8 + (c & 7));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const f32x4_t x = f32x4_t{sum[0][v], sum[1][v], sum[2][v], sum[3][v]};
+                const bf16x4_t hi = __builtin_convertvector(x, bf16x4_t);
+                *reinterpret_cast<bf16x4_t *>(dst + v * 8) = hi;
+                *reinterpret_cast<bf16x4_t *>(dst + (16 + v) * 8) =
+                    __builtin_convertvector(x - __builtin_convertvector(hi, f32x4_t), bf16x4_t);
+            }
+        }
+        __syncthreads();
+    }
+    const u32x4_t *Uq = reinterpret_cast<const u32x4_t *>(Uf) + lane;
+    float *po = slab;  // [KH][16][kOutPitch]
+#pragma unroll
+    for (int dd = 0; dd < NDB; ++dd) {
+        if (dd > 0) {
+#pragma unroll
+            for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)((kh * NFB + f) * 4 + db0 + dd) * 64];
+        }
+        f32x16_t o;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+#pragma unroll
+        for (int f = 0; f < NPF; ++f)
+            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq[(kh * NFB + f) * 64]),
+                                                        __builtin_bit_cast(bf16x8_t, bv[f]), o, 0, 0, 0);
+#pragma unroll
+        for (int f = NPF; f < NFB; ++f)
+            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8_t, Uq[(kh * NFB + f) * 64]),
+                __builtin_bit_cast(bf16x8_t, pv[(size_t)((kh * NFB + f) * 4 + db0 + dd) * 64]), o, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 8; ++v)  // slot 8 (v / 4) + 4 hf + v % 4, its remainder's row eight registers on
+            po[(kh * 16 + 8 * (v / 4) + 4 * hf + (v % 4)) * kOutPitch + (db0 + dd) * 32 + n] = o[v] + o[v + 8];
+    }
+    __syncthreads();
+    for (int item = tid; item < n_rep * 128; item += WAVES * 64) {
+        const int hh = item >> 7, dim = item & 127;
+        float num = po[hh * kOutPitch + dim];
+        if constexpr (KH == 2) num += po[(16 + hh) * kOutPitch + dim];
+        const size_t slot = ((size_t)b * H_q + g * n_rep + hh) * splits + split;
+        part_o[slot * 128 + dim] = num;
+        if (dim == 0) {
+            float M = -INFINITY, den = 0.0f;
+#pragma unroll
+            for (int ww = 0; ww < WAVES; ++ww) M = fmaxf(M, ml[ww * 16 + hh]);
+#pragma unroll
+            for (int ww = 0; ww < WAVES; ++ww) {
+                const float mw = ml[ww * 16 + hh];
+                den += (mw == -INFINITY ? 0.0f : __expf(mw - M)) * ml[(WAVES + ww) * 16 + hh];
+            }
+            part_ml[slot * 2 + 0] = M;
+            part_ml[slot * 2 + 1] = den;
+        }
+    }
+}
+
+constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512;
+
+// Groups in flight per wavefront.
+static constexpr int absorb_rg(int ngv, int occ) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 ? 4 : 2; }
+
+static size_t absorb_lds(int waves, int ngv, int occ, int n_rep, int FZ, int chunk)
+{
+    const int rg = absorb_rg(ngv, occ);
+    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)waves * (kTileBytes + 128) + (size_t)chunk * 4;
+    const int slab = slab_bytes(waves, n_rep, slab_groups(waves, n_rep, ngv, occ)), out = 2 * 16 * kOutPitch * 4;
+    const size_t merge = (size_t)ngv * 8192 + (size_t)2 * waves * 16 * 4 + (size_t)(slab > out ? slab : out);
+    return main > merge ? main : merge;
+}
+
+// Groups of 128 ranks of A^V that a wavefront keeps sums for: 2, 3, 4 or 6 (0: more than the registers hold).
+static int absorb_ngv(int r_v)
+{
+    const int g = (r_v + 127) / 128;
+    return g <= 2 ? 2 : g <= 4 ? g : g <= 6 ? 6 : 0;
+}
+
+bool gather_absorb_shape_ok(const xkv_shape &s)
+{
+    const int FZ = (s.r_k / 16 + 7) / 8 * 8;
+    const long long widest = s.r_k > s.r_v ? s.r_k : s.r_v;
+    return s.L < (1 << 24) && s.L * widest * 2 < (1LL << 32) && absorb_ngv(s.r_v) != 0 && absorb_lds(4, 4, 1, 16, FZ, 8192) <= kAbsorbLdsMax && absorb_lds(4, 6, 1, 16, FZ, 8192) <= kAbsorbLdsMax;
+}
+
+void gather_absorb_plan(const xkv_shape &s, Plan &p)
+{
+    // Tiles are 128 rows.  Where every compute unit gets more than one (and U fits 256 registers a lane), two workgroups
+    // share a compute unit, so that the one streams while the other merges; else one with twice the registers, all of
+    // them for requests in flight.  About 1024 workgroups, two rounds of two: at 16 sequences x 8 heads x 4096 rows of
+    // ranks 512 a pass of four layers took 1489 us (512 of twice the length 1492, 2048 of half of it 1512, one workgroup of
+    // eight wavefronts per compute unit 1513: its wavefronts finish up to 12 us apart).
+    const int tile = 128, rows = p.rows > 0 ? p.rows : 1;
+    const int tiles = (s.k + tile - 1) / tile;
+    p.ab_occ = absorb_ngv(s.r_v) <= 4 && (long long)rows * tiles > 256 ? 2 : 1;
+    int splits = ((p.ab_occ == 2 ? 1024 : 256) + rows - 1) / rows;
+    splits = splits > tiles ? tiles : splits;
+    if (splits < (s.k + 4095) / 4096) splits = (s.k + 4095) / 4096;
+    if (splits > p.max_splits) splits = p.max_splits;
+    p.ab_chunk = (tiles + splits - 1) / splits * tile;
+    p.ab_splits = (s.k + p.ab_chunk - 1) / p.ab_chunk;
+}
+
+hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
+                                const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,
+                                float *part_ml, int qbits, hipStream_t st)
+{
+    const size_t per_head = (size_t)(pa.F8k + pa.F8v) * 256;  // pieces of 16 B
+    const u32x4_t *pv = (B_packed ? (const u32x4_t *)B_packed + (size_t)layer * s.H_kv * per_head : (const u32x4_t *)pa.pack) +
+                        (size_t)pa.F8k * 256;
+    const size_t seq_stride = (B_packed ? (size_t)s.G : 1) * s.H_kv * per_head;
+    const int ngv = absorb_ngv(s.r_v);
+    const size_t lds = absorb_lds(4, ngv, p.ab_occ, p.n_rep, pa.FZ, p.ab_chunk);
+    if (ngv == 0 || lds > kAbsorbLdsMax || p.ab_splits > p.max_splits) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((long long)p.ab_splits * s.H_kv * s.batch));
+#define XKV_AB(NV, OC, QB)                                                                                              \
+    do {                                                                                                                \
+        static DynamicLdsOnce attr;                                                                                     \
+        constexpr int RG = absorb_rg(NV, OC);                                                                           \
+        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<4, NV, RG, QB, OC>, kAbsorbLdsMax);         \
+        if (e != hipSuccess) return e;                                                                                  \
+        profile_begin(1, st);                                                                                           \
+        hipLaunchKernelGGL((gather_absorb_kernel<4, NV, RG, QB, OC>), grid, dim3(256), lds, st, A_k, A_v,               \
+                           (const u32x4_t *)pa.Pz, pa.z_stride / 8, pv, seq_stride, per_head, idx, counts, part_o,      \
+                           part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.ab_splits, p.ab_chunk, pa.FZ, p.scale);    \
+        profile_end(1, st);                                                                                             \
+    } while (0)
+#define XKV_AB_Q(NV, OC)       \
+    do {                       \
+        if (qbits == 0)        \
+            XKV_AB(NV, OC, 0); \
+        else if (qbits == 4)   \
+            XKV_AB(NV, OC, 4); \
+        else                   \
+            XKV_AB(NV, OC, 3); \
+    } while (0)
+    if (p.ab_occ == 2) {
+        if (ngv == 2)
+            XKV_AB_Q(2, 2);
+        else if (ngv == 3)
+            XKV_AB_Q(3, 2);
+        else
+            XKV_AB_Q(4, 2);
+    } else {
+        if (ngv == 2)
+            XKV_AB_Q(2, 1);
+        else if (ngv == 3)
+            XKV_AB_Q(3, 1);
+        else if (ngv == 4)
+            XKV_AB_Q(4, 1);
+        else
+            XKV_AB_Q(6, 1);
+    }
+#undef XKV_AB_Q
+#undef XKV_AB
+    return hipGetLastError();
+}
+
+}  // namespace xkv

@@ -33,15 +33,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 constexpr int kMaxChunkTokens = 4096;  // selected tokens per workgroup (their ids sit in LDS)
 constexpr int kGroup = 8;  // fragments (of 16 ranks) per LDS stage: 8 x 4 KiB = 32 KiB, two stages
 
-// blocks [0, blocks_per_head) of a (sequence, KV head) pack B, the next kPackQBlocks the Q^T fragments
-__global__ __launch_bounds__(256) void pack_b_kernel(PackArgs a)
-{
-    if ((int)blockIdx.x < a.blocks_per_head)
-        pack_b_block(a, blockIdx.x, blockIdx.y, blockIdx.z);
-    else if (a.pack_q)
-        pack_q_block(a, (int)blockIdx.x - a.blocks_per_head, blockIdx.y, blockIdx.z);
-}
-
 __device__ __forceinline__ bf16x8_t pack8(const f32x16_t &c, int j)
 {
     f32x8_t x;
@@ -623,9 +614,9 @@ size_t gather_attend_pack_bytes(const xkv_shape &s) { return q_pack_bytes(s) + l
 size_t gather_attend_group_pack_bytes(const xkv_shape &s) { return layer_pack_bytes(s) * (size_t)s.G; }
 
 PackArgs gather_attend_pack_args(const xkv_shape &s, int layer, const void *B_k, const void *B_v, const void *q,
-                                  void *pack_ws, bool with_b)
+                                  void *pack_ws, bool with_b, bool absorb)
 {
-    PackArgs a;
+    PackArgs a{};
     a.B_k = (const bf16_t *)B_k;
     a.B_v = (const bf16_t *)B_v;
     a.q = (const bf16_t *)q;
@@ -642,7 +633,14 @@ PackArgs gather_attend_pack_args(const xkv_shape &s, int layer, const void *B_k,
     a.batch = s.batch;
     a.dst_G = 1;
     a.dst_layer = 0;
-    a.blocks_per_head = with_b ? ((a.F8k + a.F8v) * 64 + 255) / 256 : 0;
+    a.FZ = (s.r_k / 16 + 7) / 8 * 8;
+    // rows that are not rotated: only the values' part of B, and the projected queries in the place of the keys' part
+    a.fa0 = absorb ? a.F8k : 0;
+    a.Pz = reinterpret_cast<bf16_t *>(a.pack);
+    a.z_stride = (size_t)(a.F8k + a.F8v) * 4 * 64 * 8;
+    a.blocks_per_head = with_b ? ((a.F8k + a.F8v - a.fa0) * 64 + 255) / 256 : 0;
+    a.blocks_q = absorb ? 0 : kPackQBlocks;
+    a.blocks_z = absorb ? (a.FZ / 2 + 3) / 4 : 0;
     return a;
 }
 
@@ -650,13 +648,12 @@ PackArgs gather_attend_pack_args(const xkv_shape &s, int layer, const void *B_k,
 hipError_t launch_pack_group(const xkv_shape &s, const void *B_k, const void *B_v, void *packed, hipStream_t st)
 {
     for (int layer = 0; layer < s.G; ++layer) {
-        PackArgs a = gather_attend_pack_args(s, layer, B_k, B_v, nullptr, nullptr, true);
+        PackArgs a = gather_attend_pack_args(s, layer, B_k, B_v, nullptr, nullptr, true, false);
         a.pack = (pack_u32x4_t *)packed;
-        a.pack_q = nullptr;
+        a.blocks_q = 0;
         a.dst_G = s.G;
         a.dst_layer = layer;
-        hipLaunchKernelGGL(pack_b_kernel, dim3(a.blocks_per_head, s.H_kv, s.batch), dim3(256), 0, st, a);
-        const hipError_t e = hipGetLastError();
+        const hipError_t e = launch_gather_prepare(a, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -667,6 +664,11 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
                                      void *pack_ws, const void *B_packed, bool packed, float *part_o, float *part_ml,
                                      hipStream_t st, const int32_t *counts, float rope_theta, int qbits)
 {
+    const bool absorb = gather_uses_absorb(p, rope_theta);
+    const PackArgs pa = gather_attend_pack_args(s, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, absorb);
+    hipError_t e = hipSuccess;
+    if (!packed && (e = launch_gather_prepare(pa, st)) != hipSuccess) return e;
+    if (absorb) return launch_gather_absorb(s, p, pa, A_k, A_v, B_packed, layer, idx, counts, part_o, part_ml, qbits, st);
     RopeTable rope{};
     const bool use_rope = rope_theta > 0.0f;
     if (use_rope)
@@ -676,14 +678,7 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
             rope.f0[j] = (float)f;
             rope.f1[j] = (float)(f256 - std::floor(f256));
         }
-    const PackArgs pa = gather_attend_pack_args(s, layer, B_k, B_v, q, pack_ws, B_packed == nullptr);
     const int F8k = pa.F8k, F8v = pa.F8v;
-    hipError_t e = hipSuccess;
-    if (!packed) {
-        hipLaunchKernelGGL(pack_b_kernel, dim3(pa.blocks_per_head + kPackQBlocks, s.H_kv, s.batch), dim3(256), 0, st, pa);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     if (p.sr_chunk > kMaxChunkTokens) return hipErrorInvalidValue;
     // where the kernel finds B: this layer of the group's pack, or the one layer packed into the workspace
     const size_t per_head = (size_t)(F8k + F8v) * 256;  // pieces of 16 B

@@ -100,8 +100,8 @@ __device__ __forceinline__ void pack_b_block(const PackArgs &a, int blk, int g, 
     // one thread per (fragment f, half hf, dim block db, 4 columns): 8 rows x 8 B in, 4 lanes' 16 B pieces out
     const int d = H_kv * 128;
     const int item = blk * 256 + threadIdx.x;
-    if (item >= (F8k + F8v) * 64) return;
-    const int c4 = item & 7, db = (item >> 3) & 3, hf = (item >> 5) & 1, fa = item >> 6;
+    if (item >= (F8k + F8v - a.fa0) * 64) return;
+    const int c4 = item & 7, db = (item >> 3) & 3, hf = (item >> 5) & 1, fa = a.fa0 + (item >> 6);
     const bool is_v = fa >= F8k;
     const int f = is_v ? fa - F8k : fa;
     const int r = is_v ? r_v : r_k;
@@ -146,6 +146,58 @@ __device__ __forceinline__ void pack_q_block(const PackArgs &a, int blk, int g, 
         raw[e2] = n < n_rep ? *reinterpret_cast<const uint32_t *>(qh + dim) : 0u;
     }
     a.pack_q[((size_t)b * a.H_kv + g) * 512 + qi] = raw;
+}
+
+// The query heads of one KV head projected into the rank space, B^K_{l,g} q_h, as operand fragments of the selected-row
+// kernel: fragment f, lane hf * 32 + column, position e = rank 16 f + 8 hf + e; columns 0 .. 15 are the high bf16 parts of
+// the head slots, 16 .. 31 their remainders.  One wavefront per 32 ranks (the products are those of project_q_frag_block);
+// zero beyond r_k and beyond the real heads.
+__device__ __forceinline__ void project_z_block(const PackArgs &a, int blk, int g, int b)
+{
+    const int i0 = (blk * 4 + wave_id()) * 32;
+    if (i0 >= a.FZ * 16) return;
+    const int d = a.H_kv * 128, n_rep = a.H_q / a.H_kv, lane = lane_id(), n = lane & 31, hf = lane >> 5;
+    const int i = i0 + n;
+    pp_f32x16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    const pack_u32x4_t *brow = reinterpret_cast<const pack_u32x4_t *>(
+                                   a.B_k + (((size_t)b * a.G + a.layer) * a.r_k + (i < a.r_k ? i : a.r_k - 1)) * d + (size_t)g * 128) + hf;
+    // (q may lie on any 4-byte boundary)
+    const uint32_t *qrow = reinterpret_cast<const uint32_t *>(a.q + ((size_t)b * a.H_q + (size_t)g * n_rep + (n < n_rep ? n : 0)) * 128) + 4 * hf;
+    pack_u32x4_t ba[8], qa[8];
+#pragma unroll
+    for (int f = 0; f < 8; ++f) {
+        ba[f] = brow[2 * f];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qa[f][e] = qrow[8 * f + e];
+    }
+#pragma unroll
+    for (int f = 0; f < 8; ++f) {
+        const pack_u32x4_t zero = pack_u32x4_t{0u, 0u, 0u, 0u};
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pp_bf16x8_t, n < n_rep ? qa[f] : zero),
+                                                      __builtin_bit_cast(pp_bf16x8_t, i < a.r_k ? ba[f] : zero), acc, 0, 0, 0);
+    }
+    bf16_t *base = a.Pz + ((size_t)b * a.H_kv + g) * a.z_stride + ((size_t)(i / 16) * 64 + ((i % 16) / 8) * 32) * 8 + i % 8;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {  // register v: head slot 8 (v / 4) + 4 hf + v % 4 of rank i
+        const int hh = 8 * (v / 4) + 4 * hf + (v % 4);
+        const bf16_t hi = f32_to_bf16(acc[v]);
+        base[(size_t)hh * 8] = hi;
+        base[(size_t)(16 + hh) * 8] = f32_to_bf16(acc[v] - bf16_to_f32(hi));
+    }
+}
+
+// Block `blk` (linear over sequence, KV head, job) of everything the selected-row kernels need of q and B_l.
+__device__ __forceinline__ void gather_prepare_block(const PackArgs &a, int blk)
+{
+    const int per_head = a.per_head(), j = blk % per_head, g = (blk / per_head) % a.H_kv, b = blk / (per_head * a.H_kv);
+    if (j < a.blocks_per_head)
+        pack_b_block(a, j, g, b);
+    else if (j < a.blocks_per_head + a.blocks_q)
+        pack_q_block(a, j - a.blocks_per_head, g, b);
+    else
+        project_z_block(a, j - a.blocks_per_head - a.blocks_q, g, b);
 }
 
 }  // namespace xkv

@@ -72,6 +72,9 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
 
     p.max_splits = 4 * (p.sr_splits > p.dense_splits ? p.sr_splits : p.dense_splits);  // one partial per wavefront
 
+    p.absorb = p.ga_mfma && gather_absorb_shape_ok(s);
+    if (p.absorb) gather_absorb_plan(s, p);
+
     const size_t b = (size_t)(s.batch > 0 ? s.batch : 1);
     size_t off = 0;
     p.off_p = off;
@@ -174,8 +177,7 @@ xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer, const void *
     const bool mfma = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_v, pack_ws);
     hipError_t e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
                                         stream);
-    // the matrix-core kernel writes one partial per split, the general one one per wavefront
-    if (e == hipSuccess) e = launch_combine(*shape, mfma ? p.sr_splits : p.sr_splits * 4, part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, 0.0f), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -223,7 +225,7 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
     void *pack_ws = at<void>(workspace, p.off_bpack);
     PackArgs pa{};
     const bool want_pack = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_packed ? B_k : B_v, pack_ws);
-    if (want_pack) pa = gather_attend_pack_args(*shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr);
+    if (want_pack) pa = gather_attend_pack_args(*shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, p.absorb);
     bool packed = false;
     if (e == hipSuccess)
         e = launch_score_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S,
@@ -238,9 +240,8 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
     int n_tail = 0;
     float *tail_o = at<float>(workspace, p.off_tail_o), *tail_ml = at<float>(workspace, p.off_tail_ml);
     if (T > 0 && e == hipSuccess) e = launch_tail(*shape, p, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
-    // the matrix-core kernel writes one partial per split, the general one one per wavefront
     if (e == hipSuccess)
-        e = launch_combine(*shape, want_pack ? p.sr_splits : p.sr_splits * 4, part_o, part_ml, out, stream, n_tail,
+        e = launch_combine(*shape, gather_partials(p, want_pack, 0.0f), part_o, part_ml, out, stream, n_tail,
                            tail_o, tail_ml);
     return hip_status(e);
 }
@@ -546,7 +547,7 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
     const bool mfma = gather_attend_uses_mfma(pa, A_k, A_v, B_k, B_v, pack_ws);
     const bool gen_ident = score_stage_uses_mfma(lp.score_shape, landmarks, nullptr, q, at<void>(ws_s, ps.off_p), nullptr);
     PackArgs pk{};
-    if (mfma) pk = gather_attend_pack_args(lp.attend_shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr);
+    if (mfma) pk = gather_attend_pack_args(lp.attend_shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, gather_uses_absorb(pa, rope_theta));
     const bool fuse = gen_ident && mfma;
     bool packed = false;
     hipError_t e = gen_ident ? hipSuccess : launch_identity(*shape, ident, lp.score_shape.batch, stream);
@@ -569,7 +570,7 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
     float *tail_o = at<float>(workspace, pa.off_tail_o), *tail_ml = at<float>(workspace, pa.off_tail_ml);
     if (T > 0 && e == hipSuccess) e = launch_tail(*shape, pa, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, mfma ? pa.sr_splits : pa.sr_splits * 4, part_o, part_ml, out, stream, n_tail, tail_o,
+        e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta), part_o, part_ml, out, stream, n_tail, tail_o,
                            tail_ml);
     return hip_status(e);
 }
@@ -637,7 +638,7 @@ xkv_status xkv_gather_attend_q(const xkv_shape *shape, int32_t layer, const void
     float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
     hipError_t e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o,
                                         part_ml, stream, counts, rope_theta, bits);
-    if (e == hipSuccess) e = launch_combine(*shape, p.sr_splits, part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -661,7 +662,7 @@ xkv_status xkv_gather_attend_ex(const xkv_shape *shape, int32_t layer, const voi
     const bool mfma = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_v, pack_ws);
     hipError_t e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
                                         stream, counts, rope_theta);
-    if (e == hipSuccess) e = launch_combine(*shape, mfma ? p.sr_splits : p.sr_splits * 4, part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, rope_theta), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -855,7 +856,7 @@ xkv_status xkv_sr_decode_q4(const xkv_shape *shape, int32_t layer, const void *A
     int n_tail = 0;
     float *tail_o = at<float>(workspace, p.off_tail_o), *tail_ml = at<float>(workspace, p.off_tail_ml);
     if (T > 0 && e == hipSuccess) e = launch_tail(*shape, p, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
-    if (e == hipSuccess) e = launch_combine(*shape, p.sr_splits, part_o, part_ml, out, stream, n_tail, tail_o, tail_ml);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream, n_tail, tail_o, tail_ml);
     return hip_status(e);
 }
 

@@ -74,6 +74,8 @@ struct Plan {
     bool dense_mfma;   // shape fits the matrix-core dense kernel
     bool ga_mfma;      // shape fits the matrix-core gather-attend kernel
     int ga_waves;      // ... with this many wavefronts (32 selected tokens each) per workgroup
+    bool absorb;       // ... and the one that keeps B_l out of the main loop (rows that are not rotated)
+    int ab_occ, ab_splits, ab_chunk;  // its workgroups per compute unit, splits per (sequence, KV head), tokens per split
     bool topk_row;     // rows short enough for the one-launch, register-resident selection
     bool score_stream; // shape fits the long-stream score kernel
     bool score_hist;   // ... and that kernel can also histogram the top digit of its scores for the top-k stage
@@ -117,9 +119,15 @@ struct PackArgs {
     const bf16_t *B_k, *B_v, *q;
     pack_u32x4_t *pack;    // packed B, [batch][dst_G][H_kv][(F8k + F8v) * 256] pieces of 16 B
     pack_u32x4_t *pack_q;  // Q^T fragments, [batch][H_kv][512] pieces
-    int G, layer, r_k, r_v, H_kv, H_q, F8k, F8v, batch;
+    bf16_t *Pz;            // projected queries, z_stride elements from one (sequence, KV head) to the next
+    size_t z_stride;
+    int G, layer, r_k, r_v, H_kv, H_q, F8k, F8v, FZ, batch;
     int dst_G, dst_layer;  // the destination holds dst_G layers per sequence; this call fills dst_layer
-    int blocks_per_head;   // 256-item blocks per (sequence, KV head) for the B items (0: B is already packed)
+    int fa0;               // first fragment row of B to pack (F8k: only the values' part)
+    // 256-thread blocks per (sequence, KV head): packing of B (0: B is already packed), Q^T fragments, projected queries
+    int blocks_per_head, blocks_q, blocks_z;
+    __host__ __device__ int per_head() const { return blocks_per_head + blocks_q + blocks_z; }
+    int blocks() const { return per_head() * H_kv * batch; }
 };
 constexpr int kPackQBlocks = 2;  // 256-item blocks per (sequence, KV head) for the Q^T fragments
 
@@ -184,7 +192,21 @@ bool gather_attend_uses_mfma(const Plan &p, const void *A_k, const void *A_v, co
                              const void *pack_ws);
 // with_b: also pack B_l into the workspace (false when the caller supplies the group's packed B)
 PackArgs gather_attend_pack_args(const xkv_shape &s, int layer, const void *B_k, const void *B_v, const void *q,
-                                 void *pack_ws, bool with_b);
+                                 void *pack_ws, bool with_b, bool absorb);
+hipError_t launch_gather_prepare(const PackArgs &a, hipStream_t st);
+// Which of the two matrix-core kernels takes a call (rope_theta as below).
+inline bool gather_uses_absorb(const Plan &p, float rope_theta) { return p.absorb && !(rope_theta > 0.0f); }
+// Partials per query head that launch_gather_attend leaves for launch_combine: one per split, or (general kernel, mfma =
+// false) one per wavefront.
+inline int gather_partials(const Plan &p, bool mfma, float rope_theta)
+{
+    return !mfma ? p.sr_splits * 4 : gather_uses_absorb(p, rope_theta) ? p.ab_splits : p.sr_splits;
+}
+bool gather_absorb_shape_ok(const xkv_shape &s);
+void gather_absorb_plan(const xkv_shape &s, Plan &p);
+hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
+                                const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,
+                                float *part_ml, int qbits, hipStream_t st);
 bool gather_attend_mfma_shape_ok(const xkv_shape &s);
 int gather_attend_mfma_waves(const xkv_shape &s);
 size_t gather_attend_pack_bytes(const xkv_shape &s);        // Q^T fragments + one layer's packed B (workspace)

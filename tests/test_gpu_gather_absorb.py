@@ -1,0 +1,110 @@
+"""The selected-row kernel that keeps B_l out of its main loop (rows that are not rotated): stage call against the
+definition -- reconstruct the selected rows, attend over them -- in double precision, where the kernel's tiles, rank groups
+and merges have their edges.
+
+Bound, element by element.  The kernel rounds two things to bf16, whose 8 significant bits make a rounding error of at most
+2^-8 of the value: the weights w (the denominator is the sum of the unrounded ones) and the result.  So
+|got - ref| <= 2^-8 (|ref| + sum_j w_j |v_j| / sum_j w_j).  The projected queries and the sums over rows are split into two
+bf16 numbers (2^-17) and accumulated in single precision: 5 % on top, and 1e-6 of the largest value, cover these.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2503_18893_amd import synth
+from paper_2503_18893_amd import binding as xb
+
+pytestmark = pytest.mark.gpu
+
+
+def torch_mod():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def reference(A_k, A_v, B_k, B_v, q, rows, scale):
+    """out, and sum_j w_j |v_j| / sum_j w_j, both [H_q][d_h]."""
+    H_q, d_h = q.shape
+    n_rep = H_q // len(rows)
+    out, mag = np.zeros((H_q, d_h)), np.zeros((H_q, d_h))
+    for g, r in enumerate(rows):
+        if len(r) == 0:
+            continue
+        cols = slice(g * d_h, (g + 1) * d_h)
+        K, V = A_k[r] @ B_k[:, cols], A_v[r] @ B_v[:, cols]
+        for h in range(g * n_rep, (g + 1) * n_rep):
+            z = scale * (K @ q[h])
+            w = np.exp(z - z.max())
+            out[h], mag[h] = w @ V / w.sum(), w @ np.abs(V) / w.sum()
+    return out, mag
+
+
+CASES = [
+    # H_kv, n_rep, r_k, r_v, batch, k: one row; both sides of a wavefront's 32 and of a tile's 128 rows; one rank group
+    (1, 1, 16, 128, 1, 1), (2, 4, 128, 128, 1, 31), (1, 7, 256, 256, 2, 33), (2, 16, 256, 144, 1, 127), (3, 5, 144, 256, 1, 129),
+    # three, four, five and six groups of A^V, unequal ranks, ragged last groups
+    (2, 7, 384, 384, 1, 300), (1, 4, 512, 512, 1, 257), (1, 8, 384, 576, 1, 200), (2, 3, 640, 768, 1, 161), (1, 9, 528, 400, 1, 130),
+    # two workgroups per compute unit (more than 256 tiles): several tiles per workgroup, ragged last one
+    (8, 4, 512, 512, 5, 1000), (4, 7, 384, 384, 9, 1111), (8, 2, 128, 64, 6, 901), (8, 16, 256, 512, 5, 915),
+    # a tile per workgroup and more ranks of A^V than it keeps sums for: the rotated rows' kernel
+    (1, 4, 128, 800, 1, 200),
+]
+
+
+@pytest.mark.parametrize("bits", [0, 4, 3])
+@pytest.mark.parametrize("H_kv,n_rep,r_k,r_v,batch,k", CASES)
+def test_selected_rows_against_the_definition(H_kv, n_rep, r_k, r_v, batch, k, bits):
+    torch = torch_mod()
+    if bits and (r_k % 32 or r_v % 32):
+        pytest.skip("quantised rows come in groups of 32 ranks")
+    L = max(k + 5, 700)
+    w = synth.LLAMA_GROUP.with_(G=2, H_kv=H_kv, H_q=H_kv * n_rep, r_k=r_k, r_v=r_v, L=L, k=k, batch=batch, q_scale=3.0,
+                                a_scale=1.0, sigma_decay=0.0)
+    rng = np.random.default_rng(1000 * r_k + 10 * r_v + k + bits)
+    d = w.d
+    case = {"A_k": synth.to_storage(rng.standard_normal((batch, L, r_k)), "bf16"),
+            "A_v": synth.to_storage(rng.standard_normal((batch, L, r_v)), "bf16"),
+            "B_k": synth.to_storage(rng.standard_normal((batch, 2, r_k, d)) / np.sqrt(r_k), "bf16"),
+            "B_v": synth.to_storage(rng.standard_normal((batch, 2, r_v, d)) / np.sqrt(r_v), "bf16"),
+            "q": synth.to_storage(rng.standard_normal((2, batch, w.H_q, 128)), "bf16")}
+    dev = synth.to_device(case, "bf16")
+    idx = np.stack([np.stack([rng.choice(L, size=k, replace=False) for _ in range(H_kv)]) for _ in range(batch)]).astype(np.int32)
+    idx[:, :, -1] = L - 1
+    idx[:, :, k // 2] = idx[:, :, 0]          # ids need not be distinct
+    counts = rng.integers(0, k + 1, size=(batch, H_kv)).astype(np.int32)
+    counts[0, 0] = 0                          # a head without rows
+    shape, layer = xb.Shape.of(w), 1
+    ws = torch.full((xb.xkv_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    q = dev["q"][layer].contiguous()
+    out = torch.empty((batch, w.H_q, 128), dtype=torch.bfloat16, device="cuda")
+    A = {n: dev[n] for n in ("A_k", "A_v")}
+    hat = {n: [synth.storage_to_f64(case[n][b]) for b in range(batch)] for n in ("A_k", "A_v")}
+    if bits:
+        for n, r in (("A_k", r_k), ("A_v", r_v)):
+            A[n] = torch.empty((batch * L, xb.xkv_quantized_row_bytes(r, bits)), dtype=torch.uint8, device="cuda")
+            xb.xkv_quantize_rows(dev[n], batch * L, r, A[n], bits=bits)
+            for b in range(batch):
+                x = oracle.dequantize_rows(*oracle.quantize_rows(case[n][b], bits))
+                hat[n][b] = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(x.astype(np.float32))).astype(np.float64)
+    idx_d = torch.from_numpy(idx).cuda()
+    for use_counts in (False, True):
+        cnt = torch.from_numpy(counts).cuda() if use_counts else None
+        if bits:
+            xb.xkv_gather_attend_q(shape, layer, A["A_k"], A["A_v"], bits, dev["B_k"], dev["B_v"], q, idx_d, cnt, 0.0, out, ws)
+        else:
+            xb.xkv_gather_attend_ex(shape, layer, A["A_k"], A["A_v"], dev["B_k"], dev["B_v"], q, idx_d, cnt, 0.0, out, ws)
+        torch.cuda.synchronize()
+        got = synth.storage_to_f64(synth.to_host(out))
+        for b in range(batch):
+            rows = [idx[b, g, :(counts[b, g] if use_counts else k)] for g in range(H_kv)]
+            ref, mag = reference(hat["A_k"][b], hat["A_v"][b], synth.storage_to_f64(case["B_k"][b, layer]),
+                                 synth.storage_to_f64(case["B_v"][b, layer]), synth.storage_to_f64(case["q"][layer, b]), rows,
+                                 oracle.default_scale(128))
+            if r_v > 768:  # (the other kernel rounds the reconstructed rows as well: the tolerance of its own tests)
+                assert np.abs(got[b] - ref).max() <= 2e-2 * max(np.abs(ref).max(), 1e-30)
+                continue
+            bound = 1.05 * 2.0 ** -8 * (np.abs(ref) + mag) + 1e-6 * np.abs(mag).max()
+            over = np.abs(got[b] - ref) - bound
+            assert over.max() <= 0, (b, float(over.max()), float(np.abs(got[b] - ref).max()), float(mag.max()))
