@@ -245,12 +245,13 @@ __global__ __launch_bounds__(256) void topk_write_kernel(const float *__restrict
 // is the same ballot scheme as topk_write_kernel, fed from the registers.
 // ------------------------------------------------------------------------------------------
 constexpr int kRowWaves = 16;
+constexpr int kRowStage = 16384;  // most ids staged in LDS
 
 template <int NV>
 __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *__restrict__ S,
                                                                  int32_t *__restrict__ idx_out, int L, int k)
 {
-    __shared__ uint32_t hist[kTopkBins * 32];
+    extern __shared__ __attribute__((aligned(16))) uint32_t hist[];  // [kTopkBins * 32]; at the end the ids, where they fit
     __shared__ uint32_t bins[kTopkBins];
     __shared__ uint32_t sh[3 + 2 * kRowWaves];
     const int row = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -258,11 +259,18 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
     const int base = w * 64 * NV + lane;
 
     uint32_t key[NV];
+    const bool whole = (w + 1) * 64 * NV <= L;  // this wavefront's segment lies within the row
+    if (whole) {  // (one lane offset for all loads: the clamped form below spends four vector instructions on each)
+        const float *Sw = Srow + w * 64 * NV;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int t = base + 64 * j;
-        key[j] = __float_as_uint(Srow[t < L ? t : L - 1]);
-        if (j % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // bounds the address registers alive at once
+        for (int j = 0; j < NV; ++j) key[j] = __float_as_uint(Sw[64 * j + lane]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            const int t = base + 64 * j;
+            key[j] = __float_as_uint(Srow[t < L ? t : L - 1]);
+            if (j % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // bounds the address registers alive at once
+        }
     }
     // Positions beyond the row get key 0, below every real key (those are clamped to >= 1; only one NaN pattern
     // maps to 0): they can then be histogrammed and compared like the rest and are never selected, k <= L.
@@ -273,7 +281,11 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const uint32_t kk = order_key(__uint_as_float(key[j]));
-        key[j] = base_v + 64 * j < L ? (kk > 1u ? kk : 1u) : 0u;
+        key[j] = kk > 1u ? kk : 1u;
+    }
+    if (!whole) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) key[j] = base_v + 64 * j < L ? key[j] : 0u;
     }
 
     // Levels 0..2 histogram into `hist`.  While many keys still match the prefix the counters are replicated per
@@ -390,10 +402,12 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
         sh[3 + kRowWaves + w] = my_eq;
     }
     __syncthreads();
-    uint32_t gt_run = 0, eq_run = 0;
-    for (int ww = 0; ww < w; ++ww) {
-        gt_run += sh[3 + ww];
-        eq_run += sh[3 + kRowWaves + ww];
+    uint32_t gt_run = 0, eq_run = 0, eq_all = 0;
+#pragma unroll
+    for (int ww = 0; ww < kRowWaves; ++ww) {
+        gt_run += ww < w ? sh[3 + ww] : 0u;
+        eq_run += ww < w ? sh[3 + kRowWaves + ww] : 0u;
+        eq_all += sh[3 + kRowWaves + ww];
     }
     int32_t *out = idx_out + (size_t)row * k;
     // The comparisons are redone rather than kept: 2 NV lane masks would not fit the scalar registers.  The empty
@@ -401,19 +415,22 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
     uint32_t Tw = T;
     int base_w = base;
     asm volatile("" : "+v"(Tw), "+v"(base_w));
-    if (my_eq == 0) {
-        // no key of this segment equals the threshold (the usual case): only the keys above it matter
+    if (need_eq == eq_all && k <= kRowStage) {
+        // Every key equal to the threshold is taken (usually there is one), so what counts is which keys reach it.  The ids
+        // meet in LDS and leave as whole lines: a store of this loop has a lane or four that write.
+        uint32_t run = (uint32_t)__builtin_amdgcn_readfirstlane((int)(gt_run + eq_run));
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const bool is_gt = key[j] > Tw;
-            const uint64_t mg = __ballot(is_gt);
-            if (is_gt) {
-                const uint32_t pos = gt_run + lanes_below(mg) + (eq_run < need_eq ? eq_run : need_eq);
-                if (pos < (uint32_t)k) out[pos] = base_w + 64 * j;
-            }
-            gt_run += (uint32_t)__popcll(mg);
+            const bool take = key[j] >= Tw;
+            const uint64_t m = __ballot(take);
+            const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, run));
+            if (take) hist[pos] = (uint32_t)(base_w + 64 * j);  // (k of them, exactly)
+            run += (uint32_t)__popcll(m);
+            asm volatile("" : "+s"(run));
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
+        __syncthreads();
+        for (int i = tid; i < k; i += kRowWaves * 64) out[i] = (int32_t)hist[i];
         return;
     }
 #pragma unroll
@@ -435,9 +452,14 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
 bool topk_row_shape_ok(const xkv_shape &s) { return s.L <= kRowWaves * 64 * 64; }
 
 template <int NV>
-static void launch_topk_row_t(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, hipStream_t st)
+static hipError_t launch_topk_row_t(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, hipStream_t st)
 {
-    hipLaunchKernelGGL(topk_row_kernel<NV>, dim3(p.rows), dim3(kRowWaves * 64), 0, st, S, idx, s.L, s.k);
+    static DynamicLdsOnce attr;
+    const hipError_t e = attr.ensure((const void *)topk_row_kernel<NV>, (size_t)kRowStage * 4);
+    if (e != hipSuccess) return e;
+    const int words = s.k <= kRowStage && s.k > kTopkBins * 32 ? s.k : kTopkBins * 32;
+    hipLaunchKernelGGL(topk_row_kernel<NV>, dim3(p.rows), dim3(kRowWaves * 64), 4 * (size_t)words, st, S, idx, s.L, s.k);
+    return hipGetLastError();
 }
 
 hipError_t launch_topk_init(const Plan &p, uint32_t *state, hipStream_t st)
@@ -452,15 +474,10 @@ hipError_t launch_topk(const xkv_shape &s, const Plan &p, const float *S, int32_
 {
     if (p.topk_row) {
         const int per_thread = (s.L + kRowWaves * 64 - 1) / (kRowWaves * 64);
-        if (per_thread <= 8)
-            launch_topk_row_t<8>(s, p, S, idx, st);
-        else if (per_thread <= 16)
-            launch_topk_row_t<16>(s, p, S, idx, st);
-        else if (per_thread <= 32)
-            launch_topk_row_t<32>(s, p, S, idx, st);
-        else
-            launch_topk_row_t<64>(s, p, S, idx, st);
-        return hipGetLastError();
+        if (per_thread <= 8) return launch_topk_row_t<8>(s, p, S, idx, st);
+        if (per_thread <= 16) return launch_topk_row_t<16>(s, p, S, idx, st);
+        if (per_thread <= 32) return launch_topk_row_t<32>(s, p, S, idx, st);
+        return launch_topk_row_t<64>(s, p, S, idx, st);
     }
     TopkScratch ws;
     ws.hist = hist;
