@@ -457,160 +457,186 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
     if (i == j) diag0[i] = v;
 }
 
-__device__ __forceinline__ double fz_readlane(double v, int l)
-{
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l), hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-    return __hiloint2double(hi, lo);
-}
-
-// (3c) Cholesky factor Lc of G + shift I, right-looking, one launch per panel of pb columns [c0, c0 + pb).
+// (3c) Cholesky factor Lc of G + shift I, right-looking, one launch per panel of PB columns [c0, c0 + PB).
 // Workgroup j owns rows i0 = c0 + 32 j .. i0 + 31 of G and touches nothing else, so the workgroups of a launch do
 // not depend on each other; what they need of the panel beyond their own rows they recompute:
-//   1. every workgroup factors the pb x pb diagonal block (current values of G, shift added) in LDS;
-//   2. it solves for the panel entries Lc[j'][c0 .. c0 + pb) of all rows j' from the diagonal block down to
-//      its own last row (one thread per row, substitution in registers) and keeps them in LDS;
-//   3. it subtracts the panel's outer product from its own rows of the trailing matrix, G[i][j'] -= Lc[i] . Lc[j'].
+//   1. every workgroup factors the PB x PB diagonal block (current values of G, shift added) in LDS and inverts the
+//      factor, one elimination over the block and an identity beside it: a step reads the pivot column and the pivot row
+//      of the identity and updates two elements of each per thread, so it needs one barrier;
+//   2. the panel entries Lc[j'][c0 .. c0 + PB) of all rows j' from the diagonal block down to its own last row are
+//      G[j'][panel] times the transposed inverse (fp64 matrix cores, 16 rows a step) and stay in LDS;
+//   3. it subtracts the panel's outer product from its own rows of the trailing matrix, G[i][j'] -= Lc[i] . Lc[j'] (fp64
+//      matrix cores again).
 // Own rows of the panel are written to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a
-// later substitution needs is a contiguous row.
+// later substitution needs is a contiguous row; the first workgroup also writes the inverses of the 16 x 16 diagonal blocks,
+// Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity), which are the diagonal blocks of its inverse.
 // shift = 1e-13 * max diagonal of the original G (diag0) keeps the factor defined when the r vectors are
 // numerically dependent (an X_cat of rank below r): such directions come out short instead of normalised and
 // contribute nothing to A B.
-constexpr int kCholRB = 32;
-__global__ __launch_bounds__(256) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Lt,
-                                                         const double *__restrict__ diag0, int r, int c0, int pb)
+// What bounds it: the chain of its 16 launches at r = 512, and in each the elimination (PB dependent steps).  With the
+// panel solved by one thread per row (496 dependent multiply-adds) and vector multiply-adds in the trailing update a launch
+// took 58 us on average
+// at r = 512, now 29 us (18 us the last one, which is the elimination alone).
+constexpr int kCholRB = 32, kCholThreads = 512, kSolveIB = 16;
+constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
+constexpr size_t chol_lds(int pb, int rows)  // the inverse, then the panel's rows (at least the space of the elimination)
 {
+    const int all = (rows + 15) / 16 * 16, least = pb + (2 * pb * (pb + 1) + chol_pitch(pb) - 1) / chol_pitch(pb);
+    return ((size_t)pb * (pb + 1) + (size_t)(all > least ? all : least) * chol_pitch(pb)) * 8;
+}
+
+__device__ __forceinline__ double fz_rsqrt(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = y * fma(-0.5 * x * y, y, 1.5);
+    return y * fma(-0.5 * x * y, y, 1.5);
+}
+
+template <int PB>
+__global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Lt,
+                                                                  double *__restrict__ Minv, const double *__restrict__ diag0,
+                                                                  int r, int c0)
+{
+    constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64, NB = 4;
     G += (size_t)blockIdx.z * r * r;
     Lt += (size_t)blockIdx.z * r * r;
+    Minv += (size_t)blockIdx.z * ((r + kSolveIB - 1) / kSolveIB) * (kSolveIB * kSolveIB);
     diag0 += (size_t)blockIdx.z * r;
     extern __shared__ __attribute__((aligned(16))) unsigned char fz_smem[];
-    const int RP = r - c0, P1 = pb + 1;
-    double *LS = reinterpret_cast<double *>(fz_smem);  // [pb][pb + 1] factor of the diagonal block
-    double *dinvs = LS + pb * P1;                       // [pb] reciprocals of its diagonal
-    double *Lp = dinvs + pb;                            // [pb][RP]: Lc[c0 + rr][c0 + c] at c * RP + rr
-    __shared__ double red[4];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int pwc = (r - c0) < pb ? (r - c0) : pb;
+    double *LI = reinterpret_cast<double *>(fz_smem);  // [PB][LP] inverse of the diagonal block's factor
+    double *P = LI + PB * LP;                           // [rows][PITCH] panel entries of Lc, the diagonal block first
+    double *D = P + PB * PITCH, *E = D + PB * LP;       // elimination: where the panel's other rows come later
+    __shared__ double red[WAVES];
+    const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), l16 = lane & 15, kk = lane >> 4;
+    const int pwc = (r - c0) < PB ? (r - c0) : PB;
     const int i0 = c0 + blockIdx.x * kCholRB;
     const int own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
     const int nrows = own_end - c0;
+    const int nq = nrows > PB ? (nrows - PB + 15) / 16 : 0;  // blocks of 16 rows below the diagonal block
 
-    // panel entries of G for this thread's first row below the diagonal block: requested now, used in step 2
-    double g0[32];
-    {
-        const bool pre = tid >= pwc && tid < nrows;
+    // operands of this wavefront's first blocks: requested now, used in step 2
+    double ga[NB][KS];
+    auto fetch = [&](int q0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < 32; ++c) g0[c] = (pre && c < pwc) ? G[(size_t)(c0 + tid) * r + c0 + c] : 0.0;
-    }
+        for (int u = 0; u < NB; ++u) {
+            const int row = c0 + PB + 16 * (q0 + WAVES * u) + l16;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const int c = 4 * ks + kk;
+                ga[u][ks] = (q0 + WAVES * u < nq && row < own_end && c < pwc) ? G[(size_t)row * r + c0 + c] : 0.0;
+            }
+        }
+    };
+    fetch(w);
     double mx = 0.0;
-    for (int i = tid; i < r; i += 256) mx = fmax(mx, diag0[i]);
+    for (int i = tid; i < r; i += kCholThreads) mx = fmax(mx, diag0[i]);
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-    if (lane == 0) red[tid >> 6] = mx;
+    if (lane == 0) red[w] = mx;
     __syncthreads();
-    const double shift = fmax(1e-13 * fmax(fmax(red[0], red[1]), fmax(red[2], red[3])), 1e-300);
+    mx = red[0];
+#pragma unroll
+    for (int ww = 1; ww < WAVES; ++ww) mx = fmax(mx, red[ww]);
+    const double shift = fmax(1e-13 * mx, 1e-300);
 
-    // ---- 1. diagonal block, by wavefront 0 alone and without LDS traffic: lane a keeps row a in registers, the
-    // entries of the pivot column are passed around with readlane.  Rows beyond the panel are identity rows.
-    if (wave_id() == 0) {
-        const int a = lane & 31;
-        double x[32];
+    // ---- 1. elimination: thread = row i and columns j0, j0 + 16 (PB = 16: half of the threads take part)
+    constexpr int NJ = PB / 16;
+    const int ei = tid / 16, j0 = tid % 16;
+    const bool in = ei < PB;
+    double d[NJ], e[NJ];
 #pragma unroll
-        for (int b2 = 0; b2 < 32; ++b2) {
-            double v = a == b2 ? 1.0 : 0.0;
-            if (a < pwc && b2 <= a) v = G[(size_t)(c0 + a) * r + c0 + b2] + (a == b2 ? shift : 0.0);
-            x[b2] = v;
-        }
-#pragma unroll
-        for (int c = 0; c < 32; ++c) {
-            const double piv = fz_readlane(x[c], c);
-            const double dinv = rsqrt(piv > shift * 1e-3 ? piv : shift * 1e-3);
-            const double l = x[c] * dinv;  // lane a > c: Lc[a][c]; lane c: the square root of the pivot
-            x[c] = l;
-            if (lane == 0 && c < pb) dinvs[c] = dinv;
-#pragma unroll
-            for (int b2 = c + 1; b2 < 32; ++b2) x[b2] -= l * fz_readlane(l, b2);
-        }
-        if (lane < pb) {
-#pragma unroll
-            for (int c = 0; c < 32; ++c)
-                if (c < pb) LS[lane * P1 + c] = c <= lane ? x[c] : 0.0;
+    for (int u = 0; u < NJ; ++u) {
+        const int j = j0 + 16 * u;
+        d[u] = ei == j ? 1.0 : 0.0;  // (rows beyond the panel are identity rows)
+        if (in && ei < pwc && j <= ei) d[u] = G[(size_t)(c0 + ei) * r + c0 + j] + (ei == j ? shift : 0.0);
+        e[u] = ei == j ? 1.0 : 0.0;
+        if (in) {
+            D[ei * LP + j] = d[u];
+            E[ei * LP + j] = e[u];
         }
     }
     __syncthreads();
-
-    // ---- 2. panel entries of the rows c0 .. own_end - 1
-    for (int rr = tid; rr < nrows; rr += 256) {
-        const int row = c0 + rr;
-        double x[32];
-        if (rr < pwc) {
+#pragma unroll 1
+    for (int c = 0; c < PB; ++c) {
+        if (in) {
+            const double piv = D[c * LP + c], lic = D[ei * LP + c];
+            const double dinv = fz_rsqrt(piv > shift * 1e-3 ? piv : shift * 1e-3);
+            const double l = lic * dinv;
 #pragma unroll
-            for (int c = 0; c < 32; ++c) x[c] = (c < pb && c <= rr) ? LS[rr * P1 + c] : 0.0;
-        } else {
-#pragma unroll
-            for (int c = 0; c < 32; ++c) {
-                double v = 0.0;
-                if (c < pwc) {
-                    v = rr == tid ? g0[c] : G[(size_t)row * r + c0 + c];
-#pragma unroll
-                    for (int c2 = 0; c2 < c; ++c2) v -= x[c2] * LS[c * P1 + c2];
-                    v *= dinvs[c];
+            for (int u = 0; u < NJ; ++u) {
+                const int j = j0 + 16 * u;
+                const double ljc = D[j * LP + c] * dinv, ecj = E[c * LP + j] * dinv;
+                if (ei > c) {
+                    if (j > c && j <= ei) D[ei * LP + j] = d[u] = d[u] - l * ljc;
+                    if (j <= c) E[ei * LP + j] = e[u] = e[u] - l * ecj;
                 }
-                x[c] = v;
+                if (ei == c) LI[c * LP + j] = j <= c ? ecj : 0.0;
+                if (j == c) P[ei * PITCH + c] = ei >= c ? l : 0.0;
             }
         }
+        __syncthreads();
+    }
+
+    // ---- 2. panel entries of the rows below the diagonal block
+    double lb[CT][KS];
 #pragma unroll
-        for (int c = 0; c < 32; ++c)
-            if (c < pb) {
-                Lp[(size_t)c * RP + rr] = x[c];
-                if (row >= i0 && c < pwc && row >= c0 + c) Lt[(size_t)(c0 + c) * r + row] = x[c];
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) lb[ct][ks] = LI[(16 * ct + l16) * LP + 4 * ks + kk];
+    for (int q0 = w; q0 < nq; q0 += WAVES * NB) {
+        if (q0 != w) fetch(q0);
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            const int q = q0 + WAVES * u;
+            if (q < nq) {
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[u][ks], lb[ct][ks], acc, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) P[(PB + 16 * q + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
+                }
             }
+        }
     }
     __syncthreads();
-
-    // ---- 3. own rows of the trailing matrix: thread = (column lane, group of 8 rows)
-    const int cl = tid & 63, rg = tid >> 6;
-    for (int jc = c0 + pwc + cl; jc < own_end; jc += 64) {
-        double acc[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) acc[v] = 0.0;
-        for (int c = 0; c < pwc; ++c) {
-            const double lj = Lp[(size_t)c * RP + (jc - c0)];
-#pragma unroll
-            for (int v = 0; v < 8; ++v) {
-                const int irow = i0 + rg * 8 + v;  // rows beyond own_end read zeros or stale LDS, and are not stored
-                acc[v] += (irow < own_end ? Lp[(size_t)c * RP + (irow - c0)] : 0.0) * lj;
-            }
+    for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
+        const int c = t / kCholRB, row = i0 + t % kCholRB;
+        if (row < own_end && c < pwc && row >= c0 + c) Lt[(size_t)(c0 + c) * r + row] = P[(row - c0) * PITCH + c];
+    }
+    if (blockIdx.x == 0)
+        for (int t = tid; t < CT * 256; t += kCholThreads) {
+            const int blk = t >> 8, ii = (t >> 4) & 15, jj = t & 15;
+            if (c0 + 16 * blk < r) Minv[(size_t)(c0 / 16 + blk) * 256 + ii * 16 + jj] = LI[(16 * blk + ii) * LP + 16 * blk + jj];
         }
+
+    // ---- 3. own rows of the trailing matrix: tiles of 16 x 16 on or below the diagonal
+    const int own0 = i0 - c0 > PB ? i0 - c0 : PB;  // first own row below the diagonal block
+    const int n_rt = nrows > own0 ? (nrows - own0 + 15) / 16 : 0;
+    for (int item = w;; item += WAVES) {
+        int rt = 0, ctile = item;  // row tile rt has (own0 - PB) / 16 + rt + 1 column tiles
+        while (rt < n_rt && ctile > (own0 - PB) / 16 + rt) {
+            ctile -= (own0 - PB) / 16 + rt + 1;
+            ++rt;
+        }
+        if (rt >= n_rt) break;
+        const int rs = own0 + 16 * rt, cs = PB + 16 * ctile;
+        double old[4];
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int irow = i0 + rg * 8 + v;
-            if (irow < own_end && jc <= irow) G[(size_t)irow * r + jc] -= acc[v];
+        for (int v = 0; v < 4; ++v) {
+            const int irow = c0 + rs + kk + 4 * v, jc = c0 + cs + l16;
+            old[v] = (irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
+        }
+        fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(rs + l16) * PITCH + 4 * ks + kk], P[(cs + l16) * PITCH + 4 * ks + kk], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int irow = c0 + rs + kk + 4 * v, jc = c0 + cs + l16;
+            if (irow < own_end && jc <= irow) G[(size_t)irow * r + jc] = old[v] - acc[v];
         }
     }
-}
-
-// (3c') Inverses of the 16 x 16 diagonal blocks of Lc: Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity).
-constexpr int kSolveIB = 16;
-__global__ __launch_bounds__(256) void diag_inverse_kernel(const double *__restrict__ Lt, double *__restrict__ Minv, int r)
-{
-    Lt += (size_t)blockIdx.z * r * r;
-    Minv += (size_t)blockIdx.z * ((r + kSolveIB - 1) / kSolveIB) * (kSolveIB * kSolveIB);
-    const int t = blockIdx.x * 256 + threadIdx.x, b = t / kSolveIB, jj = t % kSolveIB;
-    if (b * kSolveIB >= r) return;
-    double x[kSolveIB];
-#pragma unroll
-    for (int ii = 0; ii < kSolveIB; ++ii) {
-        double v = ii == jj ? 1.0 : 0.0;
-        const int row = b * kSolveIB + ii;
-        if (ii > jj && row < r) {
-#pragma unroll
-            for (int k = 0; k < ii; ++k)
-                if (k >= jj) v -= Lt[(size_t)(b * kSolveIB + k) * r + row] * x[k];
-        }
-        if (ii >= jj && row < r) v /= Lt[(size_t)row * r + row];
-        x[ii] = ii >= jj ? v : 0.0;
-    }
-#pragma unroll
-    for (int ii = 0; ii < kSolveIB; ++ii) Minv[(size_t)b * (kSolveIB * kSolveIB) + ii * kSolveIB + jj] = x[ii];
 }
 
 // (3d) V = Lc^-1 W by blocked forward substitution on the fp64 matrix cores.  Rows of W^T (Wn [n][r]) are
@@ -1144,8 +1170,10 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
     double *Minv = reinterpret_cast<double *>(ws + f.off_minv);
     int *rotations = reinterpret_cast<int *>(ws + f.off_rot);
     static_assert(kJacobiSweeps <= 16, "the rotation counters have 16 slots per sequence");
-    static DynamicLdsOnce attr;
-    if (hipError_t e0 = attr.ensure((const void *)chol_panel_kernel, 160 * 1024 - 256); e0 != hipSuccess) return e0;
+    static DynamicLdsOnce attr_c32, attr_c16;
+    static_assert(chol_lds(32, 512) <= 160 * 1024 - 256 && chol_lds(16, 1024) <= 160 * 1024 - 256, "the panel fits the LDS");
+    if (hipError_t e0 = attr_c32.ensure((const void *)chol_panel_kernel<32>, 160 * 1024 - 256); e0 != hipSuccess) return e0;
+    if (hipError_t e0 = attr_c16.ensure((const void *)chol_panel_kernel<16>, 160 * 1024 - 256); e0 != hipSuccess) return e0;
     hipError_t e = hipSuccess;
     const long long vcount = (long long)r * n, x_seq = (long long)n * s.L;
     for (int b0 = 0; b0 < s.batch && e == hipSuccess; b0 += f.bc) {
@@ -1177,12 +1205,13 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
             hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                f.g_splits);
             for (int c0 = 0; c0 < r; c0 += f.chol_pb) {
-                const int pb = f.chol_pb;
-                const size_t lds = ((size_t)pb * (pb + 1) + pb + (size_t)pb * (r - c0)) * 8;
-                hipLaunchKernelGGL(chol_panel_kernel, dim3((r - c0 + kCholRB - 1) / kCholRB, 1, nb), dim3(256), lds, st, Gm, Lt,
-                                   diag0, r, c0, pb);
+                const dim3 grid((r - c0 + kCholRB - 1) / kCholRB, 1, nb);
+                const size_t lds = chol_lds(f.chol_pb, r - c0);
+                if (f.chol_pb == 32)
+                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, diag0, r, c0);
+                else
+                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, diag0, r, c0);
             }
-            hipLaunchKernelGGL(diag_inverse_kernel, dim3(blocks256((r + 15) / 16 * 16), 1, nb), dim3(256), 0, st, Lt, Minv, r);
             if (r <= 512)
                 hipLaunchKernelGGL((orth_solve_kernel<8, 2>), dim3((n + 31) / 32, 1, nb), dim3(256), 0, st, Wn, Lt, Minv, Vt, n, r);
             else
