@@ -1038,7 +1038,8 @@ __global__ __launch_bounds__(1024) void ritz_order_kernel(const double *__restri
         double sum = 0.0;
         for (int i = lane; i < r; i += kWave) sum = fma(Gt[(size_t)c * r + i], Gt[(size_t)c * r + i], sum);
         sum = fz_wave_sum_f64(sum);
-        if (lane == 0) lam[c] = sqrt(sum);
+        // (a NaN would compare as neither larger nor equal and leave places of `order` unwritten: it goes last)
+        if (lane == 0) lam[c] = sum >= 0.0 ? sqrt(sum) : -1.0;
     }
     __syncthreads();
     const int c = threadIdx.x;
@@ -1047,7 +1048,7 @@ __global__ __launch_bounds__(1024) void ritz_order_kernel(const double *__restri
         const double mine = lam[c];
         for (int j = 0; j < r; ++j) rank += (lam[j] > mine || (lam[j] == mine && j < c)) ? 1 : 0;
         order[rank] = c;
-        if (sigma && rank < r_out) sigma[(size_t)blockIdx.x * r_out + rank] = (float)sqrt(mine);
+        if (sigma && rank < r_out) sigma[(size_t)blockIdx.x * r_out + rank] = (float)sqrt(mine);  // (NaN for the -1)
     }
 }
 

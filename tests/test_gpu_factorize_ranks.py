@@ -63,3 +63,20 @@ def test_ranks_around_the_block_sizes(r, batch, rank):
         assert np.abs(gram - np.diag(lam)).max() <= 1e-4 * lam.max()
         assert (sigma[b][1:] <= sigma[b][:-1]).all()
         np.testing.assert_allclose(sigma[b] ** 2, lam, rtol=0, atol=1e-4 * lam.max())
+
+
+def test_a_nan_in_the_input_stays_a_value():
+    """The directions are ordered by their singular values; without an order among NaN the places of the list stayed
+    unwritten and were used as row numbers all the same.  The other sequence of the batch is not touched."""
+    G, H_kv, d_h, L, r = 1, 2, 64, 300, 40
+    n = G * H_kv * d_h
+    rng = np.random.default_rng(3)
+    X = rng.standard_normal((2, G, H_kv, L, d_h)).astype(np.float32)
+    X[0, 0, 1, 17, 5] = np.nan
+    A, B, sigma = factorize(X, G, H_kv, d_h, L, r, 3)
+    assert np.isnan(sigma[0]).any()
+    assert np.isfinite(A[1]).all() and np.isfinite(B[1]).all()
+    assert np.abs(B[1] @ B[1].T - np.eye(r)).max() <= 1e-5
+    flat = X[1].astype(np.float64).transpose(2, 0, 1, 3).reshape(L, n)
+    ref_A = flat @ B[1].T
+    assert np.abs(A[1] - ref_A).max() <= 1e-5 * np.abs(ref_A).max()
