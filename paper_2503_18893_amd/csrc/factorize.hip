@@ -364,36 +364,49 @@ __global__ __launch_bounds__(256) void init_v_kernel(float *__restrict__ Vt, lon
 // fp64 matrix-core instruction v_mfma_f64_16x16x4_f64: D[16][16] += A[16][4] B[4][16], one double per lane for A
 // (row lane % 16, k = lane / 16) and for B (column lane % 16, k = lane / 16); lane l holds D[l / 16 + 4 v][l % 16]
 // in element v of its four results.
+typedef __attribute__((ext_vector_type(2))) double fz_f64x2_t;
 typedef __attribute__((ext_vector_type(4))) double fz_f64x4_t;
 
-__device__ __forceinline__ void fz_gram_fetch(float (&fa)[8][2], float (&fb)[8][2], const float *__restrict__ Wn, int n0,
-                                              int n_begin, int n_end, int r, const int (&ci)[2], const int (&cj)[2], int kk)
+__device__ __forceinline__ void fz_gram_fetch(float (&fa)[8][2], float (&fb)[8][2], const float *__restrict__ Xn,
+                                              const float *__restrict__ Wn, int n0, int n_begin, int n_end, int r,
+                                              const int (&ci)[2], const int (&cj)[2], int kk)
 {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int row = n0 + 4 * q + kk;
         const bool ok = row < n_end;
-        const float *wr = Wn + (size_t)(ok ? row : n_begin) * r;
+        const size_t at = (size_t)(ok ? row : n_begin) * r;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            fa[q][u] = (ok && ci[u] < r) ? wr[ci[u]] : 0.0f;
-            fb[q][u] = (ok && cj[u] < r) ? wr[cj[u]] : 0.0f;
+            fa[q][u] = (ok && ci[u] < r) ? Xn[at + ci[u]] : 0.0f;
+            fb[q][u] = (ok && cj[u] < r) ? Wn[at + cj[u]] : 0.0f;
         }
     }
 }
 
-// (3b) Gram matrix of the r vectors, products and sums in fp64: G[i][j] = sum_n W[n][i] W[n][j].  One wavefront
-// per 32 x 32 block on or below the diagonal and per range of n (one partial plane per range, added up in a
-// fixed order by gram_sum_kernel); a step multiplies 4 rows of W, widened to fp64 as they are loaded.
-__global__ __launch_bounds__(256) void gram_f64_kernel(const float *__restrict__ Wn, double *__restrict__ planes, int n,
+// (3b) Products of r vectors with r vectors, products and sums in fp64: G[i][j] = sum_n X[n][i] W[n][j].  One wavefront
+// per 32 x 32 block and per range of n (one partial plane per range, added up in a fixed order by the next kernel); a
+// step multiplies 4 rows, widened to fp64 as they are loaded.  LOWER: X = W, the blocks on or below the diagonal (the
+// Gram matrix of the orthonormalisation); otherwise all of them (the Rayleigh-Ritz matrix, X = V: 59 us at r = 512, n =
+// 4096 where one workgroup per block without matrix instructions took 466).
+template <bool LOWER>
+__global__ __launch_bounds__(256) void gram_f64_kernel(const float *__restrict__ Xn, long long x_seq,
+                                                       const float *__restrict__ Wn, double *__restrict__ planes, int n,
                                                        int r, int splits, int n_pairs)
 {
+    Xn += (size_t)blockIdx.z * x_seq;
     Wn += (size_t)blockIdx.z * n * r;
     planes += (size_t)blockIdx.z * splits * r * r;
     const int pair = blockIdx.x * 4 + wave_id();
     if (pair >= n_pairs) return;
     int bi, bj;
-    fz_lower_pair(pair, bi, bj);
+    if (LOWER) {
+        fz_lower_pair(pair, bi, bj);
+    } else {
+        const int gb = (r + 31) / 32;
+        bi = pair / gb;
+        bj = pair % gb;
+    }
     const int split = blockIdx.y, lane = lane_id(), col = lane & 15, kk = lane >> 4;
     const int n_begin = (int)((long long)n * split / splits), n_end = (int)((long long)n * (split + 1) / splits);
     fz_f64x4_t acc[2][2];
@@ -410,7 +423,7 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const float *__restrict__
     // eight steps (32 rows of W) at a time; the loads of the next eight are requested before the 32 products of
     // the current ones
     float fa[8][2], fb[8][2];
-    fz_gram_fetch(fa, fb, Wn, n_begin, n_begin, n_end, r, ci, cj, kk);
+    fz_gram_fetch(fa, fb, Xn, Wn, n_begin, n_begin, n_end, r, ci, cj, kk);
     for (int n0 = n_begin; n0 < n_end; n0 += 32) {
         double da[8][2], db[8][2];
 #pragma unroll
@@ -420,7 +433,7 @@ __global__ __launch_bounds__(256) void gram_f64_kernel(const float *__restrict__
                 da[q][u] = (double)fa[q][u];
                 db[q][u] = (double)fb[q][u];
             }
-        if (n0 + 32 < n_end) fz_gram_fetch(fa, fb, Wn, n0 + 32, n_begin, n_end, r, ci, cj, kk);
+        if (n0 + 32 < n_end) fz_gram_fetch(fa, fb, Xn, Wn, n0 + 32, n_begin, n_end, r, ci, cj, kk);
 #pragma unroll
         for (int q = 0; q < 8; ++q)
 #pragma unroll
@@ -485,11 +498,12 @@ constexpr size_t chol_lds(int pb, int rows)  // the inverse, then the panel's ro
     return ((size_t)pb * (pb + 1) + (size_t)(all > least ? all : least) * chol_pitch(pb)) * 8;
 }
 
+// 1 / sqrt(x): the hardware's estimate y (better than 2^-20) and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with
+// e = 1 - x y^2: a chain of four dependent operations where two Newton steps are eight.
 __device__ __forceinline__ double fz_rsqrt(double x)
 {
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * fma(-0.5 * x * y, y, 1.5);
-    return y * fma(-0.5 * x * y, y, 1.5);
+    const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 template <int PB>
@@ -730,28 +744,32 @@ __global__ __launch_bounds__(256) void orth_solve_kernel(const float *__restrict
 // A^T A = Lambda is diagonal and descending and any leading block of rows of B spans the best subspace of that size
 // that the basis contains.  M is r x r, symmetric positive semi-definite, fp64.
 //
-// Eigen-solver: one-sided (Hestenes) Jacobi on the columns of M itself, in blocks.  Plane rotations J are applied from
-// the right until the columns of M J are mutually orthogonal; then J^T M^2 J is diagonal, so J holds the eigenvectors
-// of M^2, which are those of M, and the column norms are the eigenvalues.  Both M J and J are stored transposed (row c
-// = column vector c), so a rotation touches two contiguous rows.  The r columns are cut into blocks of NC / 2; a launch
-// is one round of a round-robin tournament between blocks, workgroup = one pair of blocks: it loads its NC column
-// vectors into LDS, runs an inner tournament over them (wavefront = one column pair per inner round: three dot
-// products, one rotation; all pairs in a sweep's first round, only the pairs between the two blocks afterwards, so that
-// every pair of columns meets exactly once per sweep), writes them back, and applies the accumulated NC x NC transform
-// to its NC rows of J^T (a 32 x 32 by 32 x r product on the fp64 matrix cores).
-// Workgroups of a launch touch disjoint rows; launch boundaries are the only synchronisation between rounds.
+// Eigen-solver: two-sided Jacobi in blocks.  Plane rotations T make M' = T M T^T more and more diagonal; their product
+// is J^T (stored as such: row c = eigenvector c in the basis V), the diagonal ends as the eigenvalues.  The r columns
+// are cut into blocks of 16; a round of a round-robin tournament between blocks rotates, for every pair of blocks,
+// every pair of columns between the two blocks once (in a sweep's first round also the pairs inside each block), so that
+// every pair of columns meets exactly once per sweep.  The rotations of a pair of blocks depend on its 32 x 32 diagonal
+// block of M alone; applying them is two 32 x 32 x 32 products per block of M and one per block of J^T.  A round is one
+// launch: it applies its rotations and finds those of the next round, for which each pair of blocks brings its diagonal
+// block up to date by itself.  Launch boundaries are the only synchronisation.
+// What bounds it: the chain of launches, and in a launch the 16 dependent inner rounds of the rotations.  One launch takes
+// 16 us (13.3 us over all that are enqueued, r = 512), eight sweeps run.  One-sided Jacobi on whole columns of 512, three dot
+// products of columns per rotation, took 63 us per launch: 13.9 against 4.1 ms; every workgroup finding the rotations
+// of its own two pairs 16 us with one sequence, but all 200 workgroups of a sequence then hold a compute unit for the 16
+// inner rounds; two launches per round 18 us.
 // The launches of kJacobiSweeps sweeps are all enqueued up front (no value is read back by the host); a sequence is
-// finished early on the device: every sweep counts, per sequence, the rotations whose two columns had a cosine above
-// kJacobiSettled, and the workgroups of the sweeps after one with a count of zero return at once.  Convergence is
+// finished early on the device: every sweep counts, per sequence, the rotations whose element alpha was above
+// kJacobiSettled sqrt(beta gamma), and the workgroups of the sweeps after one with a count of zero return at once.  Convergence is
 // quadratic by then: what a sweep without such a rotation leaves behind is of the order of the square of that bound.
 // ------------------------------------------------------------------------------------------------
 
-// (4z) Wn[c][i] = Vt[i][c]: the basis in the layout the orthonormalisation reads, for its second pass.
-__global__ __launch_bounds__(256) void transpose_v_kernel(const float *__restrict__ Vt, float *__restrict__ Wn, int n, int r)
+// (4z) Vn[c][i] = Vt[i][c]: the basis in the layout in which the fp64 products read it.
+__global__ __launch_bounds__(256) void transpose_v_kernel(const float *__restrict__ Vt, float *__restrict__ Vn, long long vn_seq, int n,
+                                                          int r)
 {
     __shared__ float tile[32][33];
     Vt += (size_t)blockIdx.z * r * n;
-    Wn += (size_t)blockIdx.z * n * r;
+    Vn += (size_t)blockIdx.z * vn_seq;
     const int c0 = blockIdx.x * 32, i0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -762,287 +780,372 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const float *__restric
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int c = c0 + ty + 8 * u, i = i0 + tx;
-        if (c < n && i < r) Wn[(size_t)c * r + i] = tile[tx][ty + 8 * u];
+        if (c < n && i < r) Vn[(size_t)c * r + i] = tile[tx][ty + 8 * u];
     }
-}
-
-// (5a) M = V W with W = C V^T, fp64 accumulation: 32 x 32 tile per workgroup.
-__global__ __launch_bounds__(256) void ritz_matrix_kernel(const float *__restrict__ Vt, const float *__restrict__ Wn,
-                                                          double *__restrict__ M, int n, int r)
-{
-    __shared__ double sv[32][33], sw[32][33];
-    Vt += (size_t)blockIdx.z * r * n;
-    Wn += (size_t)blockIdx.z * n * r;
-    M += (size_t)blockIdx.z * r * r;
-    const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // ty 0..7
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int c0 = 0; c0 < n; c0 += 32) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int row = ty + 8 * u;
-            sv[row][tx] = (i0 + row < r && c0 + tx < n) ? (double)Vt[(size_t)(i0 + row) * n + c0 + tx] : 0.0;
-            sw[row][tx] = (c0 + row < n && j0 + tx < r) ? (double)Wn[(size_t)(c0 + row) * r + j0 + tx] : 0.0;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int c = 0; c < 32; ++c) {
-            const double wv = sw[c][tx];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] = fma(sv[ty + 8 * u][c], wv, acc[u]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (i0 + ty + 8 * u < r && j0 + tx < r) M[(size_t)(i0 + ty + 8 * u) * r + j0 + tx] = acc[u];
 }
 
 constexpr int kJacobiSweeps = 10;        // most sweeps of the block Jacobi eigen-solver (each: every pair of column blocks once)
-constexpr double kJacobiSettled = 1e-7;  // a sweep whose rotations all stayed below this cosine was the last one needed
+constexpr double kJacobiSettled = 1e-7;  // a sweep whose elements all stayed below this cosine was the last one needed
 
-// (5b) Gt = (M + M^T) / 2 (row c = column c of the symmetric matrix), Jt = identity, rotation counts zero.
-__global__ __launch_bounds__(256) void jacobi_init_kernel(const double *__restrict__ M, double *__restrict__ Gt,
-                                                          double *__restrict__ Jt, int *__restrict__ rotations, int r)
+// (5b) M = (S + S^T) / 2 with S the sum of its planes, Jt = identity, rotation counts zero.
+__global__ __launch_bounds__(256) void jacobi_init_kernel(const double *__restrict__ planes, double *__restrict__ M,
+                                                          double *__restrict__ Jt, int *__restrict__ rotations, int r,
+                                                          int splits)
 {
     if (blockIdx.x == 0 && threadIdx.x < kJacobiSweeps) rotations[blockIdx.z * kJacobiSweeps + threadIdx.x] = 0;
+    planes += (size_t)blockIdx.z * splits * r * r;
     M += (size_t)blockIdx.z * r * r;
-    Gt += (size_t)blockIdx.z * r * r;
     Jt += (size_t)blockIdx.z * r * r;
     const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (long long)r * r) return;
     const int i = (int)(idx / r), j = (int)(idx % r);
-    Gt[idx] = 0.5 * (M[idx] + M[(size_t)j * r + i]);
+    double x = 0.0, y = 0.0;
+    for (int s = 0; s < splits; ++s) {
+        x += planes[(size_t)s * r * r + idx];
+        y += planes[(size_t)s * r * r + (size_t)j * r + i];
+    }
+    M[idx] = 0.5 * (x + y);
     Jt[idx] = i == j ? 1.0 : 0.0;
 }
 
-// Opponent of player `who` in round `round` of a round-robin tournament of m players (m even): player m - 1 stays,
-// the others rotate.  Every pair meets exactly once in m - 1 rounds.
-__device__ __forceinline__ int fz_opponent(int who, int round, int m)
+// The value of the next lane of the same 16 (the last lane takes the first one's).
+__device__ __forceinline__ double fz_next_of_16(double v)
 {
-    const int q = m - 1;
-    if (who == q) return round % q;
-    if (who == round % q) return q;
-    return ((2 * round - who) % q + q) % q;
-}
-
-__device__ __forceinline__ double fz_wave_sum_f64(double v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
-}
-
-// The same sum for code where every lane of the wavefront is active, through the data-parallel lane permutations of
-// the vector ALU instead of LDS round trips: four steps leave the sum of each row of 16 lanes in all of its lanes
-// (neighbour, other pair of the quad, other quad of the half row, other half row), the four row sums are then read
-// out as scalars.  CTRL: quad_perm(1,0,3,2) = 0xB1, quad_perm(2,3,0,1) = 0x4E, row_half_mirror = 0x141, row_mirror =
-// 0x140.
-template <int CTRL> __device__ __forceinline__ double fz_dpp_f64(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x12F, 0xF, 0xF, false);  // row_ror:15
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x12F, 0xF, 0xF, false);
     return __hiloint2double(hi, lo);
 }
 
-__device__ __forceinline__ double fz_wave_sum_all_lanes_f64(double v)
+__device__ __forceinline__ double fz_from_lane(double v, int l)
 {
-    v += fz_dpp_f64<0xB1>(v);
-    v += fz_dpp_f64<0x4E>(v);
-    v += fz_dpp_f64<0x141>(v);
-    v += fz_dpp_f64<0x140>(v);
-    double sum = 0.0;
-#pragma unroll
-    for (int row = 0; row < kWave; row += 16)
-        sum += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), row),
-                                __builtin_amdgcn_readlane(__double2loint(v), row));
-    return sum;
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * l, __double2hiint(v)), __builtin_amdgcn_ds_bpermute(4 * l, __double2loint(v)));
 }
 
-// (5c) one tournament round between column blocks.  NC local columns (two blocks of NC / 2), NC / 2 wavefronts.
-template <int NC>
-__global__ __launch_bounds__(NC / 2 * 64) void jacobi_round_kernel(double *__restrict__ Gt, double *__restrict__ Jt,
-                                                                  int *rotations, int r, int n_blocks,
-                                                                  int sweep, int round)
+// The rotation that makes [[beta, alpha], [alpha, gamma]] diagonal: new a = cs a - sn b, new b = sn a + cs b, |angle| <=
+// 45 degrees.  cos 2t = |gamma - beta| / h, sin 2t = +-2 alpha / h, then the half angle; two reciprocal square roots and
+// no division.  An element that is zero to working accuracy stays as it is.
+__device__ __forceinline__ void fz_rotation(double alpha, double beta, double gamma, double &cs, double &sn)
 {
-    // rotations[sequence][sweep]: written by the launches of that sweep only, read by those of the next
-    rotations += blockIdx.z * kJacobiSweeps;
-    if (sweep > 0 && rotations[sweep - 1] == 0) return;  // same value for the whole workgroup
-    __shared__ int big_rotations;
-    if (threadIdx.x == 0) big_rotations = 0;
-    extern __shared__ double fz_sm[];
-    // r <= 64 kMaxIt (512 for NC = 32, 1024 for NC = 16); the local columns are kept at that pitch and zero beyond r,
-    // so that the loops over a column need no per-element bounds (zeros rotate into zeros)
-    constexpr int kMaxIt = NC == 32 ? 8 : 16, RP = kMaxIt * kWave;
-    double *cols = fz_sm;                 // [NC][RP]
-    double *T = fz_sm + (size_t)NC * RP;  // [NC][NC]: row c = coefficients of local column c in terms of the old ones
-    Gt += (size_t)blockIdx.z * r * r;
-    Jt += (size_t)blockIdx.z * r * r;
-    constexpr int BS = NC / 2, THREADS = NC / 2 * 64;
-    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-    // this workgroup's pair of blocks: the blockIdx.x-th pair of the round
-    int P = -1, Q = -1;
-    {
-        int seen = 0;
-        for (int a = 0; a < n_blocks && P < 0; ++a) {
-            const int bq = fz_opponent(a, round, n_blocks);
-            if (a < bq) {
-                if (seen == (int)blockIdx.x) {
-                    P = a;
-                    Q = bq;
-                }
-                ++seen;
-            }
-        }
+    const double dif = gamma - beta, a2 = 2.0 * alpha;
+    const double rh = fz_rsqrt(fma(dif, dif, a2 * a2));
+    const double u = fma(0.5 * fabs(dif), rh, 0.5), rc = fz_rsqrt(u);
+    const bool on = alpha * alpha > 1e-30 * fabs(beta * gamma);
+    cs = on ? u * rc : 1.0;
+    sn = on ? (dif >= 0.0 ? alpha : -alpha) * rh * rc : 0.0;
+}
+
+// (5c) round k of the tournament: M' = T M T^T and J^T' = T J^T with the rotations T that the launch before found, and
+// beside them the rotations of round k + 1.  Workgroups x < pairs find rotations; the next pairs (pairs + 1) / 2 make block
+// (p, q), p >= q, of M' and its mirror image, in the other buffer; the others the rows of J^T of one pair, 64 positions.
+// The first launch, k = -1, only finds the rotations of round 0.
+constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34;
+
+// The first column of local column c of pair number x in this round of the round-robin tournament of m = n_blocks players:
+// the last player meets t = round % (m - 1), and t + x meets t - x modulo m - 1.
+__device__ __forceinline__ void fz_pair_of_blocks(int x, int round, int n_blocks, int (&b)[2])
+{
+    const int m1 = n_blocks - 1, t = round % m1, u = (t + x) % m1, v = x == 0 ? m1 : (t - x + m1) % m1;
+    b[0] = (u < v ? u : v) * kJacBS;
+    b[1] = (u < v ? v : u) * kJacBS;
+}
+
+__device__ __forceinline__ int fz_pair_column(const int (&b)[2], int c) { return (c < kJacBS ? b[0] : b[1]) + (c & 15); }
+
+// Which pair of round `round` a block is in, and as which half (inverse of fz_pair_of_blocks).
+__device__ __forceinline__ void fz_pair_of_block(int b, int round, int n_blocks, int &x, int &half)
+{
+    const int m1 = n_blocks - 1, t = round % m1;
+    int other;
+    if (b == m1 || b == t) {
+        x = 0;
+        other = b == t ? m1 : t;
+    } else {
+        const int up = (b - t + m1) % m1, down = (t - b + m1) % m1;
+        x = up < down ? up : down;
+        other = (2 * t - b + 2 * m1) % m1;
     }
-    auto gcol = [&](int c) { return c < BS ? P * BS + c : Q * BS + (c - BS); };  // columns >= r do not exist
-    // Rows move between memory and LDS a wavefront at a time: local column w and w + NC / 2, 64 consecutive elements
-    // per request, all requests of a wavefront issued before the first is awaited.
-    auto rows_to_lds = [&](const double *__restrict__ src) __attribute__((always_inline)) {
-        double v[2][kMaxIt];
+    half = b > other ? 1 : 0;
+}
+
+// The rotations of pair of blocks x in round `round`, from its 32 x 32 diagonal block of M' (M as it is where T_old is null,
+// otherwise the three 16 x 16 blocks of T_old M T_old^T that make it up).
+// Thread = one 2 x 2 block of pairs, rows x columns.  The 16 x 16 rotations between the two halves, inner round t:
+// a = w meets b = 16 + (w + t) % 16.  A thread keeps the elements of its pairs in registers; from one inner round to the
+// next the b side moves on by one pair, along the columns with a lane permutation, along the rows through LDS.  One
+// barrier per inner round.  Rows and columns beyond the matrix are zero and are not rotated.
+__device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, const double *T_old, double *T, int *count, int r,
+                                                  int n_blocks, int round, int x)
+{
+    __shared__ double G[kJacNC * kJacLP], Ts[kJacNC * kJacLP];
+    __shared__ __attribute__((aligned(16))) double dg[2][16][4];     // alpha, beta, gamma of the next round's pairs
+    __shared__ __attribute__((aligned(16))) fz_f64x2_t mv[2][16][16];  // elements on the move
+    __shared__ int big_rotations;
+    T += (size_t)x * kJacNC * kJacNC;  // row c = coefficients of new column c in the old ones
+    const int tid = threadIdx.x, lane = lane_id(), pr = tid >> 4, pc = tid & 15;
+    int blk[2];
+    fz_pair_of_blocks(x, round, n_blocks, blk);
+    if (T_old) {
+        constexpr int KS = kJacNC / 4, YP = 18;
+        __shared__ double Y[3][kJacNC * YP];
+        const int w = wave_id(), l16 = lane & 15, kk = lane >> 4, before = round + n_blocks - 2;  // the round before, modulo n_blocks - 1
+        int px[2], half[2], pb[2][2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            fz_pair_of_block(blk[h] / kJacBS, before, n_blocks, px[h], half[h]);
+            fz_pair_of_blocks(px[h], before, n_blocks, pb[h]);
+        }
+        // parts 0, 1, 2 = (a, c) = (0, 0), (1, 1), (0, 1)
+        double ma[2][KS], tc[2][KS], ta0[KS];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int gc = gcol(w + BS * u);
+            const int item = w + 4 * u, part = item >> 1, mt = item & 1, a = part == 1 ? 1 : 0, c = part == 0 ? 0 : 1;
+            const int row = (mt ? (a ? pb[1][1] : pb[0][1]) : (a ? pb[1][0] : pb[0][0])) + l16;
+            const double *Tc = T_old + (size_t)(c ? px[1] : px[0]) * kJacNC * kJacNC + (16 * (c ? half[1] : half[0]) + l16) * kJacNC;
 #pragma unroll
-            for (int it = 0; it < kMaxIt; ++it) {
-                const int i = lane + kWave * it;
-                v[u][it] = (gc < r && i < r) ? src[(size_t)gc * r + i] : 0.0;
+            for (int ks = 0; ks < KS; ++ks) {
+                const int i = 4 * ks + kk, col = (i < kJacBS ? (c ? pb[1][0] : pb[0][0]) : (c ? pb[1][1] : pb[0][1])) + (i & 15);
+                ma[u][ks] = (item < 6 && row < r && col < r) ? M[(size_t)row * r + col] : 0.0;
+                tc[u][ks] = Tc[i];
             }
         }
+        const int sa = w == 1 ? 1 : 0, sc0 = w == 0 ? 0 : 1;  // wavefronts 0 .. 2: the part they finish
+        const double *Ta = T_old + (size_t)(sa ? px[1] : px[0]) * kJacNC * kJacNC + (16 * (sa ? half[1] : half[0]) + l16) * kJacNC;
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int ks = 0; ks < KS; ++ks) ta0[ks] = Ta[4 * ks + kk];
 #pragma unroll
-            for (int it = 0; it < kMaxIt; ++it) cols[(w + BS * u) * RP + lane + kWave * it] = v[u][it];
-    };
-    rows_to_lds(Gt);
-    for (int idx = tid; idx < NC * NC; idx += THREADS) T[idx] = (idx / NC == idx % NC) ? 1.0 : 0.0;
-    __syncthreads();
-    // In the sweep's first round the inner tournament is complete (every pair of the NC columns: that is where the
-    // pairs inside a block meet, once per sweep, every block being in exactly one workgroup of the round); in the
-    // other rounds only the BS x BS pairs between the two blocks are left to visit.
-    const bool complete = round == 0;
-    const int inner_rounds = complete ? NC - 1 : BS;
-    for (int t = 0; t < inner_rounds; ++t) {
-        // wavefront w plays the w-th pair of the inner round
-        int a, b;
-        if (complete) {
-            // the pairs of round t of the tournament (fz_opponent): the last player meets t, and player t + j meets
-            // player t - j (modulo NC - 1) for j = 1 .. NC / 2 - 1; wavefront w takes pair number w of that list
-            constexpr int q = NC - 1;
-            const int x = w == 0 ? t % q : (t + w) % q, y = w == 0 ? q : (t - w + q) % q;
-            a = x < y ? x : y;
-            b = x < y ? y : x;
-        } else {
-            a = w;
-            b = BS + (w + t) % BS;
-        }
-        if (gcol(a) < r && gcol(b) < r) {
-            double *ga = cols + a * RP + lane, *gb = cols + b * RP + lane;
-            // the lane's elements of both columns stay in registers from the dot products to the rotation
-            // (all LDS reads are requested before the first wait)
-            double x[kMaxIt], y[kMaxIt];
+        for (int u = 0; u < 2; ++u) {
+            const int item = w + 4 * u;
+            if (item < 6) {
+                fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int it = 0; it < kMaxIt; ++it) {
-                x[it] = ga[kWave * it];
-                y[it] = gb[kWave * it];
-            }
-            double alpha = 0.0, beta = 0.0, gamma = 0.0;
+                for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ma[u][ks], tc[u][ks], acc, 0, 0, 0);
 #pragma unroll
-            for (int it = 0; it < kMaxIt; ++it) {
-                alpha = fma(x[it], y[it], alpha);
-                beta = fma(x[it], x[it], beta);
-                gamma = fma(y[it], y[it], gamma);
-            }
-            alpha = fz_wave_sum_all_lanes_f64(alpha);
-            beta = fz_wave_sum_all_lanes_f64(beta);
-            gamma = fz_wave_sum_all_lanes_f64(gamma);
-            // rotate unless the two columns are already orthogonal to working accuracy (or one of them is zero)
-            // (cosine of the two columns)^2 = alpha^2 / (beta gamma).  The rotation angle: tan(2 theta) = 2 alpha /
-            // (gamma - beta), the smaller root of the tangent written with one square root and one division.
-            const double a_sq = alpha * alpha, bg = beta * gamma;
-            if (a_sq > 1e-30 * bg && beta > 0.0 && gamma > 0.0) {
-                if (lane == 0 && a_sq > kJacobiSettled * kJacobiSettled * bg) atomicAdd(&big_rotations, 1);
-                const double dif = gamma - beta, a2 = 2.0 * alpha;
-                const double hyp = sqrt(dif * dif + a2 * a2);
-                const double tn = (dif >= 0.0 ? a2 : -a2) / (fabs(dif) + hyp);
-                const double cs = rsqrt(1.0 + tn * tn), sn = cs * tn;
-#pragma unroll
-                for (int it = 0; it < kMaxIt; ++it) {
-                    ga[kWave * it] = cs * x[it] - sn * y[it];
-                    gb[kWave * it] = sn * x[it] + cs * y[it];
-                }
-                if (lane < NC) {
-                    const double x = T[a * NC + lane], y = T[b * NC + lane];
-                    T[a * NC + lane] = cs * x - sn * y;
-                    T[b * NC + lane] = sn * x + cs * y;
-                }
+                for (int v = 0; v < 4; ++v) Y[item >> 1][(16 * (item & 1) + kk + 4 * v) * YP + l16] = acc[v];
             }
         }
         __syncthreads();
-    }
+        if (w < 3) {
+            fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int gc = gcol(w + BS * u);
+            for (int ks = 0; ks < KS; ++ks)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta0[ks], Y[w][(4 * ks + kk) * YP + l16], acc, 0, 0, 0);
 #pragma unroll
-        for (int it = 0; it < kMaxIt; ++it) {
-            const int i = lane + kWave * it;
-            if (gc < r && i < r) Gt[(size_t)gc * r + i] = cols[(w + BS * u) * RP + i];
-        }
-    }
-    if (tid == 0 && big_rotations > 0) atomicAdd(&rotations[sweep], big_rotations);
-    __syncthreads();
-    // the same transform on this workgroup's rows of J^T: load them where the columns were, combine, store
-    rows_to_lds(Jt);
-    __syncthreads();
-    // J^T_new = T J^T_old on the fp64 matrix cores: result tiles of 16 local rows x 16 positions, NC / 4 steps each.
-    // A wavefront keeps its A operands (the NC x NC transform) in registers and walks the position tiles; its B
-    // operands are the old rows in LDS, so writing the new rows to memory in place disturbs nothing.
-    {
-        constexpr int MT = NC / 16, KS = NC / 4;
-        const int lr = lane & 15, lk = lane >> 4;
-        double ta[MT][KS];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) ta[mt][ks] = T[(16 * mt + lr) * NC + 4 * ks + lk];
-        const int n_tiles = (r + 15) / 16;
-        for (int nt = w; nt < n_tiles; nt += NC / 2) {
-            const int i = 16 * nt + lr;
-            double tb[KS];
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) tb[ks] = cols[(4 * ks + lk) * RP + i];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[mt][ks], tb[ks], acc, 0, 0, 0);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int gc = gcol(16 * mt + lk + 4 * v);
-                    if (gc < r && i < r) Jt[(size_t)gc * r + i] = acc[v];
-                }
+            for (int v = 0; v < 4; ++v) {
+                G[(16 * sa + kk + 4 * v) * kJacLP + 16 * sc0 + l16] = acc[v];
+                if (w == 2) G[(16 + l16) * kJacLP + kk + 4 * v] = acc[v];
             }
         }
+    } else {
+        const int lj = tid & 31, li = tid >> 5, cj = fz_pair_column(blk, lj);
+        double g[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int ri = fz_pair_column(blk, li + 8 * u);
+            g[u] = (ri < r && cj < r) ? M[(size_t)ri * r + cj] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) G[(li + 8 * u) * kJacLP + lj] = g[u];
+    }
+    if (tid == 0) big_rotations = 0;
+    __syncthreads();
+
+    int big = 0;
+    auto note = [&](double al, double be, double ga) __attribute__((always_inline)) {
+        if (pr == pc && al * al > kJacobiSettled * kJacobiSettled * fabs(be * ga)) ++big;
+    };
+    double ta[2], tb[2];  // rows a, b of pair pc of T, columns 2 pr and 2 pr + 1
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        ta[u] = pc == 2 * pr + u ? 1.0 : 0.0;
+        tb[u] = 16 + pc == 2 * pr + u ? 1.0 : 0.0;
+    }
+    if (round == 0) {
+        // once per sweep, every block being in exactly one pair of the round: the pairs inside the two blocks, as halves
+        // of 8, then of 4, 2 and 1 that meet each other
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            Ts[pc * kJacLP + 2 * pr + u] = ta[u];
+            Ts[(16 + pc) * kJacLP + 2 * pr + u] = tb[u];
+        }
+        for (int h = 8; h >= 1; h >>= 1)
+            for (int t = 0; t < h; ++t) {
+                const int ar = pr / h * 2 * h + pr % h, br = pr / h * 2 * h + h + (pr + t) % h;
+                const int ac = pc / h * 2 * h + pc % h, bc = pc / h * 2 * h + h + (pc + t) % h;
+                __syncthreads();
+                double cc, sc;
+                fz_rotation(G[ac * kJacLP + bc], G[ac * kJacLP + ac], G[bc * kJacLP + bc], cc, sc);
+                const double cr = fz_from_lane(cc, (lane & 48) | pr), sr = fz_from_lane(sc, (lane & 48) | pr);
+                note(G[ac * kJacLP + bc], G[ac * kJacLP + ac], G[bc * kJacLP + bc]);
+                const double aa = G[ar * kJacLP + ac], ab = G[ar * kJacLP + bc], ba = G[br * kJacLP + ac], bb = G[br * kJacLP + bc];
+                const double x0 = cr * aa - sr * ba, x1 = cr * ab - sr * bb, y0 = sr * aa + cr * ba, y1 = sr * ab + cr * bb;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const double x = Ts[ac * kJacLP + 2 * pr + u], y = Ts[bc * kJacLP + 2 * pr + u];
+                    Ts[ac * kJacLP + 2 * pr + u] = cc * x - sc * y;
+                    Ts[bc * kJacLP + 2 * pr + u] = sc * x + cc * y;
+                }
+                __syncthreads();
+                G[ar * kJacLP + ac] = cc * x0 - sc * x1;
+                G[ar * kJacLP + bc] = pr == pc ? 0.0 : sc * x0 + cc * x1;
+                G[br * kJacLP + ac] = pr == pc ? 0.0 : cc * y0 - sc * y1;
+                G[br * kJacLP + bc] = sc * y0 + cc * y1;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            ta[u] = Ts[pc * kJacLP + 2 * pr + u];
+            tb[u] = Ts[(16 + pc) * kJacLP + 2 * pr + u];
+        }
+    }
+    double aa = G[pr * kJacLP + pc], ab = G[pr * kJacLP + 16 + pc], ba = G[(16 + pr) * kJacLP + pc], bb = G[(16 + pr) * kJacLP + 16 + pc];
+    double al = G[pc * kJacLP + 16 + pc], be = G[pc * kJacLP + pc], ga = G[(16 + pc) * kJacLP + 16 + pc];
+    for (int t = 0; t < kJacBS; ++t) {
+        const int par = t & 1;
+        double cc, sc;
+        fz_rotation(al, be, ga, cc, sc);
+        // (every 16 lanes compute the rotations of all pairs, for their columns; the one of their row is among them)
+        const double cr = fz_from_lane(cc, (lane & 48) | pr), sr = fz_from_lane(sc, (lane & 48) | pr);
+        note(al, be, ga);
+        const double x0 = cr * aa - sr * ba, x1 = cr * ab - sr * bb, y0 = sr * aa + cr * ba, y1 = sr * ab + cr * bb;
+        aa = cc * x0 - sc * x1;
+        ab = fz_next_of_16(pr == pc ? 0.0 : sc * x0 + cc * x1);
+        ba = pr == pc ? 0.0 : cc * y0 - sc * y1;
+        bb = fz_next_of_16(sc * y0 + cc * y1);
+        mv[par][pr][pc] = fz_f64x2_t{ba, bb};
+        if (pr == pc) *reinterpret_cast<fz_f64x2_t *>(dg[par][pc]) = fz_f64x2_t{ab, aa};
+        if (pr == ((pc + 1) & 15)) dg[par][pc][2] = bb;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const double x = ta[u], y = tb[u];
+            ta[u] = cc * x - sc * y;
+            tb[u] = fz_next_of_16(sc * x + cc * y);
+        }
+        __syncthreads();
+        const fz_f64x2_t m = mv[par][(pr + 1) & 15][pc], c2 = *reinterpret_cast<const fz_f64x2_t *>(dg[par][pc]);
+        ba = m[0];
+        bb = m[1];
+        al = c2[0];
+        be = c2[1];
+        ga = dg[par][pc][2];
+    }
+    *reinterpret_cast<fz_f64x2_t *>(T + pc * kJacNC + 2 * pr) = fz_f64x2_t{ta[0], ta[1]};
+    *reinterpret_cast<fz_f64x2_t *>(T + (16 + pc) * kJacNC + 2 * pr) = fz_f64x2_t{tb[0], tb[1]};
+    if (big > 0) atomicAdd(&big_rotations, big);
+    __syncthreads();
+    if (tid == 0 && big_rotations > 0) atomicAdd(count, big_rotations);
+}
+
+__global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restrict__ Ma, double *__restrict__ Mb,
+                                                           double *__restrict__ Jt, const double *__restrict__ T,
+                                                           double *__restrict__ T_next, long long t_seq, int *rotations, int r,
+                                                           int n_blocks, int k)
+{
+    // rotations[sequence][sweep]: written by the workgroups that find the rotations of that sweep; final before a launch
+    // that applies the sweep's last ones, and a sweep without any ends the work of all later launches
+    rotations += blockIdx.z * kJacobiSweeps;
+    Ma += (size_t)blockIdx.z * r * r;
+    T += (size_t)blockIdx.z * t_seq;
+    const int n_pairs = n_blocks / 2, n_tri = n_pairs * (n_pairs + 1) / 2, m1 = n_blocks - 1;
+    int x = (int)blockIdx.x;
+    if (x < n_pairs) {
+        const int sweep = (k + 1) / m1;
+        if (sweep == kJacobiSweeps || (sweep > 0 && rotations[sweep - 1] == 0)) return;  // same for the whole workgroup
+        fz_find_rotations(Ma, k < 0 ? nullptr : T, T_next + (size_t)blockIdx.z * t_seq, rotations + sweep, r, n_blocks, (k + 1) % m1, x);
+        return;
+    }
+    x -= n_pairs;
+    const int round = k % m1;
+    if (k >= m1 && rotations[k / m1 - 1] == 0) return;
+    __shared__ double Y[kJacNC * kJacLP];
+    Mb += (size_t)blockIdx.z * r * r;
+    Jt += (size_t)blockIdx.z * r * r;
+    constexpr int KS = kJacNC / 4;
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id(), l16 = lane & 15, kk = lane >> 4;
+    if (x >= n_tri) {  // wavefront = 16 positions
+        const int p = (x - n_tri) % n_pairs, i = (x - n_tri) / n_pairs * 64 + 16 * w + l16;
+        int blk[2];
+        fz_pair_of_blocks(p, round, n_blocks, blk);
+        const double *Tp = T + (size_t)p * kJacNC * kJacNC;
+        double tv[KS], ta[2][KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int c = fz_pair_column(blk, 4 * ks + kk);
+            tv[ks] = (c < r && i < r) ? Jt[(size_t)c * r + i] : 0.0;
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) ta[mt][ks] = Tp[(16 * mt + l16) * kJacNC + 4 * ks + kk];
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[mt][ks], tv[ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int c = fz_pair_column(blk, 16 * mt + kk + 4 * v);
+                if (c < r && i < r) Jt[(size_t)c * r + i] = acc[v];
+            }
+        }
+        return;
+    }
+    int p, q, bp[2], bq[2];
+    fz_lower_pair(x, p, q);
+    fz_pair_of_blocks(p, round, n_blocks, bp);
+    fz_pair_of_blocks(q, round, n_blocks, bq);
+    const double *Tp = T + (size_t)p * kJacNC * kJacNC, *Tq = T + (size_t)q * kJacNC * kJacNC;
+    const int mt = w >> 1, nt = w & 1;  // wavefront = one tile of 16 x 16
+    double xa[KS], tq[KS], tp[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        const int ra = fz_pair_column(bp, 16 * mt + l16), cb = fz_pair_column(bq, 4 * ks + kk);
+        xa[ks] = (ra < r && cb < r) ? Ma[(size_t)ra * r + cb] : 0.0;
+        tq[ks] = Tq[(16 * nt + l16) * kJacNC + 4 * ks + kk];
+        tp[ks] = Tp[(16 * mt + l16) * kJacNC + 4 * ks + kk];
+    }
+    fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[ks], tq[ks], acc, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Y[(16 * mt + kk + 4 * v) * kJacLP + 16 * nt + l16] = acc[v];
+    __syncthreads();
+    acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[ks], Y[(4 * ks + kk) * kJacLP + 16 * nt + l16], acc, 0, 0, 0);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Y[(16 * mt + kk + 4 * v) * kJacLP + 16 * nt + l16] = acc[v];
+    __syncthreads();
+    const int lj = tid & 31, li = tid >> 5;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // M' stays symmetric to the last bit
+        const int i = li + 8 * u, ra = fz_pair_column(bp, i), cb = fz_pair_column(bq, lj);
+        const bool swap = p == q && i > lj;
+        if (ra < r && cb < r) Mb[(size_t)ra * r + cb] = Y[(swap ? lj : i) * kJacLP + (swap ? i : lj)];
+        const int rb = fz_pair_column(bq, i), ca = fz_pair_column(bp, lj);
+        if (p != q && rb < r && ca < r) Mb[(size_t)rb * r + ca] = Y[lj * kJacLP + i];
     }
 }
 
-// (5d) eigenvalues = norms of the rows of Gt; order[k] = the column with the k-th largest one (ties: smaller index);
-// sigma (nullable) receives the singular values sqrt(lambda) of the leading r_out, in that order.
-__global__ __launch_bounds__(1024) void ritz_order_kernel(const double *__restrict__ Gt, int *__restrict__ order,
+// (5d) eigenvalues = |diagonal| of the rotated matrix; order[k] = the column with the k-th largest one (ties: smaller
+// index); sigma (nullable) receives the singular values sqrt(lambda) of the leading r_out, in that order.  A sweep is an
+// odd number of rounds, each from one buffer to the other, so the matrix lies in Mb after an odd number of sweeps.
+__global__ __launch_bounds__(1024) void ritz_order_kernel(const double *__restrict__ Ma, const double *__restrict__ Mb,
+                                                          const int *__restrict__ rotations, int *__restrict__ order,
                                                           float *__restrict__ sigma, int r, int r_out)
 {
     __shared__ double lam[1024];
-    Gt += (size_t)blockIdx.x * r * r;
+    rotations += blockIdx.x * kJacobiSweeps;
+    int sweeps = 1;
+    while (sweeps < kJacobiSweeps && rotations[sweeps - 1] != 0) ++sweeps;
+    const double *M = (sweeps & 1 ? Mb : Ma) + (size_t)blockIdx.x * r * r;
     order += (size_t)blockIdx.x * r;
-    const int lane = lane_id(), w = wave_id();
-    for (int c = w; c < r; c += 16) {
-        double sum = 0.0;
-        for (int i = lane; i < r; i += kWave) sum = fma(Gt[(size_t)c * r + i], Gt[(size_t)c * r + i], sum);
-        sum = fz_wave_sum_f64(sum);
+    const int c = threadIdx.x;
+    if (c < r) {
         // (a NaN would compare as neither larger nor equal and leave places of `order` unwritten: it goes last)
-        if (lane == 0) lam[c] = sum >= 0.0 ? sqrt(sum) : -1.0;
+        const double v = fabs(M[(size_t)c * r + c]);
+        lam[c] = v >= 0.0 ? v : -1.0;
     }
     __syncthreads();
-    const int c = threadIdx.x;
     if (c < r) {
         int rank = 0;
         const double mine = lam[c];
@@ -1052,7 +1155,25 @@ __global__ __launch_bounds__(1024) void ritz_order_kernel(const double *__restri
     }
 }
 
-// (5e) the leading r_out rotated basis vectors: Vr[k][c] = sum_j Jt[order[k]][j] Vt[j][c], thread = column c, eight k.
+// (5e) the leading r_out rotated basis vectors: Vr[k][c] = sum_j Jt[order[k]][j] Vt[j][c] on the fp64 matrix cores.
+// Wavefront = 32 k x 64 positions c, eight products per four j; four steps at a time, their operands requested before the
+// products of the four before.  The matrix cores bound it (27 us at r = 512, n = 4096); 69 us, thread = position with vector multiply-adds
+// 170 us.
+__device__ __forceinline__ void fz_rotate_fetch(double (&ja)[4][2], float (&vb)[4][4], const double *const (&jrow)[2],
+                                                const float *__restrict__ Vt, int j0, int r, int n, const int (&cc)[4], int kk)
+{
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int j = j0 + 4 * s + kk;
+        const bool ok = j < r;
+        const int jj = ok ? j : 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) ja[s][u] = ok ? jrow[u][jj] : 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) vb[s][v] = Vt[(size_t)jj * n + cc[v]];
+    }
+}
+
 __global__ __launch_bounds__(256) void rotate_basis_kernel(const double *__restrict__ Jt, const int *__restrict__ order,
                                                            const float *__restrict__ Vt, float *__restrict__ Vr, int n,
                                                            int r, int r_out, long long vr_seq)
@@ -1061,21 +1182,52 @@ __global__ __launch_bounds__(256) void rotate_basis_kernel(const double *__restr
     order += (size_t)blockIdx.z * r;
     Vt += (size_t)blockIdx.z * r * n;
     Vr += (size_t)blockIdx.z * vr_seq;
-    const int c = blockIdx.x * 256 + threadIdx.x, k0 = blockIdx.y * 8;
-    const double *jrow[8];
+    const int lane = lane_id(), l16 = lane & 15, kk = lane >> 4, c0 = (blockIdx.x * 4 + wave_id()) * 64, k0 = blockIdx.y * 32;
+    if (c0 >= n) return;
+    const double *jrow[2];
+    int cc[4];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) jrow[u] = Jt + (size_t)order[k0 + u < r_out ? k0 + u : r_out - 1] * r;
-    double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const int cc = c < n ? c : n - 1;
-    for (int j = 0; j < r; ++j) {
-        const double v = (double)Vt[(size_t)j * n + cc];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] = fma(jrow[u][j], v, acc[u]);
+    for (int u = 0; u < 2; ++u) {
+        const int k = k0 + 16 * u + l16;
+        jrow[u] = Jt + (size_t)order[k < r_out ? k : r_out - 1] * r;
     }
-    if (c < n)
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (k0 + u < r_out) Vr[(size_t)(k0 + u) * n + c] = (float)acc[u];
+    for (int v = 0; v < 4; ++v) cc[v] = c0 + 16 * v + l16 < n ? c0 + 16 * v + l16 : n - 1;
+    fz_f64x4_t acc[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[u][v] = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+    double ja[4][2];
+    float vb[4][4];
+    fz_rotate_fetch(ja, vb, jrow, Vt, 0, r, n, cc, kk);
+    for (int j0 = 0; j0 < r; j0 += 16) {
+        double a[4][2], b[4][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) a[s][u] = ja[s][u];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) b[s][v] = (double)vb[s][v];
+        }
+        if (j0 + 16 < r) fz_rotate_fetch(ja, vb, jrow, Vt, j0 + 16, r, n, cc, kk);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][u], b[s][v], acc[u][v], 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = k0 + 16 * u + kk + 4 * e;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (k < r_out && c0 + 16 * v + l16 < n) Vr[(size_t)k * n + c0 + 16 * v + l16] = (float)acc[u][v][e];
+        }
 }
 
 // (4a) B_out[l][i][c] = Vt[i][l * d + c] in the storage type.
@@ -1201,8 +1353,8 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
         // Vt <- orthonormal basis of the columns of Wn (Cholesky-QR: r x r Gram matrix, Cholesky factor, solve; fp64)
         auto orthonormalise = [&]() {
             const int gb = (r + 31) / 32, pairs = gb * (gb + 1) / 2;
-            hipLaunchKernelGGL(gram_f64_kernel, dim3((pairs + 3) / 4, f.g_splits, nb), dim3(256), 0, st, Wn, planes, n, r,
-                               f.g_splits, pairs);
+            hipLaunchKernelGGL(gram_f64_kernel<true>, dim3((pairs + 3) / 4, f.g_splits, nb), dim3(256), 0, st, Wn, vcount, Wn,
+                               planes, n, r, f.g_splits, pairs);
             hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                f.g_splits);
             for (int c0 = 0; c0 < r; c0 += f.chol_pb) {
@@ -1235,7 +1387,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
         // Cholesky-QR once more on the basis itself: after the last multiplication by C the weakest directions are
         // orthonormal only to fp32 rounding times the spread of the spectrum; a second pass on a matrix that is already
         // nearly orthonormal brings them to fp32 rounding
-        hipLaunchKernelGGL(transpose_v_kernel, dim3((n + 31) / 32, (r + 31) / 32, nb), dim3(256), 0, st, Vt, Wn, n, r);
+        hipLaunchKernelGGL(transpose_v_kernel, dim3((n + 31) / 32, (r + 31) / 32, nb), dim3(256), 0, st, Vt, Wn, vcount, n, r);
         orthonormalise();
         if (e != hipSuccess) break;
         // ---- rotation to singular vectors (5): Wn = C Vt^T once more, M = Vt Wn, eigenvectors of M by block Jacobi
@@ -1251,33 +1403,31 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                 hipLaunchKernelGGL(sum_planes_kernel, dim3(blocks256(vcount), 1, nb), dim3(256), 0, st, part, Wn, vcount,
                                    f.w_splits, vcount, (long long)f.part_seq);
         }
-        double *Mr = planes, *Gt = Gm, *Jt = Lt;  // r x r each per sequence
+        double *Ma = Gm, *Mb = planes, *Jt = Lt;  // r x r each per sequence
+        // the rotations of two rounds, 32 x 32 per pair of blocks, at most 16 (r + 32) doubles each, where C (no longer needed)
+        // and the transposed basis are: n^2 / 2 doubles or more, n a multiple of 64
+        const long long tj_seq = (long long)n * n / 2;
+        double *Tj[2] = {reinterpret_cast<double *>(part), reinterpret_cast<double *>(C)};
         int *order = reinterpret_cast<int *>(Minv);
-        const int rb = (r + 31) / 32;
-        hipLaunchKernelGGL(ritz_matrix_kernel, dim3(rb, rb, nb), dim3(256), 0, st, Vt, Wn, Mr, n, r);
-        hipLaunchKernelGGL(jacobi_init_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, Mr, Gt, Jt, rotations, r);
+        const int gb = (r + 31) / 32;
+        hipLaunchKernelGGL(transpose_v_kernel, dim3((n + 31) / 32, gb, nb), dim3(256), 0, st, Vt, part, (long long)f.part_seq, n, r);
+        hipLaunchKernelGGL(gram_f64_kernel<false>, dim3((gb * gb + 3) / 4, f.g_splits, nb), dim3(256), 0, st, part,
+                           (long long)f.part_seq, Wn, planes, n, r, f.g_splits, gb * gb);
+        hipLaunchKernelGGL(jacobi_init_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Ma, Jt,
+                           rotations, r, f.g_splits);
         {
-            const int nc = r <= 512 ? 32 : 16, bs = nc / 2;
-            const int n_blocks = std::max(2, ((r + bs - 1) / bs + 1) / 2 * 2);  // an even number of column blocks
-            const size_t lds = ((size_t)nc * (nc == 32 ? 512 : 1024) + (size_t)nc * nc) * 8;  // columns at their full pitch
-            static DynamicLdsOnce attr32, attr16;
-            e = nc == 32 ? attr32.ensure((const void *)jacobi_round_kernel<32>, 160 * 1024 - 256)
-                         : attr16.ensure((const void *)jacobi_round_kernel<16>, 160 * 1024 - 256);
-            if (e != hipSuccess) break;
-            for (int sweep = 0; sweep < kJacobiSweeps; ++sweep)
-                for (int round = 0; round < n_blocks - 1; ++round) {
-                    if (nc == 32)
-                        hipLaunchKernelGGL(jacobi_round_kernel<32>, dim3(n_blocks / 2, 1, nb), dim3(16 * 64), lds, st, Gt, Jt,
-                                           rotations, r, n_blocks, sweep, round);
-                    else
-                        hipLaunchKernelGGL(jacobi_round_kernel<16>, dim3(n_blocks / 2, 1, nb), dim3(8 * 64), lds, st, Gt, Jt,
-                                           rotations, r, n_blocks, sweep, round);
-                }
+            const int n_blocks = std::max(2, ((r + kJacBS - 1) / kJacBS + 1) / 2 * 2);  // an even number of column blocks
+            const int n_pairs = n_blocks / 2, grid = n_pairs * (n_pairs + 1) / 2 + n_pairs * ((r + 63) / 64);
+            for (int k = -1; k < kJacobiSweeps * (n_blocks - 1); ++k) {
+                const bool odd = k & 1;
+                hipLaunchKernelGGL(jacobi_round_kernel, dim3(k < 0 ? n_pairs : n_pairs + grid, 1, nb), dim3(256), 0, st,
+                                   k >= 0 && odd ? Mb : Ma, odd ? Ma : Mb, Jt, Tj[odd], Tj[!odd], tj_seq, rotations, r, n_blocks, k);
+            }
         }
-        hipLaunchKernelGGL(ritz_order_kernel, dim3(nb), dim3(1024), 0, st, Gt, order,
+        hipLaunchKernelGGL(ritz_order_kernel, dim3(nb), dim3(1024), 0, st, Ma, Mb, rotations, order,
                            sigma_out ? sigma_out + (size_t)b0 * r_out : nullptr, r, r_out);
         float *Vr = Wn;  // [r_out][n] per sequence, in the place of W
-        hipLaunchKernelGGL(rotate_basis_kernel, dim3((n + 255) / 256, (r_out + 7) / 8, nb), dim3(256), 0, st, Jt, order, Vt,
+        hipLaunchKernelGGL(rotate_basis_kernel, dim3((n + 255) / 256, (r_out + 31) / 32, nb), dim3(256), 0, st, Jt, order, Vt,
                            Vr, n, r, r_out, vcount);
         if ((e = hipGetLastError()) != hipSuccess) break;
         T *Bb = reinterpret_cast<T *>(B_out) + (size_t)b0 * s.G * r_out * d;
