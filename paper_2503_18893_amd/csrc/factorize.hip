@@ -22,6 +22,7 @@
 #include "xkv_common.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace xkv {
 namespace {
@@ -470,32 +471,36 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
     if (i == j) diag0[i] = v;
 }
 
-// (3c) Cholesky factor Lc of G + shift I, right-looking, one launch per panel of PB columns [c0, c0 + PB).
-// Workgroup j owns rows i0 = c0 + 32 j .. i0 + 31 of G and touches nothing else, so the workgroups of a launch do
-// not depend on each other; what they need of the panel beyond their own rows they recompute:
-//   1. every workgroup factors the PB x PB diagonal block (current values of G, shift added) in LDS and inverts the
-//      factor, one elimination over the block and an identity beside it: a step reads the pivot column and the pivot row
-//      of the identity and updates two elements of each per thread, so it needs one barrier;
-//   2. the panel entries Lc[j'][c0 .. c0 + PB) of all rows j' from the diagonal block down to its own last row are
-//      G[j'][panel] times the transposed inverse (fp64 matrix cores, 16 rows a step) and stay in LDS;
-//   3. it subtracts the panel's outer product from its own rows of the trailing matrix, G[i][j'] -= Lc[i] . Lc[j'] (fp64
-//      matrix cores again).
-// Own rows of the panel are written to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a
-// later substitution needs is a contiguous row; the first workgroup also writes the inverses of the 16 x 16 diagonal blocks,
-// Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity), which are the diagonal blocks of its inverse.
+// (3c) Cholesky factor Lc of G + shift I, right-looking in panels of PB columns, and beside it the inverses of the
+// diagonal blocks.  A launch has two kinds of workgroups:
+//   * workgroup j >= 1 owns the 32 rows from c0 + PB + 32 (j - 1) of G and touches nothing else.  The panel entries
+//     Lc[j'][c0 .. c0 + PB) of all rows below the diagonal block down to its own last row are G[j'][panel] times the
+//     transposed inverse of the diagonal block's factor (fp64 matrix cores, 16 rows a step) and stay in LDS; it subtracts
+//     the panel's outer product from its own rows of the trailing matrix, G[i][j'] -= Lc[i] . Lc[j'].  Own rows of the
+//     panel are written to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a later substitution
+//     needs is a contiguous row;
+//   * workgroup 0 prepares the next panel: it brings the next diagonal block up to date by itself (its 32 panel rows and one
+//     outer product), factors and inverts it, and leaves the inverse in LI for the next launch (two places in turn, the
+//     other workgroups of this launch still read theirs), the factor's columns in Lt and the inverses of the 16 x 16
+//     diagonal blocks in Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity).  The first launch, c0 = -PB,
+//     has only this workgroup.
+// The elimination runs in one wavefront without a barrier: lane i holds row i of the block and lane 32 + i column i of an
+// identity, and step c is the same for both: t = x[c] / sqrt(pivot), x[j] -= (t of lane j) t for j > c.  What t leaves in
+// the lanes are column c of the factor and row c of its inverse.  The elements move one register down at each step, so
+// that the steps are a loop.
 // shift = 1e-13 * max diagonal of the original G (diag0) keeps the factor defined when the r vectors are
 // numerically dependent (an X_cat of rank below r): such directions come out short instead of normalised and
 // contribute nothing to A B.
-// What bounds it: the chain of its 16 launches at r = 512, and in each the elimination (PB dependent steps).  With the
-// panel solved by one thread per row (496 dependent multiply-adds) and vector multiply-adds in the trailing update a launch
-// took 58 us on average
-// at r = 512, now 29 us (18 us the last one, which is the elimination alone).
+// What bounds it: the chain of its 16 launches at r = 512, and in each the elimination (PB dependent steps, 9 us), which
+// here runs beside the trailing update of the same launch.  Every workgroup eliminating the block before its update
+// took 29 us per launch on average, now 21.6 us.
 constexpr int kCholRB = 32, kCholThreads = 512, kSolveIB = 16;
 constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
-constexpr size_t chol_lds(int pb, int rows)  // the inverse, then the panel's rows (at least the space of the elimination)
+constexpr size_t chol_lds(int pb, int rows)  // panel rows below the diagonal block; workgroup 0: its rows and two blocks
 {
-    const int all = (rows + 15) / 16 * 16, least = pb + (2 * pb * (pb + 1) + chol_pitch(pb) - 1) / chol_pitch(pb);
-    return ((size_t)pb * (pb + 1) + (size_t)(all > least ? all : least) * chol_pitch(pb)) * 8;
+    const size_t all = (size_t)((rows + 15) / 16 * 16) * chol_pitch(pb);
+    const size_t head = (size_t)pb * chol_pitch(pb) + 3 * (size_t)pb * (pb + 1);
+    return (all > head ? all : head) * 8;
 }
 
 // 1 / sqrt(x): the hardware's estimate y (better than 2^-20) and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with
@@ -506,44 +511,121 @@ __device__ __forceinline__ double fz_rsqrt(double x)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
+__device__ __forceinline__ double fz_readlane(double x, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
 template <int PB>
 __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Lt,
-                                                                  double *__restrict__ Minv, const double *__restrict__ diag0,
-                                                                  int r, int c0)
+                                                                  double *__restrict__ Minv, const double *LI_now,
+                                                                  double *LI_next, long long li_seq,
+                                                                  const double *__restrict__ diag0, int r, int c0)
 {
     constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64, NB = 4;
     G += (size_t)blockIdx.z * r * r;
     Lt += (size_t)blockIdx.z * r * r;
     Minv += (size_t)blockIdx.z * ((r + kSolveIB - 1) / kSolveIB) * (kSolveIB * kSolveIB);
+    LI_now += blockIdx.z * li_seq;
     diag0 += (size_t)blockIdx.z * r;
     extern __shared__ __attribute__((aligned(16))) unsigned char fz_smem[];
-    double *LI = reinterpret_cast<double *>(fz_smem);  // [PB][LP] inverse of the diagonal block's factor
-    double *P = LI + PB * LP;                           // [rows][PITCH] panel entries of Lc, the diagonal block first
-    double *D = P + PB * PITCH, *E = D + PB * LP;       // elimination: where the panel's other rows come later
-    __shared__ double red[WAVES];
+    double *P = reinterpret_cast<double *>(fz_smem);  // [rows][PITCH] panel entries of Lc
     const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), l16 = lane & 15, kk = lane >> 4;
-    const int pwc = (r - c0) < PB ? (r - c0) : PB;
-    const int i0 = c0 + blockIdx.x * kCholRB;
-    const int own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
-    const int nrows = own_end - c0;
-    const int nq = nrows > PB ? (nrows - PB + 15) / 16 : 0;  // blocks of 16 rows below the diagonal block
+    const int d0 = c0 + PB;  // first row below the diagonal block
 
-    // operands of this wavefront's first blocks: requested now, used in step 2
+    // the inverse as the second operand of the product with the panel (rows of the inverse = columns of the result)
+    double lb[CT][KS];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) lb[ct][ks] = c0 >= 0 ? LI_now[(16 * ct + l16) * PB + 4 * ks + kk] : 0.0;
     double ga[NB][KS];
-    auto fetch = [&](int q0) __attribute__((always_inline)) {
+    auto fetch = [&](int q0, int n_q, int end) __attribute__((always_inline)) {  // 16 rows each, blocks q0, q0 + WAVES, ..
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            const int row = c0 + PB + 16 * (q0 + WAVES * u) + l16;
+            const int row = d0 + 16 * (q0 + WAVES * u) + l16;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int c = 4 * ks + kk;
-                ga[u][ks] = (q0 + WAVES * u < nq && row < own_end && c < pwc) ? G[(size_t)row * r + c0 + c] : 0.0;
-            }
+            for (int ks = 0; ks < KS; ++ks)
+                ga[u][ks] = (q0 + WAVES * u < n_q && row < end) ? G[(size_t)row * r + c0 + 4 * ks + kk] : 0.0;
         }
     };
-    fetch(w);
+    auto panel_rows = [&](int q, const double (&g)[KS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(g[ks], lb[ct][ks], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) P[(16 * q + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
+        }
+    };
+    auto outer = [&](int rs, int cs) __attribute__((always_inline)) {  // tile of 16 x 16 of the panel's outer product
+        fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(rs + l16) * PITCH + 4 * ks + kk], P[(cs + l16) * PITCH + 4 * ks + kk], acc, 0, 0, 0);
+        return acc;
+    };
+
+    if (blockIdx.x > 0) {
+        const int i0 = d0 + ((int)blockIdx.x - 1) * kCholRB;
+        const int own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
+        const int n_q = (own_end - d0 + 15) / 16;
+        for (int q0 = w; q0 < n_q; q0 += WAVES * NB) {
+            fetch(q0, n_q, own_end);
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (q0 + WAVES * u < n_q) panel_rows(q0 + WAVES * u, ga[u]);
+        }
+        __syncthreads();
+        for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
+            const int c = t / kCholRB, row = i0 + t % kCholRB;
+            if (row < own_end) Lt[(size_t)(c0 + c) * r + row] = P[(row - d0) * PITCH + c];
+        }
+        // own rows of the trailing matrix: tiles on or below the diagonal
+        const int own_t = (i0 - d0) / 16, n_rt = (own_end - i0 + 15) / 16;  // row tile rt has own_t + rt + 1 column tiles
+        for (int item = w;; item += WAVES) {
+            int rt = 0, ctile = item;
+            while (rt < n_rt && ctile > own_t + rt) {
+                ctile -= own_t + rt + 1;
+                ++rt;
+            }
+            if (rt >= n_rt) break;
+            const int rs = i0 - d0 + 16 * rt, cs = 16 * ctile;
+            double old[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int irow = d0 + rs + kk + 4 * v, jc = d0 + cs + l16;
+                old[v] = (irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
+            }
+            const fz_f64x4_t acc = outer(rs, cs);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int irow = d0 + rs + kk + 4 * v, jc = d0 + cs + l16;
+                // (the next diagonal block is workgroup 0's: it reads what this launch began with)
+                if (irow < own_end && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
+            }
+        }
+        return;
+    }
+
+    // ---- workgroup 0: the next diagonal block, rows and columns d0 .. d0 + pwc - 1
+    double *D = P + PB * PITCH, *LF = D + PB * LP, *LI = LF + PB * LP;  // [PB][LP] block, its factor, the inverse
+    __shared__ double red[WAVES];
+    const int pwc = (r - d0) < PB ? (r - d0) : PB;
     double mx = 0.0;
     for (int i = tid; i < r; i += kCholThreads) mx = fmax(mx, diag0[i]);
+    double g0[CT][4];  // this wavefront's tile (w / CT, w % CT) of the block
+    const int tr = w / CT, tc = w % CT;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = 16 * tr + kk + 4 * v, j = 16 * tc + l16;
+        g0[0][v] = (w < CT * CT && i < pwc && j <= i) ? G[(size_t)(d0 + i) * r + d0 + j] : 0.0;
+    }
+    if (c0 >= 0 && w < CT) {
+        fetch(w, CT, d0 + pwc);
+        panel_rows(w, ga[0]);
+    }
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
     if (lane == 0) red[w] = mx;
     __syncthreads();
@@ -551,105 +633,50 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
 #pragma unroll
     for (int ww = 1; ww < WAVES; ++ww) mx = fmax(mx, red[ww]);
     const double shift = fmax(1e-13 * mx, 1e-300);
-
-    // ---- 1. elimination: thread = row i and columns j0, j0 + 16 (PB = 16: half of the threads take part)
-    constexpr int NJ = PB / 16;
-    const int ei = tid / 16, j0 = tid % 16;
-    const bool in = ei < PB;
-    double d[NJ], e[NJ];
-#pragma unroll
-    for (int u = 0; u < NJ; ++u) {
-        const int j = j0 + 16 * u;
-        d[u] = ei == j ? 1.0 : 0.0;  // (rows beyond the panel are identity rows)
-        if (in && ei < pwc && j <= ei) d[u] = G[(size_t)(c0 + ei) * r + c0 + j] + (ei == j ? shift : 0.0);
-        e[u] = ei == j ? 1.0 : 0.0;
-        if (in) {
-            D[ei * LP + j] = d[u];
-            E[ei * LP + j] = e[u];
-        }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int c = 0; c < PB; ++c) {
-        if (in) {
-            const double piv = D[c * LP + c], lic = D[ei * LP + c];
-            const double dinv = fz_rsqrt(piv > shift * 1e-3 ? piv : shift * 1e-3);
-            const double l = lic * dinv;
-#pragma unroll
-            for (int u = 0; u < NJ; ++u) {
-                const int j = j0 + 16 * u;
-                const double ljc = D[j * LP + c] * dinv, ecj = E[c * LP + j] * dinv;
-                if (ei > c) {
-                    if (j > c && j <= ei) D[ei * LP + j] = d[u] = d[u] - l * ljc;
-                    if (j <= c) E[ei * LP + j] = e[u] = e[u] - l * ecj;
-                }
-                if (ei == c) LI[c * LP + j] = j <= c ? ecj : 0.0;
-                if (j == c) P[ei * PITCH + c] = ei >= c ? l : 0.0;
-            }
-        }
-        __syncthreads();
-    }
-
-    // ---- 2. panel entries of the rows below the diagonal block
-    double lb[CT][KS];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) lb[ct][ks] = LI[(16 * ct + l16) * LP + 4 * ks + kk];
-    for (int q0 = w; q0 < nq; q0 += WAVES * NB) {
-        if (q0 != w) fetch(q0);
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int q = q0 + WAVES * u;
-            if (q < nq) {
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[u][ks], lb[ct][ks], acc, 0, 0, 0);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) P[(PB + 16 * q + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
-                }
-            }
-        }
-    }
-    __syncthreads();
-    for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
-        const int c = t / kCholRB, row = i0 + t % kCholRB;
-        if (row < own_end && c < pwc && row >= c0 + c) Lt[(size_t)(c0 + c) * r + row] = P[(row - c0) * PITCH + c];
-    }
-    if (blockIdx.x == 0)
-        for (int t = tid; t < CT * 256; t += kCholThreads) {
-            const int blk = t >> 8, ii = (t >> 4) & 15, jj = t & 15;
-            if (c0 + 16 * blk < r) Minv[(size_t)(c0 / 16 + blk) * 256 + ii * 16 + jj] = LI[(16 * blk + ii) * LP + 16 * blk + jj];
-        }
-
-    // ---- 3. own rows of the trailing matrix: tiles of 16 x 16 on or below the diagonal
-    const int own0 = i0 - c0 > PB ? i0 - c0 : PB;  // first own row below the diagonal block
-    const int n_rt = nrows > own0 ? (nrows - own0 + 15) / 16 : 0;
-    for (int item = w;; item += WAVES) {
-        int rt = 0, ctile = item;  // row tile rt has (own0 - PB) / 16 + rt + 1 column tiles
-        while (rt < n_rt && ctile > (own0 - PB) / 16 + rt) {
-            ctile -= (own0 - PB) / 16 + rt + 1;
-            ++rt;
-        }
-        if (rt >= n_rt) break;
-        const int rs = own0 + 16 * rt, cs = PB + 16 * ctile;
-        double old[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int irow = c0 + rs + kk + 4 * v, jc = c0 + cs + l16;
-            old[v] = (irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
-        }
+    if (w < CT * CT) {
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+        if (c0 >= 0) acc = outer(16 * tr, 16 * tc);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(rs + l16) * PITCH + 4 * ks + kk], P[(cs + l16) * PITCH + 4 * ks + kk], acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int irow = c0 + rs + kk + 4 * v, jc = c0 + cs + l16;
-            if (irow < own_end && jc <= irow) G[(size_t)irow * r + jc] = old[v] - acc[v];
+        for (int v = 0; v < 4; ++v) {  // (rows beyond the matrix are identity rows)
+            const int i = 16 * tr + kk + 4 * v, j = 16 * tc + l16;
+            D[i * LP + j] = (i < pwc && j <= i) ? g0[0][v] - acc[v] + (i == j ? shift : 0.0) : i == j ? 1.0 : 0.0;
         }
+    }
+    __syncthreads();
+    if (w == 0) {
+        const int i = lane & 31;
+        const bool lower = lane < 32;
+        double x[PB];  // x[j]: element c + j of row i of the block, or of column i of the identity, at step c
+#pragma unroll
+        for (int j = 0; j < PB; ++j) x[j] = i >= PB ? 0.0 : lower ? D[i * LP + j] : (i == j ? 1.0 : 0.0);
+        double *out = lower ? LF + i * LP : LI + i;
+        const int step = lower ? 1 : LP;
+        auto steps = [&](auto first) __attribute__((always_inline)) {  // eight steps of at most PB - 1 - C0 elements
+            constexpr int C0 = decltype(first)::value, W = PB - 1 - C0;
+#pragma unroll 1
+            for (int c = C0; c < C0 + 8; ++c) {
+                double piv = fz_readlane(x[0], c);
+                piv = piv > shift * 1e-3 ? piv : shift * 1e-3;
+                const double t = lane < c ? 0.0 : x[0] * fz_rsqrt(piv);
+                if (i < PB) out[c * step] = t;
+#pragma unroll
+                for (int j = 1; j <= W; ++j) x[j - 1] = fma(-fz_readlane(t, c + j), t, x[j]);
+            }
+        };
+        steps(std::integral_constant<int, 0>{});
+        steps(std::integral_constant<int, 8>{});
+        if constexpr (PB == 32) {
+            steps(std::integral_constant<int, 16>{});
+            steps(std::integral_constant<int, 24>{});
+        }
+    }
+    __syncthreads();
+    for (int t = tid; t < PB * PB; t += kCholThreads) {
+        const int c = t / PB, i = t % PB;
+        if (i < pwc && c <= i) Lt[(size_t)(d0 + c) * r + d0 + i] = LF[i * LP + c];
+        if (LI_next) (LI_next + blockIdx.z * li_seq)[t] = LI[c * LP + i];
+        const int ii = c & 15, jj = i & 15;
+        if (c / 16 == i / 16 && d0 + (c & ~15) < r) Minv[(size_t)((d0 + c) / 16) * 256 + ii * 16 + jj] = LI[c * LP + i];
     }
 }
 
@@ -1357,13 +1384,21 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                                planes, n, r, f.g_splits, pairs);
             hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                f.g_splits);
-            for (int c0 = 0; c0 < r; c0 += f.chol_pb) {
-                const dim3 grid((r - c0 + kCholRB - 1) / kCholRB, 1, nb);
-                const size_t lds = chol_lds(f.chol_pb, r - c0);
-                if (f.chol_pb == 32)
-                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, diag0, r, c0);
+            // the inverse of a panel's diagonal block goes from one launch to the next through `planes`, which has been
+            // added up; where no further launch reads it (two panels at most, r^2 may be less than two blocks), nowhere
+            const int pb = f.chol_pb;
+            const long long li_seq = (long long)f.g_splits * r * r;
+            for (int c0 = -pb; c0 + pb < r; c0 += pb) {
+                const dim3 grid(1 + std::max(0, c0 < 0 ? 0 : (r - c0 - pb + kCholRB - 1) / kCholRB), 1, nb);
+                const size_t lds = chol_lds(pb, c0 < 0 ? 0 : r - c0 - pb);
+                double *now = planes + ((c0 / pb) & 1) * pb * pb, *next = planes + ((c0 / pb + 1) & 1) * pb * pb;
+                if (c0 + 2 * pb >= r) next = nullptr;
+                if (pb == 32)
+                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, now, next, li_seq,
+                                       diag0, r, c0);
                 else
-                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, diag0, r, c0);
+                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, now, next, li_seq,
+                                       diag0, r, c0);
             }
             if (r <= 512)
                 hipLaunchKernelGGL((orth_solve_kernel<8, 2>), dim3((n + 31) / 32, 1, nb), dim3(256), 0, st, Wn, Lt, Minv, Vt, n, r);
