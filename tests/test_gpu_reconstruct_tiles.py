@@ -1,0 +1,35 @@
+"""xkv_reconstruct in bf16 at the edges of its tiles: 128 tokens (in eights) x 256 dims (two KV heads), slabs of 32 ranks of
+which the last may be half.
+
+Bound per element: the products are exact in fp32 and their sum is rounded at most r times, r 2^-24 sum |a b|, then the
+result is rounded to bf16 once (8 significant bits, 2^-8 of its size at most)."""
+import numpy as np
+import pytest
+
+from paper_2503_18893_amd import synth
+from paper_2503_18893_amd import binding as xb
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [1, 127, 129, 1100])
+@pytest.mark.parametrize("H_kv,r,batch", [(1, 16, 1), (2, 32, 3), (3, 48, 1), (4, 64, 2), (5, 112, 1), (8, 512, 1), (1, 1024, 2)])
+def test_tiles_against_fp64(H_kv, r, batch, L):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    G, layer, d_h = 2, 1, 128
+    rng = np.random.default_rng(L * 100 + r)
+    shape = xb.Shape(G=G, H_kv=H_kv, H_q=H_kv, d_h=d_h, r_k=r, r_v=r, L=L, k=1, batch=batch, dtype="bf16")
+    A = torch.from_numpy(rng.standard_normal((batch, L, r)).astype(np.float32)).bfloat16().cuda()
+    B = torch.from_numpy(rng.standard_normal((batch, G, r, H_kv * d_h)).astype(np.float32)).bfloat16().cuda()
+    guard = 64
+    X = torch.full((batch * H_kv * L * d_h + guard,), 7.0, dtype=torch.bfloat16, device="cuda")
+    xb.xkv_reconstruct(shape, layer, A, B, r, X[:batch * H_kv * L * d_h])
+    torch.cuda.synchronize()
+    assert (X[batch * H_kv * L * d_h:] == 7.0).all()
+    got = X[:batch * H_kv * L * d_h].double().cpu().numpy().reshape(batch, H_kv, L, d_h)
+    A64, B64 = A.double().cpu().numpy(), B[:, layer].double().cpu().numpy()
+    want = np.matmul(A64, B64).reshape(batch, L, H_kv, d_h).transpose(0, 2, 1, 3)
+    size = np.matmul(np.abs(A64), np.abs(B64)).reshape(batch, L, H_kv, d_h).transpose(0, 2, 1, 3)
+    assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + (1 + 2.0 ** -8) * r * 2.0 ** -24 * size).all()
