@@ -21,7 +21,9 @@ __global__ __launch_bounds__(256) void gather_attend_generic_kernel(
     float *__restrict__ part_o, float *__restrict__ part_ml, int G, int layer, int L, int r_k, int r_v, int H_kv,
     int H_q, int d_h, int k, int splits, int chunk, float scale, float rope_theta)
 {
-    constexpr int TM = 4;
+    // Latency bound: the rank loops issue the loads of UN ranks before the products of the first (one rank at a time, with k =
+    // 32 rows of rank 32 in two rounds of one workgroup, the kernel took 28 us; with this and one round for each of two workgroups 14 us)
+    constexpr int TM = 4, UN = JP == 1 ? 8 : JP == 2 ? 4 : 2;
     const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
     const int n_rep = H_q / H_kv, d = H_kv * d_h;
     const int lane = lane_id(), w = wave_id();
@@ -67,6 +69,7 @@ __global__ __launch_bounds__(256) void gather_attend_generic_kernel(
 #pragma unroll
             for (int jj = 0; jj < JP; ++jj) kh[mm][jj] = vh[mm][jj] = 0.0f;
 
+#pragma unroll UN
         for (int i = 0; i < r_k; ++i) {
             float bv[JP];
 #pragma unroll
@@ -81,6 +84,7 @@ __global__ __launch_bounds__(256) void gather_attend_generic_kernel(
                 for (int jj = 0; jj < JP; ++jj) kh[mm][jj] = fmaf(a, bv[jj], kh[mm][jj]);
             }
         }
+#pragma unroll UN
         for (int i = 0; i < r_v; ++i) {
             float bv[JP];
 #pragma unroll

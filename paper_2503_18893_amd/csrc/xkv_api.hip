@@ -55,20 +55,30 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     // the matrix-core kernel walks 32 selected tokens per wavefront and iteration, the general one 16 per workgroup
     p.ga_mfma = gather_attend_mfma_shape_ok(s);
     p.ga_waves = p.ga_mfma ? gather_attend_mfma_waves(s) : 0;
-    const int gran = p.ga_mfma ? 32 * p.ga_waves : 64;
+    int gran = p.ga_mfma ? 32 * p.ga_waves : 64;
     // (its workgroups occupy a compute unit alone, so about one workgroup per compute unit; but at least four
     // splits per (sequence, KV head): the splits of a head share its packed B in their XCD's L2, and with fewer of
     // them more than 8 packs (2 MiB) are live per XCD and the re-streamed fragments start to miss)
     const int ga_splits = ceil_div(256, rows) < 4 ? 4 : ceil_div(256, rows);
     int splits = clampi(p.ga_mfma ? ga_splits : want, 1, clampi(ceil_div(s.k, gran), 1, 64));
     if (splits < ceil_div(s.k, 4096)) splits = ceil_div(s.k, 4096);  // a workgroup keeps at most 4096 token ids in LDS
-    p.sr_chunk = ceil_div(ceil_div(s.k, splits), gran) * gran;
-    p.sr_splits = ceil_div(s.k, p.sr_chunk);
+    const int sr_want = splits;
 
     splits = clampi(want, 1, clampi(ceil_div(s.L, 256), 1, 128));
     p.dense_mfma = dense_mfma_shape_ok(s);
     p.dense_chunk = ceil_div(ceil_div(s.L, splits), 128) * 128;  // 4 wavefronts x 32-token blocks
     p.dense_splits = ceil_div(s.L, p.dense_chunk);
+
+    // the general kernel: down to the 16 tokens of one round per workgroup where the partials of full attention leave room for
+    // that many splits (its time is the rounds of its workgroups one after the other)
+    splits = sr_want;
+    if (!p.ga_mfma && splits < p.dense_splits) {
+        gran = 16;
+        splits = clampi(want, 1, clampi(ceil_div(s.k, gran), 1, p.dense_splits));
+        if (splits < sr_want) splits = sr_want;
+    }
+    p.sr_chunk = ceil_div(ceil_div(s.k, splits), gran) * gran;
+    p.sr_splits = ceil_div(s.k, p.sr_chunk);
 
     p.max_splits = 4 * (p.sr_splits > p.dense_splits ? p.sr_splits : p.dense_splits);  // one partial per wavefront
 
