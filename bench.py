@@ -286,7 +286,7 @@ def main():
             if line.startswith("traffic_bytes_per_launch:"):
                 traffic = int(float(line.split(":")[1]))
     roofline = {"kernel": {"score": "score_stream_kernel / score_mfma_kernel (low-rank score stream + GQA max-pool)",
-                           "gather_attend": "gather_attend_mfma_kernel (gather-reconstruct + sparse attention)"}[dom],
+                           "gather_attend": "gather_absorb_kernel (gather of the selected rows + sparse attention on the factors)"}[dom],
                 "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "alg_bytes_per_launch": kern_bytes[dom], "ms_per_launch": round(kern_ms[dom], 5),

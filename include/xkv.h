@@ -176,8 +176,9 @@ XKV_API xkv_status xkv_score(const xkv_shape *shape, int32_t layer_in_group, con
 XKV_API xkv_status xkv_topk(const xkv_shape *shape, const float *score, int32_t *idx_out, void *workspace,
                             size_t workspace_bytes, void *hip_stream);
 
-/* Stages 3-4 on their own: reconstruct the rows idx [batch][H_kv][k] of K and V (Eq. 3)
- * and attend over them.  Ids must lie in [0, L); they need not be sorted or distinct. */
+/* Stages 3-4 on their own: attention over the rows idx [batch][H_kv][k] of the reconstructed K and V (Eq. 3).  The
+ * bf16 kernel forms the rows themselves only where they are rotated (rope_theta > 0 in the calls that take it); otherwise
+ * it multiplies the gathered rows of A with B_l q and sums them before B^V_l, the same function.  Ids must lie in [0, L); they need not be sorted or distinct. */
 XKV_API xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer_in_group, const void *A_k,
                                      const void *A_v, const void *B_k, const void *B_v, const void *q,
                                      const int32_t *idx, void *out, void *workspace, size_t workspace_bytes,
@@ -280,8 +281,8 @@ XKV_API xkv_status xkv_gather_attend_ex(const xkv_shape *shape, int32_t layer_in
  *     w_h = softmax_j( s_h[I_j] ),      o_h = ( sum_j w_hj A^V[I_j, :] ) B^V_g,
  * which equals softmax(q_h K^_g^T / sqrt(d_h)) V^_g with K^ = A^K[I] B^K, V^ = A^V[I] B^V up to rounding order
  * (K^ and V^ are never rounded to the storage type here).  Only valid where nothing is applied to the reconstructed
- * rows -- not with the rotary embedding of Sec. 4 "Implementation details" applied after reconstruction.  xkv_sr_decode remains the named
- * gather-reconstruct path; this is an additional one.
+ * rows -- not with the rotary embedding of Sec. 4 "Implementation details" applied after reconstruction.  xkv_sr_decode
+ * chooses the form by itself (see xkv_gather_attend); here it is this one by definition.
  *   xkv_head_scores: stage 1 + 2a; heads_out [batch][H_kv][L][nrp] fp32 (device, 16-byte aligned), nrp = H_q/H_kv
  *     rounded up to a power of two, padding written as 0; score_out (nullable) [batch][H_kv][L] is the pooled
  *     score and is the maximum of exactly the values in heads_out.

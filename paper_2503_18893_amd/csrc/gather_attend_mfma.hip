@@ -1,4 +1,5 @@
-// bf16 matrix-core path of selective reconstruction + sparse attention (Sec. 3.2, Eq. 3):
+// bf16 matrix-core path of selective reconstruction + sparse attention (Sec. 3.2, Eq. 3) that forms every selected row: for keys
+// that are rotated after the reconstruction, and for shapes that the regrouped form (gather_absorb.hip) does not take:
 //   K^_g = A^K[I_g,:] B^K_{l,g},  V^_g = A^V[I_g,:] B^V_{l,g},  out_h = softmax(scale K^_g q_h)^T V^_g.
 //
 // Everything is one chain of v_mfma_f32_32x32x16_bf16 whose operand layouts are chosen so that the
