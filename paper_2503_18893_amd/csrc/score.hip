@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void project_q_kernel(const T *__restrict__ B_
 // score, general path: one thread per token, fp32 FMA.  Each thread walks its row of A^K once
 // per block of up to 8 query heads; P is read through wave-uniform (scalar) loads.
 // ------------------------------------------------------------------------------------------
-template <typename T>
+template <typename T, int HB>  // query heads per walk over the row
 __global__ __launch_bounds__(256) void score_generic_kernel(const T *__restrict__ A_k,      // [batch][L][r_k]
                                                             const float *__restrict__ P,   // [batch][H_q][r_k]
                                                             float *__restrict__ S,         // [batch][H_kv][L]
@@ -61,20 +61,24 @@ __global__ __launch_bounds__(256) void score_generic_kernel(const T *__restrict_
     const float *Pb = P + (size_t)b * H_q * r_k;
     for (int g = 0; g < H_kv; ++g) {
         float best = -INFINITY;
-        for (int h0 = 0; h0 < n_rep; h0 += 8) {
-            float acc[8];
+        for (int h0 = 0; h0 < n_rep; h0 += HB) {
+            float acc[HB];
 #pragma unroll
-            for (int hh = 0; hh < 8; ++hh) acc[hh] = 0.0f;
+            for (int hh = 0; hh < HB; ++hh) acc[hh] = 0.0f;
             const float *Pg = Pb + (size_t)(g * n_rep + h0) * r_k;
-            const int nh = n_rep - h0 < 8 ? n_rep - h0 : 8;
+            const int nh = n_rep - h0 < HB ? n_rep - h0 : HB;
+            // (heads beyond nh take the last one's P again and are not used: no branch between the loads)
+            const float *Ph[HB];
+#pragma unroll
+            for (int hh = 0; hh < HB; ++hh) Ph[hh] = Pg + (size_t)(hh < nh ? hh : nh - 1) * r_k;
+#pragma unroll (HB == 4 ? 8 : 2)
             for (int i = 0; i < r_k; ++i) {
                 const float a = to_f32(Arow[i]);
 #pragma unroll
-                for (int hh = 0; hh < 8; ++hh)
-                    if (hh < nh) acc[hh] = fmaf(a, Pg[(size_t)hh * r_k + i], acc[hh]);
+                for (int hh = 0; hh < HB; ++hh) acc[hh] = fmaf(a, Ph[hh][i], acc[hh]);
             }
 #pragma unroll
-            for (int hh = 0; hh < 8; ++hh)
+            for (int hh = 0; hh < HB; ++hh)
                 if (hh < nh) best = fmaxf(best, scale * acc[hh]);
         }
         S[((size_t)b * H_kv + g) * L + t] = best;
@@ -1014,14 +1018,14 @@ static hipError_t launch_score_generic(const xkv_shape &s, const Plan &p, int la
         hipLaunchKernelGGL(project_q_kernel<float>, pgrid, block, 0, st, (const float *)B_k, (const float *)q, P, s.G,
                            layer, s.r_k, s.H_kv, s.H_q, s.d_h);
         profile_begin(0, st);
-        hipLaunchKernelGGL(score_generic_kernel<float>, grid, block, 0, st, (const float *)A_k, P, S, s.L, s.r_k,
+        hipLaunchKernelGGL((s.H_q <= 4 * s.H_kv ? score_generic_kernel<float, 4> : score_generic_kernel<float, 8>), grid, block, 0, st, (const float *)A_k, P, S, s.L, s.r_k,
                            s.H_kv, s.H_q, p.scale);
         profile_end(0, st);
     } else {
         hipLaunchKernelGGL(project_q_kernel<bf16_t>, pgrid, block, 0, st, (const bf16_t *)B_k, (const bf16_t *)q, P,
                            s.G, layer, s.r_k, s.H_kv, s.H_q, s.d_h);
         profile_begin(0, st);
-        hipLaunchKernelGGL(score_generic_kernel<bf16_t>, grid, block, 0, st, (const bf16_t *)A_k, P, S, s.L, s.r_k,
+        hipLaunchKernelGGL((s.H_q <= 4 * s.H_kv ? score_generic_kernel<bf16_t, 4> : score_generic_kernel<bf16_t, 8>), grid, block, 0, st, (const bf16_t *)A_k, P, S, s.L, s.r_k,
                            s.H_kv, s.H_q, p.scale);
         profile_end(0, st);
     }
