@@ -865,7 +865,8 @@ __device__ __forceinline__ void fz_rotation(double alpha, double beta, double ga
 // beside them the rotations of round k + 1.  Workgroups x < pairs find rotations; the next pairs (pairs + 1) / 2 make block
 // (p, q), p >= q, of M' and its mirror image, in the other buffer; the others the rows of J^T of one pair, 64 positions.
 // The first launch, k = -1, only finds the rotations of round 0.
-constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34;
+constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34, kJacTile = kJacNC * kJacLP;
+constexpr int kJacLds = 2 * kJacTile + 2 * 256 * 2 + 2 * 16 * 4;  // doubles
 
 // The first column of local column c of pair number x in this round of the round-robin tournament of m = n_blocks players:
 // the last player meets t = round % (m - 1), and t + x meets t - x modulo m - 1.
@@ -901,11 +902,13 @@ __device__ __forceinline__ void fz_pair_of_block(int b, int round, int n_blocks,
 // next the b side moves on by one pair, along the columns with a lane permutation, along the rows through LDS.  One
 // barrier per inner round.  Rows and columns beyond the matrix are zero and are not rotated.
 __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, const double *T_old, double *T, int *count, int r,
-                                                  int n_blocks, int round, int x)
+                                                  int n_blocks, int round, int x, double *sm)
 {
-    __shared__ double G[kJacNC * kJacLP], Ts[kJacNC * kJacLP];
-    __shared__ __attribute__((aligned(16))) double dg[2][16][4];     // alpha, beta, gamma of the next round's pairs
-    __shared__ __attribute__((aligned(16))) fz_f64x2_t mv[2][16][16];  // elements on the move
+    // LDS: the diagonal block; T in the sweep's first round, the elements on the move and alpha, beta, gamma of the next
+    // inner round's pairs -- before any of these the intermediate of the three parts
+    double *G = sm, *Ts = sm + kJacTile;
+    auto mv = reinterpret_cast<fz_f64x2_t (*)[16][16]>(Ts + kJacTile);  // [2]
+    auto dg = reinterpret_cast<double (*)[16][4]>(Ts + kJacTile + 2 * 256 * 2);  // [2]
     __shared__ int big_rotations;
     T += (size_t)x * kJacNC * kJacNC;  // row c = coefficients of new column c in the old ones
     const int tid = threadIdx.x, lane = lane_id(), pr = tid >> 4, pc = tid & 15;
@@ -913,7 +916,8 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
     fz_pair_of_blocks(x, round, n_blocks, blk);
     if (T_old) {
         constexpr int KS = kJacNC / 4, YP = 18;
-        __shared__ double Y[3][kJacNC * YP];
+        auto Y = reinterpret_cast<double (*)[kJacNC * YP]>(Ts);  // [3]
+        static_assert(3 * kJacNC * YP <= kJacLds - kJacTile, "in the place of what comes later");
         const int w = wave_id(), l16 = lane & 15, kk = lane >> 4, before = round + n_blocks - 2;  // the round before, modulo n_blocks - 1
         int px[2], half[2], pb[2][2];
 #pragma unroll
@@ -1072,18 +1076,19 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     rotations += blockIdx.z * kJacobiSweeps;
     Ma += (size_t)blockIdx.z * r * r;
     T += (size_t)blockIdx.z * t_seq;
+    __shared__ __attribute__((aligned(16))) double sm[kJacLds];  // both kinds of workgroups: several share a compute unit
     const int n_pairs = n_blocks / 2, n_tri = n_pairs * (n_pairs + 1) / 2, m1 = n_blocks - 1;
     int x = (int)blockIdx.x;
     if (x < n_pairs) {
         const int sweep = (k + 1) / m1;
         if (sweep == kJacobiSweeps || (sweep > 0 && rotations[sweep - 1] == 0)) return;  // same for the whole workgroup
-        fz_find_rotations(Ma, k < 0 ? nullptr : T, T_next + (size_t)blockIdx.z * t_seq, rotations + sweep, r, n_blocks, (k + 1) % m1, x);
+        fz_find_rotations(Ma, k < 0 ? nullptr : T, T_next + (size_t)blockIdx.z * t_seq, rotations + sweep, r, n_blocks, (k + 1) % m1, x, sm);
         return;
     }
     x -= n_pairs;
     const int round = k % m1;
     if (k >= m1 && rotations[k / m1 - 1] == 0) return;
-    __shared__ double Y[kJacNC * kJacLP];
+    double *Y = sm;
     Mb += (size_t)blockIdx.z * r * r;
     Jt += (size_t)blockIdx.z * r * r;
     constexpr int KS = kJacNC / 4;
