@@ -868,7 +868,7 @@ __device__ __forceinline__ void fz_rotation(double alpha, double beta, double ga
 constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34, kJacTile = kJacNC * kJacLP;
 constexpr int kJacLds = 2 * kJacTile + 2 * 256 * 2 + 2 * 16 * 4;  // doubles
 
-// The first column of local column c of pair number x in this round of the round-robin tournament of m = n_blocks players:
+// First columns of the two blocks of pair number x in a round of the round-robin tournament of m = n_blocks players:
 // the last player meets t = round % (m - 1), and t + x meets t - x modulo m - 1.
 __device__ __forceinline__ void fz_pair_of_blocks(int x, int round, int n_blocks, int (&b)[2])
 {
