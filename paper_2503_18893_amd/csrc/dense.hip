@@ -100,8 +100,6 @@ __global__ __launch_bounds__(256) void dense_generic_kernel(const T *__restrict_
 // loaded after the maxima took 13.5 us with 64 partials (d_h = 128, 32 heads) and
 // 4.1 us with 8, now 6.5 and 3.9 us.
 // ------------------------------------------------------------------------------------------
-constexpr int kMaxCombineParts = 1024;  // partials per query head that one merge takes (splits and tail together)
-
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ part_o,
                                                       const float *__restrict__ part_ml, T *__restrict__ out,

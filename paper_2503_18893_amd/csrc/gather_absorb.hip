@@ -543,6 +543,8 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
     p.ab_occ = absorb_ngv(s.r_v) <= 4 && (long long)rows * tiles > 256 ? 2 : 1;
     int splits = ((p.ab_occ == 2 ? 1024 : 256) + rows - 1) / rows;
     splits = splits > tiles ? tiles : splits;
+    // the merge has to take these partials and those of an uncompressed tail (one sequence of one KV head, k of a million)
+    if (splits > kMaxCombineParts - kTailParts) splits = kMaxCombineParts - kTailParts;
     if (splits < (s.k + 4095) / 4096) splits = (s.k + 4095) / 4096;
     if (splits > p.max_splits) splits = p.max_splits;
     p.ab_chunk = (tiles + splits - 1) / splits * tile;

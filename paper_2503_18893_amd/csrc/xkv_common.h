@@ -83,6 +83,7 @@ struct Plan {
     int score_waves;   // wavefronts per workgroup of that kernel (8, or 4 at large ranks)
 };
 
+constexpr int kMaxCombineParts = 1024;  // partials per query head that one merge takes (splits and tail together)
 constexpr int kTailParts = 32;   // partials per query head for the uncompressed tail (8 splits x 4 wavefronts)
 constexpr int kTopkLevels = 4;   // 8-bit digits of the 32-bit order key
 constexpr int kTopkBins = 256;

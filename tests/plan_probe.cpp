@@ -1,0 +1,18 @@
+// Prints what make_plan decides for shapes read from stdin, one "G H_kv H_q d_h r_k r_v L k batch dtype" a line, as
+// name=value pairs.  Linked with the library's objects by tests/test_plan.py; host only.
+#include <cstdio>
+
+#include "xkv_common.h"
+
+int main()
+{
+    xkv_shape s{};
+    while (std::scanf("%d %d %d %d %d %d %d %d %d %d", &s.G, &s.H_kv, &s.H_q, &s.d_h, &s.r_k, &s.r_v, &s.L, &s.k, &s.batch,
+                      &s.dtype) == 10) {
+        xkv::Plan p;
+        if (xkv::make_plan(s, p) != XKV_OK) return 1;
+        std::printf("absorb=%d occ=%d splits=%d chunk=%d max_splits=%d sr_splits=%d merge_limit=%d tail_parts=%d\n", (int)p.absorb,
+                    p.ab_occ, p.ab_splits, p.ab_chunk, p.max_splits, p.sr_splits, xkv::kMaxCombineParts, xkv::kTailParts);
+    }
+    return 0;
+}

@@ -108,3 +108,23 @@ def test_selected_rows_against_the_definition(H_kv, n_rep, r_k, r_v, batch, k, b
             bound = 1.05 * 2.0 ** -8 * (np.abs(ref) + mag) + 1e-6 * np.abs(mag).max()
             over = np.abs(got[b] - ref) - bound
             assert over.max() <= 0, (b, float(over.max()), float(np.abs(got[b] - ref).max()), float(mag.max()))
+
+
+def test_a_million_selected_rows_and_a_tail():
+    """One KV head, every token of a long context selected: as many splits as the merge takes beside the tail's partials."""
+    torch = torch_mod()
+    L, r, T = 1 << 20, 16, 5
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)
+    A_k, A_v, B_k, B_v, q = rnd(1, L, r), rnd(1, L, r), rnd(1, 1, r, 128), rnd(1, 1, r, 128), rnd(1, 1, 128)
+    K_t, V_t = rnd(1, 1, T, 128), rnd(1, 1, T, 128)
+    shape = xb.Shape(G=1, H_kv=1, H_q=1, d_h=128, r_k=r, r_v=r, L=L, k=L, batch=1)
+    out = torch.empty((1, 1, 128), dtype=torch.bfloat16, device="cuda")
+    xb.xkv_sr_decode_tail(shape, 0, A_k, A_v, B_k, B_v, q, K_t, V_t, T, out, None, None, xb.alloc_workspace(shape))
+    torch.cuda.synchronize()
+    K = torch.cat([A_k[0].double() @ B_k[0, 0].double(), K_t[0, 0].double()])
+    V = torch.cat([A_v[0].double() @ B_v[0, 0].double(), V_t[0, 0].double()])
+    w = torch.softmax(K @ q[0, 0].double() / 128 ** 0.5, 0)
+    ref, mag = w @ V, w @ V.abs()
+    bound = 1.05 * 2.0 ** -8 * (ref.abs() + mag) + 1e-6 * mag.max()
+    assert ((out[0, 0].double() - ref).abs() <= bound).all(), float(((out[0, 0].double() - ref).abs() - bound).max())

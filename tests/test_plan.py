@@ -1,0 +1,40 @@
+"""How a shape is split over workgroups (make_plan, host code): the limits that the launches rely on.  No GPU needed."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2503_18893_amd import build as xbuild
+
+
+@pytest.fixture(scope="module")
+def plan_of(tmp_path_factory):
+    """Plans of a list of dicts with the shape's fields (the rest: one layer of the Llama shape)."""
+    objs = [os.path.join(xbuild.OBJ_DIR, src.replace(".hip", ".o")) for src in xbuild.SOURCES]
+    if not all(os.path.exists(o) for o in objs):
+        xbuild.build_library()
+    exe = str(tmp_path_factory.mktemp("plan") / "probe")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "plan_probe.cpp")
+    subprocess.run([xbuild._hipcc(), *xbuild.HIPCC_FLAGS, "-x", "hip", src, "-x", "none", *objs, "-o", exe], check=True,
+                   capture_output=True)
+
+    def run(shapes):
+        base = dict(G=1, H_kv=8, H_q=32, d_h=128, r_k=512, r_v=512, L=1, k=1, batch=1, dtype=1)
+        lines = []
+        for sh in shapes:
+            f = {**base, **sh}
+            f["L"] = max(f["L"], f["k"])
+            lines.append(" ".join(str(f[n]) for n in base))
+        out = subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.splitlines()
+        assert len(out) == len(shapes)
+        return [{n: int(v) for n, v in (kv.split("=") for kv in line.split())} for line in out]
+    return run
+
+
+def test_partials_of_a_step_fit_the_merge(plan_of):
+    """Selected rows and uncompressed tail together, wherever the limit of 4096 rows per workgroup leaves room for both."""
+    shapes = [dict(H_kv=h, H_q=h, batch=b, r_k=r, r_v=r, k=k) for h, b in ((1, 1), (2, 1), (1, 3), (8, 1), (8, 5))
+              for r in (16, 384) for k in (1, 129, 4097, 100_000, 500_000, 1 << 20, (1 << 20) + 1, 3_000_000, 992 * 4096)]
+    for sh, p in zip(shapes, plan_of(shapes)):
+        assert p["absorb"] == 1 and p["splits"] * p["chunk"] >= sh["k"] > (p["splits"] - 1) * p["chunk"], (sh, p)
+        assert p["splits"] + p["tail_parts"] <= p["merge_limit"] and p["splits"] <= p["max_splits"], (sh, p)
