@@ -503,7 +503,7 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
     }
 }
 
-constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512;
+constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512, kAbsorbLdsPair = 80 * 1024;  // for one workgroup, for each of two
 
 // Groups in flight per wavefront.
 static constexpr int absorb_rg(int ngv, int occ) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 ? 4 : 2; }
@@ -533,22 +533,43 @@ bool gather_absorb_shape_ok(const xkv_shape &s)
 
 void gather_absorb_plan(const xkv_shape &s, Plan &p)
 {
-    // Tiles are 128 rows.  Where every compute unit gets more than one (and U fits 256 registers a lane), two workgroups
-    // share a compute unit, so that the one streams while the other merges; else one with twice the registers, all of
-    // them for requests in flight.  About 1024 workgroups, two rounds of two: at 16 sequences x 8 heads x 4096 rows of
-    // ranks 512 a pass of four layers took 1489 us (512 of twice the length 1492, 2048 of half of it 1512, one workgroup of
-    // eight wavefronts per compute unit 1513: its wavefronts finish up to 12 us apart).
+    // Tiles are 128 rows.  Where every compute unit gets more than one, U fits 256 registers a lane and two workgroups fit the
+    // LDS, two share a compute unit, so that the one streams while the other merges; else one with twice the registers, all of
+    // them for requests in flight.  (16 sequences x 8 heads x 4096 rows of ranks 512: two 179 us; one of eight wavefronts 182.
+    // A workgroup of the first kind without room for its partner has neither: 85 us at 4 x 8 x 4096 rows of ranks 768 : 512
+    // where one of the second kind takes 66.)
     const int tile = 128, rows = p.rows > 0 ? p.rows : 1;
-    const int tiles = (s.k + tile - 1) / tile;
-    p.ab_occ = absorb_ngv(s.r_v) <= 4 && (long long)rows * tiles > 256 ? 2 : 1;
-    int splits = ((p.ab_occ == 2 ? 1024 : 256) + rows - 1) / rows;
-    splits = splits > tiles ? tiles : splits;
-    // the merge has to take these partials and those of an uncompressed tail (one sequence of one KV head, k of a million)
-    if (splits > kMaxCombineParts - kTailParts) splits = kMaxCombineParts - kTailParts;
-    if (splits < (s.k + 4095) / 4096) splits = (s.k + 4095) / 4096;
-    if (splits > p.max_splits) splits = p.max_splits;
-    p.ab_chunk = (tiles + splits - 1) / splits * tile;
-    p.ab_splits = (s.k + p.ab_chunk - 1) / p.ab_chunk;
+    const int tiles = (s.k + tile - 1) / tile, ngv = absorb_ngv(s.r_v), FZ = (s.r_k / 16 + 7) / 8 * 8;
+    // a workgroup keeps 4096 ids at most where the partials allow it; the merge takes these partials and those of an
+    // uncompressed tail (one sequence of one KV head, k of a million)
+    const int fewest = (s.k + 4095) / 4096;
+    int most = kMaxCombineParts - kTailParts;
+    if (most < fewest) most = fewest;
+    if (most > p.max_splits) most = p.max_splits;
+    // Lists are cut so that the workgroups make whole rounds of the chip: a few more than a round take as long as two (6 x 8 x
+    // 2048 rows of ranks 768 as 288 workgroups 92 us, as 192 73).  Of the cuts into the first rounds possible the one that is
+    // done first is taken, the start and the merge of a workgroup counted as one tile.  (Two rounds instead of one for the
+    // same time leave twice the partials: 1 x 8 x 16384 rows 58 us, one round 53.)
+    auto cut = [&](int occ) {
+        const int slots = 256 * occ, first = (rows + slots - 1) / slots;
+        long long best = 0;
+        for (int rounds = first; rounds < first + 4; ++rounds) {
+            int splits = (int)((long long)slots * rounds / rows);
+            splits = splits > most ? most : splits;
+            splits = splits < fewest ? fewest : splits;
+            splits = splits > tiles ? tiles : splits;
+            const int per = (tiles + splits - 1) / splits, used = (tiles + per - 1) / per;
+            const long long time = ((long long)rows * used + slots - 1) / slots * (per + 1);
+            if (best > 0 && time >= best) continue;
+            best = time;
+            p.ab_chunk = per * tile;
+            p.ab_splits = used;
+        }
+        p.ab_occ = occ;
+        p.ab_lds = absorb_lds(4, ngv, occ, p.n_rep, FZ, p.ab_chunk);
+    };
+    if (ngv <= 4 && (long long)rows * tiles > 256) cut(2);
+    if (p.ab_occ != 2 || p.ab_lds > kAbsorbLdsPair) cut(1);
 }
 
 hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
@@ -560,8 +581,7 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
                         (size_t)pa.F8k * 256;
     const size_t seq_stride = (B_packed ? (size_t)s.G : 1) * s.H_kv * per_head;
     const int ngv = absorb_ngv(s.r_v);
-    const size_t lds = absorb_lds(4, ngv, p.ab_occ, p.n_rep, pa.FZ, p.ab_chunk);
-    if (ngv == 0 || lds > kAbsorbLdsMax || p.ab_splits > p.max_splits) return hipErrorInvalidValue;
+    if (ngv == 0 || p.ab_lds > kAbsorbLdsMax || p.ab_splits > p.max_splits) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((long long)p.ab_splits * s.H_kv * s.batch));
 #define XKV_AB(NV, OC, QB)                                                                                              \
     do {                                                                                                                \
@@ -570,7 +590,7 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
         const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<4, NV, RG, QB, OC>, kAbsorbLdsMax);         \
         if (e != hipSuccess) return e;                                                                                  \
         profile_begin(1, st);                                                                                           \
-        hipLaunchKernelGGL((gather_absorb_kernel<4, NV, RG, QB, OC>), grid, dim3(256), lds, st, A_k, A_v,               \
+        hipLaunchKernelGGL((gather_absorb_kernel<4, NV, RG, QB, OC>), grid, dim3(256), p.ab_lds, st, A_k, A_v,          \
                            (const u32x4_t *)pa.Pz, pa.z_stride / 8, pv, seq_stride, per_head, idx, counts, part_o,      \
                            part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.ab_splits, p.ab_chunk, pa.FZ, p.scale);    \
         profile_end(1, st);                                                                                             \

@@ -76,6 +76,7 @@ struct Plan {
     int ga_waves;      // ... with this many wavefronts (32 selected tokens each) per workgroup
     bool absorb;       // ... and the one that keeps B_l out of the main loop (rows that are not rotated)
     int ab_occ, ab_splits, ab_chunk;  // its workgroups per compute unit, splits per (sequence, KV head), tokens per split
+    size_t ab_lds;     // its LDS per workgroup
     bool topk_row;     // rows short enough for the one-launch, register-resident selection
     bool score_stream; // shape fits the long-stream score kernel
     bool score_hist;   // ... and that kernel can also histogram the top digit of its scores for the top-k stage

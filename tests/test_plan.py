@@ -38,3 +38,23 @@ def test_partials_of_a_step_fit_the_merge(plan_of):
     for sh, p in zip(shapes, plan_of(shapes)):
         assert p["absorb"] == 1 and p["splits"] * p["chunk"] >= sh["k"] > (p["splits"] - 1) * p["chunk"], (sh, p)
         assert p["splits"] + p["tail_parts"] <= p["merge_limit"] and p["splits"] <= p["max_splits"], (sh, p)
+
+
+def test_workgroups_per_compute_unit_follow_from_the_lds(plan_of):
+    """Two workgroups are counted on only where both fit, and one round of workgroups is not left for a few of a second."""
+    shapes = [dict(batch=b, k=k, r_k=rk, r_v=rv) for b in (1, 2, 3, 4, 5, 6, 16) for k in (500, 2048, 4096, 16384)
+              for rk in (16, 128, 384, 512, 528, 640, 768, 1024) for rv in (16, 256, 384, 512, 576, 768)]
+    shared = 0
+    for sh, p in zip(shapes, plan_of(shapes)):
+        if not p["absorb"]:
+            continue
+        slots, work, tiles = 256 * p["occ"], 8 * sh["batch"] * p["splits"], (sh["k"] + 127) // 128
+        assert p["lds"] * p["occ"] <= 160 * 1024, (sh, p)
+        assert p["occ"] == 1 or sh["r_v"] <= 512, (sh, p)
+        shared += p["occ"] == 2
+        # no cut of the lists would be done a whole round of tiles earlier
+        time = -(-work // slots) * (p["chunk"] // 128 + 1)
+        for per in range(1, tiles + 1):
+            splits = -(-tiles // per)
+            assert time <= -(-8 * sh["batch"] * splits // slots) * (per + 1) + 1, (sh, p, per)
+    assert shared > 100
