@@ -399,7 +399,9 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
     constexpr int KH = WAVES == 8 ? 2 : 1, NDB = WAVES >= 4 ? 1 : 4 / WAVES, NFB = NGV * 8 / KH;
     const u32x4_t *pv = pack_v + (size_t)b * pack_seq_stride + (size_t)g * pack_head_stride + lane;
     const int db0 = WAVES >= 4 ? (w & 3) : w * NDB, kh = WAVES == 8 ? w >> 2 : 0;
-    constexpr int NPF = NFB < 16 ? NFB : NGV == 6 || OCC == 2 ? 16 : NFB < 32 ? NFB : 32;  // fragments requested ahead of the merge
+    // fragments requested ahead of the merge: what the registers hold beside U.  (Six groups: 32 instead of 16 take 0.5 us off a
+    // step of one tile per workgroup, 24.6 -> 24.1 us; with 3-bit rows they cost 2 % of 16 x 8 x 4096 rows, 180 -> 184 us.)
+    constexpr int NPF = OCC == 2 || (NGV == 6 && QB == 3) ? 16 : NFB < 32 ? NFB : 32;
     u32x4_t bv[NPF];
 #pragma unroll
     for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)((kh * NFB + f) * 4 + db0) * 64];
@@ -505,12 +507,15 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
 
 constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512, kAbsorbLdsPair = 80 * 1024;  // for one workgroup, for each of two
 
-// Groups in flight per wavefront.
-static constexpr int absorb_rg(int ngv, int occ) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 ? 4 : 2; }
+// Groups in flight per wavefront.  The groups of A^K are padded to whole rings; the deep ring of four is left where it would
+// add two groups or more to a tile (r_k = 640 or 768 with r_v = 512, 16 x 8 x 4096 rows: 199 -> 197 us in bf16, 194 -> 169
+// in 4 bits, where the padding is de-quantised too).  Three for six groups of A^V are slower (384 : 576 175 -> 191 us).
+static constexpr int absorb_rg(int ngv, int occ, bool deep) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 && deep ? 4 : 2; }
+static bool absorb_deep(int FZ) { return (FZ / 8 + 3) % 4 >= 2; }
 
 static size_t absorb_lds(int waves, int ngv, int occ, int n_rep, int FZ, int chunk)
 {
-    const int rg = absorb_rg(ngv, occ);
+    const int rg = absorb_rg(ngv, occ, absorb_deep(FZ));
     const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)waves * (kTileBytes + 128) + (size_t)chunk * 4;
     const int slab = slab_bytes(waves, n_rep, slab_groups(waves, n_rep, ngv, occ)), out = 2 * 16 * kOutPitch * 4;
     const size_t merge = (size_t)ngv * 8192 + (size_t)2 * waves * 16 * 4 + (size_t)(slab > out ? slab : out);
@@ -526,9 +531,9 @@ static int absorb_ngv(int r_v)
 
 bool gather_absorb_shape_ok(const xkv_shape &s)
 {
-    const int FZ = (s.r_k / 16 + 7) / 8 * 8;
+    // (up to r_k = 1024 the projected queries, 64 KiB there, fit the LDS beside the tiles and the ids)
     const long long widest = s.r_k > s.r_v ? s.r_k : s.r_v;
-    return s.L < (1 << 24) && s.L * widest * 2 < (1LL << 32) && absorb_ngv(s.r_v) != 0 && absorb_lds(4, 4, 1, 16, FZ, 8192) <= kAbsorbLdsMax && absorb_lds(4, 6, 1, 16, FZ, 8192) <= kAbsorbLdsMax;
+    return s.L < (1 << 24) && s.L * widest * 2 < (1LL << 32) && s.r_k <= 1024 && absorb_ngv(s.r_v) != 0;
 }
 
 void gather_absorb_plan(const xkv_shape &s, Plan &p)
@@ -583,10 +588,10 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
     const int ngv = absorb_ngv(s.r_v);
     if (ngv == 0 || p.ab_lds > kAbsorbLdsMax || p.ab_splits > p.max_splits) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((long long)p.ab_splits * s.H_kv * s.batch));
-#define XKV_AB(NV, OC, QB)                                                                                              \
+#define XKV_AB(NV, OC, DP, QB)                                                                                          \
     do {                                                                                                                \
         static DynamicLdsOnce attr;                                                                                     \
-        constexpr int RG = absorb_rg(NV, OC);                                                                           \
+        constexpr int RG = absorb_rg(NV, OC, DP);                                                                       \
         const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<4, NV, RG, QB, OC>, kAbsorbLdsMax);         \
         if (e != hipSuccess) return e;                                                                                  \
         profile_begin(1, st);                                                                                           \
@@ -595,31 +600,33 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
                            part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.ab_splits, p.ab_chunk, pa.FZ, p.scale);    \
         profile_end(1, st);                                                                                             \
     } while (0)
-#define XKV_AB_Q(NV, OC)       \
-    do {                       \
-        if (qbits == 0)        \
-            XKV_AB(NV, OC, 0); \
-        else if (qbits == 4)   \
-            XKV_AB(NV, OC, 4); \
-        else                   \
-            XKV_AB(NV, OC, 3); \
+#define XKV_AB_Q(NV, OC, DP)       \
+    do {                           \
+        if (qbits == 0)            \
+            XKV_AB(NV, OC, DP, 0); \
+        else if (qbits == 4)       \
+            XKV_AB(NV, OC, DP, 4); \
+        else                       \
+            XKV_AB(NV, OC, DP, 3); \
     } while (0)
     if (p.ab_occ == 2) {
         if (ngv == 2)
-            XKV_AB_Q(2, 2);
+            XKV_AB_Q(2, 2, false);
         else if (ngv == 3)
-            XKV_AB_Q(3, 2);
+            XKV_AB_Q(3, 2, false);
         else
-            XKV_AB_Q(4, 2);
+            XKV_AB_Q(4, 2, false);
     } else {
         if (ngv == 2)
-            XKV_AB_Q(2, 1);
+            XKV_AB_Q(2, 1, false);
         else if (ngv == 3)
-            XKV_AB_Q(3, 1);
+            XKV_AB_Q(3, 1, false);
+        else if (ngv == 4 && absorb_deep(pa.FZ))
+            XKV_AB_Q(4, 1, true);
         else if (ngv == 4)
-            XKV_AB_Q(4, 1);
+            XKV_AB_Q(4, 1, false);
         else
-            XKV_AB_Q(6, 1);
+            XKV_AB_Q(6, 1, false);
     }
 #undef XKV_AB_Q
 #undef XKV_AB

@@ -58,3 +58,15 @@ def test_workgroups_per_compute_unit_follow_from_the_lds(plan_of):
             splits = -(-tiles // per)
             assert time <= -(-8 * sh["batch"] * splits // slots) * (per + 1) + 1, (sh, p, per)
     assert shared > 100
+
+
+def test_which_shapes_keep_b_out_of_the_main_loop(plan_of):
+    """r_k up to 1024, r_v up to 768, row offsets of one sequence within 32 bits -- and then the launch fits the LDS, at any head
+    count and at the most ids per workgroup."""
+    shapes = [dict(r_k=rk, r_v=rv, H_q=8 * n, k=k, L=L) for rk in (16, 640, 1008, 1024, 1040, 1280) for rv in (16, 512, 768, 784)
+              for n in (1, 16) for k in (1, 4_000_000) for L in (1, 3_000_000, (1 << 24) - 1)]
+    for sh, p in zip(shapes, plan_of(shapes)):
+        L = max(sh["L"], sh["k"])
+        ok = sh["r_k"] <= 1024 and sh["r_v"] <= 768 and L * max(sh["r_k"], sh["r_v"]) * 2 < 1 << 32
+        assert p["absorb"] == ok, (sh, p)
+        assert not ok or p["lds"] <= 160 * 1024 - 512, (sh, p)
