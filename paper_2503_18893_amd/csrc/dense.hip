@@ -94,10 +94,10 @@ __global__ __launch_bounds__(256) void dense_generic_kernel(const T *__restrict_
 // ------------------------------------------------------------------------------------------
 // Merge the split partials of one (sequence, query head) with the log-sum-exp rule and write
 // the normalised output in the storage dtype.  A partial that saw no token has max = -inf.
-// Latency is all there is to it, so every load is requested at once: (maximum, sum) of every partial, and the first eight
-// partials of each of the 256 / (d_h / 4) groups of threads that share the partials between them (thread = VEC columns of
-// one group's partials, the groups are added up at the end).  One thread per column, four partials at a time and the sums
-// loaded after the maxima took 13.5 us with 64 partials (d_h = 128, 32 heads) and
+// Latency is all there is to it, so every load is requested at once: (maximum, sum) of every partial, and the first BATCH
+// partials of each of the groups of 2^tpg threads that share the partials between them (thread = VEC columns of one
+// group's partials, a group covers all columns, the groups are added up at the end).  One thread per column, four partials
+// at a time and the sums loaded after the maxima took 13.5 us with 64 partials (d_h = 128, 32 heads) and
 // 4.1 us with 8, now 6.5 and 3.9 us.
 // ------------------------------------------------------------------------------------------
 template <typename T, int VEC>
@@ -105,39 +105,48 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
                                                       const float *__restrict__ part_ml, T *__restrict__ out,
                                                       int H_q, int d_h, int n_part,
                                                       const float *__restrict__ part_o2,
-                                                      const float *__restrict__ part_ml2, int n_part2)
+                                                      const float *__restrict__ part_ml2, int n_part2, int tpg)
 {
     typedef __attribute__((ext_vector_type(VEC))) float vec_t;
     // the second set of partials (n_part2 may be 0) has the same layout; it holds the uncompressed tail tokens
     const int h = blockIdx.x, b = blockIdx.y;
     const size_t base = ((size_t)b * H_q + h) * n_part, base2 = ((size_t)b * H_q + h) * n_part2;
-    constexpr int BATCH = 8, PER = kMaxCombineParts / 256;
+    constexpr int BATCH = VEC == 1 ? 16 : 8, PER = kMaxCombineParts / 256;
     __shared__ float sm_w[kMaxCombineParts], sm_red[2][4];
     __shared__ vec_t sm_acc[256];
     const int n_all = n_part + n_part2, cols = d_h / VEC;
-    const int tpg = cols <= 32 ? 32 : 64, n_grp = 256 / tpg, grp = threadIdx.x / tpg, lc = threadIdx.x % tpg;
-    auto fetch = [&](int s0, int j, vec_t (&v)[BATCH]) __attribute__((always_inline)) {  // partials s0, s0 + n_grp, ..
+    const int n_grp = (int)blockDim.x >> tpg, grp = (int)threadIdx.x >> tpg, j = (int)threadIdx.x & ((1 << tpg) - 1);
+    const int jc = j < cols ? j : cols - 1;
+    // partials s1 + grp, s1 + grp + n_grp, .. (a load under a lane's condition would be waited for: lanes beyond the last one
+    // read the last one again, and whole steps beyond it are left out)
+    auto fetch = [&](int s1, vec_t (&v)[BATCH]) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
-            const int s = s0 + n_grp * u;
+            if (s1 + n_grp * u >= n_all) break;
+            const int t = s1 + n_grp * u + grp, s = t < n_all ? t : n_all - 1;
             const float *p = s < n_part ? part_o + (base + s) * d_h : part_o2 + (base2 + (s - n_part)) * d_h;
-            v[u] = (s < n_all && j < cols) ? *reinterpret_cast<const vec_t *>(p + VEC * j) : vec_t(0.0f);
+            v[u] = *reinterpret_cast<const vec_t *>(p + VEC * jc);
         }
     };
     // up to 64 partials: every wavefront holds (maximum, sum) of all of them, a lane each, and needs neither LDS nor a
-    // barrier for the weights (lane s: weight of partial s); more: a thread each, PER at most
+    // barrier for the weights (lane s: weight of partial s); more: a thread of 256 each, PER at most
     const bool few = n_all <= kWave;
     const int lane = lane_id(), first = few ? lane : (int)threadIdx.x;
     float pm[PER], pl[PER];
     vec_t v[BATCH];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int s = first + 256 * u;
-        const float *p = s < n_part ? part_ml + (base + s) * 2 : part_ml2 + (base2 + (s - n_part)) * 2;
-        pm[u] = s < n_all ? p[0] : -INFINITY;
-        pl[u] = s < n_all ? p[1] : 0.0f;
+        const int s = first + 256 * u, sc = s < n_all ? s : n_all - 1;
+        const float *p = sc < n_part ? part_ml + (base + sc) * 2 : part_ml2 + (base2 + (sc - n_part)) * 2;
+        pm[u] = -INFINITY;
+        pl[u] = 0.0f;
+        if (256 * u < n_all) {  // (the same in every thread)
+            const float m = p[0], l = p[1];
+            pm[u] = s < n_all ? m : -INFINITY;
+            pl[u] = s < n_all ? l : 0.0f;
+        }
     }
-    fetch(grp, lc, v);
+    fetch(0, v);
     float M = pm[0], den, weight = 0.0f;
     if (few) {
         for (int off = 1; off < n_all; off <<= 1) M = fmaxf(M, __shfl_xor(M, off, kWave));
@@ -170,31 +179,36 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
         __syncthreads();
         den = (sm_red[1][0] + sm_red[1][1]) + (sm_red[1][2] + sm_red[1][3]);
     }
-    const int n_sum = n_all < n_grp ? n_all : n_grp;  // groups that have a partial
-    for (int j0 = 0; j0 < cols; j0 += tpg) {
-        const int j = j0 + lc;
-        vec_t num = vec_t(0.0f);
-        for (int s1 = 0; s1 < n_all; s1 += n_grp * BATCH) {  // (the same number of rounds in every thread: lanes exchange)
-            const int s0 = s1 + grp;
-            if (j0 > 0 || s1 > 0) fetch(s0, j, v);
+    vec_t num = vec_t(0.0f);
+    auto add_up = [&](auto weight_of) __attribute__((always_inline)) {  // (the same number of rounds in every thread: lanes exchange)
+        for (int s1 = 0; s1 < n_all; s1 += n_grp * BATCH) {
+            if (s1 > 0) fetch(s1, v);
+            float wt[BATCH];
 #pragma unroll
             for (int u = 0; u < BATCH; ++u) {
-                const int s = s0 + n_grp * u;
-                if (s1 + n_grp * u >= n_all) break;
-                const float wt = few ? __shfl(weight, s & 63, kWave) : s < n_all ? sm_w[s] : 0.0f;
-                if (s < n_all) num += wt * v[u];
+                const int s = s1 + n_grp * u + grp;
+                wt[u] = weight_of(s < n_all ? s : n_all - 1);
             }
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u)
+                if (s1 + n_grp * u + grp < n_all) num += wt[u] * v[u];
         }
-        if (j0 > 0) __syncthreads();  // (the sums of the columns before have been read)
+    };
+    if (few)
+        add_up([&](int s) __attribute__((always_inline)) { return __shfl(weight, s, kWave); });
+    else
+        add_up([&](int s) __attribute__((always_inline)) { return sm_w[s]; });
+    const int n_sum = n_all < n_grp ? n_all : n_grp;  // groups that have a partial
+    if (n_sum > 1) {
         sm_acc[threadIdx.x] = num;
         __syncthreads();
-        if (grp == 0 && j < cols) {
-            for (int k = 1; k < n_sum; ++k) num += sm_acc[k * tpg + lc];
-            // a head with no token at all (every list empty, no tail) has den == 0: its output is defined as zero
-            T *o = out + ((size_t)b * H_q + h) * d_h + VEC * j;
+    }
+    if (grp == 0 && j < cols) {
+        for (int k = 1; k < n_sum; ++k) num += sm_acc[(k << tpg) + j];
+        // a head with no token at all (every list empty, no tail) has den == 0: its output is defined as zero
+        T *o = out + ((size_t)b * H_q + h) * d_h + VEC * j;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) o[e] = from_f32<T>(den > 0.0f ? num[e] / den : 0.0f);
-        }
+        for (int e = 0; e < VEC; ++e) o[e] = from_f32<T>(den > 0.0f ? num[e] / den : 0.0f);
     }
 }
 
@@ -444,9 +458,16 @@ hipError_t launch_combine(const xkv_shape &s, int n_part, const float *part_o, c
     if (n_part + n_part2 > kMaxCombineParts) return hipErrorInvalidValue;
     // four columns per thread where the rows of the partials can be read that way (the caller's workspace may begin anywhere)
     const bool vec = s.d_h % 4 == 0 && (((uintptr_t)part_o | (n_part2 > 0 ? (uintptr_t)part_o2 : 0)) & 15u) == 0;
+    // A group of threads covers the columns (d_h <= 256); at most eight groups, no more than there are partials, and whole
+    // wavefronts: 256 threads for each of 2048 output rows of 128 columns and two partials cost 1.2 us of 28, groups of 64
+    // threads in four rounds 40 of 180 us at 255 columns.  More than 64 partials need the 256 threads for their weights.
+    int tpg = 3;
+    while ((1 << tpg) < (vec ? s.d_h / 4 : s.d_h)) ++tpg;
+    const int n_all = n_part + n_part2, grps = n_all < 8 ? n_all : 8;
+    const int threads = n_all > kWave || (grps << tpg) > 256 ? 256 : ((grps << tpg) + 63) / 64 * 64;
     auto launch = [&](auto kernel, auto *o) {
-        hipLaunchKernelGGL(kernel, dim3(s.H_q, s.batch), dim3(256), 0, st, part_o, part_ml, o, s.H_q, s.d_h, n_part, part_o2,
-                           part_ml2, n_part2);
+        hipLaunchKernelGGL(kernel, dim3(s.H_q, s.batch), dim3(threads), 0, st, part_o, part_ml, o, s.H_q, s.d_h, n_part, part_o2,
+                           part_ml2, n_part2, tpg);
     };
     if (s.dtype == XKV_F32)
         vec ? launch(combine_kernel<float, 4>, (float *)out) : launch(combine_kernel<float, 1>, (float *)out);
