@@ -72,8 +72,10 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(const T *__restrict__ 
 //  - B slab [32 ranks][32 pieces of 8 dims]: piece p of rank i in place p ^ 4 (i % 4), row by row as it lies in memory; the
 //    products want the ranks contiguous per lane, which the transposing LDS read does (ds_read_b64_tr_b16);
 //  - result rounded to bf16 once, staged in LDS, written as whole 128 B lines.
-// All three without bank conflicts in what the LDS serves at a time.  Token tiles go to the dies in turn, the column
-// tiles of a token tile to the same die (its rows of A are read once from memory).
+// All three without bank conflicts in what the LDS serves at a time.  Token tiles, counted over all sequences, go to the dies
+// in turn, the column tiles of a token tile to the same die (its rows of A are read once from memory).  (With every
+// sequence beginning at the first die 16 of 256 tokens kept two of the eight busy: 23.4 us, now 14.6; 64 of 100 tokens,
+// rank 128, 33.5 us, now 8.0.)
 // What bounds it: the copies into LDS (24 KiB per slab and workgroup, 403 MB from L2 at 8.5 TB/s) before the products:
 // 47 us at L = 32768, r = 512, H_kv = 8 (34 GFLOP, 0.73 PFLOP/s; the products alone are 14 us, memory 18 us).  Eight wavefronts
 // of 32 tokens x 128 dims, every wavefront reading all of B_l's fragments for its 32 tokens and B_l transposed by 2 B
@@ -108,13 +110,14 @@ __device__ __forceinline__ void rc_lds_barrier()
 __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const bf16_t *__restrict__ A,
                                                                         const bf16_t *__restrict__ B,
                                                                         bf16_t *__restrict__ X, int G, int layer,
-                                                                        int L, int r, int H_kv, int col_tiles)
+                                                                        int L, int r, int H_kv, int col_tiles,
+                                                                        int tok_tiles, int batch)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char rc_smem[];
-    const int b = blockIdx.y, d = H_kv * 128;
-    const int tok_tile = (int)(blockIdx.x & 7) + 8 * ((int)(blockIdx.x >> 3) / col_tiles), col_tile = (int)(blockIdx.x >> 3) % col_tiles;
-    const int t0 = tok_tile * kRcTok, c0 = col_tile * kRcDims;
-    if (t0 >= L) return;  // (the grid counts token tiles in eights)
+    const int d = H_kv * 128, grp = (int)(blockIdx.x >> 3) / col_tiles, col_tile = (int)(blockIdx.x >> 3) - grp * col_tiles;
+    const int tile = (int)(blockIdx.x & 7) + 8 * grp, b = __builtin_amdgcn_readfirstlane(tile / tok_tiles);
+    if (b >= batch) return;  // (the grid counts token tiles in eights)
+    const int t0 = (tile - b * tok_tiles) * kRcTok, c0 = col_tile * kRcDims;
     const int lane = lane_id(), w = wave_id(), n = lane & 31, hf = lane >> 5;
     const unsigned char *Ab = reinterpret_cast<const unsigned char *>(A + (size_t)b * L * r);
     const unsigned char *Bb = reinterpret_cast<const unsigned char *>(B + ((size_t)b * G + layer) * (size_t)r * d);
@@ -242,8 +245,9 @@ hipError_t launch_reconstruct(const xkv_shape &s, int layer, const void *A, cons
         static DynamicLdsOnce attr;
         if (hipError_t e0 = attr.ensure((const void *)reconstruct_mfma_kernel, kRcLds); e0 != hipSuccess) return e0;
         const int tok_tiles = (s.L + kRcTok - 1) / kRcTok, col_tiles = (s.H_kv * 128 + kRcDims - 1) / kRcDims;
-        hipLaunchKernelGGL(reconstruct_mfma_kernel, dim3((tok_tiles + 7) / 8 * 8 * col_tiles, s.batch), dim3(kRcThreads), kRcLds, st,
-                           (const bf16_t *)A, (const bf16_t *)B, (bf16_t *)X, s.G, layer, s.L, r, s.H_kv, col_tiles);
+        const long long tiles = ((long long)tok_tiles * s.batch + 7) / 8 * 8 * col_tiles;
+        hipLaunchKernelGGL(reconstruct_mfma_kernel, dim3((unsigned)tiles), dim3(kRcThreads), kRcLds, st, (const bf16_t *)A,
+                           (const bf16_t *)B, (bf16_t *)X, s.G, layer, s.L, r, s.H_kv, col_tiles, tok_tiles, s.batch);
         return hipGetLastError();
     }
     const int d = s.H_kv * s.d_h;
