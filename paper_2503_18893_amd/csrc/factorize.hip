@@ -33,20 +33,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t fz_u32x4_t;
 typedef __attribute__((ext_vector_type(4))) float fz_f32x4_t;
 typedef __attribute__((address_space(3))) void fz_lds_void_t;
 
-__device__ __forceinline__ void fz_copy16_global_to_lds(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
-}
-// s_waitcnt bounding only the number of outstanding vector-memory operations (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-#define FZ_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (0xF << 8) | (((n) >> 4) << 14))
-
-__device__ __forceinline__ void fz_lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // ------------------------------------------------------------------------------------------------
 // (1) X [G*H_kv][L][d_h] (one sequence, every layer and head of the group) -> Xt [n][Lp], row
 //     cb * d_h + j = channel j of column block cb, zero beyond token L.  64 x 64 tiles through LDS.
@@ -148,7 +134,7 @@ __device__ __forceinline__ void fz_lower_patch_tile(int t, int T, int &tm, int &
 __device__ __forceinline__ void fz_issue_slab(const unsigned char *const (&rowp)[8], size_t off, uint32_t dst)
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) fz_copy16_global_to_lds(rowp[j] + off, dst + j * 1024);
+    for (int j = 0; j < 8; ++j) copy16_global_to_lds(rowp[j] + off, dst + j * 1024);
 }
 
 // One k-step of a wavefront: its 2 + 4 operand fragments (32 rows each, the lane's 16 B piece), and the 8 products.
@@ -269,8 +255,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs a)
     fz_issue_slab(rowp, next_slab(), lds0);
     fz_u32x4_t a0[2], q0[4], a1[2], q1[4];
     for (int i = 0; i < n_sb; ++i) {
-        FZ_WAIT_VMCNT(0);   // slab i is in LDS
-        fz_lds_barrier();   // ... for every wavefront; and nobody reads the other stage any more
+        XKV_WAIT_VMCNT(0);   // slab i is in LDS
+        lds_barrier();   // ... for every wavefront; and nobody reads the other stage any more
         if (i + 1 < n_sb) fz_issue_slab(rowp, next_slab(), lds0 + (uint32_t)(((i + 1) & 1) * kGemmStage));
         const fz_u32x4_t *st = reinterpret_cast<const fz_u32x4_t *>(fz_smem + (i & 1) * kGemmStage);
         fz_read_frags(a0, q0, st, arow, qrow, h ^ sw);

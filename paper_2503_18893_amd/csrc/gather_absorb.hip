@@ -281,9 +281,7 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
     }
     for (int e = tid + PN * WAVES * 64; e < nkp * 512; e += WAVES * 64)
         Pl[e] = e < p_total ? psrc[e] : u32x4_t{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
 
     f32x4_t U[NGV * 8];
 #pragma unroll

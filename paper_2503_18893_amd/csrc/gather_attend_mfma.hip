@@ -44,21 +44,6 @@ __device__ __forceinline__ bf16x8_t pack8(const f32x16_t &c, int j)
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// 16 B per lane straight from global memory into LDS at lds_base + lane * 16 (lds_base is wave-uniform).
-// Issued as inline assembly on purpose: the compiler then does not tie later LDS reads of the *other*
-// buffer to this copy (it cannot tell the buffers apart and would drain the whole vector-memory queue before
-// every group); completion is awaited explicitly with XKV_WAIT_VMCNT before the barrier that publishes
-// the buffer.  The copy still counts as one outstanding vector-memory operation, which only makes the
-// compiler's own waits for register loads more conservative, never less.
-__device__ __forceinline__ void copy16_global_to_lds(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
-}
-
-// s_waitcnt that only bounds the number of outstanding vector-memory operations (gfx9 encoding: vmcnt is
-// split over bits 3:0 and 15:14; expcnt and lgkmcnt are left at "no wait").
-#define XKV_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (0xF << 8) | (((n) >> 4) << 14))
-
 // Wavefronts per workgroup (WAVES, template parameter): 8 with 32 selected tokens each per tile (256 tokens);
 // 4 when there are too few selected tokens to give every compute unit a 256-token tile.
 // LDS map (bytes): B fragments [2][kGroup][4][64][16] | A tiles [WAVES][512][16] | Q fragments [8][64][16] | ids
@@ -93,9 +78,7 @@ __device__ __forceinline__ void run_group(f32x16_t (&acc)[4], u32x4_t (&areg)[2 
     // Outstanding at this point, youngest first: the 8 gathers issued during the previous group, then the B copies
     // for this group, then older gathers.  The barrier orders LDS only: the gathers stay in flight across it.
     XKV_WAIT_VMCNT(kGroup);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < 32 / WAVES; ++i) copy16_global_to_lds(bsrc_next + i * (WAVES * 64), dma_dst + i * (WAVES * 1024));
 #pragma unroll
@@ -208,9 +191,7 @@ __device__ __forceinline__ void run_pair_q(f32x16_t (&acc)[4], u32x4_t (&creg)[Q
     constexpr int NG = QuantTile<QB>::NG, PITCH = QuantTile<QB>::PITCH;
     const int n = lane & 31, hf = lane >> 5;
     XKV_WAIT_VMCNT(0);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < 32 / WAVES; ++i) copy16_global_to_lds(bsrc1 + i * (WAVES * 64), dma_buf1 + i * (WAVES * 1024));
     // this pair's codes (and parameters) into the code tile, then the registers take the next pair's
@@ -231,9 +212,7 @@ __device__ __forceinline__ void run_pair_q(f32x16_t (&acc)[4], u32x4_t (&creg)[Q
     q_steps<IS_K, QB>(acc, Bl + lane, Ct + n * PITCH, 0, hf);
     __builtin_amdgcn_sched_barrier(0);
     XKV_WAIT_VMCNT(NG);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
 #pragma unroll
     for (int i = 0; i < 32 / WAVES; ++i) copy16_global_to_lds(bsrc2 + i * (WAVES * 64), dma_buf0 + i * (WAVES * 1024));
     __builtin_amdgcn_sched_barrier(0);

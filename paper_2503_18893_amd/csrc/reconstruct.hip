@@ -93,20 +93,6 @@ constexpr int kRcLdsA = kRcTok * kRcSlab * 2, kRcLdsB = kRcSlab * kRcDims * 2, k
 constexpr int kRcLds = kRcStages * kRcStage;
 static_assert(kRcLds >= kRcTok * kRcDims * 2, "the result is staged where the slabs were");
 
-__device__ __forceinline__ void rc_copy16_global_to_lds(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
-}
-// s_waitcnt bounding only the number of outstanding vector-memory operations (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-#define RC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (0xF << 8) | (((n) >> 4) << 14))
-
-__device__ __forceinline__ void rc_lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const bf16_t *__restrict__ A,
                                                                         const bf16_t *__restrict__ B,
                                                                         bf16_t *__restrict__ X, int G, int layer,
@@ -145,12 +131,12 @@ __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const b
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int at = kRcSlab * s + 8 * apc[j];
-            rc_copy16_global_to_lds(ap[j] + (at < r ? at : r - 8) * 2, __builtin_amdgcn_readfirstlane(st + (2 * w + j) * 1024));
+            copy16_global_to_lds(ap[j] + (at < r ? at : r - 8) * 2, __builtin_amdgcn_readfirstlane(st + (2 * w + j) * 1024));
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = kRcSlab * s + brow[j];
-            rc_copy16_global_to_lds(Bb + (size_t)(i < r ? i : r - 1) * d * 2 + bcol[j],
+            copy16_global_to_lds(Bb + (size_t)(i < r ? i : r - 1) * d * 2 + bcol[j],
                                     __builtin_amdgcn_readfirstlane(st + kRcLdsA + (4 * w + j) * 1024));
         }
     };
@@ -196,10 +182,10 @@ __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const b
     if (n_slabs > 1) issue(1);
     for (int s = 0; s < n_slabs; ++s) {
         if (s + 1 < n_slabs)
-            RC_WAIT_VMCNT(6);  // slab s is there, slab s + 1 may be on its way
+            XKV_WAIT_VMCNT(6);  // slab s is there, slab s + 1 may be on its way
         else
-            RC_WAIT_VMCNT(0);
-        rc_lds_barrier();  // ... for every wavefront, and nobody reads slab s - 1 any more
+            XKV_WAIT_VMCNT(0);
+        lds_barrier();  // ... for every wavefront, and nobody reads slab s - 1 any more
         if (s + 2 < n_slabs) issue(s + 2);
         const unsigned char *st = rc_smem + (s % kRcStages) * kRcStage;
         step(st, 0);
@@ -208,7 +194,7 @@ __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const b
 
     // lane (token n, hf) holds dims 32 dd + 8 (v / 4) + 4 hf + v % 4.  Round once, stage [128 tokens][8 pieces of 8 dims] per
     // wavefront, piece p of token t in place p ^ (t / 2 % 8), store whole lines
-    rc_lds_barrier();
+    lds_barrier();
     unsigned char *ot = rc_smem + w * (kRcTok * 128);
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt)

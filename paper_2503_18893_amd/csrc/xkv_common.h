@@ -55,6 +55,29 @@ __device__ __forceinline__ uint32_t order_key(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// 16 B per lane straight from global memory into LDS at lds_base + lane * 16 (lds_base is wave-uniform).
+// Issued as inline assembly on purpose: the compiler then does not tie later LDS reads of the *other*
+// buffer to this copy (it cannot tell the buffers apart and would drain the whole vector-memory queue before
+// every group); completion is awaited explicitly with XKV_WAIT_VMCNT before the barrier that publishes
+// the buffer.  The copy still counts as one outstanding vector-memory operation, which only makes the
+// compiler's own waits for register loads more conservative, never less.
+__device__ __forceinline__ void copy16_global_to_lds(const void *gptr, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_base), "v"(gptr) : "memory", "m0");
+}
+
+// s_waitcnt that only bounds the number of outstanding vector-memory operations (gfx9 encoding: vmcnt is
+// split over bits 3:0 and 15:14; expcnt and lgkmcnt are left at "no wait").
+#define XKV_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (7 << 4) | (0xF << 8) | (((n) >> 4) << 14))
+
+// Workgroup barrier that orders LDS only: __syncthreads() also waits for every outstanding vector-memory operation.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---------------------------------------------------------------------------------------------
 // Host-side plan: how a shape is split over workgroups and where each scratch array lives.
 // ---------------------------------------------------------------------------------------------
