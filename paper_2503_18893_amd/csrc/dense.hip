@@ -456,8 +456,7 @@ hipError_t launch_combine(const xkv_shape &s, int n_part, const float *part_o, c
                           hipStream_t st, int n_part2, const float *part_o2, const float *part_ml2)
 {
     if (n_part + n_part2 > kMaxCombineParts) return hipErrorInvalidValue;
-    // four columns per thread where the rows of the partials can be read that way (the caller's workspace may begin anywhere)
-    const bool vec = s.d_h % 4 == 0 && (((uintptr_t)part_o | (n_part2 > 0 ? (uintptr_t)part_o2 : 0)) & 15u) == 0;
+    const bool vec = s.d_h % 4 == 0;  // four columns per thread (the partials begin on 256-byte boundaries of the workspace)
     // A group of threads covers the columns (d_h <= 256); at most eight groups, no more than there are partials, and whole
     // wavefronts: 256 threads for each of 2048 output rows of 128 columns and two partials cost 1.2 us of 28, groups of 64
     // threads in four rounds 40 of 180 us at 255 columns.  More than 64 partials need the 256 threads for their weights.

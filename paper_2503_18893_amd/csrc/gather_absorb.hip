@@ -46,15 +46,16 @@ hipError_t launch_gather_prepare(const PackArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+constexpr int kAbWaves = 4;     // wavefronts per workgroup, 32 rows each
 constexpr int kOutPitch = 132;  // floats per row of the last product's result
 // The wavefronts' sums U are merged PG groups of 128 ranks at a time, [wavefront][rank][head slots, whole quads] floats: a
 // lane of U holds a quad of slots of one rank.
 __host__ __device__ inline int slab_quads(int n_rep) { return (n_rep + 3) / 4; }
-__host__ __device__ inline int slab_bytes(int waves, int n_rep, int pg) { return waves * pg * 128 * slab_quads(n_rep) * 16; }
-__host__ __device__ inline int slab_groups(int waves, int n_rep, int ngv, int occ)  // (two workgroups share the LDS at occ 2)
+__host__ __device__ inline int slab_bytes(int n_rep, int pg) { return kAbWaves * pg * 128 * slab_quads(n_rep) * 16; }
+__host__ __device__ inline int slab_groups(int n_rep, int ngv, int occ)  // (two workgroups share the LDS at occ 2)
 {
     int pg = ngv;
-    while (pg > 1 && slab_bytes(waves, n_rep, pg) > (occ == 2 ? 44 : 100) * 1024) --pg;
+    while (pg > 1 && slab_bytes(n_rep, pg) > (occ == 2 ? 44 : 100) * 1024) --pg;
     return pg;
 }
 
@@ -139,17 +140,17 @@ __device__ __forceinline__ float max_over_rows(float x)  // over the four lanes 
     return fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
 }
 
-// WAVES wavefronts of 32 rows each; NGV groups of 128 ranks of A^V (U has NGV * 32 registers); RG groups in flight (a
+// NGV groups of 128 ranks of A^V (U has NGV * 32 registers); RG groups in flight (a
 // divisor of NGV).  QB: 0 = rows of A in bf16, 4 or 3 = quantised rows.
-template <int WAVES, int NGV, int RG, int QB, int OCC>
-__global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
+template <int NGV, int RG, int QB, int OCC>
+__global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     const void *__restrict__ A_k, const void *__restrict__ A_v, const u32x4_t *__restrict__ Pz, size_t pz_head_stride,
     const u32x4_t *__restrict__ pack_v, size_t pack_seq_stride, size_t pack_head_stride, const int32_t *__restrict__ idx,
     const int32_t *__restrict__ counts, float *__restrict__ part_o, float *__restrict__ part_ml, int L, int r_k, int r_v,
     int H_kv, int H_q, int k, int splits, int chunk, int FZ, float scale)
 {
     static_assert(NGV % RG == 0, "a tile's groups of A^V start at ring entry 0");
-    constexpr int TILE = WAVES * 32;
+    constexpr int WAVES = kAbWaves, TILE = WAVES * 32;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     // workgroup id -> (KV head fastest: the heads of a sequence gather from the same rows' lines), split, sequence
     const int g = blockIdx.x % H_kv, split = (blockIdx.x / H_kv) % splits, b = blockIdx.x / (H_kv * splits);
@@ -394,18 +395,17 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
 
     // ---- merge of the wavefronts and the product with B^V.  The rows of B^V that this wavefront multiplies are requested
     // first: fragments of 16 ranks x its 32 channels.
-    constexpr int KH = WAVES == 8 ? 2 : 1, NDB = WAVES >= 4 ? 1 : 4 / WAVES, NFB = NGV * 8 / KH;
-    const u32x4_t *pv = pack_v + (size_t)b * pack_seq_stride + (size_t)g * pack_head_stride + lane;
-    const int db0 = WAVES >= 4 ? (w & 3) : w * NDB, kh = WAVES == 8 ? w >> 2 : 0;
+    constexpr int NFB = NGV * 8;
+    const u32x4_t *pv = pack_v + (size_t)b * pack_seq_stride + (size_t)g * pack_head_stride + w * 64 + lane;
     // fragments requested ahead of the merge: what the registers hold beside U.  (Six groups: 32 instead of 16 take 0.5 us off a
     // step of one tile per workgroup, 24.6 -> 24.1 us; with 3-bit rows they cost 2 % of 16 x 8 x 4096 rows, 180 -> 184 us.)
     constexpr int NPF = OCC == 2 || (NGV == 6 && QB == 3) ? 16 : NFB < 32 ? NFB : 32;
     u32x4_t bv[NPF];
 #pragma unroll
-    for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)((kh * NFB + f) * 4 + db0) * 64];
+    for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)f * 256];
 
     const float l_a = l_run + __shfl_xor(l_run, 16, kWave), l_tot = l_a + __shfl_xor(l_a, 32, kWave);
-    const int PG = slab_groups(WAVES, n_rep, NGV, OCC), NQ = slab_quads(n_rep);
+    const int PG = slab_groups(n_rep, NGV, OCC), NQ = slab_quads(n_rep);
     uint16_t *Uf = reinterpret_cast<uint16_t *>(smem_raw);                         // [NGV * 8][64][8]
     float *ml = reinterpret_cast<float *>(smem_raw + NGV * 8 * 1024);               // [2][WAVES][16]
     float *slab = ml + 2 * WAVES * 16;
@@ -458,36 +458,22 @@ __global__ __launch_bounds__(WAVES * 64, OCC) void gather_absorb_kernel(
         __syncthreads();
     }
     const u32x4_t *Uq = reinterpret_cast<const u32x4_t *>(Uf) + lane;
-    float *po = slab;  // [KH][16][kOutPitch]
+    float *po = slab;  // [16][kOutPitch]
+    f32x16_t o;
 #pragma unroll
-    for (int dd = 0; dd < NDB; ++dd) {
-        if (dd > 0) {
+    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
 #pragma unroll
-            for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)((kh * NFB + f) * 4 + db0 + dd) * 64];
-        }
-        f32x16_t o;
+    for (int f = 0; f < NFB; ++f)
+        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq[f * 64]),
+                                                    __builtin_bit_cast(bf16x8_t, f < NPF ? bv[f < NPF ? f : 0] : pv[(size_t)f * 256]), o, 0, 0, 0);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[v] = 0.0f;
-#pragma unroll
-        for (int f = 0; f < NPF; ++f)
-            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq[(kh * NFB + f) * 64]),
-                                                        __builtin_bit_cast(bf16x8_t, bv[f]), o, 0, 0, 0);
-#pragma unroll
-        for (int f = NPF; f < NFB; ++f)
-            o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                __builtin_bit_cast(bf16x8_t, Uq[(kh * NFB + f) * 64]),
-                __builtin_bit_cast(bf16x8_t, pv[(size_t)((kh * NFB + f) * 4 + db0 + dd) * 64]), o, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 8; ++v)  // slot 8 (v / 4) + 4 hf + v % 4, its remainder's row eight registers on
-            po[(kh * 16 + 8 * (v / 4) + 4 * hf + (v % 4)) * kOutPitch + (db0 + dd) * 32 + n] = o[v] + o[v + 8];
-    }
+    for (int v = 0; v < 8; ++v)  // slot 8 (v / 4) + 4 hf + v % 4, its remainder's row eight registers on
+        po[(8 * (v / 4) + 4 * hf + (v % 4)) * kOutPitch + w * 32 + n] = o[v] + o[v + 8];
     __syncthreads();
     for (int item = tid; item < n_rep * 128; item += WAVES * 64) {
         const int hh = item >> 7, dim = item & 127;
-        float num = po[hh * kOutPitch + dim];
-        if constexpr (KH == 2) num += po[(16 + hh) * kOutPitch + dim];
         const size_t slot = ((size_t)b * H_q + g * n_rep + hh) * splits + split;
-        part_o[slot * 128 + dim] = num;
+        part_o[slot * 128 + dim] = po[hh * kOutPitch + dim];
         if (dim == 0) {
             float M = -INFINITY, den = 0.0f;
 #pragma unroll
@@ -511,12 +497,12 @@ constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512, kAbsorbLdsPair = 80 * 1024;  
 static constexpr int absorb_rg(int ngv, int occ, bool deep) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 && deep ? 4 : 2; }
 static bool absorb_deep(int FZ) { return (FZ / 8 + 3) % 4 >= 2; }
 
-static size_t absorb_lds(int waves, int ngv, int occ, int n_rep, int FZ, int chunk)
+static size_t absorb_lds(int ngv, int occ, int n_rep, int FZ, int chunk)
 {
     const int rg = absorb_rg(ngv, occ, absorb_deep(FZ));
-    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)waves * (kTileBytes + 128) + (size_t)chunk * 4;
-    const int slab = slab_bytes(waves, n_rep, slab_groups(waves, n_rep, ngv, occ)), out = 2 * 16 * kOutPitch * 4;
-    const size_t merge = (size_t)ngv * 8192 + (size_t)2 * waves * 16 * 4 + (size_t)(slab > out ? slab : out);
+    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)kAbWaves * (kTileBytes + 128) + (size_t)chunk * 4;
+    const int slab = slab_bytes(n_rep, slab_groups(n_rep, ngv, occ)), out = 16 * kOutPitch * 4;
+    const size_t merge = (size_t)ngv * 8192 + (size_t)2 * kAbWaves * 16 * 4 + (size_t)(slab > out ? slab : out);
     return main > merge ? main : merge;
 }
 
@@ -569,7 +555,7 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
             p.ab_splits = used;
         }
         p.ab_occ = occ;
-        p.ab_lds = absorb_lds(4, ngv, occ, p.n_rep, FZ, p.ab_chunk);
+        p.ab_lds = absorb_lds(ngv, occ, p.n_rep, FZ, p.ab_chunk);
     };
     if (ngv <= 4 && (long long)rows * tiles > 256) cut(2);
     if (p.ab_occ != 2 || p.ab_lds > kAbsorbLdsPair) cut(1);
@@ -590,10 +576,10 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
     do {                                                                                                                \
         static DynamicLdsOnce attr;                                                                                     \
         constexpr int RG = absorb_rg(NV, OC, DP);                                                                       \
-        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<4, NV, RG, QB, OC>, kAbsorbLdsMax);         \
+        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<NV, RG, QB, OC>, kAbsorbLdsMax);         \
         if (e != hipSuccess) return e;                                                                                  \
         profile_begin(1, st);                                                                                           \
-        hipLaunchKernelGGL((gather_absorb_kernel<4, NV, RG, QB, OC>), grid, dim3(256), p.ab_lds, st, A_k, A_v,          \
+        hipLaunchKernelGGL((gather_absorb_kernel<NV, RG, QB, OC>), grid, dim3(256), p.ab_lds, st, A_k, A_v,          \
                            (const u32x4_t *)pa.Pz, pa.z_stride / 8, pv, seq_stride, per_head, idx, counts, part_o,      \
                            part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.ab_splits, p.ab_chunk, pa.FZ, p.scale);    \
         profile_end(1, st);                                                                                             \
