@@ -41,25 +41,35 @@ def reference(A_k, A_v, B_k, B_v, q, rows, scale):
     return out, mag
 
 
+# (H_kv, n_rep, r_k, r_v, batch, k), then workgroups per compute unit and tiles of 128 rows per workgroup that the case is
+# for: tests/test_plan.py checks on the host that it gets them (0 workgroups: the other kernel)
 CASES = [
-    # H_kv, n_rep, r_k, r_v, batch, k: one row; both sides of a wavefront's 32 and of a tile's 128 rows; one rank group
-    (1, 1, 16, 128, 1, 1), (2, 4, 128, 128, 1, 31), (1, 7, 256, 256, 2, 33), (2, 16, 256, 144, 1, 127), (3, 5, 144, 256, 1, 129),
+    # one row; both sides of a wavefront's 32 and of a tile's 128 rows; one rank group
+    (1, 1, 16, 128, 1, 1, 1, 1), (2, 4, 128, 128, 1, 31, 1, 1), (1, 7, 256, 256, 2, 33, 1, 1), (2, 16, 256, 144, 1, 127, 1, 1),
+    (3, 5, 144, 256, 1, 129, 1, 1),
     # three, four, five and six groups of A^V, unequal ranks, ragged last groups
-    (2, 7, 384, 384, 1, 300), (1, 4, 512, 512, 1, 257), (1, 8, 384, 576, 1, 200), (2, 3, 640, 768, 1, 161), (1, 9, 528, 400, 1, 130),
-    # two workgroups per compute unit (more than 256 tiles): several tiles per workgroup, ragged last one
-    (8, 4, 512, 512, 5, 1000), (4, 7, 384, 384, 9, 1111), (8, 2, 128, 64, 6, 901), (8, 16, 256, 512, 5, 915),
-    # a tile per workgroup and more ranks of A^V than it keeps sums for: the rotated rows' kernel
-    (1, 4, 128, 800, 1, 200),
+    (2, 7, 384, 384, 1, 300, 1, 1), (1, 4, 512, 512, 1, 257, 1, 1), (1, 8, 384, 576, 1, 200, 1, 1), (2, 3, 640, 768, 1, 161, 1, 1),
+    (1, 9, 528, 400, 1, 130, 1, 1),
+    # two workgroups per compute unit (more than 256 tiles), the last tile ragged
+    (8, 4, 512, 512, 5, 1000, 2, 1), (4, 7, 384, 384, 9, 1111, 2, 1), (8, 2, 128, 64, 6, 901, 2, 1), (8, 16, 256, 512, 5, 915, 2, 1),
+    # several tiles per workgroup: the sums rescaled, requests from one tile's A^V to the next tile's A^K, and with more than
+    # four tiles ids beyond the first 128 of a wavefront.  Two workgroups per compute unit, then one (r_k in rings of two and
+    # of four groups, six groups of A^V)
+    (8, 1, 64, 256, 64, 700, 2, 6), (8, 4, 512, 512, 16, 1500, 2, 3), (8, 2, 384, 384, 16, 1300, 2, 3),
+    (8, 1, 640, 512, 32, 1100, 1, 9), (4, 2, 896, 512, 64, 300, 1, 3), (2, 16, 1024, 416, 128, 260, 1, 3), (8, 3, 512, 768, 32, 600, 1, 5),
+    # more ranks of A^V than a wavefront keeps sums for: the rotated rows' kernel
+    (1, 4, 128, 800, 1, 200, 0, 0),
 ]
 
 
 @pytest.mark.parametrize("bits", [0, 4, 3])
-@pytest.mark.parametrize("H_kv,n_rep,r_k,r_v,batch,k", CASES)
+@pytest.mark.parametrize("H_kv,n_rep,r_k,r_v,batch,k", [c[:6] for c in CASES])
 def test_selected_rows_against_the_definition(H_kv, n_rep, r_k, r_v, batch, k, bits):
     torch = torch_mod()
     if bits and (r_k % 32 or r_v % 32):
         pytest.skip("quantised rows come in groups of 32 ranks")
     L = max(k + 5, 700)
+    seqs = range(batch) if batch <= 9 else (0, batch // 2, batch - 1)  # that are compared
     w = synth.LLAMA_GROUP.with_(G=2, H_kv=H_kv, H_q=H_kv * n_rep, r_k=r_k, r_v=r_v, L=L, k=k, batch=batch, q_scale=3.0,
                                 a_scale=1.0, sigma_decay=0.0)
     rng = np.random.default_rng(1000 * r_k + 10 * r_v + k + bits)
@@ -75,17 +85,18 @@ def test_selected_rows_against_the_definition(H_kv, n_rep, r_k, r_v, batch, k, b
     idx[:, :, k // 2] = idx[:, :, 0]          # ids need not be distinct
     counts = rng.integers(0, k + 1, size=(batch, H_kv)).astype(np.int32)
     counts[0, 0] = 0                          # a head without rows
+    counts[-1, -1] = max(k - 1, 1)            # ... and one that ends in the last tile
     shape, layer = xb.Shape.of(w), 1
     ws = torch.full((xb.xkv_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
     q = dev["q"][layer].contiguous()
     out = torch.empty((batch, w.H_q, 128), dtype=torch.bfloat16, device="cuda")
     A = {n: dev[n] for n in ("A_k", "A_v")}
-    hat = {n: [synth.storage_to_f64(case[n][b]) for b in range(batch)] for n in ("A_k", "A_v")}
+    hat = {n: {b: synth.storage_to_f64(case[n][b]) for b in seqs} for n in ("A_k", "A_v")}
     if bits:
         for n, r in (("A_k", r_k), ("A_v", r_v)):
             A[n] = torch.empty((batch * L, xb.xkv_quantized_row_bytes(r, bits)), dtype=torch.uint8, device="cuda")
             xb.xkv_quantize_rows(dev[n], batch * L, r, A[n], bits=bits)
-            for b in range(batch):
+            for b in seqs:
                 x = oracle.dequantize_rows(*oracle.quantize_rows(case[n][b], bits))
                 hat[n][b] = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(x.astype(np.float32))).astype(np.float64)
     idx_d = torch.from_numpy(idx).cuda()
@@ -97,7 +108,7 @@ def test_selected_rows_against_the_definition(H_kv, n_rep, r_k, r_v, batch, k, b
             xb.xkv_gather_attend_ex(shape, layer, A["A_k"], A["A_v"], dev["B_k"], dev["B_v"], q, idx_d, cnt, 0.0, out, ws)
         torch.cuda.synchronize()
         got = synth.storage_to_f64(synth.to_host(out))
-        for b in range(batch):
+        for b in seqs:
             rows = [idx[b, g, :(counts[b, g] if use_counts else k)] for g in range(H_kv)]
             ref, mag = reference(hat["A_k"][b], hat["A_v"][b], synth.storage_to_f64(case["B_k"][b, layer]),
                                  synth.storage_to_f64(case["B_v"][b, layer]), synth.storage_to_f64(case["q"][layer, b]), rows,

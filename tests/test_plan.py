@@ -5,6 +5,7 @@ import subprocess
 import pytest
 
 from paper_2503_18893_amd import build as xbuild
+from test_gpu_gather_absorb import CASES
 
 
 @pytest.fixture(scope="module")
@@ -70,3 +71,9 @@ def test_which_shapes_keep_b_out_of_the_main_loop(plan_of):
         ok = sh["r_k"] <= 1024 and sh["r_v"] <= 768 and L * max(sh["r_k"], sh["r_v"]) * 2 < 1 << 32
         assert p["absorb"] == ok, (sh, p)
         assert not ok or p["lds"] <= 160 * 1024 - 512, (sh, p)
+
+
+def test_the_kernels_tests_reach_the_tiles_they_name(plan_of):
+    shapes = [dict(H_kv=h, H_q=h * n, r_k=rk, r_v=rv, batch=b, k=k) for h, n, rk, rv, b, k, _, _ in CASES]
+    for case, p in zip(CASES, plan_of(shapes)):
+        assert (p["occ"], p["chunk"] // 128) == case[6:] and p["absorb"] == (case[6] > 0), (case, p)
