@@ -268,10 +268,11 @@ def main():
                                                                      idx, out, ws)),
     }
     # algorithmic bytes of the kernels alone: the score kernel reads the projected queries, not B^K_l (the projection
-    # pre-pass does), so the r_K d term of the score stage is left out; the gather-reconstruct kernel reads B^K_l and
-    # B^V_l itself (in fragment order), so its figure is the stage's: selected rows plus B once
+    # pre-pass does), so the r_K d term of the score stage is left out; so does the selected-row kernel where it regroups the
+    # products, and reads the rows and B^V_l once; the kernel that forms every row (larger ranks, other types) reads both B
+    regrouped = w.dtype == "bf16" and w.d_h == 128 and w.r_k % 16 == 0 and w.r_v % 16 == 0 and w.r_k <= 1024 and w.r_v <= 768
     kern_bytes = {"score": w.batch * (e * w.L * w.r_k + 4 * w.H_kv * w.L),
-                  "gather_attend": bytes_gather}
+                  "gather_attend": bytes_gather - (w.batch * e * w.r_k * w.d if regrouped else 0)}
     for kname in kern_ms:
         stages[kname]["kernel_ms"] = round(kern_ms[kname], 5)
         stages[kname]["kernel_GBps"] = round(kern_bytes[kname] / (kern_ms[kname] * 1e-3) / 1e9, 1)
@@ -286,7 +287,8 @@ def main():
             if line.startswith("traffic_bytes_per_launch:"):
                 traffic = int(float(line.split(":")[1]))
     roofline = {"kernel": {"score": "score_stream_kernel / score_mfma_kernel (low-rank score stream + GQA max-pool)",
-                           "gather_attend": "gather_absorb_kernel (gather of the selected rows + sparse attention on the factors)"}[dom],
+                           "gather_attend": "gather_absorb_kernel (gather of the selected rows + sparse attention on the factors)"
+                                            if regrouped else "gather-reconstruct + sparse attention kernel"}[dom],
                 "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "alg_bytes_per_launch": kern_bytes[dom], "ms_per_launch": round(kern_ms[dom], 5),

@@ -1430,8 +1430,8 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                                    f.w_splits, vcount, (long long)f.part_seq);
         }
         double *Ma = Gm, *Mb = planes, *Jt = Lt;  // r x r each per sequence
-        // the rotations of two rounds, 32 x 32 per pair of blocks, at most 16 (r + 32) doubles each, where C (no longer needed)
-        // and the transposed basis are: n^2 / 2 doubles or more, n a multiple of 64
+        // the rotations of two rounds, 32 x 32 per pair of blocks, where C (no longer needed) and the transposed basis are: at
+        // most (r + 31) / 32 pairs, and n^2 / 2 doubles are 1024 for each of n / 32 pairs or more, n a multiple of 64, n >= r
         const long long tj_seq = (long long)n * n / 2;
         double *Tj[2] = {reinterpret_cast<double *>(part), reinterpret_cast<double *>(C)};
         int *order = reinterpret_cast<int *>(Minv);
