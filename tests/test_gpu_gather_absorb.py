@@ -55,7 +55,7 @@ CASES = [
     # several tiles per workgroup: the sums rescaled, requests from one tile's A^V to the next tile's A^K, and with more than
     # four tiles ids beyond the first 128 of a wavefront.  Two workgroups per compute unit, then one (r_k in rings of two and
     # of four groups, six groups of A^V)
-    (8, 1, 64, 256, 64, 700, 2, 6), (8, 4, 512, 512, 16, 1500, 2, 3), (8, 2, 384, 384, 16, 1300, 2, 3),
+    (8, 1, 16, 144, 128, 700, 2, 6), (8, 4, 512, 512, 16, 2200, 2, 3), (8, 2, 384, 384, 16, 1300, 2, 2),
     (8, 1, 640, 512, 32, 1100, 1, 9), (4, 2, 896, 512, 64, 300, 1, 3), (2, 16, 1024, 416, 128, 260, 1, 3), (8, 3, 512, 768, 32, 600, 1, 5),
     # more ranks of A^V than a wavefront keeps sums for: the rotated rows' kernel
     (1, 4, 128, 800, 1, 200, 0, 0),
