@@ -177,8 +177,9 @@ XKV_API xkv_status xkv_topk(const xkv_shape *shape, const float *score, int32_t 
                             size_t workspace_bytes, void *hip_stream);
 
 /* Stages 3-4 on their own: attention over the rows idx [batch][H_kv][k] of the reconstructed K and V (Eq. 3).  The
- * bf16 kernel forms the rows themselves only where they are rotated (rope_theta > 0 in the calls that take it); otherwise
- * it multiplies the gathered rows of A with B_l q and sums them before B^V_l, the same function.  Ids must lie in [0, L); they need not be sorted or distinct. */
+ * bf16 kernel forms the rows themselves only where they are rotated (rope_theta > 0 in the calls that take it) or of
+ * ranks r_k > 1024, r_v > 768; otherwise it multiplies the gathered rows of A with B_l q and sums them before B^V_l, the
+ * same function.  Ids must lie in [0, L); they need not be sorted or distinct. */
 XKV_API xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer_in_group, const void *A_k,
                                      const void *A_v, const void *B_k, const void *B_v, const void *q,
                                      const int32_t *idx, void *out, void *workspace, size_t workspace_bytes,

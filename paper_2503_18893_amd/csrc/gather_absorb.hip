@@ -524,9 +524,10 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
 {
     // Tiles are 128 rows.  Where every compute unit gets more than one, U fits 256 registers a lane and two workgroups fit the
     // LDS, two share a compute unit, so that the one streams while the other merges; else one with twice the registers, all of
-    // them for requests in flight.  (16 sequences x 8 heads x 4096 rows of ranks 512: two 179 us; one of eight wavefronts 182.
-    // A workgroup of the first kind without room for its partner has neither: 85 us at 4 x 8 x 4096 rows of ranks 768 : 512
-    // where one of the second kind takes 66.)
+    // them for requests in flight.  (At 16 sequences x 8 heads x 4096 rows of ranks 512 a pass of four layers took 1489 us; one
+    // workgroup of eight wavefronts per compute unit 1513: its wavefronts finish up to 12 us apart.  A workgroup of the first
+    // kind without room for its partner has neither: 85 us at 4 x 8 x 4096 rows of ranks 768 : 512 where one of the second
+    // kind takes 66, 217 and 196 at 16 x 8 x 4096 of 640 : 512.)
     const int tile = 128, rows = p.rows > 0 ? p.rows : 1;
     const int tiles = (s.k + tile - 1) / tile, ngv = absorb_ngv(s.r_v), FZ = (s.r_k / 16 + 7) / 8 * 8;
     // a workgroup keeps 4096 ids at most where the partials allow it; the merge takes these partials and those of an
@@ -536,12 +537,12 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
     if (most < fewest) most = fewest;
     if (most > p.max_splits) most = p.max_splits;
     // Lists are cut so that the workgroups make whole rounds of the chip: a few more than a round take as long as two (6 x 8 x
-    // 2048 rows of ranks 768 as 288 workgroups 92 us, as 192 73).  A round is one workgroup per compute unit; where two share
+    // 2048 rows of ranks 768 as 288 workgroups 92 us, as 192 67).  A round is one workgroup per compute unit; where two share
     // one it is counted as two rounds of both, so that later workgroups fill the gaps that uneven ends leave.  Of the cuts
     // into the first rounds possible the one that is done first is taken, the start and the merge of a workgroup counted as
     // one tile.  (One round of both is 0 to 8 % faster at two to eight tiles per workgroup, 177 against 180 us at 16 x 8 x 4096 rows
     // of ranks 512, but a weight is exact only for the largest logit of a wavefront's list, and with longer lists the
-    // rounding of the others shows more: error 2.14e-3 against 2.09e-3.)
+    // rounding of the others shows more: error 2.14e-3 against 2.09e-3; forming every row 3.20e-3.)
     auto cut = [&](int occ) {
         const int slots = occ == 2 ? 1024 : 256, first = (rows + slots - 1) / slots;
         long long best = 0;
