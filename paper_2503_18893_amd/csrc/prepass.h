@@ -15,6 +15,22 @@ typedef __attribute__((ext_vector_type(16))) float pp_f32x16_t;
 __host__ __device__ inline int mfma_gph(int n_rep) { return 16 / n_rep; }
 __host__ __device__ inline int mfma_blocks(int H_kv, int n_rep) { return (H_kv + 2 * mfma_gph(n_rep) - 1) / (2 * mfma_gph(n_rep)); }
 
+// A wavefront's projected queries of one KV head (acc: lane (n, hf), rank i = i0 + n, register v = head slot 8 (v / 4) + 4 hf +
+// v % 4, zero beyond r_k and beyond the real heads) as operand fragments of the selected-row kernel: fragment f, lane hf * 32
+// + column, position e = rank 16 f + 8 hf + e; columns 0 .. 15 are the high bf16 parts of the head slots, 16 .. 31 their
+// remainders.
+__device__ __forceinline__ void store_z(bf16_t *Pz_head, const pp_f32x16_t &acc, int i, int hf)
+{
+    bf16_t *base = Pz_head + ((size_t)(i / 16) * 64 + ((i % 16) / 8) * 32) * 8 + i % 8;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        const int hh = 8 * (v / 4) + 4 * hf + (v % 4);
+        const bf16_t hi = f32_to_bf16(acc[v]);
+        base[(size_t)hh * 8] = hi;
+        base[(size_t)(16 + hh) * 8] = f32_to_bf16(acc[v] - bf16_to_f32(hi));
+    }
+}
+
 // One wavefront per (slot position, block of 32 ranks): P_g [head slots x 32 ranks] = Q_g [slots x d_h] . B_g^T on
 // the matrix cores, both operands straight from global memory (lane (x, hf) holds 8 consecutive head
 // dims of query slot x / of row i0 + x of B^K_l, KV head g).  In the result lane (n, hf) holds rank i0 + n
@@ -22,6 +38,8 @@ __host__ __device__ inline int mfma_blocks(int H_kv, int n_rep) { return (H_kv +
 // both at their place in the fragment layout.  Positions are (block, half, u); positions without a KV
 // head, ranks beyond r_k and the unused tail of a half are written as zeros.
 // Pfrag layout: [batch][block][part(hi,lo)][F8 fragments][64 lanes][8 bf16], F8 = roundup(r_k/16, 8).
+// With a.Pz the same values also go to the selected-row kernel's operand, which saves a second pass over B^K_l (a packed
+// step of four layers at 16 sequences of ranks 768, 64 rows per head: 556 -> 534 us).
 __device__ __forceinline__ void project_q_frag_block(const ProjArgs &a, int blk_x, int b)
 {
     const bf16_t *__restrict__ B_k = a.B_k, *__restrict__ q = a.q;
@@ -66,6 +84,7 @@ __device__ __forceinline__ void project_q_frag_block(const ProjArgs &a, int blk_
     }
     // this lane's rank and where it sits in the fragment layout
     const int i = i0 + n;
+    if (a.Pz && g < H_kv) store_z(a.Pz + ((size_t)b * H_kv + g) * a.z_stride, acc, i, hf);
     const int f = i / 16, khf = (i % 16) / 8, e = i % 8;
     const size_t part_stride = (size_t)F8 * 64 * 8;
     bf16_t *base = Pfrag + ((size_t)b * nblk + blk) * 2 * part_stride + ((size_t)f * 64 + khf * 32) * 8 + e;
@@ -148,10 +167,9 @@ __device__ __forceinline__ void pack_q_block(const PackArgs &a, int blk, int g, 
     a.pack_q[((size_t)b * a.H_kv + g) * 512 + qi] = raw;
 }
 
-// The query heads of one KV head projected into the rank space, B^K_{l,g} q_h, as operand fragments of the selected-row
-// kernel: fragment f, lane hf * 32 + column, position e = rank 16 f + 8 hf + e; columns 0 .. 15 are the high bf16 parts of
-// the head slots, 16 .. 31 their remainders.  One wavefront per 32 ranks (the products are those of project_q_frag_block);
-// zero beyond r_k and beyond the real heads.
+// The query heads of one KV head projected into the rank space, B^K_{l,g} q_h, for the selected-row kernel (see store_z),
+// where no projection with B^K_l for the scores runs in the same launch.  One wavefront per 32 ranks (the products are
+// those of project_q_frag_block).
 __device__ __forceinline__ void project_z_block(const PackArgs &a, int blk, int g, int b)
 {
     const int i0 = (blk * 4 + wave_id()) * 32;
@@ -178,14 +196,7 @@ __device__ __forceinline__ void project_z_block(const PackArgs &a, int blk, int 
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pp_bf16x8_t, n < n_rep ? qa[f] : zero),
                                                       __builtin_bit_cast(pp_bf16x8_t, i < a.r_k ? ba[f] : zero), acc, 0, 0, 0);
     }
-    bf16_t *base = a.Pz + ((size_t)b * a.H_kv + g) * a.z_stride + ((size_t)(i / 16) * 64 + ((i % 16) / 8) * 32) * 8 + i % 8;
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {  // register v: head slot 8 (v / 4) + 4 hf + v % 4 of rank i
-        const int hh = 8 * (v / 4) + 4 * hf + (v % 4);
-        const bf16_t hi = f32_to_bf16(acc[v]);
-        base[(size_t)hh * 8] = hi;
-        base[(size_t)(16 + hh) * 8] = f32_to_bf16(acc[v] - bf16_to_f32(hi));
-    }
+    store_z(a.Pz + ((size_t)b * a.H_kv + g) * a.z_stride, acc, i, hf);
 }
 
 // Block `blk` (linear over sequence, KV head, job) of everything the selected-row kernels need of q and B_l.

@@ -1152,7 +1152,7 @@ hipError_t launch_score_stage(const xkv_shape &s, const Plan &p, int layer, cons
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
     const int gph = mfma_gph(n_rep), nblk = mfma_blocks(s.H_kv, n_rep);
     bf16_t *Pfrag = (bf16_t *)P_ws;
-    ProjArgs pj;
+    ProjArgs pj{};
     pj.B_k = (const bf16_t *)B_k;
     pj.q = (const bf16_t *)q;
     pj.Pfrag = Pfrag;
@@ -1168,10 +1168,22 @@ hipError_t launch_score_stage(const xkv_shape &s, const Plan &p, int layer, cons
     const bool zero_hist = p.score_stream && p.score_hist && row_hist && chunk_hist;
     const int zero_words = zero_hist ? p.rows * kTopkLevels * kTopkBins : 0;  // a multiple of 1024
     if (fuse_pack || zero_hist) {
+        PackArgs pk = fuse_pack ? *fuse_pack : PackArgs{};
+        // The selected-row kernel's projected queries are the same ones unless the scores come from other factors (landmarks).
+        // Where a second pass has the chip's idle wavefronts to itself it is done sooner than the further stores of the first
+        // (one sequence of 8 heads, ranks 512: 191 against 194 us for four layers; 16 sequences 1485 against 1470), and so with
+        // one query head per KV head, where a wavefront stores more for less (16 sequences: 391 against 398).
+        const bool same = B_k && B_k == pk.B_k && q == pk.q && layer == pk.layer && s.G == pk.G && s.r_k == pk.r_k &&
+                          s.H_kv == pk.H_kv && s.H_q == pk.H_q && s.batch == pk.batch && F8 == pk.FZ;
+        if (same && pk.blocks_z > 0 && n_rep > 1 && (long long)s.batch * s.H_kv * (F8 / 2) >= 512) {
+            pj.Pz = pk.Pz;
+            pj.z_stride = pk.z_stride;
+            pk.blocks_z = 0;
+        }
         const int n_proj = pj.blocks_x * s.batch;
-        const int n_pack = fuse_pack ? fuse_pack->blocks() : 0;
-        hipLaunchKernelGGL(prepass_kernel, dim3(n_proj + n_pack + zero_words / 1024), dim3(256), 0, st, pj,
-                           fuse_pack ? *fuse_pack : PackArgs{}, n_proj, n_pack, row_hist, zero_words);
+        const int n_pack = fuse_pack ? pk.blocks() : 0;
+        hipLaunchKernelGGL(prepass_kernel, dim3(n_proj + n_pack + zero_words / 1024), dim3(256), 0, st, pj, pk, n_proj, n_pack,
+                           row_hist, zero_words);
         if (packed_done) *packed_done = fuse_pack != nullptr;
     } else {
         hipLaunchKernelGGL(project_q_frag_kernel, dim3(pj.blocks_x, s.batch), dim3(256), 0, st, pj);
@@ -1249,7 +1261,7 @@ hipError_t launch_score_q4_stage(const xkv_shape &s, const Plan &p, int layer, c
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
     const int gph = mfma_gph(n_rep), nblk = mfma_blocks(s.H_kv, n_rep);
     bf16_t *Pfrag = (bf16_t *)P_ws;
-    ProjArgs pj;
+    ProjArgs pj{};
     pj.B_k = (const bf16_t *)B_k;
     pj.q = (const bf16_t *)q;
     pj.Pfrag = Pfrag;

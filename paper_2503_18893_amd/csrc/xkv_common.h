@@ -137,6 +137,8 @@ typedef __attribute__((ext_vector_type(4))) uint32_t pack_u32x4_t;
 struct ProjArgs {
     const bf16_t *B_k, *q;
     bf16_t *Pfrag;
+    bf16_t *Pz;  // (nullable) the same values once more, as the selected-row kernel reads them: see PackArgs
+    size_t z_stride;
     int G, layer, r_k, H_kv, H_q, d_h, F8;
     int blocks_x;  // 256-thread blocks per sequence
 };

@@ -139,3 +139,35 @@ def test_a_million_selected_rows_and_a_tail():
     ref, mag = w @ V, w @ V.abs()
     bound = 1.05 * 2.0 ** -8 * (ref.abs() + mag) + 1e-6 * mag.max()
     assert ((out[0, 0].double() - ref).abs() <= bound).all(), float(((out[0, 0].double() - ref).abs() - bound).max())
+
+
+# (H_kv, n_rep, r_k, r_v, batch): batch H_kv ceil(r_k / 128) 4 wavefronts, from 512 of them on one projection of the queries serves
+# the scores and the selected rows.  Both sides of that, rank counts that end within a fragment, within 8 fragments and at 1024, 2 to
+# 16 query heads per KV head and one, which keeps two projections
+ONE_PROJECTION = [(8, 4, 512, 512, 4), (8, 4, 512, 512, 3), (3, 5, 144, 256, 22), (1, 16, 80, 16, 128), (2, 9, 1024, 768, 8), (5, 2, 272, 640, 9), (8, 1, 256, 128, 8)]
+
+
+@pytest.mark.parametrize("H_kv,n_rep,r_k,r_v,batch", ONE_PROJECTION)
+def test_whole_step_equals_its_stages(H_kv, n_rep, r_k, r_v, batch):
+    """The step (B_l packed once, and in its plain layout) against the stage call on its selection, bit for bit: the projected
+    queries come from the launch that projects them for the scores in the first two, from one of their own in the third."""
+    torch = torch_mod()
+    L, k = 300, 40
+    gen = torch.Generator(device="cuda").manual_seed(r_k + r_v)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)
+    A_k, A_v, B_k, B_v = rnd(batch, L, r_k), rnd(batch, L, r_v), rnd(batch, 2, r_k, H_kv * 128), rnd(batch, 2, r_v, H_kv * 128)
+    q = rnd(batch, H_kv * n_rep, 128) * 0.05
+    shape = xb.Shape(G=2, H_kv=H_kv, H_q=H_kv * n_rep, d_h=128, r_k=r_k, r_v=r_v, L=L, k=k, batch=batch)
+    packed = torch.empty(xb.xkv_packed_b_bytes(shape), dtype=torch.uint8, device="cuda")
+    xb.xkv_pack_b(shape, B_k, B_v, packed)
+    ws = xb.alloc_workspace(shape)
+    idx = torch.empty((batch, H_kv, k), dtype=torch.int32, device="cuda")
+    got = []
+    for call in (lambda out: xb.xkv_sr_decode_packed(shape, 1, A_k, A_v, B_k, packed, q, out, idx, None, ws),
+                 lambda out: xb.xkv_sr_decode(shape, 1, A_k, A_v, B_k, B_v, q, out, idx, None, ws),
+                 lambda out: xb.xkv_gather_attend(shape, 1, A_k, A_v, B_k, B_v, q, idx, out, ws)):
+        ws.fill_(0xFF)                         # nothing may be left over from the call before
+        got.append(torch.full((batch, H_kv * n_rep, 128), float("nan"), dtype=torch.bfloat16, device="cuda"))
+        call(got[-1])
+        torch.cuda.synchronize()
+    assert torch.isfinite(got[2]).all() and torch.equal(got[0], got[2]) and torch.equal(got[1], got[2])
