@@ -61,54 +61,67 @@ __global__ __launch_bounds__(256) void landmark_kernel(const T *__restrict__ K, 
     if (lane == 0 && neg_m) neg_m[(size_t)row * n_c + j] = -worst;
 }
 
-// The same for bf16 keys of 128 channels and chunks of 4, 8, 12 or 16 tokens, read once and line-wise: an
-// instruction covers 4 rows (lane l: row l / 16, the 16 B piece l % 16), the rows of a chunk stay in registers for
-// the cosine pass, sums over channels run across the 16 lanes of a row, sums over rows across the 4 lane groups.
+// The same for bf16 keys of 128 channels and chunks of 4, 8, 12 or 16 tokens, read once and line-wise.  A wavefront takes
+// four chunks, one per row of 16 lanes: lane l holds the 16 B piece l % 16 of every key of chunk l / 16, so that a request
+// covers two whole lines of four keys, sums over a chunk's keys stay in the lane and only sums over channels run across the
+// 16 lanes, as operand modifiers of additions.  Root and quotient are taken once per key, by lane i of the chunk's 16 for its
+// key i.  The stream of keys bounds it as long as little else is done per key (keys across the rows of lanes, exchanges
+// through LDS and a root and a quotient in every lane: 36 us for 8 x 50001 keys in chunks of 8, now 19.7; 102 MB, 16 us
+// to read).
 typedef __attribute__((ext_vector_type(4))) uint32_t lm_u32x4_t;
-__global__ __launch_bounds__(256) void landmark_bf16_128_kernel(const bf16_t *__restrict__ K, bf16_t *__restrict__ Lm,
-                                                                float *__restrict__ neg_m, int L, int c, int n_c)
+template <int CTRL> __device__ __forceinline__ float lm_dpp(float x)
 {
-    const int j = blockIdx.x * 4 + wave_id(), row = blockIdx.y;
-    if (j >= n_c) return;
-    const int lane = lane_id(), rg = lane >> 4, pc = lane & 15;
-    const int t0 = j * c, t1 = (t0 + c < L) ? t0 + c : L;
-    const lm_u32x4_t *Kr = reinterpret_cast<const lm_u32x4_t *>(K + (size_t)row * L * 128);
-    lm_u32x4_t xs[4];
-    float sum[8];
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+// over the 16 lanes of a row, neighbours first: lanes 1 0 3 2, then 2 3 0 1, then the two mirrored orders
+__device__ __forceinline__ float lm_row_sum(float v)
+{
+    v += lm_dpp<0xB1>(v);
+    v += lm_dpp<0x4E>(v);
+    v += lm_dpp<0x141>(v);
+    v += lm_dpp<0x140>(v);
+    return v;
+}
+
+template <int C>
+__global__ __launch_bounds__(256) void landmark_bf16_128_kernel(const bf16_t *__restrict__ K, bf16_t *__restrict__ Lm,
+                                                                float *__restrict__ neg_m, int L, int n_c)
+{
+    const int j0 = (blockIdx.x * 4 + wave_id()) * 4, row = blockIdx.y;
+    if (j0 >= n_c) return;
+    const int lane = lane_id(), pc = lane & 15;
+    const int j = j0 + (lane >> 4) < n_c ? j0 + (lane >> 4) : n_c - 1;  // (lanes beyond the last chunk repeat it)
+    const int t0 = j * C, nt = L - t0 < C ? L - t0 : C;                  // first key of the chunk, keys that it has
+    const lm_u32x4_t *Kc = reinterpret_cast<const lm_u32x4_t *>(K + ((size_t)row * L + t0) * 128) + pc;
+    lm_u32x4_t xs[C];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sum[e] = 0.0f;
+    for (int i = 0; i < C; ++i) xs[i] = __builtin_nontemporal_load(Kc + 16 * (i < nt ? i : nt - 1));
+    if (nt < C) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int t = t0 + 4 * i + rg;
-        xs[i] = lm_u32x4_t{0u, 0u, 0u, 0u};
-        if (4 * i < c && t < t1) xs[i] = Kr[(size_t)t * 16 + pc];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sum[2 * e] += __uint_as_float(xs[i][e] << 16);
-            sum[2 * e + 1] += __uint_as_float(xs[i][e] & 0xFFFF0000u);
-        }
+        for (int i = 1; i < C; ++i)
+            if (i >= nt) xs[i] = lm_u32x4_t{0u, 0u, 0u, 0u};
     }
-    const float inv = 1.0f / (float)(t1 - t0);
+    const float inv = 1.0f / (float)nt;
     float mean[8], mm = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        float v = sum[e];
-        v += __shfl_xor(v, 16, kWave);
-        v += __shfl_xor(v, 32, kWave);
-        mean[e] = v * inv;
+        float s4[4];  // (keys i, i + 4, .. first)
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const float x = __uint_as_float(e & 1 ? xs[i][e >> 1] & 0xFFFF0000u : xs[i][e >> 1] << 16);
+            s4[i & 3] = i < 4 ? x : s4[i & 3] + x;
+        }
+        mean[e] = ((s4[0] + s4[1]) + (s4[2] + s4[3]) + 0.0f) * inv;  // (+ 0: the mean of negative zeros is zero)
         mm += mean[e] * mean[e];
     }
+    mm = lm_row_sum(mm);
+    lm_u32x4_t pk;
 #pragma unroll
-    for (int o2 = 1; o2 < 16; o2 <<= 1) mm += __shfl_xor(mm, o2, kWave);
-    if (rg == 0) {
-        lm_u32x4_t pk;
+    for (int e = 0; e < 4; ++e) pk[e] = (uint32_t)f32_to_bf16(mean[2 * e]) | ((uint32_t)f32_to_bf16(mean[2 * e + 1]) << 16);
+    reinterpret_cast<lm_u32x4_t *>(Lm + ((size_t)row * n_c + j) * 128)[pc] = pk;
+    float xm_l = 0.0f, xx_l = 0.0f;  // of the key that this lane stands for
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = (uint32_t)f32_to_bf16(mean[2 * e]) | ((uint32_t)f32_to_bf16(mean[2 * e + 1]) << 16);
-        reinterpret_cast<lm_u32x4_t *>(Lm + ((size_t)row * n_c + j) * 128)[pc] = pk;
-    }
-    float worst = INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < C; ++i) {
         float xm = 0.0f, xx = 0.0f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -116,18 +129,19 @@ __global__ __launch_bounds__(256) void landmark_bf16_128_kernel(const bf16_t *__
             xm += x0 * mean[2 * e] + x1 * mean[2 * e + 1];
             xx += x0 * x0 + x1 * x1;
         }
-#pragma unroll
-        for (int o2 = 1; o2 < 16; o2 <<= 1) {
-            xm += __shfl_xor(xm, o2, kWave);
-            xx += __shfl_xor(xx, o2, kWave);
-        }
-        const float den = sqrtf(xx) * sqrtf(mm);
-        const float cs = den > 0.0f ? xm / den : 0.0f;
-        if (4 * i < c && t0 + 4 * i + rg < t1) worst = fminf(worst, cs);
+        xm = lm_row_sum(xm);
+        xx = lm_row_sum(xx);
+        xm_l = pc == i ? xm : xm_l;
+        xx_l = pc == i ? xx : xx_l;
     }
-    worst = fminf(worst, __shfl_xor(worst, 16, kWave));
-    worst = fminf(worst, __shfl_xor(worst, 32, kWave));
-    if (lane == 0 && neg_m) neg_m[(size_t)row * n_c + j] = -worst;
+    const float den = sqrtf(xx_l) * sqrtf(mm);
+    const float cs = den > 0.0f ? xm_l / den : 0.0f;
+    float worst = pc < nt ? fminf(INFINITY, cs) : INFINITY;
+    worst = fminf(worst, lm_dpp<0xB1>(worst));
+    worst = fminf(worst, lm_dpp<0x4E>(worst));
+    worst = fminf(worst, lm_dpp<0x141>(worst));
+    worst = fminf(worst, lm_dpp<0x140>(worst));
+    if (pc == 0 && neg_m) neg_m[(size_t)row * n_c + j] = -worst;
 }
 
 // `copies` identity matrices [d_h][d_h] in the storage type.
@@ -201,8 +215,12 @@ hipError_t launch_landmarks(const xkv_shape &s, const void *K_rope, int c, void 
     const int n_c = (s.L + c - 1) / c;
     dim3 grid((n_c + 3) / 4, s.batch * s.H_kv);
     if (s.dtype == XKV_BF16 && s.d_h == 128 && c % 4 == 0 && c <= 16 && (((uintptr_t)K_rope | (uintptr_t)landmarks) & 15u) == 0) {
-        hipLaunchKernelGGL(landmark_bf16_128_kernel, grid, dim3(256), 0, st, (const bf16_t *)K_rope, (bf16_t *)landmarks,
-                           neg_min_cos, s.L, c, n_c);
+        const dim3 grid4((n_c + 15) / 16, s.batch * s.H_kv);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid4, dim3(256), 0, st, (const bf16_t *)K_rope, (bf16_t *)landmarks, neg_min_cos, s.L, n_c);
+        };
+        c == 4 ? launch(landmark_bf16_128_kernel<4>) : c == 8 ? launch(landmark_bf16_128_kernel<8>)
+            : c == 12 ? launch(landmark_bf16_128_kernel<12>) : launch(landmark_bf16_128_kernel<16>);
         return hipGetLastError();
     }
     if (s.dtype == XKV_F32)
