@@ -1034,7 +1034,9 @@ static hipError_t launch_score_generic(const xkv_shape &s, const Plan &p, int la
 
 // Whether a shape goes to the long-stream kernel, with how many 32-token tiles per workgroup, and whether its
 // LDS also has room for the top-digit histograms.  One 8-wavefront workgroup per compute unit in a single
-// round; every wavefront gets at least 8 tiles of its own.
+// round.  It pays as soon as most compute units have a few tiles (us with the projection, this kernel against the other: ranks 512,
+// 1024 tiles 15.2 / 14.7, 1256 tiles 16.6 / 20.3, 2256 26.0 / 31.9, 3750 28.6 / 35.7; ranks 256 12.4 / 10.7, 13.0 / 13.8, 3750
+// tiles 19.2 / 21.6), with a single group of 128 ranks only where every wavefront has eight tiles of its own (5000 tiles 17.7 / 17.6).
 bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, int *waves)
 {
     *tiles_per_wg = 0;
@@ -1047,7 +1049,7 @@ bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, i
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
     const int n_tiles = (s.L + 31) / 32;
     const int pairs = s.batch * mfma_blocks(s.H_kv, n_rep);
-    if ((long long)pairs * n_tiles < 256LL * kScoreWaves * 8) return false;
+    if ((long long)pairs * n_tiles < (s.r_k > 128 ? 1200 : 256 * kScoreWaves * 8)) return false;
     const size_t lds_max = 160 * 1024 - 512, lds_p = (size_t)2 * F8 * 64 * 16;
     const size_t lds_hist = (size_t)2 * mfma_gph(n_rep) * kTopkBins * 4;
     int wv = kScoreWaves;
