@@ -4,6 +4,7 @@
 //   S[g,t] = max_{h: rho(h)=g} s[h,t]             (App. B.1 Alg. 2, GQA pooling)
 #include "xkv_common.h"
 #include "prepass.h"
+#include "dense_block.h"
 
 namespace xkv {
 
@@ -151,21 +152,69 @@ __global__ __launch_bounds__(256) void project_q_frag_kernel(ProjArgs a)
     project_q_frag_block(a, blockIdx.x, blockIdx.y);
 }
 
-// One launch for the small passes that precede the score kernel: blocks [0, n_proj) project the queries, the next
-// n_pack make what the selected-row kernels need of q and (unless the caller brought a packed B) B_l
-// (see prepass.h), the rest clear the row histograms that the score kernel adds to (zero_words a
-// multiple of 4).
-__global__ __launch_bounds__(256) void prepass_kernel(ProjArgs pj, PackArgs pk, int n_proj, int n_pack,
-                                                      uint32_t *__restrict__ zero, int zero_words)
+// One launch for the small passes that precede the score kernel and depend on nothing but the call's inputs: with TAIL first
+// the blocks that attend over the uncompressed tail (dense_block.h), then n_proj blocks that project the queries, n_pack that make what
+// the selected-row kernels need of q and (unless the caller brought a packed B) B_l (see prepass.h), and the rest clear the
+// row histograms that the score kernel adds to (zero_words a multiple of 4).
+// The tail was a launch of its own behind the selected rows: a few workgroups, 5 us for one round of loads, as long as the
+// projection takes beside them (four layers of one sequence, ranks 512, 100 tokens of tail: 20 of 202 us).
+template <bool TAIL>
+__global__ __launch_bounds__(256, TAIL ? 2 : 1) void prepass_kernel(DenseArgs tail, int n_tail, ProjArgs pj, PackArgs pk, int n_proj,
+                                                                    int n_pack, uint32_t *__restrict__ zero, int zero_words)
 {
-    if ((int)blockIdx.x < n_proj) {
-        project_q_frag_block(pj, (int)blockIdx.x % pj.blocks_x, (int)blockIdx.x / pj.blocks_x);
-    } else if ((int)blockIdx.x < n_proj + n_pack) {
-        gather_prepare_block(pk, (int)blockIdx.x - n_proj);
+    int blk = (int)blockIdx.x;
+    if constexpr (TAIL) {
+        extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+        if (blk < n_tail) {
+            const int row = blk / tail.splits;
+            dense::mfma_block(tail, blk % tail.splits, row % tail.H_kv, row / tail.H_kv, smem);
+            return;
+        }
+        blk -= n_tail;
+    }
+    if (blk < n_proj) {
+        project_q_frag_block(pj, blk % pj.blocks_x, blk / pj.blocks_x);
+    } else if (blk < n_proj + n_pack) {
+        gather_prepare_block(pk, blk - n_proj);
     } else {
-        const int i = 4 * (((int)blockIdx.x - n_proj - n_pack) * 256 + (int)threadIdx.x);
+        const int i = 4 * ((blk - n_proj - n_pack) * 256 + (int)threadIdx.x);
         if (i < zero_words) *reinterpret_cast<u32x4_t *>(zero + i) = u32x4_t{0u, 0u, 0u, 0u};
     }
+}
+
+// The launch before the scores: projection of the queries into pj.Pfrag, and whatever of the rest is asked for.
+static hipError_t launch_prepass(const xkv_shape &s, ProjArgs pj, const PackArgs *fuse_pack, const DenseArgs *tail, uint32_t *zero,
+                                 int zero_words, hipStream_t st)
+{
+    if (!fuse_pack && !tail && zero_words == 0) {
+        hipLaunchKernelGGL(project_q_frag_kernel, dim3(pj.blocks_x, s.batch), dim3(256), 0, st, pj);
+        return hipGetLastError();
+    }
+    PackArgs pk = fuse_pack ? *fuse_pack : PackArgs{};
+    const int n_rep = s.H_q / s.H_kv;
+    // The selected-row kernel's projected queries are the same ones unless the scores come from other factors (landmarks).
+    // Where a second pass has the chip's idle wavefronts to itself it is done sooner than the further stores of the first
+    // (one sequence of 8 heads, ranks 512: 191 against 194 us for four layers; 16 sequences 1485 against 1470), and so with
+    // one query head per KV head, where a wavefront stores more for less (16 sequences: 391 against 398).
+    const bool same = pj.B_k && pj.B_k == pk.B_k && pj.q == pk.q && pj.layer == pk.layer && s.G == pk.G && s.r_k == pk.r_k &&
+                      s.H_kv == pk.H_kv && s.H_q == pk.H_q && s.batch == pk.batch && pj.F8 == pk.FZ;
+    if (same && pk.blocks_z > 0 && n_rep > 1 && (long long)s.batch * s.H_kv * (pj.F8 / 2) >= 512) {
+        pj.Pz = pk.Pz;
+        pj.z_stride = pk.z_stride;
+        pk.blocks_z = 0;
+    }
+    const int n_proj = pj.blocks_x * s.batch, n_pack = fuse_pack ? pk.blocks() : 0, n_tail = tail ? tail->blocks() : 0;
+    const dim3 grid(n_tail + n_proj + n_pack + (zero_words + 1023) / 1024);
+    if (tail) {
+        static DynamicLdsOnce attr;
+        const hipError_t e = attr.ensure((const void *)prepass_kernel<true>, dense::kLdsBytes);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(prepass_kernel<true>, grid, dim3(256), dense::kLdsBytes, st, *tail, n_tail, pj, pk, n_proj, n_pack, zero,
+                           zero_words);
+    } else {
+        hipLaunchKernelGGL(prepass_kernel<false>, grid, dim3(256), 0, st, DenseArgs{}, 0, pj, pk, n_proj, n_pack, zero, zero_words);
+    }
+    return hipGetLastError();
 }
 
 // Heads per KV head rounded up to a power of two: the row length of the per-head score array.
@@ -1142,13 +1191,14 @@ bool score_stage_uses_mfma(const xkv_shape &s, const void *A_k, const void *B_k,
 hipError_t launch_score_stage(const xkv_shape &s, const Plan &p, int layer, const void *A_k, const void *B_k,
                               const void *q, void *P_ws, float *S, uint32_t *row_hist, uint32_t *chunk_hist,
                               bool *hist_done, const PackArgs *fuse_pack, bool *packed_done, hipStream_t st,
-                              float *S_heads)
+                              float *S_heads, const DenseArgs *tail)
 {
     if (hist_done) *hist_done = false;
     if (packed_done) *packed_done = false;
     // per-head scores come from either matrix-core kernel, or from the general one
     const bool mfma = score_stage_uses_mfma(s, A_k, B_k, q, P_ws, S_heads);
     if (!mfma && !B_k) return hipErrorInvalidValue;  // only the matrix-core projection generates an identity B_l
+    if (!mfma && tail) return hipErrorInvalidValue;
     if (!mfma) return launch_score_generic(s, p, layer, A_k, B_k, q, (float *)P_ws, S, S_heads, st);
     const int n_rep = s.H_q / s.H_kv;
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
@@ -1169,29 +1219,9 @@ hipError_t launch_score_stage(const xkv_shape &s, const Plan &p, int layer, cons
     // the row histograms of the top-k stage are cleared in the same launch when the score kernel will add to them
     const bool zero_hist = p.score_stream && p.score_hist && row_hist && chunk_hist;
     const int zero_words = zero_hist ? p.rows * kTopkLevels * kTopkBins : 0;  // a multiple of 1024
-    if (fuse_pack || zero_hist) {
-        PackArgs pk = fuse_pack ? *fuse_pack : PackArgs{};
-        // The selected-row kernel's projected queries are the same ones unless the scores come from other factors (landmarks).
-        // Where a second pass has the chip's idle wavefronts to itself it is done sooner than the further stores of the first
-        // (one sequence of 8 heads, ranks 512: 191 against 194 us for four layers; 16 sequences 1485 against 1470), and so with
-        // one query head per KV head, where a wavefront stores more for less (16 sequences: 391 against 398).
-        const bool same = B_k && B_k == pk.B_k && q == pk.q && layer == pk.layer && s.G == pk.G && s.r_k == pk.r_k &&
-                          s.H_kv == pk.H_kv && s.H_q == pk.H_q && s.batch == pk.batch && F8 == pk.FZ;
-        if (same && pk.blocks_z > 0 && n_rep > 1 && (long long)s.batch * s.H_kv * (F8 / 2) >= 512) {
-            pj.Pz = pk.Pz;
-            pj.z_stride = pk.z_stride;
-            pk.blocks_z = 0;
-        }
-        const int n_proj = pj.blocks_x * s.batch;
-        const int n_pack = fuse_pack ? pk.blocks() : 0;
-        hipLaunchKernelGGL(prepass_kernel, dim3(n_proj + n_pack + zero_words / 1024), dim3(256), 0, st, pj, pk, n_proj, n_pack,
-                           row_hist, zero_words);
-        if (packed_done) *packed_done = fuse_pack != nullptr;
-    } else {
-        hipLaunchKernelGGL(project_q_frag_kernel, dim3(pj.blocks_x, s.batch), dim3(256), 0, st, pj);
-    }
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_prepass(s, pj, fuse_pack, tail, row_hist, zero_words, st);
     if (e != hipSuccess) return e;
+    if (packed_done) *packed_done = fuse_pack != nullptr;
     const bf16_t *A = (const bf16_t *)A_k;
     switch (n_rep) {
     case 1: return launch_score_mfma_t<1>(s, p, A, Pfrag, S, F8, row_hist, chunk_hist, hist_done, S_heads, st);
@@ -1257,7 +1287,8 @@ bool score_q4_shape_ok(const xkv_shape &s)
 
 // Projection (as for the bf16 stream) and the score kernel over quantised rows; S and S_heads are both written.
 hipError_t launch_score_q4_stage(const xkv_shape &s, const Plan &p, int layer, const void *Aq_k, const void *B_k,
-                                 const void *q, void *P_ws, float *S, float *S_heads, hipStream_t st)
+                                 const void *q, void *P_ws, float *S, float *S_heads, hipStream_t st, const PackArgs *fuse_pack,
+                                 const DenseArgs *tail)
 {
     const int n_rep = s.H_q / s.H_kv;
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
@@ -1275,8 +1306,7 @@ hipError_t launch_score_q4_stage(const xkv_shape &s, const Plan &p, int layer, c
     pj.d_h = s.d_h;
     pj.F8 = F8;
     pj.blocks_x = ((F8 / 2) * 2 * gph * nblk + 3) / 4;
-    hipLaunchKernelGGL(project_q_frag_kernel, dim3(pj.blocks_x, s.batch), dim3(256), 0, st, pj);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_prepass(s, pj, fuse_pack, tail, nullptr, 0, st);
     if (e != hipSuccess) return e;
     const unsigned char *A = (const unsigned char *)Aq_k;
     switch (n_rep) {

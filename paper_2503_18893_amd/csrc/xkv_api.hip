@@ -191,21 +191,33 @@ xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer, const void *
     return hip_status(e);
 }
 
-// SR step; K_tail / V_tail (T > 0 tokens per KV head, uncompressed) are attended together with the selected rows.
-// Dense pass over the T uncompressed tail tokens (at most 8 splits) into their own set of partials; *n_part is how
-// many partials per query head it wrote.
-static hipError_t launch_tail(const xkv_shape &shape, const Plan &p, const void *K_tail, const void *V_tail, const void *q,
-                              int T, float *tail_o, float *tail_ml, int *n_part, hipStream_t stream)
+// The uncompressed tail of a step (T > 0 tokens per KV head): a context of its own for the dense kernel, cut into at most kTailParts
+// partials per query head, a second set that the step's merge takes into the same softmax.  Where the matrix-core kernel
+// takes it, `args` can go along with the launch that projects the queries; run() is for the other cases.
+struct Tail {
+    xkv_shape shape;
+    Plan plan;
+    const void *K, *V, *q;
+    float *o, *ml;
+    int parts = 0;  // partials per query head
+    DenseArgs args;
+    bool mfma = false;
+    hipError_t run(hipStream_t stream) const { return parts > 0 ? launch_dense(shape, plan, K, V, q, o, ml, stream) : hipSuccess; }
+};
+static Tail make_tail(const xkv_shape &shape, const Plan &p, const void *K, const void *V, const void *q, int T, float *o, float *ml)
 {
-    xkv_shape ts = shape;
-    ts.L = T;
-    Plan tp = p;
-    const int splits = clampi(ceil_div(T, 512), 1, kTailParts / 4);
-    tp.dense_chunk = ceil_div(ceil_div(T, splits), 128) * 128;
-    tp.dense_splits = ceil_div(T, tp.dense_chunk);
-    const hipError_t e = launch_dense(ts, tp, K_tail, V_tail, q, tail_o, tail_ml, stream);
-    *n_part = dense_uses_mfma(tp, K_tail, V_tail, q) ? tp.dense_splits : tp.dense_splits * 4;
-    return e;
+    Tail t{shape, p, K, V, q, o, ml};
+    if (T <= 0) return t;
+    t.shape.L = T;
+    t.mfma = dense_uses_mfma(p, K, V, q);
+    // (a workgroup of the matrix-core kernel takes 128 tokens a round, 5 us for the first: 333 tokens 9 us in one workgroup per
+    // head.  The general kernel leaves a partial per wavefront.)
+    const int splits = t.mfma ? clampi(ceil_div(T, 128), 1, kTailParts / 2) : clampi(ceil_div(T, 512), 1, kTailParts / 4);
+    t.plan.dense_chunk = ceil_div(ceil_div(T, splits), 128) * 128;
+    t.plan.dense_splits = ceil_div(T, t.plan.dense_chunk);
+    t.parts = t.mfma ? t.plan.dense_splits : t.plan.dense_splits * 4;
+    t.args = dense_args(t.shape, t.plan, K, V, q, o, ml);
+    return t;
 }
 
 // B_packed (nullable): the group's B_l in fragment order from xkv_pack_b; B_v may then be NULL.
@@ -237,22 +249,21 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
     const bool want_pack = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_packed ? B_k : B_v, pack_ws);
     if (want_pack) pa = gather_attend_pack_args(*shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, p.absorb);
     bool packed = false;
+    const Tail tail = make_tail(*shape, p, K_tail, V_tail, q, T, at<float>(workspace, p.off_tail_o), at<float>(workspace, p.off_tail_ml));
+    const bool tail_first = tail.mfma && score_stage_uses_mfma(*shape, A_k, B_k, q, at<void>(workspace, p.off_p), nullptr);
     if (e == hipSuccess)
         e = launch_score_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S,
                                p.score_hist ? topk_row_hist(p, state) : nullptr,
-                               p.score_hist ? hist : nullptr, &level0_done, want_pack ? &pa : nullptr, &packed, stream);
+                               p.score_hist ? hist : nullptr, &level0_done, want_pack ? &pa : nullptr, &packed, stream, nullptr,
+                               tail_first ? &tail.args : nullptr);
     if (e == hipSuccess) e = launch_topk(*shape, p, S, idx, hist, state, level0_done, stream);
     if (e == hipSuccess)
         e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_packed ? B_k : B_v, q, idx, pack_ws, B_packed, packed,
                                  part_o, part_ml, stream);
-    // The uncompressed tail goes through the dense kernel as a context of T tokens of its own (at most 8 splits),
-    // into a second set of partials; the merge below is one softmax over selected rows and tail.
-    int n_tail = 0;
-    float *tail_o = at<float>(workspace, p.off_tail_o), *tail_ml = at<float>(workspace, p.off_tail_ml);
-    if (T > 0 && e == hipSuccess) e = launch_tail(*shape, p, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
+    // the merge is one softmax over the selected rows and the tail
+    if (!tail_first && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, gather_partials(p, want_pack, 0.0f), part_o, part_ml, out, stream, n_tail,
-                           tail_o, tail_ml);
+        e = launch_combine(*shape, gather_partials(p, want_pack, 0.0f), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -559,12 +570,15 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
     PackArgs pk{};
     if (mfma) pk = gather_attend_pack_args(lp.attend_shape, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, gather_uses_absorb(pa, rope_theta));
     const bool fuse = gen_ident && mfma;
+    const Tail tail = make_tail(*shape, pa, K_tail, V_tail, q, T, at<float>(workspace, pa.off_tail_o), at<float>(workspace, pa.off_tail_ml));
+    const bool tail_first = gen_ident && tail.mfma;
     bool packed = false;
     hipError_t e = gen_ident ? hipSuccess : launch_identity(*shape, ident, lp.score_shape.batch, stream);
     if (e == hipSuccess)
         e = launch_score_stage(lp.score_shape, ps, 0, landmarks, gen_ident ? nullptr : ident, q, at<void>(ws_s, ps.off_p), S,
                                ps.score_hist ? topk_row_hist(ps, state) : nullptr,
-                               ps.score_hist ? hist : nullptr, &level0_done, fuse ? &pk : nullptr, &packed, stream);
+                               ps.score_hist ? hist : nullptr, &level0_done, fuse ? &pk : nullptr, &packed, stream, nullptr,
+                               tail_first ? &tail.args : nullptr);
     // top ceil(k / c) chunks per KV head, union with the outliers, expansion to rows
     if (e == hipSuccess) e = launch_topk(lp.score_shape, ps, S, chunks, hist, state, level0_done, stream);
     int32_t *rows = rows_out ? rows_out : at<int32_t>(workspace, pa.off_idx);
@@ -575,13 +589,9 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
     if (e == hipSuccess)
         e = launch_gather_attend(lp.attend_shape, pa, layer, A_k, A_v, B_k, B_v, q, rows, pack_ws, B_packed, packed, part_o,
                                  part_ml, stream, counts, rope_theta, qbits);
-    // the uncompressed tail, as in xkv_sr_decode_tail: a dense pass over its T tokens into a second set of partials
-    int n_tail = 0;
-    float *tail_o = at<float>(workspace, pa.off_tail_o), *tail_ml = at<float>(workspace, pa.off_tail_ml);
-    if (T > 0 && e == hipSuccess) e = launch_tail(*shape, pa, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
+    if (!tail_first && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta), part_o, part_ml, out, stream, n_tail, tail_o,
-                           tail_ml);
+        e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -796,21 +806,22 @@ static xkv_status sr_decode_absorbed_impl(const xkv_shape *shape, int32_t layer,
     float *heads = at<float>(workspace, a.off_heads);
     uint32_t *hist = at<uint32_t>(workspace, p.off_hist), *state = at<uint32_t>(workspace, p.off_state);
     bool level0_done = false;
+    const Tail tail = make_tail(*shape, p, K_tail, V_tail, q, T, at<float>(workspace, p.off_tail_o), at<float>(workspace, p.off_tail_ml));
+    const bool tail_first = tail.mfma && (q4 || score_stage_uses_mfma(*shape, A_k, B_k, q, at<void>(workspace, p.off_p), heads));
+    const DenseArgs *ta = tail_first ? &tail.args : nullptr;
     hipError_t e =
-        q4 ? launch_score_q4_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S, heads, stream)
+        q4 ? launch_score_q4_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S, heads, stream, nullptr, ta)
            : launch_score_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S,
                                 p.score_hist ? topk_row_hist(p, state) : nullptr,
-                                p.score_hist ? hist : nullptr, &level0_done, nullptr, nullptr, stream, heads);
+                                p.score_hist ? hist : nullptr, &level0_done, nullptr, nullptr, stream, heads, ta);
     if (e == hipSuccess) e = launch_topk(*shape, p, S, idx, hist, state, level0_done, stream);
     float *po = at<float>(workspace, a.off_po), *pml = at<float>(workspace, a.off_pml);
     if (e == hipSuccess)
         e = launch_absorbed(*shape, a, layer, A_v, B_v, heads, idx, po, pml, at<float>(workspace, a.off_part_u),
                             at<float>(workspace, a.off_part_ml), stream, q4);
-    // the uncompressed tail, if any, joins the same softmax through its own set of partials (as in xkv_sr_decode_tail)
-    int n_tail = 0;
-    float *tail_o = at<float>(workspace, p.off_tail_o), *tail_ml = at<float>(workspace, p.off_tail_ml);
-    if (T > 0 && e == hipSuccess) e = launch_tail(*shape, p, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
-    if (e == hipSuccess) e = launch_combine(*shape, a.slices, po, pml, out, stream, n_tail, tail_o, tail_ml);
+    // the uncompressed tail, if any, joins the same softmax through its own set of partials
+    if (!tail_first && e == hipSuccess) e = tail.run(stream);
+    if (e == hipSuccess) e = launch_combine(*shape, a.slices, po, pml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -857,16 +868,17 @@ xkv_status xkv_sr_decode_q4(const xkv_shape *shape, int32_t layer, const void *A
     int32_t *idx = idx_out ? idx_out : at<int32_t>(workspace, p.off_idx);
     uint32_t *hist = at<uint32_t>(workspace, p.off_hist), *state = at<uint32_t>(workspace, p.off_state);
     float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
+    const Tail tail = make_tail(*shape, p, K_tail, V_tail, q, T, at<float>(workspace, p.off_tail_o), at<float>(workspace, p.off_tail_ml));
+    const PackArgs pa = gather_attend_pack_args(*shape, layer, B_k, B_v, q, pack_ws, true, gather_uses_absorb(p, rope_theta));
     hipError_t e = launch_score_q4_stage(*shape, p, layer, Aq_k, B_k, q, at<void>(workspace, p.off_p), S,
-                                         at<float>(workspace, a.off_heads), stream);
+                                         at<float>(workspace, a.off_heads), stream, &pa, tail.mfma ? &tail.args : nullptr);
     if (e == hipSuccess) e = launch_topk(*shape, p, S, idx, hist, state, false, stream);
     if (e == hipSuccess)
-        e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
+        e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, true, part_o, part_ml,
                                  stream, nullptr, rope_theta, 4);
-    int n_tail = 0;
-    float *tail_o = at<float>(workspace, p.off_tail_o), *tail_ml = at<float>(workspace, p.off_tail_ml);
-    if (T > 0 && e == hipSuccess) e = launch_tail(*shape, p, K_tail, V_tail, q, T, tail_o, tail_ml, &n_tail, stream);
-    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream, n_tail, tail_o, tail_ml);
+    if (!tail.mfma && e == hipSuccess) e = tail.run(stream);
+    if (e == hipSuccess)
+        e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 

@@ -158,6 +158,15 @@ struct PackArgs {
 };
 constexpr int kPackQBlocks = 2;  // 256-item blocks per (sequence, KV head) for the Q^T fragments
 
+// Attention over L uncompressed tokens on the matrix cores (dense_block.h).
+struct DenseArgs {
+    const bf16_t *K, *V, *q;  // [batch][H_kv][L][128], [batch][H_q][128]
+    float *part_o, *part_ml;  // one partial per (sequence, query head, split)
+    int L, H_kv, H_q, splits, chunk, batch;
+    float scale;
+    int blocks() const { return splits * H_kv * batch; }
+};
+
 // Raises a kernel's dynamic-LDS limit the first time the kernel is launched on each device.  One static instance
 // per kernel; safe for concurrent host threads (the attribute call is idempotent, the flag word is atomic).
 struct DynamicLdsOnce {
@@ -188,7 +197,8 @@ bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, i
 hipError_t launch_score_stage(const xkv_shape &s, const Plan &p, int layer, const void *A_k, const void *B_k,
                               const void *q, void *P_ws, float *S, uint32_t *row_hist, uint32_t *chunk_hist,
                               bool *hist_done, const PackArgs *fuse_pack, bool *packed_done, hipStream_t st,
-                              float *S_heads = nullptr);
+                              float *S_heads = nullptr, const DenseArgs *tail = nullptr);
+// tail (nullable; matrix-core path only): an uncompressed tail attended in the projection launch.
 // Whether that stage runs on the matrix-core kernels for these operands.  Only then may B_k be NULL, which stands for
 // an identity B_l (landmark scoring): the projection generates its rows instead of reading them.
 bool score_stage_uses_mfma(const xkv_shape &s, const void *A_k, const void *B_k, const void *q, const void *P_ws,
@@ -247,6 +257,7 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
 hipError_t launch_dense(const xkv_shape &s, const Plan &p, const void *K, const void *V, const void *q, float *part_o,
                         float *part_ml, hipStream_t st);
 bool dense_mfma_shape_ok(const xkv_shape &s);
+DenseArgs dense_args(const xkv_shape &s, const Plan &p, const void *K, const void *V, const void *q, float *part_o, float *part_ml);
 hipError_t launch_combine(const xkv_shape &s, int n_part, const float *part_o, const float *part_ml, void *out,
                           hipStream_t st, int n_part2 = 0, const float *part_o2 = nullptr,
                           const float *part_ml2 = nullptr);
@@ -276,7 +287,8 @@ __host__ __device__ inline size_t quant_row_bytes(int r) { return ((size_t)r * 5
 __host__ __device__ inline size_t quant_row_bytes(int r, int bits) { return bits == 3 ? (size_t)r / 2 : quant_row_bytes(r); }
 bool score_q4_shape_ok(const xkv_shape &s);
 hipError_t launch_score_q4_stage(const xkv_shape &s, const Plan &p, int layer, const void *Aq_k, const void *B_k,
-                                 const void *q, void *P_ws, float *S, float *S_heads, hipStream_t st);
+                                 const void *q, void *P_ws, float *S, float *S_heads, hipStream_t st,
+                                 const PackArgs *fuse_pack = nullptr, const DenseArgs *tail = nullptr);
 hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, void *out, hipStream_t st);
 // Cross-layer factorization of the caches of one group (see factorize.hip).
 bool factorize_shape_ok(const xkv_shape &s, int r);
