@@ -9,6 +9,7 @@
 // within-chunk minimum cosine (Alg. 1), the union of the top chunks with the static outliers and its expansion
 // to token rows (Alg. 2, last two steps).
 #include "xkv_common.h"
+#include "expand_block.h"
 
 namespace xkv {
 namespace {
@@ -153,58 +154,16 @@ template <typename T> __global__ __launch_bounds__(256) void identity_kernel(T *
     B[i] = from_f32<T>(rw == col ? 1.0f : 0.0f);
 }
 
-// Alg. 2, last steps, one workgroup per (sequence, KV head): union of the k_ch selected chunks (ascending, no
-// repeats) with the o static outliers (ascending, no repeats), expanded to token rows in ascending order.  rows gets
-// (k_ch + o) * c entries, of which the first counts[row] are real (only the context's last chunk can be short, and
-// it can only be the last of the union); the rest is filled with row 0 and ignored by the attention kernel.
-__global__ __launch_bounds__(256) void expand_chunks_kernel(const int32_t *__restrict__ chunks, int k_ch,
-                                                            const int32_t *__restrict__ outliers, int o, int c, int L, int n_c,
-                                                            int32_t *__restrict__ rows, int32_t *__restrict__ counts)
+// The union of chunks and outliers as a launch of its own, one workgroup per (sequence, KV head).
+__global__ __launch_bounds__(256) void expand_chunks_kernel(const int32_t *__restrict__ chunks, int k_ch, ExpandArgs e)
 {
     extern __shared__ int32_t lds_i[];
-    int32_t *ch_s = lds_i, *ou_s = ch_s + k_ch, *lb_s = ou_s + o, *dup_s = lb_s + o, *merged = dup_s + o;  // [k_ch + o]
-    __shared__ int n_merged;
-    const int row = blockIdx.x, cap = (k_ch + o) * c, tid = threadIdx.x;
-    auto clampc = [&](int v) { return v < 0 ? 0 : (v >= n_c ? n_c - 1 : v); };
-    for (int a = tid; a < k_ch; a += 256) ch_s[a] = clampc(chunks[(size_t)row * k_ch + a]);
-    for (int b = tid; b < o; b += 256) ou_s[b] = clampc(outliers[(size_t)row * o + b]);
-    __syncthreads();
-    // both lists are ascending without repeats: an element's place in the union is its own index plus the number of
-    // elements of the other list in front of it (outliers that are also selected chunks are dropped)
-    for (int b = tid; b < o; b += 256) {
-        int lo = 0, hi = k_ch;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (ch_s[mid] < ou_s[b]) lo = mid + 1; else hi = mid;
-        }
-        lb_s[b] = lo;
-        dup_s[b] = (lo < k_ch && ch_s[lo] == ou_s[b]) ? 1 : 0;
+    const int row = blockIdx.x;
+    for (int a = threadIdx.x; a < k_ch; a += 256) {
+        const int v = chunks[(size_t)row * k_ch + a];
+        lds_i[a] = v < 0 ? 0 : (v >= e.n_c ? e.n_c - 1 : v);
     }
-    __syncthreads();
-    for (int a = tid; a < k_ch; a += 256) {
-        int before = 0;
-        for (int b = 0; b < o; ++b) before += (!dup_s[b] && ou_s[b] < ch_s[a]) ? 1 : 0;
-        merged[a + before] = ch_s[a];
-    }
-    for (int b = tid; b < o; b += 256) {
-        if (!dup_s[b]) {
-            int before = 0;
-            for (int b2 = 0; b2 < b; ++b2) before += dup_s[b2] ? 0 : 1;
-            merged[lb_s[b] + before] = ou_s[b];
-        }
-    }
-    if (tid == 0) {
-        int n = k_ch;
-        for (int b = 0; b < o; ++b) n += dup_s[b] ? 0 : 1;
-        n_merged = n;
-    }
-    __syncthreads();
-    const int n = n_merged;
-    int total = n * c;
-    if (n > 0 && merged[n - 1] == n_c - 1) total -= n_c * c - L;  // the short last chunk
-    int32_t *out = rows + (size_t)row * cap;
-    for (int i = tid; i < cap; i += 256) out[i] = i < total ? merged[i / c] * c + i % c : 0;
-    if (tid == 0) counts[row] = total;
+    expand_block(lds_i, k_ch, e, row, lds_i + k_ch, 256);
 }
 
 }  // namespace
@@ -243,12 +202,10 @@ hipError_t launch_identity(const xkv_shape &s, void *B, int copies, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_expand_chunks(const xkv_shape &s, const int32_t *chunks, int k_ch, const int32_t *outliers, int o, int c,
-                                int32_t *rows, int32_t *counts, hipStream_t st)
+hipError_t launch_expand_chunks(int rows, const int32_t *chunks, int k_ch, const ExpandArgs &e, hipStream_t st)
 {
-    const int n_c = (s.L + c - 1) / c;
-    hipLaunchKernelGGL(expand_chunks_kernel, dim3(s.batch * s.H_kv), dim3(256), (size_t)(2 * k_ch + 4 * o) * sizeof(int32_t), st,
-                       chunks, k_ch, outliers, o, c, s.L, n_c, rows, counts);
+    hipLaunchKernelGGL(expand_chunks_kernel, dim3(rows), dim3(256), ((size_t)k_ch + expand_lds_words(k_ch, e.o)) * sizeof(int32_t), st,
+                       chunks, k_ch, e);
     return hipGetLastError();
 }
 

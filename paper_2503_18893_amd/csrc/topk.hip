@@ -11,7 +11,11 @@
 // knows the threshold key T and how many keys equal to T are still needed (ties go to the smaller token
 // id), sums the counts of the chunks before its own and writes the selected ids in ascending order with
 // wavefront ballots.
+#include <cmath>
+#include <type_traits>
+
 #include "xkv_common.h"
+#include "expand_block.h"
 
 namespace xkv {
 
@@ -234,6 +238,8 @@ __global__ __launch_bounds__(256) void topk_write_kernel(const float *__restrict
     }
 }
 
+constexpr int kRowWaves = 16, kRowThreads = kRowWaves * 64;  // one workgroup per row in both kernels below
+
 // ------------------------------------------------------------------------------------------
 // Rows of up to 65536 scores: the whole selection in one launch.  One workgroup of 16 wavefronts owns a row
 // and keeps its keys in registers (NV per thread; wavefront w holds the contiguous segment
@@ -243,14 +249,14 @@ __global__ __launch_bounds__(256) void topk_write_kernel(const float *__restrict
 // 16 NV <= 1024 keys), so the clustered top digits cost no serialised atomics; the replicas are summed, the
 // first wavefront finds the bin of the k-th key, and the pass repeats on the next digit.  The ordered write
 // counts the keys to take with ballots, from the registers: where all keys equal to the threshold are taken and the ids fit,
-// they are collected in LDS and leave as whole lines; otherwise as in topk_write_kernel, stored one by one.
+// they are collected in LDS and leave as whole lines; otherwise as in topk_write_kernel, stored one by one.  expand.rows: the ids
+// are chunks and go on to the rows that they stand for (expand_block.h; a launch of its own took 5 to 7 us).
 // ------------------------------------------------------------------------------------------
-constexpr int kRowWaves = 16;
 constexpr int kRowStage = 16384;  // most ids staged in LDS
 
-template <int NV>
-__global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *__restrict__ S,
-                                                                 int32_t *__restrict__ idx_out, int L, int k)
+template <int NV, bool EXPAND>
+__global__ __launch_bounds__(kRowThreads) void topk_row_kernel(const float *__restrict__ S, int32_t *__restrict__ idx_out, int L, int k,
+                                                               ExpandArgs expand)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t hist[];  // [kTopkBins * 32]; at the end the ids, where they fit
     __shared__ uint32_t bins[kTopkBins];
@@ -301,11 +307,11 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
         const bool per_wave = level == 3;
         const bool direct = !per_wave && level > 0 && n_match <= 4096u;  // uniform over the workgroup
         if (per_wave) {
-            for (int i = tid; i < kRowWaves * kTopkBins; i += kRowWaves * 64) hist[i] = 0;
+            for (int i = tid; i < kRowWaves * kTopkBins; i += kRowThreads) hist[i] = 0;
         } else if (direct) {
             if (tid < kTopkBins) hist[tid] = 0;
         } else {
-            for (int i = tid; i < kTopkBins * 32; i += kRowWaves * 64) hist[i] = 0;
+            for (int i = tid; i < kTopkBins * 32; i += kRowThreads) hist[i] = 0;
         }
         __syncthreads();
         const uint32_t inc = (per_wave || direct) ? 1u : 1u << (16 * (lane & 1));
@@ -430,8 +436,12 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
             asm volatile("" : "+s"(run));
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
-        for (int i = tid; i < k; i += kRowWaves * 64) out[i] = (int32_t)hist[i];
+        if constexpr (EXPAND) {
+            expand_block((const int32_t *)hist, k, expand, row, (int32_t *)hist + k, kRowThreads);
+        } else {
+            __syncthreads();
+            for (int i = tid; i < k; i += kRowThreads) out[i] = (int32_t)hist[i];
+        }
         return;
     }
     if (my_eq == 0) {
@@ -448,34 +458,488 @@ __global__ __launch_bounds__(kRowWaves * 64) void topk_row_kernel(const float *_
             gt_run += (uint32_t)__popcll(mg);
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        return;
-    }
+    } else {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        const int t = base_w + 64 * j;
-        const bool is_gt = key[j] > Tw, is_eq = key[j] == Tw;
-        const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
-        const uint32_t gt_me = gt_run + lanes_below(mg), eq_me = eq_run + lanes_below(me);
-        if (is_gt || (is_eq && eq_me < need_eq)) {
-            const uint32_t pos = gt_me + (eq_me < need_eq ? eq_me : need_eq);
-            if (pos < (uint32_t)k) out[pos] = t;
+        for (int j = 0; j < NV; ++j) {
+            const int t = base_w + 64 * j;
+            const bool is_gt = key[j] > Tw, is_eq = key[j] == Tw;
+            const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
+            const uint32_t gt_me = gt_run + lanes_below(mg), eq_me = eq_run + lanes_below(me);
+            if (is_gt || (is_eq && eq_me < need_eq)) {
+                const uint32_t pos = gt_me + (eq_me < need_eq ? eq_me : need_eq);
+                if (pos < (uint32_t)k) out[pos] = t;
+            }
+            gt_run += (uint32_t)__popcll(mg);
+            eq_run += (uint32_t)__popcll(me);
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
-        gt_run += (uint32_t)__popcll(mg);
-        eq_run += (uint32_t)__popcll(me);
-        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (EXPAND) {  // (ids written by this workgroup; ties, or too many for LDS)
+        __syncthreads();
+        for (int i = tid; i < k; i += kRowThreads) hist[i] = (uint32_t)out[i];
+        expand_block((const int32_t *)hist, k, expand, row, (int32_t *)hist + k, kRowThreads);
     }
 }
 
-bool topk_row_shape_ok(const xkv_shape &s) { return s.L <= kRowWaves * 64 * 64; }
+// ------------------------------------------------------------------------------------------
+// Long rows (kRowFloor to kRowMost scores, budgets that leave the lists below room): one launch that starts from a guess.  The
+// histogram of kRowSamples scores, 16 in a row at 256 places, over equal slices of their range gives a value that the k largest and
+// a margin reach.  Every wavefront compacts those of its scores that do into a list of its own in LDS, and the exact selection works
+// on these lists, ten scores a lane at most, on 11-bit digits of the keys' distance from the guess.  The selected ids set bits
+// of a bitmap, which is read off in order.  The guess only decides how much is left to do: where fewer than k scores
+// or more than the lists hold reach it (many equal scores, say), radix passes over the whole row follow.
+// The time is the instructions per score of four wavefronts per SIMD (a microsecond for two and a half of them at 65536 scores; a
+// workgroup reads such a row in three) and, in all that runs once, the fetching of the code: loops are kept rolled.  Scores
+// 1024 apart belong to one thread, so that neighbours, which are alike, spread over all lists.
+// Against the row in registers (below 20480 scores the same), 8 rows, k a sixteenth: 32768 scores 14.5 -> 12.7 us, 40001 22.9 ->
+// 15.0, 65536 22.4 -> 18.3; against the five launches 32 rows of 131072 38.5 -> 21.8, 128 rows 110 -> 22.  8 rows of 32768 equal
+// scores, the guess in vain: 42 -> 55.
+// ------------------------------------------------------------------------------------------
+constexpr int kRowFloor = 20480, kRowMost = 131072, kRowSamples = 4096, kRowBins = 2048;
+constexpr int kRowRounds = 10, kRowList = 64 * kRowRounds;  // entries of a wavefront's list
+constexpr int kRowExpect = 8192;  // scores that may be expected to reach the guess
+constexpr float kRowSigmas = 4.5f;  // margin in standard deviations of the samples' rank
+
+// Inclusive sum over the lanes below and this one.
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t scan_step(uint32_t x)
+{
+    return x + __builtin_amdgcn_update_dpp(0u, x, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x)
+{
+    x = scan_step<0x111, 0xF>(x);  // within rows of 16: from 1, 2, 4 and 8 lanes below
+    x = scan_step<0x112, 0xF>(x);
+    x = scan_step<0x114, 0xF>(x);
+    x = scan_step<0x118, 0xF>(x);
+    x = scan_step<0x142, 0xA>(x);  // row 0's total to row 1, row 2's to row 3, then that of both to the upper half
+    return scan_step<0x143, 0xC>(x);
+}
+template <int CTRL> __device__ __forceinline__ float max_step(float x)
+{
+    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(x), __float_as_uint(x), CTRL, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float x)  // the same in every lane
+{
+    x = max_step<0x111>(x);
+    x = max_step<0x112>(x);
+    x = max_step<0x114>(x);
+    x = max_step<0x118>(x);
+    x = max_step<0x142>(x);
+    x = max_step<0x143>(x);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
+
+struct RowShared {
+    uint32_t wave[3][kRowWaves], pick[2][4];
+    float lo[kRowWaves], hi[kRowWaves];
+};
+// LDS of the guess: lists, bins, bitmap
+constexpr int kRowListWords = 2 * kRowWaves * kRowList, kRowMapWords = kRowMost / 32;
+constexpr int kRowWords = kRowListWords + kRowBins + kRowMapWords;
+
+// Sum over the threads above this one of `mine`; *all: over all threads.  part: kRowWaves words that nobody reads any more.
+// One barrier.
+__device__ __forceinline__ uint32_t sum_above(uint32_t mine, uint32_t *part)
+{
+    const uint32_t s = wave_scan(mine), all = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
+    const int w = wave_id();
+    if (lane_id() == 0) part[w] = all;
+    __syncthreads();
+    uint32_t above = all - s;
+#pragma unroll
+    for (int ww = 1; ww < kRowWaves; ++ww) above += ww > w ? part[ww] : 0u;
+    return above;
+}
+__device__ __forceinline__ uint32_t sum_below(uint32_t mine, uint32_t *part)
+{
+    const uint32_t s = wave_scan(mine);
+    const int w = wave_id();
+    if (lane_id() == 63) part[w] = s;
+    __syncthreads();
+    uint32_t below = s - mine;
+#pragma unroll
+    for (int ww = 0; ww < kRowWaves - 1; ++ww) below += ww < w ? part[ww] : 0u;
+    return below;
+}
+
+// Bounds (as floats' bits) from the samples: about r_lo of them reach lo_bits, about r_hi hi_bits.  bins: zero before and after.
+__device__ __forceinline__ void guess_bounds(const float (&x)[4], uint32_t r_lo, uint32_t r_hi, uint32_t *bins, RowShared &sh,
+                                             uint32_t &lo_bits, uint32_t &hi_bits)
+{
+    static_assert(kRowSamples == 4 * kRowThreads && kRowBins == 2 * kRowThreads, "four samples and two bins per thread");
+    const int w = wave_id(), tid = threadIdx.x;
+    // (scores that are not finite count as the nearest end of the others' range; NaN as the lower end)
+    float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (fabsf(x[u]) < INFINITY) {
+            mn = fminf(mn, x[u]);
+            mx = fmaxf(mx, x[u]);
+        }
+    mn = -wave_max_dpp(-mn);
+    mx = wave_max_dpp(mx);
+    if (lane_id() == 0) {
+        sh.lo[w] = mn;
+        sh.hi[w] = mx;
+    }
+    if (tid < 2) sh.pick[tid][0] = tid == 0 ? 0u : kRowBins - 1;
+    __syncthreads();
+#pragma unroll
+    for (int ww = 0; ww < kRowWaves; ++ww) {
+        mn = fminf(mn, sh.lo[ww]);
+        mx = fmaxf(mx, sh.hi[ww]);
+    }
+    const float range = mx - mn, scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) atomicAdd(&bins[(uint32_t)fminf(fmaxf((x[u] - mn) * scale, 0.0f), (float)(kRowBins - 1))], 1u);
+    __syncthreads();
+    const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
+    bins[2 * tid] = 0;
+    bins[2 * tid + 1] = 0;
+    const uint32_t above = sum_above(c0 + c1, sh.wave[0]);
+    auto pick = [&](int which, uint32_t r) __attribute__((always_inline)) {
+        if (above < r && r <= above + c1 + c0) sh.pick[which][0] = 2 * tid + (r <= above + c1 ? 1 : 0);
+    };
+    pick(0, r_lo);
+    pick(1, r_hi);
+    __syncthreads();
+    const uint32_t b_lo = sh.pick[0][0], b_hi = sh.pick[1][0];
+    const float width = range * (1.0f / kRowBins);
+    // (a hundredth of a slice lower: a rounded edge would leave out scores that the slice has)
+    lo_bits = __float_as_uint(scale == 0.0f || b_lo == 0 ? -INFINITY : fmaf((float)b_lo - 0.01f, width, mn));
+    hi_bits = __float_as_uint(fmaf((float)b_hi + 1.0f, width, mn));
+}
+
+// Set bits of map[0 .. words) in ascending order to out; at most `k` are set.  One barrier; whoever set the bits has passed one.
+__device__ __forceinline__ void write_map(const uint32_t *map, int words, uint32_t k, RowShared &sh, int32_t *out)
+{
+    const int per = (words + kRowThreads - 1) / kRowThreads, first = (int)threadIdx.x * per;
+    uint32_t n = 0;
+    for (int i = 0; i < per; ++i) n += first + i < words ? (uint32_t)__popc(map[first + i]) : 0u;
+    uint32_t pos = sum_below(n, sh.wave[2]);
+    for (int i = 0; i < per; ++i) {
+        uint32_t m = first + i < words ? map[first + i] : 0u;
+        while (m != 0) {
+            if (pos < k) out[pos] = 32 * (first + i) + __ffs((int)m) - 1;
+            ++pos;
+            m &= m - 1;
+        }
+    }
+}
+
+// Adds the k_rem lowest set bits of eq to map.  One barrier; the bits have been set before one.
+__device__ __forceinline__ void lowest_bits(const uint32_t *eq, uint32_t *map, int words, uint32_t k_rem, RowShared &sh)
+{
+    const int per = (words + kRowThreads - 1) / kRowThreads, first = (int)threadIdx.x * per;
+    uint32_t n = 0;
+    for (int i = 0; i < per; ++i) n += first + i < words ? (uint32_t)__popc(eq[first + i]) : 0u;
+    uint32_t before = sum_below(n, sh.wave[0]);
+    for (int i = 0; i < per && first + i < words; ++i) {
+        uint32_t m = eq[first + i], take = 0;
+        for (; m != 0 && before < k_rem; ++before) {
+            take |= m & -m;
+            m &= m - 1;
+        }
+        map[first + i] |= take;
+    }
+}
+
+// The k largest by (key, lower id first) of the scores in the wavefronts' lists (the scores' bits, then their ids; `count` in this
+// wavefront's), all of whose keys are >= lo; hi: a key that few exceed (any value is right).  Sets the bits of their ids in map
+// (zero before; `words` of them) and returns true, or false where there are fewer than k or a list was too short.
+// bins: zero.
+__device__ __forceinline__ bool select_from_lists(uint32_t *lists, uint32_t count, uint32_t k, uint32_t lo, uint32_t hi, uint32_t *bins,
+                                                  uint32_t *map, int words, RowShared &sh)
+{
+    const int lane = lane_id(), w = wave_id(), tid = threadIdx.x;
+    if (lane == 0) sh.wave[2][w] = count;
+    const uint32_t mine = count < kRowList ? count : kRowList;
+    const uint32_t *list = lists + w * 2 * kRowList + lane;
+    uint32_t d[kRowRounds], id[kRowRounds];  // distances from lo
+#pragma unroll
+    for (int j = 0; j < kRowRounds; ++j) {
+        d[j] = id[j] = 0;
+        if ((uint32_t)(64 * j) < mine) {  // (the same in the wavefront)
+            d[j] = order_key(__uint_as_float(list[64 * j])) - lo;
+            id[j] = list[64 * j + kRowList];
+        }
+    }
+    auto real = [&](int j) __attribute__((always_inline)) { return (uint32_t)(64 * j + lane) < mine; };
+    // undecided: distances in [base, base + 2^width), of which k_rem are taken, and everything above is
+    uint32_t base = 0, k_rem = k, in_bin = 0;
+    int width = 32, shift = 32 - __clz((int)((hi > lo ? hi - lo : 0u) | 1u)) - 11;
+    shift = shift < 0 ? 0 : shift;
+    for (int level = 0;; ++level) {
+        // (where the bins don't span the interval, the last one takes the rest of it)
+#pragma unroll
+        for (int j = 0; j < kRowRounds; ++j) {
+            if ((uint32_t)(64 * j) >= mine) break;
+            const uint32_t x = d[j] - base, bin = x >> shift;
+            if (real(j) && d[j] >= base && (width == 32 || x >> width == 0u)) atomicAdd(&bins[bin < kRowBins ? bin : kRowBins - 1], 1u);
+        }
+        __syncthreads();
+        if (level == 0) {
+            uint32_t n = 0, most = 0;
+#pragma unroll
+            for (int ww = 0; ww < kRowWaves; ++ww) {
+                n += sh.wave[2][ww];
+                most = sh.wave[2][ww] > most ? sh.wave[2][ww] : most;
+            }
+            if (n < k || most > kRowList) return false;
+        }
+        const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
+        bins[2 * tid] = 0;
+        bins[2 * tid + 1] = 0;
+        const uint32_t above = sum_above(c0 + c1, sh.wave[level & 1]);
+        uint32_t *pick = sh.pick[level & 1];
+        if (above < k_rem && k_rem <= above + c1 + c0) {
+            const bool odd = k_rem <= above + c1;
+            pick[0] = 2 * tid + (odd ? 1 : 0);
+            pick[1] = k_rem - above - (odd ? 0u : c1);
+            pick[2] = odd ? c1 : c0;
+        }
+        __syncthreads();
+        const uint32_t bin = pick[0];
+        k_rem = pick[1];
+        in_bin = pick[2];
+        base += bin << shift;
+        const bool rest = shift + 11 < width && bin == kRowBins - 1;
+        if (!rest) width = shift;
+        if (in_bin == k_rem || width == 0) break;  // all of them are taken, or they are equal
+        shift = width > 11 ? width - 11 : 0;
+    }
+    const bool ties = in_bin != k_rem;  // distances above base are taken, and the k_rem lowest ids of those equal to it
+#pragma unroll
+    for (int j = 0; j < kRowRounds; ++j) {
+        if ((uint32_t)(64 * j) >= mine) break;
+        if (real(j) && (ties ? d[j] > base : d[j] >= base)) atomicOr(&map[id[j] >> 5], 1u << (id[j] & 31));
+    }
+    if (ties) {
+        uint32_t *eq = lists;  // (all entries are in registers)
+        __syncthreads();
+        for (int i = tid; i < words; i += kRowThreads) eq[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kRowRounds; ++j)
+            if (real(j) && d[j] == base) atomicOr(&eq[id[j] >> 5], 1u << (id[j] & 31));
+        __syncthreads();
+        lowest_bits(eq, map, words, k_rem, sh);
+    }
+    __syncthreads();
+    return true;
+}
+
+// Calls f(bits, id, real) for every score of the row in groups of 8 x 1024, thread tid taking scores tid, tid + 1024, ..; the next two
+// groups are in flight.  (Beyond the row `real` is false; it is a constant in all groups but the last.)
+template <typename F> __device__ __forceinline__ void for_scores(const float *__restrict__ Srow, int L, F f)
+{
+    constexpr int U = 8, GROUP = U * kRowThreads;
+    const int tid = threadIdx.x;
+    uint32_t v[2][U];
+    auto fetch = [&](int t0, uint32_t (&x)[U]) __attribute__((always_inline)) {  // (always requested: the waits count requests)
+        if (t0 + GROUP <= L) {
+#pragma unroll
+            for (int j = 0; j < U; ++j) x[j] = __float_as_uint((Srow + t0 + kRowThreads * j)[(uint32_t)tid]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int t = t0 + kRowThreads * j + tid;
+                x[j] = __float_as_uint(Srow[(uint32_t)(t < L ? t : L - 1)]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(0, v[0]);
+    fetch(GROUP, v[1]);
+    for (int t0 = 0; t0 < L; t0 += 2 * GROUP) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int g0 = t0 + GROUP * h;
+            if (g0 + GROUP <= L) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) f(v[h][j], g0 + kRowThreads * j + tid, std::true_type());
+            } else if (g0 < L) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) f(v[h][j], g0 + kRowThreads * j + tid, g0 + kRowThreads * j + tid < L);
+            }
+            fetch(g0 + 2 * GROUP, v[h]);
+        }
+    }
+}
+
+// The same selection by four radix passes over the row: where the guess did not help.  Sets the bits of the
+// selected ids in map (`words`, cleared here).  hist: kTopkBins * 32 words.
+__device__ __forceinline__ void select_by_radix(const float *__restrict__ Srow, int L, uint32_t k, uint32_t *hist, uint32_t *map, int words,
+                                                RowShared &sh)
+{
+    const int tid = threadIdx.x, lane = lane_id();
+    uint32_t prefix = 0, k_rem = k, in_bin = 0;
+    __syncthreads();
+    for (int i = tid; i < kTopkBins * 32; i += kRowThreads) hist[i] = 0;
+    for (int i = tid; i < words; i += kRowThreads) map[i] = 0;
+    for (int level = 0; level < kTopkLevels; ++level) {
+        __syncthreads();
+        // (counters replicated 32 times: scores cluster in few bins at the top levels)
+        for_scores(Srow, L, [&](uint32_t bits, int, auto real) __attribute__((always_inline)) {
+            const uint32_t key = order_key(__uint_as_float(bits));
+            if (real && (level == 0 || key >> (32 - 8 * level) == prefix)) atomicAdd(&hist[(key >> (24 - 8 * level) & 0xFFu) * 32 + (lane & 31)], 1u);
+        });
+        __syncthreads();
+        uint32_t sum = 0;  // four threads per bin, eight counters each
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int at = (tid >> 2) * 32 + (tid & 3) * 8 + ((i + (tid >> 2)) & 7);
+            sum += hist[at];
+            hist[at] = 0;
+        }
+        sum += __builtin_amdgcn_update_dpp(0u, sum, 0xB1, 0xF, 0xF, true);
+        sum += __builtin_amdgcn_update_dpp(0u, sum, 0x4E, 0xF, 0xF, true);
+        const uint32_t c = (tid & 3) == 0 ? sum : 0u, above = sum_above(c, sh.wave[level & 1]);
+        if (above < k_rem && k_rem <= above + c) {
+            sh.pick[level & 1][0] = tid >> 2;
+            sh.pick[level & 1][1] = k_rem - above;
+            sh.pick[level & 1][2] = c;
+        }
+        __syncthreads();
+        prefix = prefix << 8 | sh.pick[level & 1][0];
+        k_rem = sh.pick[level & 1][1];
+        in_bin = sh.pick[level & 1][2];
+        if (in_bin == k_rem && level < kTopkLevels - 1) {  // everything from here up
+            prefix <<= 24 - 8 * level;
+            break;
+        }
+    }
+    const bool ties = in_bin != k_rem;
+    uint32_t *eq = hist;
+    if (ties) {
+        for (int i = tid; i < words; i += kRowThreads) eq[i] = 0;  // (hist is read)
+        __syncthreads();
+    }
+    for_scores(Srow, L, [&](uint32_t bits, int t, auto real) __attribute__((always_inline)) {
+        const uint32_t key = order_key(__uint_as_float(bits));
+        // 64 neighbouring scores per wavefront: their bits are two words of the map
+        const uint64_t m = __ballot(real && (ties ? key > prefix : key >= prefix)), e = ties ? __ballot(real && key == prefix) : 0;
+        if (lane < 2 && real) {
+            map[(t >> 5) + lane] = (uint32_t)(m >> (32 * lane));
+            if (ties) eq[(t >> 5) + lane] = (uint32_t)(e >> (32 * lane));
+        }
+    });
+    __syncthreads();
+    if (ties) lowest_bits(eq, map, words, k_rem, sh);
+    __syncthreads();
+}
+
+// r_lo, r_hi: ranks among the samples, see guess_bounds.  expand as above.
+__global__ __launch_bounds__(kRowThreads) void topk_long_kernel(const float *__restrict__ S, int32_t *__restrict__ idx_out, int L, int k,
+                                                               uint32_t r_lo, uint32_t r_hi, ExpandArgs expand)
+{
+    // bitmap, bins, lists (counters of the radix passes; at the end, with `expand`, the ids and what their union needs)
+    extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
+    __shared__ RowShared sh;
+    const int row = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const float *Srow = S + (size_t)row * L;
+    const int words = (L + 63) / 64 * 2;
+    uint32_t *map = smem, *bins = smem + kRowMapWords, *lists = bins + kRowBins;
+    bool done;
+    {
+        float sample[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            sample[u] = Srow[(uint32_t)(16 * w + 4 * u + (lane >> 4)) * (uint32_t)(L - 16) / 255u + (lane & 15)];
+        bins[2 * tid] = 0;
+        bins[2 * tid + 1] = 0;
+        for (int i = tid; i < words; i += kRowThreads) map[i] = 0;
+        uint32_t lo_bits, hi_bits;
+        guess_bounds(sample, r_lo, r_hi, bins, sh, lo_bits, hi_bits);
+        lo_bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo_bits);
+        // Scores that reach the bound.  Their bits as signed numbers are in order above zero; below a negative bound lie exactly
+        // the larger unsigned numbers: turned over, they are in the same order.
+        const uint32_t flip = (int)lo_bits < 0 ? 0x7FFFFFFFu : 0u;
+        const int bound = (int)(lo_bits ^ flip);
+        uint32_t *list = lists + w * 2 * kRowList, count = 0;  // scores, then ids: one store of two words; counted on where it is full
+        for_scores(Srow, L, [&](uint32_t bits, int t, auto real) __attribute__((always_inline)) {
+            const bool take = real && (int)(bits ^ flip) >= bound;
+            const uint64_t m = __ballot(take);
+            const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, count));
+            const uint32_t at = pos < kRowList ? pos : kRowList - 1;  // (a list that overflows is not used)
+            if (take) {
+                list[at] = bits;
+                list[at + kRowList] = (uint32_t)t;
+            }
+            count += (uint32_t)__popcll(m);
+        });
+        done = select_from_lists(lists, count, k, order_key(__uint_as_float(lo_bits)), order_key(__uint_as_float(hi_bits)), bins, map, words, sh);
+    }
+    if (!done) select_by_radix(Srow, L, k, lists, map, words, sh);
+    if (expand.rows) {
+        int32_t *ids = (int32_t *)bins;
+        write_map(map, words, k, sh, ids);
+        expand_block(ids, k, expand, row, ids + k, kRowThreads);
+    } else {
+        write_map(map, words, k, sh, idx_out + (size_t)row * k);
+    }
+}
+
+// Ranks among the samples for a row's guess (0: none).  Margin: kRowSigmas standard deviations of the number of samples that the k
+// largest scores have, and an eighth of k for scores that come in clusters.
+static uint32_t row_guess(int L, int k, uint32_t *r_hi)
+{
+    *r_hi = 0;
+    if (L < kRowFloor || L > kRowMost) return 0;
+    const double share = (double)k / L, mean = share * kRowSamples, dev = kRowSigmas * std::sqrt(mean * (1.0 - share)) + mean / 8 + 4.0;
+    const double reach = (mean + 2 * dev) * L / kRowSamples;
+    if ((reach < L ? reach : L) > kRowExpect) return 0;
+    *r_hi = mean > dev ? (uint32_t)(mean - dev) : 0u;
+    return (uint32_t)(mean + dev) + 1u;
+}
+
+bool topk_row_shape_ok(const xkv_shape &s)
+{
+    uint32_t r_hi;
+    return s.L <= kRowThreads * 64 || row_guess(s.L, s.k, &r_hi) > 0;
+}
+
+// Whether the rows of the chunks fit `most` words of LDS behind `before`; then *ex is set and *words is raised to what they need.
+static bool with_expansion(const xkv_shape &s, const ExpandArgs *expand, bool *expanded, size_t before, size_t most, ExpandArgs *ex, size_t *words)
+{
+    if (!expand) return false;
+    const size_t need = before + s.k + expand_lds_words(s.k, expand->o);
+    if (need > most) return false;
+    *ex = *expand;
+    *expanded = true;
+    if (*words < need) *words = need;
+    return true;
+}
 
 template <int NV>
-static hipError_t launch_topk_row_t(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, hipStream_t st)
+static hipError_t launch_topk_row_t(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, const ExpandArgs *expand,
+                                    bool *expanded, hipStream_t st)
+{
+    size_t words = s.k <= kRowStage && s.k > kTopkBins * 32 ? s.k : kTopkBins * 32;
+    ExpandArgs ex{};
+    static DynamicLdsOnce attr, attr_expand;  // (two kernels: rows of a few thousand scores take 8.0 us, 8.3 with the expansion in the code)
+    if (with_expansion(s, expand, expanded, 0, kRowStage, &ex, &words)) {
+        const hipError_t e = attr_expand.ensure((const void *)topk_row_kernel<NV, true>, (size_t)kRowStage * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((topk_row_kernel<NV, true>), dim3(p.rows), dim3(kRowThreads), 4 * words, st, S, idx, s.L, s.k, ex);
+    } else {
+        const hipError_t e = attr.ensure((const void *)topk_row_kernel<NV, false>, (size_t)kRowStage * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((topk_row_kernel<NV, false>), dim3(p.rows), dim3(kRowThreads), 4 * words, st, S, idx, s.L, s.k, ex);
+    }
+    return hipGetLastError();
+}
+
+static hipError_t launch_topk_long(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, uint32_t r_lo, uint32_t r_hi,
+                                   const ExpandArgs *expand, bool *expanded, hipStream_t st)
 {
     static DynamicLdsOnce attr;
-    const hipError_t e = attr.ensure((const void *)topk_row_kernel<NV>, (size_t)kRowStage * 4);
+    const hipError_t e = attr.ensure((const void *)topk_long_kernel, (size_t)kRowWords * 4);
     if (e != hipSuccess) return e;
-    const int words = s.k <= kRowStage && s.k > kTopkBins * 32 ? s.k : kTopkBins * 32;
-    hipLaunchKernelGGL(topk_row_kernel<NV>, dim3(p.rows), dim3(kRowWaves * 64), 4 * (size_t)words, st, S, idx, s.L, s.k);
+    size_t words = kRowWords;
+    ExpandArgs ex{};
+    with_expansion(s, expand, expanded, kRowMapWords, kRowWords, &ex, &words);
+    hipLaunchKernelGGL(topk_long_kernel, dim3(p.rows), dim3(kRowThreads), 4 * words, st, S, idx, s.L, s.k, r_lo, r_hi, ex);
     return hipGetLastError();
 }
 
@@ -487,14 +951,18 @@ hipError_t launch_topk_init(const Plan &p, uint32_t *state, hipStream_t st)
 }
 
 hipError_t launch_topk(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, uint32_t *hist,
-                       uint32_t *state, bool level0_done, hipStream_t st)
+                       uint32_t *state, bool level0_done, hipStream_t st, const ExpandArgs *expand, bool *expanded)
 {
+    if (expanded) *expanded = false;
     if (p.topk_row) {
-        const int per_thread = (s.L + kRowWaves * 64 - 1) / (kRowWaves * 64);
-        if (per_thread <= 8) return launch_topk_row_t<8>(s, p, S, idx, st);
-        if (per_thread <= 16) return launch_topk_row_t<16>(s, p, S, idx, st);
-        if (per_thread <= 32) return launch_topk_row_t<32>(s, p, S, idx, st);
-        return launch_topk_row_t<64>(s, p, S, idx, st);
+        uint32_t r_hi;
+        const uint32_t r_lo = row_guess(s.L, s.k, &r_hi);
+        if (r_lo > 0) return launch_topk_long(s, p, S, idx, r_lo, r_hi, expand, expanded, st);
+        const int per_thread = (s.L + kRowThreads - 1) / kRowThreads;
+        if (per_thread <= 8) return launch_topk_row_t<8>(s, p, S, idx, expand, expanded, st);
+        if (per_thread <= 16) return launch_topk_row_t<16>(s, p, S, idx, expand, expanded, st);
+        if (per_thread <= 32) return launch_topk_row_t<32>(s, p, S, idx, expand, expanded, st);
+        return launch_topk_row_t<64>(s, p, S, idx, expand, expanded, st);
     }
     TopkScratch ws;
     ws.hist = hist;

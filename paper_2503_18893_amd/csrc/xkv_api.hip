@@ -580,10 +580,12 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
                                ps.score_hist ? hist : nullptr, &level0_done, fuse ? &pk : nullptr, &packed, stream, nullptr,
                                tail_first ? &tail.args : nullptr);
     // top ceil(k / c) chunks per KV head, union with the outliers, expansion to rows
-    if (e == hipSuccess) e = launch_topk(lp.score_shape, ps, S, chunks, hist, state, level0_done, stream);
     int32_t *rows = rows_out ? rows_out : at<int32_t>(workspace, pa.off_idx);
     int32_t *counts = count_out ? count_out : at<int32_t>(workspace, lp.off_counts);
-    if (e == hipSuccess) e = launch_expand_chunks(*shape, chunks, lp.k_ch, outliers, o, c, rows, counts, stream);
+    const ExpandArgs ex{outliers, o, c, shape->L, lp.n_c, rows, counts};
+    bool expanded = false;
+    if (e == hipSuccess) e = launch_topk(lp.score_shape, ps, S, chunks, hist, state, level0_done, stream, &ex, &expanded);
+    if (e == hipSuccess && !expanded) e = launch_expand_chunks(ps.rows, chunks, lp.k_ch, ex, stream);
     // Eq. 3 and attention over the rows that are real
     float *part_o = at<float>(workspace, pa.off_part_o), *part_ml = at<float>(workspace, pa.off_part_ml);
     if (e == hipSuccess)

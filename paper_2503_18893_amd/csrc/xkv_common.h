@@ -167,6 +167,13 @@ struct DenseArgs {
     int blocks() const { return splits * H_kv * batch; }
 };
 
+// Selected chunks and static outliers to token rows (expand_block.h): rows [..][(k_ch + o) c], counts [..] per (sequence, KV head).
+struct ExpandArgs {
+    const int32_t *outliers;  // [..][o]
+    int o, c, L, n_c;         // outliers, tokens per chunk, tokens, chunks
+    int32_t *rows, *counts;
+};
+
 // Raises a kernel's dynamic-LDS limit the first time the kernel is launched on each device.  One static instance
 // per kernel; safe for concurrent host threads (the attribute call is idempotent, the flag word is atomic).
 struct DynamicLdsOnce {
@@ -209,8 +216,10 @@ inline int head_pitch_of(int n_rep) { return n_rep <= 1 ? 1 : n_rep <= 2 ? 2 : n
 bool topk_row_shape_ok(const xkv_shape &s);
 hipError_t launch_topk_init(const Plan &p, uint32_t *state, hipStream_t st);
 // level0_done: launch_topk_init ran and the level-0 histograms were already accumulated by the score stage.
+// expand (nullable): the ids are chunks, and their rows are written as well; *expanded tells whether they were.
 hipError_t launch_topk(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, uint32_t *hist,
-                       uint32_t *state, bool level0_done, hipStream_t st);
+                       uint32_t *state, bool level0_done, hipStream_t st, const ExpandArgs *expand = nullptr,
+                       bool *expanded = nullptr);
 // pack_ws: workspace for the operands in fragment order (Q^T fragments, then this layer's packed B).
 // B_packed (nullable): the group's B already in fragment order (xkv_pack_b), then nothing of B is packed per call.
 // packed: pack_ws already holds this call's fragments (written by the launch that projected the queries).
@@ -297,8 +306,7 @@ size_t factorize_workspace_bytes(const xkv_shape &s, int r);
 hipError_t launch_landmarks(const xkv_shape &s, const void *K_rope, int c, void *landmarks, float *neg_min_cos,
                             hipStream_t st);
 hipError_t launch_identity(const xkv_shape &s, void *B, int copies, hipStream_t st);
-hipError_t launch_expand_chunks(const xkv_shape &s, const int32_t *chunks, int k_ch, const int32_t *outliers, int o, int c,
-                                int32_t *rows, int32_t *counts, hipStream_t st);
+hipError_t launch_expand_chunks(int rows, const int32_t *chunks, int k_ch, const ExpandArgs &e, hipStream_t st);
 // r_out <= r: how many of the leading singular directions are written; sigma_out (nullable) [batch][r_out].
 hipError_t launch_factorize(const xkv_shape &s, const void *X, int r, int r_out, int iters, uint32_t seed, void *A_out,
                             void *B_out, float *sigma_out, void *ws, hipStream_t st);

@@ -1,0 +1,46 @@
+"""The selection that starts from a guess out of samples: every length at which its way changes, values for which the guess
+does not help (few distinct ones, all equal, outliers that are not finite) and scores whose place is not random."""
+import numpy as np
+import pytest
+
+from paper_2503_18893_amd import synth
+from paper_2503_18893_amd import binding as xb
+
+pytestmark = pytest.mark.gpu
+
+VALUES = {
+    "normal": lambda g, L: g.standard_normal(L),
+    "negative": lambda g, L: -np.exp(g.standard_normal(L)),
+    "offset": lambda g, L: 1000.0 + 0.01 * g.standard_normal(L),
+    "heavy": lambda g, L: g.standard_cauchy(L) ** 3,
+    "few_values": lambda g, L: g.integers(0, 5, L).astype(np.float64),
+    "equal": lambda g, L: np.full(L, -0.0),
+    "two_thirds_equal": lambda g, L: np.maximum(g.standard_normal(L), 0.43),
+    "rising": lambda g, L: np.linspace(-3.0, 5.0, L),
+    "cluster": lambda g, L: g.standard_normal(L) + 9.0 * (np.abs(np.arange(L) - 0.7 * L) < 0.04 * L),
+    "periodic": lambda g, L: np.cos(2 * np.pi * np.arange(L) * 2048 / L) + 1e-3 * g.standard_normal(L),
+    "not_finite": lambda g, L: np.where(g.random(L) < 0.3, -np.inf, np.where(g.random(L) < 0.001, np.inf, g.standard_normal(L))),
+}
+
+
+@pytest.mark.parametrize("L,k", [(2047, 100), (2048, 1), (2048, 2047), (4096, 256), (8192, 4000), (8193, 512), (16385, 1024),
+                                 (20000, 6000), (32768, 2048), (32769, 7000), (40001, 1777), (65535, 4096), (65536, 9000),
+                                 (65537, 4096), (100001, 300), (131072, 4096), (131072, 9000), (131073, 4096)])
+def test_selected_ids_are_the_largest_in_order(L, k):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    g = np.random.default_rng(L + k)
+    S = np.stack([f(g, L) for f in VALUES.values()]).astype(np.float32)[None]
+    w = synth.Workload("topk_rows", G=1, H_kv=S.shape[1], H_q=S.shape[1], d_h=16, r_k=16, r_v=16, L=L, k=k, batch=1, dtype="f32",
+                       a_scale=1.0, sigma_decay=0.5, q_scale=0.3)
+    shape = xb.Shape.of(w)
+    idx = torch.full((1, S.shape[1], k), -7, dtype=torch.int32, device="cuda")
+    ws = xb.alloc_workspace(shape)
+    xb.xkv_topk(shape, torch.from_numpy(S).cuda(), idx, ws)
+    got = idx.cpu().numpy()[0]
+    u = S[0].view(np.uint32).astype(np.int64)
+    key = np.where(u >> 31, 0xFFFFFFFF - u, u + 0x80000000)   # -0 below +0, as the library orders them
+    for row, name in enumerate(VALUES):
+        want = np.sort(np.lexsort((np.arange(L), -key[row]))[:k])
+        assert np.array_equal(got[row], want), name
