@@ -18,6 +18,14 @@
 // The 16 result lanes of a logit tile hold, slot by slot, exactly the rows that the weights operand wants in that lane, so
 // logits become weights without leaving the registers (online softmax, U rescaled once per tile).  At the end the wavefronts' U are added in LDS,
 // split into a bf16 high part and remainder (again 16 + 16 rows of one operand) and multiplied with B^V.
+//
+// KEPT: the logits are there already, so that the keys' half falls away and a row costs its values alone: from the score stage
+// (the absorbed step: every query head's score of every token) or, for rotated keys, from the KEYS form of
+// gather_attend_mfma_kernel (of every selected row).  The weights stay single precision there: they meet the rows as a high part
+// and a remainder, two matrix instructions each.  Quantised rows are not rounded to bf16 either: the operand is the code itself,
+// 16 + c (exact), the group's step goes into the weights (w step, split as before), and what is left of the affine map,
+// w (lo - 16 step), is one product per tile for all groups of 32 ranks.  (4 x 8 x 4096 rows of ranks 512: 4 bits 24 us, and 1.5 for
+// packing B^V beside the projection, against 27 of vector multiply-adds and 12 for merging them and B^V; bf16 32 us against 53.)
 #include "xkv_common.h"
 
 #include "prepass.h"
@@ -82,6 +90,22 @@ template <int QB> __device__ __forceinline__ u32x4_t dequant_word(uint32_t codes
     return __builtin_bit_cast(u32x4_t, __builtin_convertvector(x, bf16x8_t));
 }
 
+// The eight codes of a word (pairs of adjacent ranks 16 bits apart) of piece u of a request, and its (step, lo) word.
+template <int QB> __device__ __forceinline__ void group_words(const RowGroup<QB> &g, int i, uint32_t (&codes)[4], uint32_t &par)
+{
+    const u32x4_t w = g.piece[i];
+    if constexpr (QB == 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) codes[u] = w[u];
+        par = g.param[i];
+    } else {  // 96 bits of codes, four units of 24, then (step, lo)
+        const uint32_t u4[4] = {w[0], (w[0] >> 24) | (w[1] << 8), (w[1] >> 16) | (w[2] << 16), w[2] >> 8};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) codes[u] = (u4[u] & 0xFFFu) | ((u4[u] << 4) & 0x0FFF0000u);
+        par = w[3];
+    }
+}
+
 // The group into the wavefront's tile.  For the logits row t sits at 272 t (a lane reads 16 bytes of its own row: 16 rows
 // then cover every bank once).  For the sums a transposing read takes 32 bytes of the four rows 4 q + i of each of the
 // quarters q of the wavefront; row t = 16 a + 8 b + 4 c + d goes to place 16 b + 8 c + 4 a + d at a pitch of 288, which
@@ -104,18 +128,8 @@ __device__ __forceinline__ void group_to_tile(const RowGroup<QB> &g, unsigned ch
         unsigned char *dst = At + place * PITCH + 64 * (lane & 3);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const u32x4_t w = g.piece[i];
             uint32_t codes[4], par;
-            if constexpr (QB == 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) codes[u] = w[u];
-                par = g.param[i];
-            } else {  // 96 bits of codes, four units of 24, then (step, lo)
-                const uint32_t u4[4] = {w[0], (w[0] >> 24) | (w[1] << 8), (w[1] >> 16) | (w[2] << 16), w[2] >> 8};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) codes[u] = (u4[u] & 0xFFFu) | ((u4[u] << 4) & 0x0FFF0000u);
-                par = w[3];
-            }
+            group_words<QB>(g, i, codes, par);
             const float step = __uint_as_float(par << 16), lo = __uint_as_float(par & 0xFFFF0000u);
             const float lo2 = fmaf(-128.0f, step, lo);
 #pragma unroll
@@ -123,6 +137,43 @@ __device__ __forceinline__ void group_to_tile(const RowGroup<QB> &g, unsigned ch
                 *reinterpret_cast<u32x4_t *>(dst + (IS_K ? 16 : 4) * i * PITCH + 16 * u) = dequant_word<QB>(codes[u], step, lo2);
         }
     }
+}
+
+// KEPT, quantised rows: the codes as bf16 numbers 16 + c (0x4180 with the code in the upper mantissa bits), laid out like the values
+// above; the steps of every row of the four groups of 32 ranks, [group][row] floats in the order in which a lane takes the rows, and
+// lo - 16 step likewise.
+constexpr int kStepBytes = 4 * 32 * 4;
+__host__ __device__ constexpr int param_bytes(int ngv) { return (1 + ngv) * kStepBytes; }  // steps of one group of 128 ranks, offsets of all
+template <int QB> __device__ __forceinline__ void codes_to_tile(const RowGroup<QB> &g, unsigned char *At, float *steps, float *offsets, int lane)
+{
+    constexpr uint32_t kMask = QB == 4 ? 0x00780078u : 0x00380038u;
+    const int r = lane >> 2, q = lane & 3, place = 16 * (r >> 3) + 8 * ((r >> 2) & 1) + (r & 3);
+    unsigned char *dst = At + place * kTileV + 64 * q;
+    const int at = 32 * q + 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
+    uint32_t sixteen = 0x41804180u;
+    asm("" : "+v"(sixteen));  // (in a register: an and-or instruction takes one constant)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        uint32_t codes[4], word;
+        group_words<QB>(g, i, codes, word);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t w = codes[u];
+            *reinterpret_cast<u32x4_t *>(dst + 4 * i * kTileV + 16 * u) =
+                u32x4_t{((w << 3) & kMask) | sixteen, (QB == 4 ? (w >> 1) & kMask : w & kMask) | sixteen,
+                        ((w >> (2 * QB - 3)) & kMask) | sixteen, ((w >> (3 * QB - 3)) & kMask) | sixteen};
+        }
+        const float step = __uint_as_float(word << 16), lo = __uint_as_float(word & 0xFFFF0000u);
+        steps[at + 8 * i] = step;
+        offsets[at + 8 * i] = fmaf(-16.0f, step, lo);
+    }
+}
+
+// x = high + remainder, both bf16
+__device__ __forceinline__ void split_bf16(const f32x8_t &x, bf16x8_t &hi, bf16x8_t &lo)
+{
+    hi = __builtin_convertvector(x, bf16x8_t);
+    lo = __builtin_convertvector(x - __builtin_convertvector(hi, f32x8_t), bf16x8_t);
 }
 
 // Row (16 lanes) and half-wavefront exchanges on the vector ALU.  permlane16_swap(x, y) trades the odd rows of x for the
@@ -141,13 +192,18 @@ __device__ __forceinline__ float max_over_rows(float x)  // over the four lanes 
 }
 
 // NGV groups of 128 ranks of A^V (U has NGV * 32 registers); RG groups in flight (a
-// divisor of NGV).  QB: 0 = rows of A in bf16, 4 or 3 = quantised rows.
-template <int NGV, int RG, int QB, int OCC>
+// divisor of NGV).  QB: 0 = rows of A in bf16, 4 or 3 = quantised rows.  KEPT: see above; `heads` [batch][H_kv][L][hp] are the
+// scaled logits of the tokens (by_place: [batch][H_kv][k][hp], of the places in the lists), A_k and Pz are not read, FZ is 0.
+// KEPT (1, 2 or 4) is how often the query heads fit the 16 slots.  Copy c stands for group c of 32 ranks (modulo KEPT): a product for
+// that group has zero weights in the other copies, so that the sums of KEPT groups share their registers (U of four heads and 512
+// ranks 32 instead of 128, which is what lets two workgroups share a compute unit with four groups in flight each), and the
+// weights times steps of KEPT groups of quantised rows are formed together.
+template <int NGV, int RG, int QB, int OCC, int KEPT>
 __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     const void *__restrict__ A_k, const void *__restrict__ A_v, const u32x4_t *__restrict__ Pz, size_t pz_head_stride,
     const u32x4_t *__restrict__ pack_v, size_t pack_seq_stride, size_t pack_head_stride, const int32_t *__restrict__ idx,
     const int32_t *__restrict__ counts, float *__restrict__ part_o, float *__restrict__ part_ml, int L, int r_k, int r_v,
-    int H_kv, int H_q, int k, int splits, int chunk, int FZ, float scale)
+    int H_kv, int H_q, int k, int splits, int chunk, int FZ, float scale, const float *__restrict__ heads, int hp, bool by_place)
 {
     static_assert(NGV % RG == 0, "a tile's groups of A^V start at ring entry 0");
     constexpr int WAVES = kAbWaves, TILE = WAVES * 32;
@@ -160,8 +216,10 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
 
     const int NGK = FZ / 8, nkp = (NGK + RG - 1) / RG * RG;  // groups of A^K, and padded to whole rings
     u32x4_t *Pl = reinterpret_cast<u32x4_t *>(smem_raw);     // [nkp][512], zero for the padding
-    unsigned char *At = smem_raw + (size_t)nkp * 8192 + w * kTileBytes;
-    int *toks = reinterpret_cast<int *>(smem_raw + (size_t)nkp * 8192 + WAVES * kTileBytes) + w * (chunk / WAVES + 32);  // this wavefront's ids, tile by tile, then 32 times the first
+    constexpr int kWaveBytes = kTileBytes + (KEPT && QB != 0 ? param_bytes(NGV) : 0), SLOTS = 16 / (KEPT ? KEPT : 1);  // slots per copy
+    unsigned char *At = smem_raw + (size_t)nkp * 8192 + w * kWaveBytes;
+    float *steps = reinterpret_cast<float *>(At + kTileBytes), *offsets = steps + kStepBytes / 4;
+    int *toks = reinterpret_cast<int *>(smem_raw + (size_t)nkp * 8192 + WAVES * kWaveBytes) + w * (chunk / WAVES + 32);  // this wavefront's ids, tile by tile, then 32 times the first
 
     int k_eff = k;  // with `counts`, only the first counts[sequence][head] ids of a row are attended over
     if (counts) {
@@ -185,14 +243,14 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
         m = m < m_end ? m : (m_end > m_begin ? m_end - 1 : 0);
         first_id[u] = ids[m];
     }
-    const u32x4_t *psrc = Pz + ((size_t)b * H_kv + g) * pz_head_stride;
+    const u32x4_t *psrc = KEPT ? nullptr : Pz + ((size_t)b * H_kv + g) * pz_head_stride;
     const int p_total = FZ * 64;  // a multiple of 512
     constexpr int PN = 8;
     u32x4_t ptmp[PN];
 #pragma unroll
     for (int j = 0; j < PN; ++j) {
         const int e = tid + j * WAVES * 64;
-        ptmp[j] = psrc[e < p_total ? e : 0];
+        if constexpr (!KEPT) ptmp[j] = psrc[e < p_total ? e : 0];
     }
     asm volatile("" : "+v"(first_id[0]), "+v"(first_id[1]));  // (keeps both loads ahead of the others, outside the branches)
 #pragma unroll
@@ -251,7 +309,7 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
         q.rows = toks + (real ? it_tile * 32 : chunk / WAVES) + (QB == 0 ? lane >> 4 : lane >> 2);
         return q;
     };
-    constexpr int NF = RowGroup<QB>::N, HS = OCC == 2 ? 2 : 4;  // requests per group; steps whose operands are read together
+    constexpr int NF = RowGroup<QB>::N, HS = KEPT && QB != 0 ? 8 : OCC == 2 ? 2 : 4;  // requests per group; steps whose operands are read together
     RowGroup<QB> ring[RG];
     // the rows of the requests [J0, J0 + N) of a group (read together, ahead of the requests), and request j
     auto rows_of = [&](const Request &q, int (&tk)[NF], int j0, int jn) __attribute__((always_inline)) {
@@ -278,21 +336,54 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
 #pragma unroll
     for (int j = 0; j < PN; ++j) {
         const int e = tid + j * WAVES * 64;
-        if (e < nkp * 512) Pl[e] = e < p_total ? ptmp[j] : u32x4_t{0u, 0u, 0u, 0u};
+        if (!KEPT && e < nkp * 512) Pl[e] = e < p_total ? ptmp[j] : u32x4_t{0u, 0u, 0u, 0u};
     }
-    for (int e = tid + PN * WAVES * 64; e < nkp * 512; e += WAVES * 64)
+    for (int e = tid + PN * WAVES * 64; !KEPT && e < nkp * 512; e += WAVES * 64)
         Pl[e] = e < p_total ? psrc[e] : u32x4_t{0u, 0u, 0u, 0u};
-    lds_barrier();
-
-    f32x4_t U[NGV * 8];
+    if constexpr (!KEPT) lds_barrier();
+    // KEPT: the logits of this lane's slot for the eight rows whose weights it holds, a tile ahead
+    const int lrow = (n & 16) + 4 * hf;  // rows lrow + 8 (e / 4) + e % 4
+    float zk[8];
+    const float *hsrc = KEPT ? heads + ((size_t)b * H_kv + g) * (by_place ? k : L) * hp + (l16 % SLOTS < n_rep ? l16 % SLOTS : 0) : nullptr;
+    auto request_logits = [&](int tile) __attribute__((always_inline)) {
+        if (by_place) {
+            const int m0 = m_begin + tile * TILE + w * 32 + lrow;
 #pragma unroll
-    for (int i = 0; i < NGV * 8; ++i) U[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int e = 0; e < 8; ++e) {
+                const int m = m0 + 8 * (e / 4) + e % 4;
+                zk[e] = hsrc[__umul24((uint32_t)(m < k ? m : k - 1), (uint32_t)hp)];
+            }
+        } else {
+            const int *r = toks + (tile < n_tiles ? tile * 32 + lrow : chunk / WAVES);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) zk[e] = hsrc[__umul24((uint32_t)r[8 * (e / 4) + e % 4], (uint32_t)hp)];
+        }
+    };
+    if constexpr (KEPT) request_logits(0);
+    constexpr int NO = KEPT && QB != 0 ? (NGV * 4 + 15) / 16 : 1;
+    f32x4_t off_sum[NO];  // sums of w (lo - 16 step): rows the slots, columns the groups of 32 ranks
+#pragma unroll
+    for (f32x4_t &x : off_sum) x = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+    constexpr int CP = KEPT ? KEPT : 1, NU = NGV * 8 / CP;  // copies; quads of sums: [set of CP groups of 32 ranks][half of 16 ranks]
+    f32x4_t U[NU];
+#pragma unroll
+    for (int i = 0; i < NU; ++i) U[i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    const int copy = l16 / SLOTS;
+    // a weights operand with all copies but `c` zero
+    auto only = [&](const bf16x8_t &x, int c) __attribute__((always_inline)) {
+        if constexpr (CP == 1) return x;
+        u32x4_t u = __builtin_bit_cast(u32x4_t, x);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = copy == c ? u[i] : 0u;
+        return __builtin_bit_cast(bf16x8_t, u);
+    };
     float m_run = -INFINITY, l_run = 0.0f;  // of slot lane % 16 (the sum: this lane's share)
     const unsigned char *krd = At + n * kTileK + 16 * hf, *vrd = At + (4 * q4 + (l16 >> 2)) * kTileV + 8 * (l16 & 3);
 
     for (int tile = 0; tile < n_tiles; ++tile) {
         // ---- logits
-        f32x16_t Z;
+        [[maybe_unused]] f32x16_t Z;
 #pragma unroll
         for (int v = 0; v < 16; ++v) Z[v] = 0.0f;
         for (int i = 0; i < nkp; i += RG) {
@@ -333,9 +424,13 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
         float z8[8], m_loc = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float z = add_row_pairs(Z[e], Z[8 + e]);
-            const int t = base + (n & 16) + 4 * hf + 8 * (e / 4) + e % 4;
-            z8[e] = t < m_end ? scale * z : -INFINITY;
+            float z;
+            if constexpr (KEPT)
+                z = zk[e];
+            else
+                z = scale * add_row_pairs(Z[e], Z[8 + e]);
+            const int t = base + lrow + 8 * (e / 4) + e % 4;
+            z8[e] = t < m_end && (!KEPT || l16 % SLOTS < n_rep) ? z : -INFINITY;
             m_loc = fmaxf(m_loc, z8[e]);
         }
         // ---- logits -> weights (bf16, as the operand); rescaling of U and of the running sum
@@ -348,30 +443,56 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
             wv[e] = z8[e] == -INFINITY ? 0.0f : __expf(z8[e] - m_new);
             l_add += wv[e];
         }
-        const bf16x8_t wf = __builtin_convertvector(wv, bf16x8_t);
+        bf16x8_t wf = __builtin_convertvector(wv, bf16x8_t), wr;
+        if constexpr (KEPT) {
+            request_logits(tile + 1);
+            split_bf16(wv, wf, wr);
+        }
+        bf16x8_t wfc[QB == 0 ? CP : 1], wrc[QB == 0 ? CP : 1];
+        if constexpr (KEPT && QB == 0) {
+#pragma unroll
+            for (int c = 0; c < CP; ++c) wfc[c] = only(wf, c), wrc[c] = only(wr, c);
+        }
         l_run = l_run * alpha + l_add;
         m_run = m_new;
         if (tile > 0) {  // rows of U are slots 4 (lane / 16) + v
             if (lane < 16) reinterpret_cast<float *>(At)[lane] = alpha;  // (the tile is between two groups)
             const f32x4_t a = reinterpret_cast<const f32x4_t *>(At)[q4];
 #pragma unroll
-            for (int i = 0; i < NGV * 8; ++i)
+            for (int i = 0; i < NU; ++i)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) U[i][v] *= a[v];
+            if constexpr (KEPT && QB != 0) {
+#pragma unroll
+                for (f32x4_t &x : off_sum) x *= a;
+            }
         }
         // ---- U += W A^V[rows]
+        [[maybe_unused]] bf16x8_t sf, sr, gf, gr;
 #pragma unroll
         for (int gv = 0; gv < NGV; ++gv) {
             const Request q = request_of();
             advance();
             int tk[NF];
             if constexpr (OCC == 1) rows_of(q, tk, 0, NF);
-            group_to_tile<QB, false>(ring[gv % RG], At, lane);
+            if constexpr (KEPT && QB != 0)
+                codes_to_tile<QB>(ring[gv % RG], At, steps, offsets + gv * (kStepBytes / 4), lane);
+            else
+                group_to_tile<QB, false>(ring[gv % RG], At, lane);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h4 = 0; h4 < 8; h4 += HS) {
                 s16x4_t v4[HS][2];
+                constexpr int NB = KEPT && QB != 0 ? (HS / 2 + KEPT - 1) / KEPT : 1;  // sets of weights for these steps
+                f32x4_t pq[NB][2];  // the steps of this lane's eight rows in its copy's group
                 if constexpr (OCC == 2) rows_of(q, tk, h4, h4 + HS);
+                if constexpr (KEPT && QB != 0) {
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) {
+                        const f32x4_t *ps = reinterpret_cast<const f32x4_t *>(steps + 16 * h4 + 32 * (KEPT * j + l16 / SLOTS) + 8 * q4);
+                        pq[j][0] = ps[0], pq[j][1] = ps[1];
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < HS; ++j) {
                     const unsigned char *p = vrd + 32 * (h4 + j);
@@ -384,15 +505,58 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < HS; ++j) {
-                    const s16x8_t v8 = __builtin_shufflevector(v4[j][0], v4[j][1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    U[gv * 8 + h4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, __builtin_bit_cast(bf16x8_t, v8),
-                                                                                U[gv * 8 + h4 + j], 0, 0, 0);
+                    const bf16x8_t v8 = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v4[j][0], v4[j][1], 0, 1, 2, 3, 4, 5, 6, 7));
+                    if constexpr (KEPT && QB != 0) {
+                        if (j % (2 * KEPT) == 0) {
+                            f32x8_t ws;
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) ws[e] = wv[e] * pq[j / (2 * KEPT)][e / 4][e % 4];
+                            split_bf16(ws, sf, sr);
+                        }
+                        if (j % 2 == 0) {
+                            gf = only(sf, (h4 + j) / 2 % CP);
+                            gr = only(sr, (h4 + j) / 2 % CP);
+                        }
+                        f32x4_t &u = U[(gv * 4 + (h4 + j) / 2) / CP * 2 + j % 2];
+                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, v8, u, 0, 0, 0);
+                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gr, v8, u, 0, 0, 0);
+                    } else if constexpr (KEPT) {
+                        f32x4_t &u = U[(gv * 4 + (h4 + j) / 2) / CP * 2 + j % 2];
+                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfc[(h4 + j) / 2 % CP], v8, u, 0, 0, 0);
+                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wrc[(h4 + j) / 2 % CP], v8, u, 0, 0, 0);
+                    } else {
+                        U[gv * 8 + h4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, v8, U[gv * 8 + h4 + j], 0, 0, 0);
+                    }
                 }
                 if (OCC == 2 || h4 + HS == 8) __builtin_amdgcn_sched_barrier(0);
             }
         }
+        if constexpr (KEPT && QB != 0) {
+#pragma unroll
+            for (int c = 0; c < NO; ++c) {
+                const int grp = 16 * c + l16 < NGV * 4 ? 16 * c + l16 : 0;  // (columns beyond the groups are not used)
+                const f32x4_t *ps = reinterpret_cast<const f32x4_t *>(offsets + 32 * grp + 8 * q4);
+                const f32x8_t o8 = __builtin_shufflevector(ps[0], ps[1], 0, 1, 2, 3, 4, 5, 6, 7);
+                bf16x8_t oh, ol;
+                split_bf16(o8, oh, ol);
+                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, oh, off_sum[c], 0, 0, 0);
+                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr, oh, off_sum[c], 0, 0, 0);
+                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, ol, off_sum[c], 0, 0, 0);
+            }
+        }
     }
 
+    const int row_copy = q4 / (SLOTS / 4);  // of this lane's rows of U
+    if constexpr (KEPT && QB != 0) {  // the rest of the affine map: column group -> all ranks of the group
+#pragma unroll
+        for (int i = 0; i < NU / 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float y = __shfl(off_sum[i * CP / 16][v], 16 * q4 + (i * CP) % 16 + row_copy, kWave);
+                U[2 * i][v] += y;
+                U[2 * i + 1][v] += y;
+            }
+    }
     // ---- merge of the wavefronts and the product with B^V.  The rows of B^V that this wavefront multiplies are requested
     // first: fragments of 16 ranks x its 32 channels.
     constexpr int NFB = NGV * 8;
@@ -428,10 +592,13 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     for (int g0 = 0; g0 < NGV; g0 += PG) {
 #pragma unroll
         for (int gv = 0; gv < NGV; ++gv)
-            if (gv >= g0 && gv < g0 + PG && q4 < NQ) {
-                f32x4_t *dst = reinterpret_cast<f32x4_t *>(slab) + ((w * PG + gv - g0) * 128 + l16) * NQ + q4;
+            if (gv >= g0 && gv < g0 + PG) {
+                // (a quad of slots per lane, of the copy that its rows belong to)
+                f32x4_t *dst = reinterpret_cast<f32x4_t *>(slab) + ((w * PG + gv - g0) * 128 + 32 * row_copy + l16) * NQ + q4 % (SLOTS / 4);
+                if (q4 % (SLOTS / 4) < NQ) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) dst[16 * j * NQ] = f4 * U[gv * 8 + j];
+                    for (int i = 0; i < 8 / CP; ++i) dst[(i / 2 * 32 * CP + 16 * (i % 2)) * NQ] = f4 * U[gv * (8 / CP) + i];
+                }
             }
         __syncthreads();
         const int ng = NGV - g0 < PG ? NGV - g0 : PG;
@@ -497,10 +664,10 @@ constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512, kAbsorbLdsPair = 80 * 1024;  
 static constexpr int absorb_rg(int ngv, int occ, bool deep) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 && deep ? 4 : 2; }
 static bool absorb_deep(int FZ) { return (FZ / 8 + 3) % 4 >= 2; }
 
-static size_t absorb_lds(int ngv, int occ, int n_rep, int FZ, int chunk)
+static size_t absorb_lds(int ngv, int occ, int n_rep, int FZ, int chunk, bool kept = false)
 {
     const int rg = absorb_rg(ngv, occ, absorb_deep(FZ));
-    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)kAbWaves * (kTileBytes + 128) + (size_t)chunk * 4;
+    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)kAbWaves * (kTileBytes + 128 + (kept ? param_bytes(ngv) : 0)) + (size_t)chunk * 4;
     const int slab = slab_bytes(n_rep, slab_groups(n_rep, ngv, occ)), out = 16 * kOutPitch * 4;
     const size_t merge = (size_t)ngv * 8192 + (size_t)2 * kAbWaves * 16 * 4 + (size_t)(slab > out ? slab : out);
     return main > merge ? main : merge;
@@ -543,8 +710,8 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
     // one tile.  (One round of both is 0 to 8 % faster at two to eight tiles per workgroup, 177 against 180 us at 16 x 8 x 4096 rows
     // of ranks 512, but a weight is exact only for the largest logit of a wavefront's list, and with longer lists the
     // rounding of the others shows more: error 2.14e-3 against 2.09e-3; forming every row 3.20e-3.)
-    auto cut = [&](int occ) {
-        const int slots = occ == 2 ? 1024 : 256, first = (rows + slots - 1) / slots;
+    auto cut = [&](int slots, int start, int *chunk, int *used_splits) {
+        const int first = (rows + slots - 1) / slots;
         long long best = 0;
         for (int rounds = first; rounds < first + 4; ++rounds) {
             int splits = (int)((long long)slots * rounds / rows);
@@ -552,52 +719,91 @@ void gather_absorb_plan(const xkv_shape &s, Plan &p)
             splits = splits < fewest ? fewest : splits;
             splits = splits > tiles ? tiles : splits;
             const int per = (tiles + splits - 1) / splits, used = (tiles + per - 1) / per;
-            const long long time = ((long long)rows * used + slots - 1) / slots * (per + 1);
+            const long long time = ((long long)rows * used + slots - 1) / slots * (per + start);
             if (best > 0 && time >= best) continue;
             best = time;
-            p.ab_chunk = per * tile;
-            p.ab_splits = used;
+            *chunk = per * tile;
+            *used_splits = used;
         }
+    };
+    auto cut_for = [&](int occ) {
+        cut(occ == 2 ? 1024 : 256, 1, &p.ab_chunk, &p.ab_splits);
         p.ab_occ = occ;
         p.ab_lds = absorb_lds(ngv, occ, p.n_rep, FZ, p.ab_chunk);
     };
-    if (ngv <= 4 && (long long)rows * tiles > 256) cut(2);
-    if (p.ab_occ != 2 || p.ab_lds > kAbsorbLdsPair) cut(1);
+    if (ngv <= 4 && (long long)rows * tiles > 256) cut_for(2);
+    if (p.ab_occ != 2 || p.ab_lds > kAbsorbLdsPair) cut_for(1);
+    // given logits: a tile is half the work or less beside the same start and merge
+    cut(p.n_rep <= 8 ? 512 : 256, 2, &p.ak_chunk, &p.ak_splits);
 }
 
 hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
                                 const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,
-                                float *part_ml, int qbits, hipStream_t st)
+                                float *part_ml, int qbits, hipStream_t st, const float *heads, bool by_place)
 {
     const size_t per_head = (size_t)(pa.F8k + pa.F8v) * 256;  // pieces of 16 B
     const u32x4_t *pv = (B_packed ? (const u32x4_t *)B_packed + (size_t)layer * s.H_kv * per_head : (const u32x4_t *)pa.pack) +
                         (size_t)pa.F8k * 256;
     const size_t seq_stride = (B_packed ? (size_t)s.G : 1) * s.H_kv * per_head;
     const int ngv = absorb_ngv(s.r_v);
-    if (ngv == 0 || p.ab_lds > kAbsorbLdsMax || p.ab_splits > p.max_splits) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((long long)p.ab_splits * s.H_kv * s.batch));
-#define XKV_AB(NV, OC, DP, QB)                                                                                          \
+    const int hp = head_pitch_of(p.n_rep), FZ = heads ? 0 : pa.FZ;
+    const int occ = p.ab_occ, splits = heads ? p.ak_splits : p.ab_splits, chunk = heads ? p.ak_chunk : p.ab_chunk;
+    const size_t lds = heads ? absorb_lds(ngv, p.n_rep <= 8 ? 2 : 1, p.n_rep, 0, chunk, true) : p.ab_lds;
+    if (ngv == 0 || lds > kAbsorbLdsMax || splits > p.max_splits) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((long long)splits * s.H_kv * s.batch));
+    const int stage = heads ? 4 : 1;
+#define XKV_AB(NV, OC, DP, QB, KP)                                                                                      \
     do {                                                                                                                \
         static DynamicLdsOnce attr;                                                                                     \
-        constexpr int RG = absorb_rg(NV, OC, DP);                                                                       \
-        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<NV, RG, QB, OC>, kAbsorbLdsMax);         \
+        constexpr int RG = KP ? (NV == 3 ? 3 : NV == 4 ? 4 : 2) : absorb_rg(NV, OC, DP);                                                                       \
+        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<NV, RG, QB, OC, KP>, kAbsorbLdsMax);     \
         if (e != hipSuccess) return e;                                                                                  \
-        profile_begin(1, st);                                                                                           \
-        hipLaunchKernelGGL((gather_absorb_kernel<NV, RG, QB, OC>), grid, dim3(256), p.ab_lds, st, A_k, A_v,          \
+        if (!by_place) profile_begin(stage, st);                                                                        \
+        hipLaunchKernelGGL((gather_absorb_kernel<NV, RG, QB, OC, KP>), grid, dim3(256), lds, st, A_k, A_v,           \
                            (const u32x4_t *)pa.Pz, pa.z_stride / 8, pv, seq_stride, per_head, idx, counts, part_o,      \
-                           part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.ab_splits, p.ab_chunk, pa.FZ, p.scale);    \
-        profile_end(1, st);                                                                                             \
+                           part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, splits, chunk, FZ, p.scale,                  \
+                           heads, hp, by_place);                                                                        \
+        if (!by_place) profile_end(stage, st);                                                                          \
     } while (0)
-#define XKV_AB_Q(NV, OC, DP)       \
-    do {                           \
-        if (qbits == 0)            \
-            XKV_AB(NV, OC, DP, 0); \
-        else if (qbits == 4)       \
-            XKV_AB(NV, OC, DP, 4); \
-        else                       \
-            XKV_AB(NV, OC, DP, 3); \
+#define XKV_AB_Q(NV, OC, DP)                  \
+    do {                                      \
+        if (qbits == 0)                       \
+            XKV_AB(NV, OC, DP, 0, 0);         \
+        else if (qbits == 4)                  \
+            XKV_AB(NV, OC, DP, 4, 0);         \
+        else                                  \
+            XKV_AB(NV, OC, DP, 3, 0);         \
     } while (0)
-    if (p.ab_occ == 2) {
+#define XKV_AB_KC(NV, OC, CPS)              \
+    do {                                    \
+        if (qbits == 0)                     \
+            XKV_AB(NV, OC, true, 0, CPS);   \
+        else if (qbits == 4)                \
+            XKV_AB(NV, OC, true, 4, CPS);   \
+        else                                \
+            XKV_AB(NV, OC, true, 3, CPS);   \
+    } while (0)
+#define XKV_AB_K(NV)                        \
+    do {                                    \
+        if (p.n_rep <= 4)                   \
+            XKV_AB_KC(NV, 2, 4);            \
+        else if (p.n_rep <= 8)              \
+            XKV_AB_KC(NV, 2, 2);            \
+        else                                \
+            XKV_AB_KC(NV, 1, 1);            \
+    } while (0)
+    if (heads) {
+        if (ngv == 2)
+            XKV_AB_K(2);
+        else if (ngv == 3)
+            XKV_AB_K(3);
+        else if (ngv == 4)
+            XKV_AB_K(4);
+        else
+            XKV_AB_K(6);
+        return hipGetLastError();
+    }
+    if (occ == 2) {
         if (ngv == 2)
             XKV_AB_Q(2, 2, false);
         else if (ngv == 3)
@@ -616,6 +822,8 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
         else
             XKV_AB_Q(6, 1, false);
     }
+#undef XKV_AB_K
+#undef XKV_AB_KC
 #undef XKV_AB_Q
 #undef XKV_AB
     return hipGetLastError();

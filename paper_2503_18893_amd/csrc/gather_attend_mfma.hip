@@ -238,13 +238,16 @@ struct RopeTable {
 };
 
 // QB: 0 = rows of A in bf16; 4 or 3 = rows given as 4-bit / 3-bit codes (A_k, A_v then point to quantised rows).
-template <int WAVES, bool ROPE, int QB>
+// KEYS: products (1) and (2) only; the scaled logits go to logits [batch][H_kv][k][hp], and the values are summed by
+// gather_absorb_kernel, where B^V meets one vector per query head instead of every row (8 x 8 x 4128 rows of ranks 512 in 4 bits:
+// 60 us and 36, against 109 for all four products).
+template <int WAVES, bool ROPE, int QB, bool KEYS>
 __global__ __launch_bounds__(WAVES * 64, 2) void gather_attend_mfma_kernel(
     const bf16_t *__restrict__ A_k, const bf16_t *__restrict__ A_v, const u32x4_t *__restrict__ pack,
     size_t pack_seq_stride, const u32x4_t *__restrict__ pack_q, const int32_t *__restrict__ idx,
     const int32_t *__restrict__ counts,
     float *__restrict__ part_o, float *__restrict__ part_ml, int L, int r_k, int r_v, int H_kv, int H_q, int k,
-    int splits, int chunk, int F16k, int F16v, float scale, const RopeTable rope)
+    int splits, int chunk, int F16k, int F16v, float scale, const RopeTable rope, float *__restrict__ logits, int hp)
 {
     constexpr int kLdsA = lds_a_bytes(WAVES), TILE = WAVES * 32;  // selected tokens per workgroup iteration
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void gather_attend_mfma_kernel(
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
     const int n = lane & 31, hf = lane >> 5;
     const int n_rep = H_q / H_kv;
-    const int PK = F16k / (2 * kGroup), PT = (F16k + F16v) / (2 * kGroup);  // pairs of groups per tile: K, total
+    const int PK = F16k / (2 * kGroup), PT = KEYS ? PK : (F16k + F16v) / (2 * kGroup);  // pairs of groups per tile: K, total
 
     // this head's B fragments (pack_seq_stride pieces from one sequence to the next: a per-call pack holds one layer,
     // a group's pack all of its layers) and its Q^T fragments, the latter kept in LDS for all wavefronts
@@ -471,6 +474,19 @@ __global__ __launch_bounds__(WAVES * 64, 2) void gather_attend_mfma_kernel(
                         const bf16x8_t qf = __builtin_bit_cast(bf16x8_t, Ql[(db * 2 + j) * 64 + lane]);
                         Z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack8(acc[db], j), qf, Z, 0, 0, 0);
                     }
+                if constexpr (KEYS) {
+                    float *dst = logits + ((size_t)b * H_kv + g) * k * hp + n;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int tt = base + 8 * (v / 4) + 4 * hf + (v % 4);
+                        if (tt < m_end && n < hp) dst[(size_t)tt * hp] = scale * Z[v];
+                    }
+#pragma unroll
+                    for (int db = 0; db < 4; ++db)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[db][v] = 0.0f;
+                    continue;
+                }
                 // online softmax; selected tokens beyond the end of this split get weight 0
                 float m_loc = -INFINITY;
 #pragma unroll
@@ -537,6 +553,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void gather_attend_mfma_kernel(
 
     // all global -> LDS copies must have landed before the buffers are reused for the merge
     XKV_WAIT_VMCNT(0);
+    if constexpr (KEYS) return;
     __syncthreads();
     // merge the eight wavefronts in LDS, then write one partial per (split, query head)
     float *mg = reinterpret_cast<float *>(smem_raw);  // [WAVES][16][132]
@@ -642,7 +659,7 @@ hipError_t launch_pack_group(const xkv_shape &s, const void *B_k, const void *B_
 hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int layer, const void *A_k, const void *A_v,
                                      const void *B_k, const void *B_v, const void *q, const int32_t *idx,
                                      void *pack_ws, const void *B_packed, bool packed, float *part_o, float *part_ml,
-                                     hipStream_t st, const int32_t *counts, float rope_theta, int qbits)
+                                     hipStream_t st, const int32_t *counts, float rope_theta, int qbits, float *logits)
 {
     const bool absorb = gather_uses_absorb(p, rope_theta);
     const PackArgs pa = gather_attend_pack_args(s, layer, B_k, B_v, q, pack_ws, B_packed == nullptr, absorb);
@@ -665,44 +682,54 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
     const u32x4_t *bsrc = B_packed ? (const u32x4_t *)B_packed + (size_t)layer * s.H_kv * per_head : (const u32x4_t *)pa.pack;
     const size_t seq_stride = (B_packed ? (size_t)s.G : 1) * s.H_kv * per_head;
     dim3 grid((unsigned)((long long)p.sr_splits * s.H_kv * s.batch));
-#define XKV_GA_LAUNCH(WV, RP, QB)                                                                                  \
+    const bool keys = use_rope && p.rope_kept && logits;
+    const int hp = head_pitch_of(p.n_rep);
+#define XKV_GA_LAUNCH(WV, RP, QB, KY)                                                                              \
     do {                                                                                                           \
         /* B, A tiles, Q, (rotation constants,) token ids */                                                      \
         const size_t lds = kLdsB + lds_a_bytes(WV) + kLdsQ + (RP ? 512 : 0) + (size_t)p.sr_chunk * 4;              \
         static DynamicLdsOnce attr;                                                                                \
-        e = attr.ensure((const void *)gather_attend_mfma_kernel<WV, RP, QB>,                                       \
+        e = attr.ensure((const void *)gather_attend_mfma_kernel<WV, RP, QB, KY>,                                   \
                         kLdsB + lds_a_bytes(WV) + kLdsQ + 512 + kMaxChunkTokens * 4);                              \
         if (e != hipSuccess) return e;                                                                             \
         profile_begin(1, st);                                                                                      \
-        hipLaunchKernelGGL((gather_attend_mfma_kernel<WV, RP, QB>), grid, dim3(WV * 64), lds, st,                  \
+        hipLaunchKernelGGL((gather_attend_mfma_kernel<WV, RP, QB, KY>), grid, dim3(WV * 64), lds, st,              \
                            (const bf16_t *)A_k, (const bf16_t *)A_v, bsrc, seq_stride, (const u32x4_t *)pa.pack_q, \
                            idx, counts, part_o, part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, p.sr_splits,       \
-                           p.sr_chunk, F8k, F8v, p.scale, rope);                                                   \
-        profile_end(1, st);                                                                                        \
+                           p.sr_chunk, F8k, F8v, p.scale, rope, logits, hp);                                       \
+        if (!KY) profile_end(1, st);                                                                               \
     } while (0)
-#define XKV_GA_LAUNCH_Q(WV, RP)                                                                                    \
+#define XKV_GA_LAUNCH_Q(WV, RP, KY)                                                                                \
     do {                                                                                                           \
         if (qbits == 4)                                                                                            \
-            XKV_GA_LAUNCH(WV, RP, 4);                                                                              \
+            XKV_GA_LAUNCH(WV, RP, 4, KY);                                                                          \
         else if (qbits == 3)                                                                                       \
-            XKV_GA_LAUNCH(WV, RP, 3);                                                                              \
+            XKV_GA_LAUNCH(WV, RP, 3, KY);                                                                          \
         else                                                                                                       \
-            XKV_GA_LAUNCH(WV, RP, 0);                                                                              \
+            XKV_GA_LAUNCH(WV, RP, 0, KY);                                                                          \
     } while (0)
     if (p.ga_waves == 8) {
-        if (use_rope)
-            XKV_GA_LAUNCH_Q(8, true);
+        if (keys)
+            XKV_GA_LAUNCH_Q(8, true, true);
+        else if (use_rope)
+            XKV_GA_LAUNCH_Q(8, true, false);
         else
-            XKV_GA_LAUNCH_Q(8, false);
+            XKV_GA_LAUNCH_Q(8, false, false);
     } else {
-        if (use_rope)
-            XKV_GA_LAUNCH_Q(4, true);
+        if (keys)
+            XKV_GA_LAUNCH_Q(4, true, true);
+        else if (use_rope)
+            XKV_GA_LAUNCH_Q(4, true, false);
         else
-            XKV_GA_LAUNCH_Q(4, false);
+            XKV_GA_LAUNCH_Q(4, false, false);
     }
 #undef XKV_GA_LAUNCH_Q
 #undef XKV_GA_LAUNCH
-    return hipGetLastError();
+    e = hipGetLastError();
+    if (!keys || e != hipSuccess) return e;
+    e = launch_gather_absorb(s, p, pa, nullptr, A_v, B_packed, layer, idx, counts, part_o, part_ml, qbits, st, logits, true);
+    profile_end(1, st);
+    return e;
 }
 
 // Wavefronts per workgroup for a shape: full 256-token tiles when there are enough selected tokens to give every

@@ -91,6 +91,12 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     off = align_up(off + b * (size_t)(2 * s.H_q + 64) * (s.r_k + 128) * sizeof(float), 256);  // fp32 P or bf16 hi/lo fragments
     p.off_score = off;
     off = align_up(off + b * s.H_kv * (size_t)s.L * sizeof(float), 256);
+    // Rotated rows: logits first, into the room of the projected queries and the pooled scores, which are done with by then, and the
+    // values' sums from the given logits.  That is a launch and a merge more (4 us), which the sums make up for from four tiles of
+    // 128 rows per compute unit on (8 x 8 x 4128 rows of ranks 512, us: 4-bit 109 -> 96, bf16 123 -> 114), and not with
+    // six groups of values' ranks, whose kernel has two groups in flight instead of four (ranks 768 71 -> 85).
+    p.rope_kept = p.absorb && s.r_v <= 512 && (long long)rows * s.k >= 131072 && s.k < (1 << 24) &&
+                  b * s.H_kv * (size_t)s.k * head_pitch_of(p.n_rep) * sizeof(float) <= off - p.off_p;
     p.off_idx = off;
     off = align_up(off + b * s.H_kv * (size_t)s.k * sizeof(int32_t), 256);
     p.off_hist = off;
@@ -590,7 +596,7 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
     float *part_o = at<float>(workspace, pa.off_part_o), *part_ml = at<float>(workspace, pa.off_part_ml);
     if (e == hipSuccess)
         e = launch_gather_attend(lp.attend_shape, pa, layer, A_k, A_v, B_k, B_v, q, rows, pack_ws, B_packed, packed, part_o,
-                                 part_ml, stream, counts, rope_theta, qbits);
+                                 part_ml, stream, counts, rope_theta, qbits, at<float>(workspace, pa.off_p));
     if (!tail_first && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
         e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
@@ -659,7 +665,7 @@ xkv_status xkv_gather_attend_q(const xkv_shape *shape, int32_t layer, const void
     hipStream_t stream = (hipStream_t)hip_stream;
     float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
     hipError_t e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o,
-                                        part_ml, stream, counts, rope_theta, bits);
+                                        part_ml, stream, counts, rope_theta, bits, at<float>(workspace, p.off_p));
     if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream);
     return hip_status(e);
 }
@@ -683,7 +689,7 @@ xkv_status xkv_gather_attend_ex(const xkv_shape *shape, int32_t layer, const voi
     void *pack_ws = at<void>(workspace, p.off_bpack);
     const bool mfma = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_v, pack_ws);
     hipError_t e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
-                                        stream, counts, rope_theta);
+                                        stream, counts, rope_theta, 0, at<float>(workspace, p.off_p));
     if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, rope_theta), part_o, part_ml, out, stream);
     return hip_status(e);
 }
@@ -700,6 +706,19 @@ static xkv_status prepare_absorbed(const xkv_shape *s, void *ws, size_t ws_bytes
     if (ws_bytes < a.total) return XKV_ERR_WORKSPACE;
     if (((uintptr_t)ws) & 255u) return XKV_ERR_INVALID_ARG;
     return XKV_OK;
+}
+
+// Whether the row sums and the product with B^V run on the matrix cores (the selected-row kernel without its keys' half,
+// gather_absorb.hip) or in the general kernels of absorbed.hip; B^V_l is then packed in the projection's launch or one of its own.
+static bool absorbed_uses_mfma(const Plan &p, const void *A_v, const void *B_v, const void *pack_ws)
+{
+    return p.absorb && (((uintptr_t)A_v | (uintptr_t)B_v | (uintptr_t)pack_ws) & 15u) == 0;
+}
+static PackArgs absorbed_pack_args(const xkv_shape &s, int layer, const void *B_v, const void *q, void *pack_ws)
+{
+    PackArgs pa = gather_attend_pack_args(s, layer, nullptr, B_v, q, pack_ws, true, true);
+    pa.blocks_z = 0;
+    return pa;
 }
 
 xkv_status xkv_absorbed_workspace_bytes(const xkv_shape *shape, size_t *bytes)
@@ -747,6 +766,16 @@ static xkv_status attend_absorbed_impl(const xkv_shape *shape, int32_t layer, co
     if ((((uintptr_t)A_v) | ((uintptr_t)head_scores)) & 15u) return XKV_ERR_INVALID_ARG;
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
+    void *pack_ws = at<void>(workspace, p.off_bpack);
+    if (absorbed_uses_mfma(p, A_v, B_v, pack_ws)) {
+        const PackArgs pa = absorbed_pack_args(*shape, layer, B_v, nullptr, pack_ws);
+        float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
+        hipError_t e = launch_gather_prepare(pa, stream);
+        if (e == hipSuccess)
+            e = launch_gather_absorb(*shape, p, pa, nullptr, A_v, nullptr, layer, idx, nullptr, part_o, part_ml, q4 ? 4 : 0, stream, head_scores);
+        if (e == hipSuccess) e = launch_combine(*shape, p.ak_splits, part_o, part_ml, out, stream);
+        return hip_status(e);
+    }
     float *po = at<float>(workspace, a.off_po), *pml = at<float>(workspace, a.off_pml);
     hipError_t e = launch_absorbed(*shape, a, layer, A_v, B_v, head_scores, idx, po, pml,
                                    at<float>(workspace, a.off_part_u), at<float>(workspace, a.off_part_ml), stream, q4);
@@ -811,19 +840,28 @@ static xkv_status sr_decode_absorbed_impl(const xkv_shape *shape, int32_t layer,
     const Tail tail = make_tail(*shape, p, K_tail, V_tail, q, T, at<float>(workspace, p.off_tail_o), at<float>(workspace, p.off_tail_ml));
     const bool tail_first = tail.mfma && (q4 || score_stage_uses_mfma(*shape, A_k, B_k, q, at<void>(workspace, p.off_p), heads));
     const DenseArgs *ta = tail_first ? &tail.args : nullptr;
+    void *pack_ws = at<void>(workspace, p.off_bpack);
+    const bool mfma = absorbed_uses_mfma(p, A_v, B_v, pack_ws);
+    PackArgs pa{};
+    if (mfma) pa = absorbed_pack_args(*shape, layer, B_v, q, pack_ws);
+    bool packed = q4;
     hipError_t e =
-        q4 ? launch_score_q4_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S, heads, stream, nullptr, ta)
+        q4 ? launch_score_q4_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S, heads, stream, mfma ? &pa : nullptr, ta)
            : launch_score_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S,
                                 p.score_hist ? topk_row_hist(p, state) : nullptr,
-                                p.score_hist ? hist : nullptr, &level0_done, nullptr, nullptr, stream, heads, ta);
+                                p.score_hist ? hist : nullptr, &level0_done, mfma ? &pa : nullptr, &packed, stream, heads, ta);
     if (e == hipSuccess) e = launch_topk(*shape, p, S, idx, hist, state, level0_done, stream);
-    float *po = at<float>(workspace, a.off_po), *pml = at<float>(workspace, a.off_pml);
-    if (e == hipSuccess)
+    float *po = at<float>(workspace, mfma ? p.off_part_o : a.off_po), *pml = at<float>(workspace, mfma ? p.off_part_ml : a.off_pml);
+    if (mfma) {
+        if (e == hipSuccess && !packed) e = launch_gather_prepare(pa, stream);
+        if (e == hipSuccess) e = launch_gather_absorb(*shape, p, pa, nullptr, A_v, nullptr, layer, idx, nullptr, po, pml, q4 ? 4 : 0, stream, heads);
+    } else if (e == hipSuccess) {
         e = launch_absorbed(*shape, a, layer, A_v, B_v, heads, idx, po, pml, at<float>(workspace, a.off_part_u),
                             at<float>(workspace, a.off_part_ml), stream, q4);
+    }
     // the uncompressed tail, if any, joins the same softmax through its own set of partials
     if (!tail_first && e == hipSuccess) e = tail.run(stream);
-    if (e == hipSuccess) e = launch_combine(*shape, a.slices, po, pml, out, stream, tail.parts, tail.o, tail.ml);
+    if (e == hipSuccess) e = launch_combine(*shape, mfma ? p.ak_splits : a.slices, po, pml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -877,7 +915,7 @@ xkv_status xkv_sr_decode_q4(const xkv_shape *shape, int32_t layer, const void *A
     if (e == hipSuccess) e = launch_topk(*shape, p, S, idx, hist, state, false, stream);
     if (e == hipSuccess)
         e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, true, part_o, part_ml,
-                                 stream, nullptr, rope_theta, 4);
+                                 stream, nullptr, rope_theta, 4, at<float>(workspace, p.off_p));
     if (!tail.mfma && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
         e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);

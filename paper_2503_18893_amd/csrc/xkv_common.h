@@ -98,8 +98,10 @@ struct Plan {
     bool ga_mfma;      // shape fits the matrix-core gather-attend kernel
     int ga_waves;      // ... with this many wavefronts (32 selected tokens each) per workgroup
     bool absorb;       // ... and the one that keeps B_l out of the main loop (rows that are not rotated)
+    bool rope_kept;    // rotated rows: logits first (room for them from off_p on), then that kernel on the values
     int ab_occ, ab_splits, ab_chunk;  // its workgroups per compute unit, splits per (sequence, KV head), tokens per split
     size_t ab_lds;     // its LDS per workgroup
+    int ak_splits, ak_chunk;  // ... where the logits are given (KEPT): one workgroup per compute unit
     bool topk_row;     // rows short enough for the one-launch, register-resident selection
     bool score_stream; // shape fits the long-stream score kernel
     bool score_hist;   // ... and that kernel can also histogram the top digit of its scores for the top-k stage
@@ -227,7 +229,9 @@ hipError_t launch_topk(const xkv_shape &s, const Plan &p, const float *S, int32_
 hipError_t launch_gather_attend(const xkv_shape &s, const Plan &p, int layer, const void *A_k, const void *A_v,
                                 const void *B_k, const void *B_v, const void *q, const int32_t *idx, void *pack_ws,
                                 const void *B_packed, bool packed, float *part_o, float *part_ml, hipStream_t st,
-                                const int32_t *counts = nullptr, float rope_theta = 0.0f, int qbits = 0);
+                                const int32_t *counts = nullptr, float rope_theta = 0.0f, int qbits = 0,
+                                float *logits = nullptr);
+// logits: room for the rotated rows' logits, needed where p.rope_kept
 // qbits 4 or 3: A_k and A_v are rows of 4-bit / 3-bit codes (quant.hip); matrix-core shapes with ranks that are
 // multiples of 32 only (gather_attend_quant_ok).
 bool gather_attend_quant_ok(const xkv_shape &s, const Plan &p, const void *Aq_k, const void *Aq_v, const void *B_k,
@@ -246,13 +250,14 @@ inline bool gather_uses_absorb(const Plan &p, float rope_theta) { return p.absor
 // false) one per wavefront.
 inline int gather_partials(const Plan &p, bool mfma, float rope_theta)
 {
-    return !mfma ? p.sr_splits * 4 : gather_uses_absorb(p, rope_theta) ? p.ab_splits : p.sr_splits;
+    return !mfma ? p.sr_splits * 4 : gather_uses_absorb(p, rope_theta) ? p.ab_splits : p.rope_kept ? p.ak_splits : p.sr_splits;
 }
 bool gather_absorb_shape_ok(const xkv_shape &s);
 void gather_absorb_plan(const xkv_shape &s, Plan &p);
 hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
                                 const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,
-                                float *part_ml, int qbits, hipStream_t st);
+                                float *part_ml, int qbits, hipStream_t st, const float *heads = nullptr,
+                                bool by_place = false);
 bool gather_attend_mfma_shape_ok(const xkv_shape &s);
 int gather_attend_mfma_waves(const xkv_shape &s);
 size_t gather_attend_pack_bytes(const xkv_shape &s);        // Q^T fragments + one layer's packed B (workspace)
@@ -262,7 +267,7 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
                                      const void *B_k, const void *B_v, const void *q, const int32_t *idx,
                                      void *pack_ws, const void *B_packed, bool packed, float *part_o, float *part_ml,
                                      hipStream_t st, const int32_t *counts = nullptr, float rope_theta = 0.0f,
-                                     int qbits = 0);
+                                     int qbits = 0, float *logits = nullptr);
 hipError_t launch_dense(const xkv_shape &s, const Plan &p, const void *K, const void *V, const void *q, float *part_o,
                         float *part_ml, hipStream_t st);
 bool dense_mfma_shape_ok(const xkv_shape &s);

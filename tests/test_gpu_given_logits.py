@@ -1,0 +1,107 @@
+"""Row sums from given logits: the absorbed step's attention and the second half of the step on rotated rows.  Query heads per KV head
+at the edges of their copies, ranks at the edges of the groups, lists shorter and longer than a tile, quantised rows."""
+import numpy as np
+import pytest
+
+from paper_2503_18893_amd import synth
+from paper_2503_18893_amd import binding as xb
+
+pytestmark = pytest.mark.gpu
+
+
+def torch_mod():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def rows_of(torch, A, bits):
+    """What the step reads (A itself or its quantised rows), and the same in double precision."""
+    if bits == 0:
+        return A, A.double()
+    b, L, r = A.shape
+    q = torch.empty((b, L, xb.xkv_quantized_row_bytes(r, bits)), dtype=torch.uint8, device="cuda")
+    xb.xkv_quantize_rows(A, b * L, r, q, bits)
+    g = A.double().view(b, L, r // 32, 32)
+    lo, hi = g.amin(-1, keepdim=True), g.amax(-1, keepdim=True)
+    n = (1 << bits) - 1
+    step = ((hi - lo).float() / n).bfloat16().float()
+    step = torch.where(step > 0, step, torch.ones_like(step))
+    codes = ((g.float() - lo.float()) * (1.0 / step)).round().clamp(0, n)
+    return q, (step.double() * codes.double() + lo).view(b, L, r)
+
+
+def workload(H_kv, n_rep, r_k, r_v, L, k, batch):
+    return synth.Workload("given_logits", G=1, H_kv=H_kv, H_q=H_kv * n_rep, d_h=128, r_k=r_k, r_v=r_v, L=L, k=k, batch=batch,
+                          dtype="bf16", a_scale=1.0, sigma_decay=0.5, q_scale=0.3)
+
+
+@pytest.mark.parametrize("bits", [0, 4])
+@pytest.mark.parametrize("n_rep,r_v,L,k,batch", [(1, 32, 300, 1, 1), (2, 96, 900, 127, 2), (4, 512, 3000, 1000, 2), (5, 384, 700, 129, 1),
+                                                 (7, 640, 2000, 600, 1), (8, 256, 1000, 1000, 3), (12, 768, 900, 400, 1), (16, 128, 5000, 4500, 1)])
+def test_attention_from_kept_scores(n_rep, r_v, L, k, batch, bits):
+    torch = torch_mod()
+    H_kv = 3
+    w = workload(H_kv, n_rep, 64, r_v, L, k, batch)
+    g = torch.Generator(device="cuda").manual_seed(L + r_v + bits)
+    A_v = torch.randn((batch, L, r_v), generator=g, device="cuda").bfloat16()
+    B_v = (torch.randn((batch, 1, r_v, H_kv * 128), generator=g, device="cuda") / r_v ** 0.5).bfloat16()
+    pitch = 1 << (n_rep - 1).bit_length()
+    heads = torch.randn((batch, H_kv, L, pitch), generator=g, device="cuda") * 3
+    idx = torch.stack([torch.randperm(L, generator=g, device="cuda")[:k].sort().values for _ in range(batch * H_kv)])
+    idx = idx.view(batch, H_kv, k).int().contiguous()
+    given, A64 = rows_of(torch, A_v, bits)
+    shape = xb.Shape.of(w)
+    ws = torch.empty(xb.xkv_absorbed_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    out = torch.empty((batch, H_kv * n_rep, 128), dtype=torch.bfloat16, device="cuda")
+    (xb.xkv_attend_absorbed_q4 if bits else xb.xkv_attend_absorbed)(shape, 0, given, B_v, heads, idx, out, ws)
+    for b in range(batch):
+        for h in range(H_kv):
+            t = idx[b, h].long()
+            W = torch.softmax(heads[b, h, t, :n_rep].double(), 0)
+            ref = (W.T @ A64[b, t]) @ B_v[b, 0, :, h * 128:(h + 1) * 128].double()
+            got = out[b, h * n_rep:(h + 1) * n_rep].double()
+            # single-precision sums (weights and sums split into 16 bits and more), one rounding to the 8 bits of bf16: at most
+            # 2^-8 of the value, half a unit of its last place where it is just above a power of two
+            assert (got - ref).abs().max() <= (2.0 ** -8 + 2.0 ** -13) * ref.abs().max() + 1e-6, (b, h)
+
+
+@pytest.mark.parametrize("bits", [0, 4, 3])
+@pytest.mark.parametrize("n_rep,r", [(4, 64), (7, 160), (1, 512)])
+def test_rotated_rows_in_two_halves(n_rep, r, bits):
+    torch = torch_mod()
+    H_kv, L, k, batch, theta = 8, 21000, 8200, 2, 500000.0
+    w = workload(H_kv, n_rep, r, r, L, k, batch)
+    g = torch.Generator(device="cuda").manual_seed(r + bits)
+    A = [torch.randn((batch, L, r), generator=g, device="cuda").bfloat16() for _ in "kv"]
+    B = [(torch.randn((batch, 1, r, H_kv * 128), generator=g, device="cuda") / r ** 0.5).bfloat16() for _ in "kv"]
+    q = torch.randn((batch, H_kv * n_rep, 128), generator=g, device="cuda").bfloat16()
+    idx = torch.stack([torch.randperm(L, generator=g, device="cuda")[:k].sort().values for _ in range(batch * H_kv)])
+    idx = idx.view(batch, H_kv, k).int().contiguous()
+    counts = torch.full((batch, H_kv), k, dtype=torch.int32, device="cuda")
+    counts[0, 1], counts[1, 2], counts[1, 3] = 1, 4097, 0
+    given = [rows_of(torch, a, bits) for a in A]
+    shape = xb.Shape.of(w)
+    ws = xb.alloc_workspace(shape)
+    out = torch.empty_like(q)
+    if bits:
+        xb.xkv_gather_attend_q(shape, 0, given[0][0], given[1][0], bits, B[0], B[1], q, idx, counts, theta, out, ws)
+    else:
+        xb.xkv_gather_attend_ex(shape, 0, A[0], A[1], B[0], B[1], q, idx, counts, theta, out, ws)
+    f = theta ** (-torch.arange(64, device="cuda", dtype=torch.float64) / 64)
+    for b in range(batch):
+        for h in range(H_kv):
+            n = int(counts[b, h])
+            t = idx[b, h, :n].long()
+            got = out[b, h * n_rep:(h + 1) * n_rep].double()
+            if n == 0:
+                assert (got == 0).all()
+                continue
+            K = given[0][1][b, t] @ B[0][b, 0, :, h * 128:(h + 1) * 128].double()
+            c, s = (t[:, None] * f).cos(), (t[:, None] * f).sin()
+            K = torch.cat((K[:, :64] * c - K[:, 64:] * s, K[:, 64:] * c + K[:, :64] * s), 1)
+            W = torch.softmax(K @ q[b, h * n_rep:(h + 1) * n_rep].double().T / 128 ** 0.5, 0)
+            ref = W.T @ (given[1][1][b, t] @ B[1][b, 0, :, h * 128:(h + 1) * 128].double())
+            # bf16 rows (quantised keys rounded once more) and rotated keys: 2^-9 of logits of a few units, which the weights carry on
+            assert (got - ref).abs().max() <= 2e-2 * ref.abs().max() + 1e-3, (b, h)
