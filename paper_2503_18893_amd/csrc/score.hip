@@ -337,6 +337,154 @@ __global__ __launch_bounds__(256) void score_mfma_kernel(const bf16_t *__restric
     }
 }
 
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// One token's head scores (NRP consecutive floats, v[] already zero beyond the real heads), as hidden stores
+// like the pooled ones below.
+template <int NRP> __device__ __forceinline__ void store_head_row(float *dst, const float (&v)[16])
+{
+    if constexpr (NRP == 1) {
+        asm volatile("global_store_dword %0, %1, off" : : "v"(dst), "v"(v[0]) : "memory");
+    } else if constexpr (NRP == 2) {
+        const f32x2_t x = {v[0], v[1]};
+        asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(dst), "v"(x) : "memory");
+    } else {
+#pragma unroll
+        for (int c = 0; c < NRP / 4; ++c) {
+            const f32x4_t x = {v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]};
+            // (a store of more than 64 bits reads its data registers a cycle or two after issue; the compiler inserts
+            // the wait states for stores it knows, not for these)
+            asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(dst + 4 * c), "v"(x) : "memory");
+        }
+    }
+}
+
+// The same for ranks above 256 (up to 1024 tiles: a wavefront has one tile, of several steps).  What counts there is how soon
+// the rows are requested: the projected queries go straight to LDS, the first kScoreRing steps of rows (8 pieces of 16 B each) are
+// requested behind them before anything is waited for, and a step's registers are refilled as soon as it is multiplied.  (With the
+// projection, us: 9000 tokens of rank 512 12.0 -> 11.1, 32768 14.9 -> 14.3, 4096 of rank 768 14.0 -> 13.1.  With one or two steps, or several tiles per
+// wavefront, the kernel above is as fast or ahead by up to 0.6.)
+constexpr int kScoreRing = 4;
+
+template <int N_REP, bool HEADS>
+__global__ __launch_bounds__(256, 2) void score_ring_kernel(const bf16_t *__restrict__ A_k,    // [batch][L][r_k]
+                                                            const bf16_t *__restrict__ Pfrag,  // see above
+                                                            float *__restrict__ S,             // [batch][H_kv][L]
+                                                            int L, int r_k, int H_kv, int F8, int tiles_per_wg,
+                                                            float scale, float *__restrict__ S_heads)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    u32x4_t *Pl = reinterpret_cast<u32x4_t *>(smem);  // [2][F8][64] fragments of 16 B per lane
+    constexpr int GPH = 16 / N_REP;
+    const int b = blockIdx.z, blk = blockIdx.y, nblk = gridDim.y;
+    const int lane = lane_id(), w = wave_id();
+    const int n = lane & 31, hf = lane >> 5;
+    const int F = r_k / 16;
+
+    // this block's P fragments (hi and lo parts): 2 F8 KiB, each wavefront every fourth
+    {
+        const u32x4_t *src = reinterpret_cast<const u32x4_t *>(Pfrag) + ((size_t)b * nblk + blk) * 2 * F8 * 64 + lane;
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)smem;
+        for (int f = w; f < 2 * F8; f += 4) copy16_global_to_lds(src + f * 64, lds0 + f * 1024);
+    }
+    const bf16_t *Ab = A_k + (size_t)b * L * r_k;
+    const int n_tiles = (L + 31) / 32;
+    const int tile_begin = blockIdx.x * tiles_per_wg;
+    const int tile_end = tile_begin + tiles_per_wg < n_tiles ? tile_begin + tiles_per_wg : n_tiles;
+    const int n_steps = F8 / 8;  // steps of 8 fragments per tile
+    int tile = tile_begin + w;
+    const bool has_work = tile < tile_end;
+    // 16 B pieces of a token's row for one step; fragments beyond the rank meet zero P fragments, so the address is only
+    // clamped, never skipped: the loop body is straight-line code.  (tile_p, step_p) is the step to request next; past the
+    // wavefront's last tile every lane requests the same piece of one row.
+    int tile_p = has_work ? tile : n_tiles - 1, step_p = 0, n_p = has_work ? n : 0, hf_p = has_work ? hf : 0;
+    auto request = [&](u32x4_t (&a)[8]) __attribute__((always_inline)) {
+        const int t = tile_p * 32 + n_p;
+        const u32x4_t *row = reinterpret_cast<const u32x4_t *>(Ab + (size_t)(t < L ? t : L - 1) * r_k) + hf_p;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int f = step_p * 8 + j;
+            a[j] = row[2 * (f < F ? f : F - 1)];
+        }
+        if (++step_p == n_steps) {
+            step_p = 0;
+            if (tile_p + 4 < tile_end) {
+                tile_p += 4;
+            } else {
+                n_p = 0;
+                hf_p = 0;
+            }
+        }
+    };
+    u32x4_t ring[kScoreRing][8];
+#pragma unroll
+    for (int s = 0; s < kScoreRing; ++s) {
+        request(ring[s]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    XKV_WAIT_VMCNT(8 * kScoreRing);  // the copies of P came first
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (!has_work) return;
+    f32x16_t acc_h, acc_l;  // separate chains for the high parts and the remainders of P
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc_h[v] = acc_l[v] = 0.0f;
+    const int my_steps = (tile_end - tile + 3) / 4 * n_steps;
+    int step = 0;
+    for (int i = 0; i < my_steps; i += kScoreRing) {
+#pragma unroll
+        for (int s = 0; s < kScoreRing; ++s) {
+            const bool real = i + s < my_steps;  // (no way out of the loop here: it would make the waits for the ring stricter)
+            if (real) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const u32x4_t ph = Pl[(step * 8 + j) * 64 + lane];
+                    const u32x4_t pl = Pl[(F8 + step * 8 + j) * 64 + lane];
+                    acc_h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ph),
+                                                                    __builtin_bit_cast(bf16x8_t, ring[s][j]), acc_h, 0, 0, 0);
+                    acc_l = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pl),
+                                                                    __builtin_bit_cast(bf16x8_t, ring[s][j]), acc_l, 0, 0, 0);
+                }
+            }
+            request(ring[s]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (!real || ++step < n_steps) continue;
+            step = 0;
+            // (stores that the compiler does not know of: it would wait for every request at the next use of the ring)
+            const int t = tile * 32 + n;
+            if (t < L) {
+#pragma unroll
+                for (int u = 0; u < GPH; ++u) {
+                    const int g = blk * 2 * GPH + hf * GPH + u;
+                    float hv[16];
+#pragma unroll
+                    for (int hh = 0; hh < 16; ++hh)
+                        hv[hh] = hh < N_REP ? acc_h[(u * N_REP + hh) & 15] + acc_l[(u * N_REP + hh) & 15] : 0.0f;
+                    if constexpr (HEADS) {
+#pragma unroll
+                        for (int hh = 0; hh < N_REP; ++hh) hv[hh] *= scale;
+                    }
+                    float best = hv[0];
+#pragma unroll
+                    for (int hh = 1; hh < N_REP; ++hh) best = fmaxf(best, hv[hh]);
+                    if constexpr (!HEADS) best *= scale;
+                    if (g < H_kv) {
+                        asm volatile("global_store_dword %0, %1, off" : : "v"(&S[((size_t)b * H_kv + g) * L + t]), "v"(best) : "memory");
+                        if constexpr (HEADS) {
+                            constexpr int NRP = head_pitch(N_REP);
+                            store_head_row<NRP>(S_heads + (((size_t)b * H_kv + g) * L + t) * NRP, hv);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc_h[v] = acc_l[v] = 0.0f;
+            tile += 4;
+        }
+    }
+}
+
 // Variant for long streams: the same contraction, but A^K is fetched line-wise and turned into operand
 // fragments through a wavefront-private LDS tile.  A group is 128 ranks (256 B) of each of the wavefront's 32
 // token rows; instruction j of a group covers rows 4j..4j+3, lane l loading the 16 B piece l%16 of row 4j + l/16,
@@ -366,29 +514,6 @@ __device__ __forceinline__ void score_group(f32x16_t &acc_h, f32x16_t &acc_l, u3
         const int t = t0 + row_step * fl;
         areg[SLOT0 + fl] = __builtin_nontemporal_load(&arow[(size_t)(t < L ? t : L - 1) * pieces]);
         __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-// One token's head scores (NRP consecutive floats, v[] already zero beyond the real heads), as hidden stores
-// like the pooled ones below.
-template <int NRP> __device__ __forceinline__ void store_head_row(float *dst, const float (&v)[16])
-{
-    if constexpr (NRP == 1) {
-        asm volatile("global_store_dword %0, %1, off" : : "v"(dst), "v"(v[0]) : "memory");
-    } else if constexpr (NRP == 2) {
-        const f32x2_t x = {v[0], v[1]};
-        asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(dst), "v"(x) : "memory");
-    } else {
-#pragma unroll
-        for (int c = 0; c < NRP / 4; ++c) {
-            const f32x4_t x = {v[4 * c], v[4 * c + 1], v[4 * c + 2], v[4 * c + 3]};
-            // (a store of more than 64 bits reads its data registers a cycle or two after issue; the compiler inserts
-            // the wait states for stores it knows, not for these)
-            asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(dst + 4 * c), "v"(x) : "memory");
-        }
     }
 }
 
@@ -1083,7 +1208,7 @@ static hipError_t launch_score_generic(const xkv_shape &s, const Plan &p, int la
 
 // Whether a shape goes to the long-stream kernel, with how many 32-token tiles per workgroup, and whether its
 // LDS also has room for the top-digit histograms.  One 8-wavefront workgroup per compute unit in a single
-// round.  It pays as soon as most compute units have a few tiles (us with the projection, this kernel against the other: ranks 512,
+// round.  It pays from 1025 tiles on, where the others' wavefronts need a second one (us with the projection, this kernel against the other: ranks 512,
 // 1024 tiles 15.2 / 14.7, 1256 tiles 16.6 / 20.3, 2256 26.0 / 31.9, 3750 28.6 / 35.7; ranks 256 12.4 / 10.7, 13.0 / 13.8, 3750
 // tiles 19.2 / 21.6), with a single group of 128 ranks only where every wavefront has eight tiles of its own (5000 tiles 17.7 / 17.6).
 bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, int *waves)
@@ -1098,7 +1223,7 @@ bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, i
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
     const int n_tiles = (s.L + 31) / 32;
     const int pairs = s.batch * mfma_blocks(s.H_kv, n_rep);
-    if ((long long)pairs * n_tiles < (s.r_k > 128 ? 1200 : 256 * kScoreWaves * 8)) return false;
+    if ((long long)pairs * n_tiles < (s.r_k > 128 ? 1025 : 256 * kScoreWaves * 8)) return false;
     const size_t lds_max = 160 * 1024 - 512, lds_p = (size_t)2 * F8 * 64 * 16;
     const size_t lds_hist = (size_t)2 * mfma_gph(n_rep) * kTopkBins * 4;
     int wv = kScoreWaves;
@@ -1164,7 +1289,18 @@ static hipError_t launch_score_mfma_t(const xkv_shape &s, const Plan &p, const b
     int tiles_per_wg = (n_tiles + wgs_per_pair - 1) / wgs_per_pair;
     tiles_per_wg = tiles_per_wg < 4 ? 4 : tiles_per_wg;
     tiles_per_wg = (tiles_per_wg + 3) / 4 * 4;
-    static DynamicLdsOnce attr_pooled, attr_heads;
+    static DynamicLdsOnce attr_pooled, attr_heads, attr_ring, attr_ring_heads;
+    if (F8 > 16 && tiles_per_wg == 4) {  // a tile per wavefront, of several steps
+        const dim3 rgrid((n_tiles + 3) / 4, nblk, s.batch);
+        auto launch = [&](auto kernel, DynamicLdsOnce &attr) {
+            if (hipError_t e0 = attr.ensure((const void *)kernel, 160 * 1024 - 512); e0 != hipSuccess) return e0;
+            profile_begin(0, st);
+            hipLaunchKernelGGL(kernel, rgrid, dim3(256), lds, st, A_k, Pfrag, S, s.L, s.r_k, s.H_kv, F8, tiles_per_wg, p.scale, S_heads);
+            profile_end(0, st);
+            return hipGetLastError();
+        };
+        return S_heads ? launch(score_ring_kernel<N_REP, true>, attr_ring_heads) : launch(score_ring_kernel<N_REP, false>, attr_ring);
+    }
     if (hipError_t e0 = attr_pooled.ensure((const void *)score_mfma_kernel<N_REP, false>, 160 * 1024 - 512); e0 != hipSuccess)
         return e0;
     if (hipError_t e0 = attr_heads.ensure((const void *)score_mfma_kernel<N_REP, true>, 160 * 1024 - 512); e0 != hipSuccess)
