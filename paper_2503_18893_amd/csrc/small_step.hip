@@ -1,0 +1,265 @@
+// A whole step of a small problem in one launch, single precision: one workgroup per (sequence, KV head) projects its queries,
+// scores its tokens, selects, and attends over the selected rows in the regrouped form (logits from the projected queries,
+// U_h = w_h^T A^V[I_g], out_h = U_h B^V_g), with the uncompressed tail, if any, in the same softmax.
+//
+// Such a step is launches and load latencies: five kernels of 3 to 14 us for 512 tokens of rank 32.  One compute unit reads a mebibyte
+// in less than these launches wait, so that is where the line lies (small_step_ok).  Two layers, us: 512 tokens of rank 32, 32
+// selected 64 -> 41; 128 selected and a tail of 33 150 -> 53; 4096 tokens of rank 48, 1024 selected 147 -> 113; 3000 of rank 64, two KV
+// heads 146 -> 137.
+// The stage call for selected rows takes the second half (WHOLE false) at the same sizes, so that the chained stages and the
+// step give the same bits.
+#include "row_select.h"
+
+namespace xkv {
+
+constexpr int kSmPart = 8192, kSmRank = 2048, kSmMap = 256;  // words: partial sums, P (once more in double precision) and U, bitmap
+constexpr int kSmLists = 2 * kRowWaves * kRowList;           // ... lists, afterwards ids and weights
+constexpr int kSmWords = kSmLists + kRowBins + kSmMap + kSmPart + 3 * kSmRank;
+
+struct SmallArgs {
+    const float *A_k, *A_v, *B_k, *B_v, *q, *K_tail, *V_tail;
+    float *out, *score_out;
+    int32_t *idx_out;
+    const int32_t *idx;  // !WHOLE
+    int G, layer, L, r_k, r_v, H_kv, H_q, d_h, k, T;
+    float scale;
+};
+
+// Scaled logits of one row for heads h0 .. h0 + 3 (those beyond nh repeat the first): P [heads][r_k] in LDS.
+__device__ __forceinline__ void row_logits(const float *__restrict__ row, const float *P, int r_k, int h0, int nh, bool vec, float scale, float (&z)[4])
+{
+    const float *Ph[4];
+    float acc[4];
+#pragma unroll
+    for (int hh = 0; hh < 4; ++hh) {
+        Ph[hh] = P + (h0 + (hh < nh ? hh : 0)) * r_k;
+        acc[hh] = 0.0f;
+    }
+    if (vec) {
+#pragma unroll 8
+        for (int i = 0; i < r_k; i += 4) {
+            const float4 x = *reinterpret_cast<const float4 *>(row + i);
+            const float x4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh) acc[hh] = fmaf(x4[e], Ph[hh][i + e], acc[hh]);
+        }
+    } else {
+#pragma unroll 8
+        for (int i = 0; i < r_k; ++i)
+#pragma unroll
+            for (int hh = 0; hh < 4; ++hh) acc[hh] = fmaf(row[i], Ph[hh][i], acc[hh]);
+    }
+#pragma unroll
+    for (int hh = 0; hh < 4; ++hh) z[hh] = scale * acc[hh];
+}
+
+template <bool WHOLE>
+__global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
+    __shared__ RowShared sh;
+    __shared__ float head_den[16];
+    uint32_t *lists = smem, *bins = lists + kSmLists, *map = bins + kRowBins;
+    float *part = reinterpret_cast<float *>(map + kSmMap), *P = part + kSmPart;
+    double *Pd = reinterpret_cast<double *>(P + kSmRank);
+    const int g = blockIdx.x % a.H_kv, b = blockIdx.x / a.H_kv, n_rep = a.H_q / a.H_kv;
+    const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int L = a.L, r_k = a.r_k, r_v = a.r_v, d_h = a.d_h, d = a.H_kv * d_h, k = a.k, T = a.T;
+    const float *A_k = a.A_k + (size_t)b * L * r_k, *A_v = a.A_v + (size_t)b * L * r_v;
+    const float *B_k = a.B_k + ((size_t)b * a.G + a.layer) * r_k * d + (size_t)g * d_h;
+    const float *B_v = a.B_v + ((size_t)b * a.G + a.layer) * r_v * d + (size_t)g * d_h;
+    const float *q = a.q + ((size_t)b * a.H_q + (size_t)g * n_rep) * d_h;
+    const float *K_t = T > 0 ? a.K_tail + ((size_t)b * a.H_kv + g) * T * d_h : nullptr, *V_t = T > 0 ? a.V_tail + ((size_t)b * a.H_kv + g) * T * d_h : nullptr;
+    const int words = (L + 63) / 64 * 2;
+
+    bins[2 * tid] = 0;
+    bins[2 * tid + 1] = 0;
+    for (int i = tid; i < words; i += kRowThreads) map[i] = 0;
+    // ---- projected queries, a rank per wavefront at a time, lanes over the head dimension: in single precision with the operations of
+    // the score stage, and in double precision for the logits of the selected rows (sums of a few dozen products taken one
+    // after the other: the attention was twice as far from the exact one with single-precision logits)
+    for (int i = w; i < r_k; i += kRowWaves)
+        for (int h0 = 0; h0 < n_rep; h0 += 4) {
+            const int nh = n_rep - h0 < 4 ? n_rep - h0 : 4;
+            float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            double accd[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int j = lane; j < d_h; j += kWave) {
+                const float bv = B_k[(size_t)i * d + j];
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh) {
+                    const float qv = q[(size_t)(h0 + (hh < nh ? hh : 0)) * d_h + j];
+                    if (WHOLE) acc[hh] = fmaf(bv, qv, acc[hh]);
+                    accd[hh] = fma((double)bv, (double)qv, accd[hh]);
+                }
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh) {
+                    if (WHOLE) acc[hh] += __shfl_xor(acc[hh], off, kWave);
+                    accd[hh] += __shfl_xor(accd[hh], off, kWave);
+                }
+            if (lane == 0)
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh)
+                    if (hh < nh) {
+                        P[(h0 + hh) * r_k + i] = acc[hh];
+                        Pd[(h0 + hh) * r_k + i] = accd[hh];
+                    }
+        }
+    __syncthreads();
+    const bool vec = r_k % 4 == 0 && ((uintptr_t)A_k & 15u) == 0;
+    const int n = k + T;
+    int32_t *ids = reinterpret_cast<int32_t *>(lists);
+    float *wt = reinterpret_cast<float *>(lists + k);  // [n_rep][k + T]
+    if constexpr (WHOLE) {
+        // ---- scores, a token per thread; the pooled ones are the wavefront's list
+        uint32_t *list = lists + w * 2 * kRowList;
+        for (int t0 = 0; t0 < L; t0 += kRowThreads) {
+            const int t = t0 + tid, at = t0 / kRowWaves + lane;
+            if (t >= L) break;
+            float best = -INFINITY;
+            for (int h0 = 0; h0 < n_rep; h0 += 4) {
+                const int nh = n_rep - h0 < 4 ? n_rep - h0 : 4;
+                float z[4];
+                row_logits(A_k + (size_t)t * r_k, P, r_k, h0, nh, vec, a.scale, z);
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh)
+                    if (hh < nh) best = fmaxf(best, z[hh]);
+            }
+            if (a.score_out) a.score_out[((size_t)b * a.H_kv + g) * L + t] = best;
+            list[at] = __float_as_uint(best);
+            list[at + kRowList] = (uint32_t)t;
+        }
+        // tokens of this wavefront: rounds of 64, the last one in part
+        const int full = L / kRowThreads, rest = L - full * kRowThreads - 64 * w;
+        const uint32_t count = (uint32_t)(64 * full + (rest < 0 ? 0 : rest < 64 ? rest : 64));
+        // ---- the k largest (the lists hold the whole row)
+        (void)select_from_lists(lists, count, (uint32_t)k, 0u, 0xFFFFFFFFu, bins, map, words, sh);
+        write_map(map, words, (uint32_t)k, sh, ids);
+        __syncthreads();
+    } else {
+        for (int j = tid; j < k; j += kRowThreads) {
+            const int t = a.idx[((size_t)b * a.H_kv + g) * k + j];
+            ids[j] = t < 0 ? 0 : (t >= L ? L - 1 : t);
+        }
+        __syncthreads();
+    }
+    if (WHOLE && a.idx_out)
+        for (int j = tid; j < k; j += kRowThreads) a.idx_out[((size_t)b * a.H_kv + g) * k + j] = ids[j];
+    // ---- logits of the selected rows, a thread per row and head, and of the tail
+    for (int i = tid; i < n_rep * k; i += kRowThreads) {
+        const int hh = i / k, j = i - hh * k;
+        const float *row = A_k + (size_t)ids[j] * r_k;
+        const double *ph = Pd + hh * r_k;
+        double z = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < r_k; ++c) z = fma((double)row[c], ph[c], z);
+        wt[hh * n + j] = (float)((double)a.scale * z);
+    }
+    for (int t = w; t < T; t += kRowWaves)
+        for (int hh = 0; hh < n_rep; ++hh) {
+            float part = 0.0f;
+            for (int j = lane; j < d_h; j += kWave) part = fmaf(K_t[(size_t)t * d_h + j], q[(size_t)hh * d_h + j], part);
+            part = wave_sum(part);
+            if (lane == 0) wt[hh * n + k + t] = a.scale * part;
+        }
+    __syncthreads();
+    // ---- weights, a wavefront per head
+    for (int hh = w; hh < n_rep; hh += kRowWaves) {
+        float m = -INFINITY, den = 0.0f;
+        for (int j = lane; j < n; j += kWave) {
+            m = fmaxf(m, wt[hh * n + j]);
+        }
+        m = wave_max(m);
+        for (int j = lane; j < n; j += kWave) {
+            const float e = expf(wt[hh * n + j] - m);
+            wt[hh * n + j] = e;
+            den += e;
+        }
+        den = wave_sum(den);
+        if (lane == 0) head_den[hh] = den;
+    }
+    __syncthreads();
+    // ---- U = w A^V[rows]: `parts` groups of threads share the rows, a thread per rank and four heads at a time
+    float *U = P;
+    const int parts = kRowThreads / r_v < kSmPart / (n_rep * r_v) ? kRowThreads / r_v : kSmPart / (n_rep * r_v);
+    if (tid < parts * r_v) {
+        const int grp = tid / r_v, c = tid - grp * r_v;
+        for (int h0 = 0; h0 < n_rep; h0 += 4) {
+            const int nh = n_rep - h0 < 4 ? n_rep - h0 : 4;
+            float u[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+            for (int j = grp; j < k; j += parts) {
+                const float x = A_v[(size_t)ids[j] * r_v + c];
+#pragma unroll
+                for (int hh = 0; hh < 4; ++hh) u[hh] = fmaf(wt[(h0 + (hh < nh ? hh : 0)) * n + j], x, u[hh]);
+            }
+#pragma unroll
+            for (int hh = 0; hh < 4; ++hh)
+                if (hh < nh) part[(grp * n_rep + h0 + hh) * r_v + c] = u[hh];
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < n_rep * r_v; i += kRowThreads) {
+        float u = 0.0f;
+        for (int p = 0; p < parts; ++p) u += part[p * n_rep * r_v + i];
+        U[i] = u;
+    }
+    __syncthreads();
+    // ---- out = (U B^V + w V_tail) / den: the ranks and the tail's tokens in `cuts` parts
+    const int cols = n_rep * d_h;
+    int cuts = kRowThreads / cols;
+    cuts = cuts < 1 ? 1 : cuts;
+    for (int i = tid; i < cols * cuts; i += kRowThreads) {
+        const int cut = i / cols, hj = i - cut * cols, hh = hj / d_h, j = hj - hh * d_h;
+        float o = 0.0f;
+#pragma unroll 8
+        for (int c = cut; c < r_v; c += cuts) o = fmaf(U[hh * r_v + c], B_v[(size_t)c * d + j], o);
+#pragma unroll 4
+        for (int t = cut; t < T; t += cuts) o = fmaf(wt[hh * n + k + t], V_t[(size_t)t * d_h + j], o);
+        part[i] = o;
+    }
+    __syncthreads();
+    for (int hj = tid; hj < cols; hj += kRowThreads) {
+        float o = 0.0f;
+        for (int cut = 0; cut < cuts; ++cut) o += part[cut * cols + hj];
+        a.out[((size_t)b * a.H_q + (size_t)g * n_rep) * d_h + hj] = o / head_den[hj / d_h];
+    }
+}
+
+// A mebibyte of A, B and the tail per workgroup at most (see above); everything else fits its LDS.
+bool small_step_ok(const xkv_shape &s, int T)
+{
+    if (s.dtype != XKV_F32 || s.H_kv < 1) return false;
+    const long long n_rep = s.H_q / s.H_kv, d_h = s.d_h;
+    const long long numbers = (long long)s.L * s.r_k + (long long)s.k * s.r_v + (s.r_k + s.r_v + 2LL * T) * d_h;
+    return numbers <= 262144 && s.L <= 4096 && n_rep <= 16 && n_rep * s.r_k <= kSmRank && n_rep * s.r_v <= kSmRank &&
+           s.r_v <= kRowThreads && n_rep * d_h <= kSmPart && s.k + n_rep * (s.k + T) <= kSmLists;
+}
+
+// idx (nullable): attend over these rows only, nothing is scored or selected
+hipError_t launch_small_step(const xkv_shape &s, int layer, const void *A_k, const void *A_v, const void *B_k, const void *B_v, const void *q,
+                             const void *K_tail, const void *V_tail, int T, void *out, int32_t *idx_out, float *score_out, float scale,
+                             const int32_t *idx, hipStream_t st)
+{
+    static DynamicLdsOnce attr, attr_rows;
+    const SmallArgs a{(const float *)A_k, (const float *)A_v, (const float *)B_k, (const float *)B_v, (const float *)q, (const float *)K_tail,
+                      (const float *)V_tail, (float *)out, score_out, idx_out, idx, s.G, layer, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.d_h, s.k, T,
+                      scale};
+    const dim3 grid(s.H_kv * s.batch);
+    if (idx) {
+        const hipError_t e = attr_rows.ensure((const void *)small_step_kernel<false>, (size_t)kSmWords * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(small_step_kernel<false>, grid, dim3(kRowThreads), (size_t)kSmWords * 4, st, a);
+    } else {
+        const hipError_t e = attr.ensure((const void *)small_step_kernel<true>, (size_t)kSmWords * 4);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(small_step_kernel<true>, grid, dim3(kRowThreads), (size_t)kSmWords * 4, st, a);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace xkv

@@ -187,6 +187,8 @@ xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer, const void *
         return XKV_ERR_INVALID_ARG;
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
+    if (small_step_ok(*shape, 0) && !g_profile[1].start)
+        return hip_status(launch_small_step(*shape, layer, A_k, A_v, B_k, B_v, q, nullptr, nullptr, 0, out, nullptr, nullptr, p.scale, idx, stream));
     float *part_o = at<float>(workspace, p.off_part_o);
     float *part_ml = at<float>(workspace, p.off_part_ml);
     void *pack_ws = at<void>(workspace, p.off_bpack);
@@ -242,6 +244,8 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
         return XKV_ERR_UNSUPPORTED;  // the packed form belongs to the matrix-core kernel
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
+    if (small_step_ok(*shape, T) && !g_profile[0].start && !g_profile[1].start)  // (a caller that times the stages gets the stages)
+        return hip_status(launch_small_step(*shape, layer, A_k, A_v, B_k, B_v, q, K_tail, V_tail, T, out, idx_out, score_out, p.scale, nullptr, stream));
     float *S = score_out ? score_out : at<float>(workspace, p.off_score);
     int32_t *idx = idx_out ? idx_out : at<int32_t>(workspace, p.off_idx);
     float *part_o = at<float>(workspace, p.off_part_o);
