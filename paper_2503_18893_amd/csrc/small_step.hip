@@ -4,8 +4,8 @@
 //
 // Such a step is launches and load latencies: five kernels of 3 to 14 us for 512 tokens of rank 32.  One compute unit reads a mebibyte
 // in less than these launches wait, so that is where the line lies (small_step_ok).  Two layers, us: 512 tokens of rank 32, 32
-// selected 64 -> 41; 128 selected and a tail of 33 150 -> 53; 4096 tokens of rank 48, 1024 selected 147 -> 113; 3000 of rank 64, two KV
-// heads 146 -> 137.
+// selected 64 -> 30; 128 selected and a tail of 33 152 -> 45; 4096 tokens of rank 48, 1024 selected 147 -> 99; 3000 of rank 64, two KV
+// heads 147 -> 120.
 // The stage call for selected rows takes the second half (WHOLE false) at the same sizes, so that the chained stages and the
 // step give the same bits.
 #include "row_select.h"
@@ -25,6 +25,65 @@ struct SmallArgs {
     float scale;
 };
 
+// Exchanges on the vector ALU.  swap16(x, y) trades the odd rows (16 lanes) of x for the even rows of y, swap32 the upper half of x
+// for the lower half of y; rot<CTRL> moves within a row.
+__device__ __forceinline__ void swap16(float &x, float &y)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ void swap32(float &x, float &y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r[0]);
+    y = __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ void swap16(double &x, double &y)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+    x = __hiloint2double((int)hi[0], (int)lo[0]);
+    y = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+__device__ __forceinline__ void swap32(double &x, double &y)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(y), false, false);
+    x = __hiloint2double((int)hi[0], (int)lo[0]);
+    y = __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+template <int CTRL> __device__ __forceinline__ float rot(float x)
+{
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
+template <int CTRL> __device__ __forceinline__ double rot(double x)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, true),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, true));
+}
+
+// Sums of four values over the wavefront: row i of the result holds that of v[i], added up in the order of an exchange with lane ^ 32,
+// ^ 16, ... ^ 1.  (A value at a time through LDS, the sixteen wavefronts' exchanges were 5 us of the kernel's 20.)
+template <typename V> __device__ __forceinline__ V wave_sum4(V (&v)[4])
+{
+    swap32(v[0], v[2]);
+    swap32(v[1], v[3]);
+    V a = v[0] + v[2], b = v[1] + v[3];  // halves: values 0, 2 and 1, 3
+    swap16(a, b);
+    a += b;
+    a += rot<0x128>(a);  // row_ror:8, :4, :2, :1
+    a += rot<0x124>(a);
+    a += rot<0x122>(a);
+    a += rot<0x121>(a);
+    return a;
+}
+
 // Scaled logits of one row for heads h0 .. h0 + 3 (those beyond nh repeat the first): P [heads][r_k] in LDS.
 __device__ __forceinline__ void row_logits(const float *__restrict__ row, const float *P, int r_k, int h0, int nh, bool vec, float scale, float (&z)[4])
 {
@@ -39,11 +98,11 @@ __device__ __forceinline__ void row_logits(const float *__restrict__ row, const 
 #pragma unroll 8
         for (int i = 0; i < r_k; i += 4) {
             const float4 x = *reinterpret_cast<const float4 *>(row + i);
-            const float x4[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int hh = 0; hh < 4; ++hh) acc[hh] = fmaf(x4[e], Ph[hh][i + e], acc[hh]);
+            for (int hh = 0; hh < 4; ++hh) {
+                const float4 p = *reinterpret_cast<const float4 *>(Ph[hh] + i);
+                acc[hh] = fmaf(x.w, p.w, fmaf(x.z, p.z, fmaf(x.y, p.y, fmaf(x.x, p.x, acc[hh]))));
+            }
         }
     } else {
 #pragma unroll 8
@@ -94,20 +153,13 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a)
                     accd[hh] = fma((double)bv, (double)qv, accd[hh]);
                 }
             }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-                for (int hh = 0; hh < 4; ++hh) {
-                    if (WHOLE) acc[hh] += __shfl_xor(acc[hh], off, kWave);
-                    accd[hh] += __shfl_xor(accd[hh], off, kWave);
-                }
-            if (lane == 0)
-#pragma unroll
-                for (int hh = 0; hh < 4; ++hh)
-                    if (hh < nh) {
-                        P[(h0 + hh) * r_k + i] = acc[hh];
-                        Pd[(h0 + hh) * r_k + i] = accd[hh];
-                    }
+            const int hh = lane >> 4;
+            const double pd = wave_sum4(accd);
+            const float pf = WHOLE ? wave_sum4(acc) : 0.0f;
+            if ((lane & 15) == 0 && hh < nh) {
+                P[(h0 + hh) * r_k + i] = pf;
+                Pd[(h0 + hh) * r_k + i] = pd;
+            }
         }
     __syncthreads();
     const bool vec = r_k % 4 == 0 && ((uintptr_t)A_k & 15u) == 0;
@@ -149,6 +201,11 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a)
     }
     if (WHOLE && a.idx_out)
         for (int j = tid; j < k; j += kRowThreads) a.idx_out[((size_t)b * a.H_kv + g) * k + j] = ids[j];
+    // the first values that the thread takes below are requested here, behind the logits' rows
+    const int parts = kRowThreads / r_v < kSmPart / (n_rep * r_v) ? kRowThreads / r_v : kSmPart / (n_rep * r_v);
+    const int grp = tid / r_v, col = tid - grp * r_v;
+    const bool sums = grp < parts;
+    const float x = sums && grp < k ? A_v[(size_t)ids[grp] * r_v + col] : 0.0f;
     // ---- logits of the selected rows, a thread per row and head, and of the tail
     for (int i = tid; i < n_rep * k; i += kRowThreads) {
         const int hh = i / k, j = i - hh * k;
@@ -185,21 +242,19 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a)
     __syncthreads();
     // ---- U = w A^V[rows]: `parts` groups of threads share the rows, a thread per rank and four heads at a time
     float *U = P;
-    const int parts = kRowThreads / r_v < kSmPart / (n_rep * r_v) ? kRowThreads / r_v : kSmPart / (n_rep * r_v);
-    if (tid < parts * r_v) {
-        const int grp = tid / r_v, c = tid - grp * r_v;
+    if (sums) {
         for (int h0 = 0; h0 < n_rep; h0 += 4) {
             const int nh = n_rep - h0 < 4 ? n_rep - h0 : 4;
             float u[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 4
             for (int j = grp; j < k; j += parts) {
-                const float x = A_v[(size_t)ids[j] * r_v + c];
+                const float v = j == grp ? x : A_v[(size_t)ids[j] * r_v + col];
 #pragma unroll
-                for (int hh = 0; hh < 4; ++hh) u[hh] = fmaf(wt[(h0 + (hh < nh ? hh : 0)) * n + j], x, u[hh]);
+                for (int hh = 0; hh < 4; ++hh) u[hh] = fmaf(wt[(h0 + (hh < nh ? hh : 0)) * n + j], v, u[hh]);
             }
 #pragma unroll
             for (int hh = 0; hh < 4; ++hh)
-                if (hh < nh) part[(grp * n_rep + h0 + hh) * r_v + c] = u[hh];
+                if (hh < nh) part[(grp * n_rep + h0 + hh) * r_v + col] = u[hh];
         }
     }
     __syncthreads();
