@@ -20,9 +20,8 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
-constexpr int kQuantPieces = 4;                   // 16-byte pieces per thread
-constexpr int kQuantBlock = 256 * kQuantPieces;  // ... and per workgroup
-constexpr int kQuantStage = 8192;                 // LDS: kQuantBlock / (r / 8) rows of at most 5 r / 8 + 12 bytes
+constexpr int kQuantPieces = 4;         // 16-byte pieces per thread (1 where the call is small)
+constexpr int kQuantSmall = 1536 * 1024;  // pieces
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -43,9 +42,9 @@ __device__ __forceinline__ float max3(float a, float b, float c)
 }
 
 // One lane per 16-byte piece (8 ranks); the four lanes of a group share min and max through two exchanges.  A
-// workgroup takes whole rows, as many as kQuantBlock pieces hold, collects the quantised rows in LDS and writes them as
+// workgroup takes whole rows, as many as 256 U pieces hold, collects the quantised rows in LDS and writes them as
 // one run of 16-byte pieces; with rows longer than that (STAGED false) every lane stores its own word.
-// The row stream and the vector ALU take about the same time, so: a thread has kQuantPieces requests in flight; rows and
+// The row stream and the vector ALU take about the same time, so: a thread of a large call has kQuantPieces requests in flight; rows and
 // offsets are 32-bit numbers from the workgroup's first row (a 64-bit division per piece took longer than the
 // quantisation), exchanges are lane permutations on the ALU, clamping is one median, two codes meet in a multiply-add before they
 // become a byte.  The two quotients take a product and a correction each: with y the rounded reciprocal of b, q = a y and
@@ -53,15 +52,16 @@ __device__ __forceinline__ float max3(float a, float b, float c)
 // 24 bits of b are ones, and a step has 8 (Markstein, IBM J. Res. Dev. 34, 1990).  Outside the range where r is exact the
 // ordinary division is used.  50001 rows of 512: 17.6 -> 15.2 us (67 MB; reading and writing as many bytes alone 11.5; with a
 // store of a word per lane and one for the parameters 16.3: rows of 320 bytes leave most lines in parts).
-template <int BITS, bool STAGED>
+template <int BITS, bool STAGED, int U>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out,
                                                             long long pieces, int r)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char stage[STAGED ? kQuantStage : 16];
+    constexpr int kBlock = 256 * U;  // pieces of a workgroup: kBlock / (r / 8) rows of at most 5 r / 8 + 12 bytes
+    __shared__ __attribute__((aligned(16))) unsigned char stage[STAGED ? 8 * kBlock : 16];
     constexpr float kQmax = (float)((1 << BITS) - 1), kQinv = 1.0f / kQmax;
     constexpr uint32_t kSmall = 0x20000000u, kLarge = 0x5F000000u;  // 2^-63, 2^63
     const uint32_t ppr = (uint32_t)r >> 3;  // pieces per row
-    const uint32_t most = STAGED ? kQuantBlock / ppr * ppr : kQuantBlock;  // pieces of a workgroup
+    const uint32_t most = STAGED ? kBlock / ppr * ppr : kBlock;  // pieces of this workgroup
     const long long first = (long long)blockIdx.x * most, row0 = first / ppr;
     const uint32_t pc0 = STAGED ? 0u : (uint32_t)(first - row0 * ppr);
     const uint32_t left = pieces - first < most ? (uint32_t)(pieces - first) : most;
@@ -75,14 +75,15 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__rest
             *reinterpret_cast<decltype(v) *>(og + o) = v;
     };
     // pieces is a multiple of 4 (r % 32 == 0), so a group's four lanes are all inside or all outside
-    q_u32x4_t raw[kQuantPieces];
+    q_u32x4_t raw[U];
 #pragma unroll
-    for (int u = 0; u < kQuantPieces; ++u) {
+    for (int u = 0; u < U; ++u) {
         const uint32_t i = u * 256 + threadIdx.x;
-        raw[u] = __builtin_nontemporal_load(Xb + (i < left ? i : left - 1));
+        const q_u32x4_t *src = Xb + (i < left ? i : left - 1);
+        raw[u] = U == 1 ? *src : __builtin_nontemporal_load(src);  // (a small call's rows may still be in the caches)
     }
 #pragma unroll
-    for (int u = 0; u < kQuantPieces; ++u) {
+    for (int u = 0; u < U; ++u) {
         const uint32_t i = u * 256 + threadIdx.x, lrow = (pc0 + i) / ppr, pc = pc0 + i - lrow * ppr;
         const bool in = i < left;
         float x[8];
@@ -155,16 +156,23 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
     const int ppr = r >> 3;
     const long long pieces = rows * (long long)ppr;
     if (pieces == 0) return hipSuccess;
-    const bool staged = ppr <= kQuantBlock;
-    const long long most = staged ? kQuantBlock / ppr * ppr : kQuantBlock, blocks = (pieces + most - 1) / most;
+    // A small call is one round of loads and stores: its pieces are spread over as many workgroups as there are, and stored as they
+    // come (two calls, their landmarks and selection, us: 4100 rows of 512, four pieces a thread 26.8, one 25.3; 12000 of 768 28.2
+    // and 27.0; 20000 of 640 37.0 with four and 39.4 with one and 64-bit row numbers).
+    const bool small = pieces <= kQuantSmall;
+    const int block = 256 * (small ? 1 : kQuantPieces);
+    const bool staged = !small && ppr <= block;
+    const long long most = staged ? block / ppr * ppr : block, blocks = (pieces + most - 1) / most;
     if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, pieces, r);
     };
     if (bits == 3)
-        staged ? launch(quantize_rows_kernel<3, true>) : launch(quantize_rows_kernel<3, false>);
+        small ? launch(quantize_rows_kernel<3, false, 1>)
+              : staged ? launch(quantize_rows_kernel<3, true, kQuantPieces>) : launch(quantize_rows_kernel<3, false, kQuantPieces>);
     else
-        staged ? launch(quantize_rows_kernel<4, true>) : launch(quantize_rows_kernel<4, false>);
+        small ? launch(quantize_rows_kernel<4, false, 1>)
+              : staged ? launch(quantize_rows_kernel<4, true, kQuantPieces>) : launch(quantize_rows_kernel<4, false, kQuantPieces>);
     return hipGetLastError();
 }
 

@@ -18,7 +18,7 @@ def torch_mod():
 
 
 @pytest.mark.parametrize("bits", [4, 3])
-@pytest.mark.parametrize("rows,r", [(257, 32), (11, 800), (3, 8192), (5, 8224), (130, 4128)])
+@pytest.mark.parametrize("rows,r", [(257, 32), (11, 800), (5, 2048), (5, 2080), (3, 8192), (5, 8224), (130, 4128), (393217, 32), (12300, 1056), (192, 65568)])
 def test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits):
     torch = torch_mod()
     rng = np.random.default_rng(rows + r)
