@@ -21,11 +21,14 @@
 //
 // KEPT: the logits are there already, so that the keys' half falls away and a row costs its values alone: from the score stage
 // (the absorbed step: every query head's score of every token) or, for rotated keys, from the KEYS form of
-// gather_attend_mfma_kernel (of every selected row).  The weights stay single precision there: they meet the rows as a high part
-// and a remainder, two matrix instructions each.  Quantised rows are not rounded to bf16 either: the operand is the code itself,
-// 16 + c (exact), the group's step goes into the weights (w step, split as before), and what is left of the affine map,
-// w (lo - 16 step), is one product per tile for all groups of 32 ranks.  (4 x 8 x 4096 rows of ranks 512: 4 bits 24 us, and 1.5 for
-// packing B^V beside the projection, against 27 of vector multiply-adds and 12 for merging them and B^V; bf16 32 us against 53.)
+// gather_attend_mfma_kernel (of every selected row).  The weights meet the rows in parts of 8 bits, a matrix instruction each: in
+// the absorbed step three, all 24 bits of them, as the general kernels have them (with two, 16 bits, and their exponentials short of a
+// unit or two, sums that cancel showed it: test_sums_keep_single_precision); with rotated keys two, where the weights of the other form are
+// rounded to 8.  Quantised rows are not rounded to bf16 either: the operand is the code itself (exact; with two parts 16 + c, which
+// takes no conversion, and whose sixteens the offsets take off again), the group's step goes into the weights (w step, split as
+// before), and what is left of the affine map, w lo or w (lo - 16 step), is one product per tile for all groups of 32 ranks.
+// (4 x 8 x 4096 rows of ranks 512: 4 bits 27 us, and 1.5 for packing B^V beside the projection, against 27 of vector multiply-adds and
+// 12 for merging them and B^V; bf16 33 us against 53.  Two parts instead of three: 24 and 32.)
 #include "xkv_common.h"
 
 #include "prepass.h"
@@ -60,10 +63,11 @@ constexpr int kOutPitch = 132;  // floats per row of the last product's result
 // lane of U holds a quad of slots of one rank.
 __host__ __device__ inline int slab_quads(int n_rep) { return (n_rep + 3) / 4; }
 __host__ __device__ inline int slab_bytes(int n_rep, int pg) { return kAbWaves * pg * 128 * slab_quads(n_rep) * 16; }
-__host__ __device__ inline int slab_groups(int n_rep, int ngv, int occ)  // (two workgroups share the LDS at occ 2)
+// (two workgroups share the LDS at occ 2; third: an operand for the third parts of U lies beside the slab)
+__host__ __device__ inline int slab_groups(int n_rep, int ngv, int occ, bool third)
 {
     int pg = ngv;
-    while (pg > 1 && slab_bytes(n_rep, pg) > (occ == 2 ? 44 : 100) * 1024) --pg;
+    while (pg > 1 && slab_bytes(n_rep, pg) > (occ == 2 ? 44 : third ? 84 : 100) * 1024) --pg;
     return pg;
 }
 
@@ -139,12 +143,12 @@ __device__ __forceinline__ void group_to_tile(const RowGroup<QB> &g, unsigned ch
     }
 }
 
-// KEPT, quantised rows: the codes as bf16 numbers 16 + c (0x4180 with the code in the upper mantissa bits), laid out like the values
-// above; the steps of every row of the four groups of 32 ranks, [group][row] floats in the order in which a lane takes the rows, and
-// lo - 16 step likewise.
+// KEPT, quantised rows: the codes as bf16 numbers, c (4 bits; EXACT) or 16 + c (0x4180 with the code in the upper mantissa bits), laid
+// out like the values above; the steps of every row of the four groups of 32 ranks, [group][row] floats in the order in which a lane
+// takes the rows, and the offsets, lo or lo - 16 step, likewise.
 constexpr int kStepBytes = 4 * 32 * 4;
 __host__ __device__ constexpr int param_bytes(int ngv) { return (1 + ngv) * kStepBytes; }  // steps of one group of 128 ranks, offsets of all
-template <int QB> __device__ __forceinline__ void codes_to_tile(const RowGroup<QB> &g, unsigned char *At, float *steps, float *offsets, int lane)
+template <int QB, bool EXACT> __device__ __forceinline__ void codes_to_tile(const RowGroup<QB> &g, unsigned char *At, float *steps, float *offsets, int lane)
 {
     constexpr uint32_t kMask = QB == 4 ? 0x00780078u : 0x00380038u;
     const int r = lane >> 2, q = lane & 3, place = 16 * (r >> 3) + 8 * ((r >> 2) & 1) + (r & 3);
@@ -159,21 +163,35 @@ template <int QB> __device__ __forceinline__ void codes_to_tile(const RowGroup<Q
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t w = codes[u];
-            *reinterpret_cast<u32x4_t *>(dst + 4 * i * kTileV + 16 * u) =
-                u32x4_t{((w << 3) & kMask) | sixteen, (QB == 4 ? (w >> 1) & kMask : w & kMask) | sixteen,
-                        ((w >> (2 * QB - 3)) & kMask) | sixteen, ((w >> (3 * QB - 3)) & kMask) | sixteen};
+            u32x4_t &to = *reinterpret_cast<u32x4_t *>(dst + 4 * i * kTileV + 16 * u);
+            if constexpr (EXACT) {
+                static_assert(QB == 4, "");
+                // the bytes 0 .. 15 are the 8-bit floating-point numbers (e4m3) 0 .. 15 times 2^-9
+                const uint32_t a = __builtin_amdgcn_perm(0u, w & 0x0F0F0F0Fu, 0x03010200u);         // bytes: ranks 0 1 4 5
+                const uint32_t b = __builtin_amdgcn_perm(0u, (w >> 4) & 0x0F0F0F0Fu, 0x03010200u);  // ranks 2 3 6 7
+                to = u32x4_t{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 512.0f, false)),
+                             __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 512.0f, false)),
+                             __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(a, 512.0f, true)),
+                             __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(b, 512.0f, true))};
+            } else {
+                to = u32x4_t{((w << 3) & kMask) | sixteen, (QB == 4 ? (w >> 1) & kMask : w & kMask) | sixteen,
+                             ((w >> (2 * QB - 3)) & kMask) | sixteen, ((w >> (3 * QB - 3)) & kMask) | sixteen};
+            }
         }
         const float step = __uint_as_float(word << 16), lo = __uint_as_float(word & 0xFFFF0000u);
         steps[at + 8 * i] = step;
-        offsets[at + 8 * i] = fmaf(-16.0f, step, lo);
+        offsets[at + 8 * i] = EXACT ? lo : fmaf(-16.0f, step, lo);
     }
 }
 
-// x = high + remainder, both bf16
-__device__ __forceinline__ void split_bf16(const f32x8_t &x, bf16x8_t &hi, bf16x8_t &lo)
+// x as a sum of N bf16 numbers, the largest first (three hold every bit of x)
+template <int N> __device__ __forceinline__ void split_bf16(f32x8_t x, bf16x8_t (&part)[N])
 {
-    hi = __builtin_convertvector(x, bf16x8_t);
-    lo = __builtin_convertvector(x - __builtin_convertvector(hi, f32x8_t), bf16x8_t);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        part[i] = __builtin_convertvector(x, bf16x8_t);
+        if (i + 1 < N) x -= __builtin_convertvector(part[i], f32x8_t);
+    }
 }
 
 // Row (16 lanes) and half-wavefront exchanges on the vector ALU.  permlane16_swap(x, y) trades the odd rows of x for the
@@ -197,8 +215,9 @@ __device__ __forceinline__ float max_over_rows(float x)  // over the four lanes 
 // KEPT (1, 2 or 4) is how often the query heads fit the 16 slots.  Copy c stands for group c of 32 ranks (modulo KEPT): a product for
 // that group has zero weights in the other copies, so that the sums of KEPT groups share their registers (U of four heads and 512
 // ranks 32 instead of 128, which is what lets two workgroups share a compute unit with four groups in flight each), and the
-// weights times steps of KEPT groups of quantised rows are formed together.
-template <int NGV, int RG, int QB, int OCC, int KEPT>
+// weights times steps of KEPT groups of quantised rows are formed together.  PARTS: 8-bit parts of a weight; with three U is split into
+// three as well before it meets B^V, and exponentials are those of the general kernels.
+template <int NGV, int RG, int QB, int OCC, int KEPT, int PARTS>
 __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     const void *__restrict__ A_k, const void *__restrict__ A_v, const u32x4_t *__restrict__ Pz, size_t pz_head_stride,
     const u32x4_t *__restrict__ pack_v, size_t pack_seq_stride, size_t pack_head_stride, const int32_t *__restrict__ idx,
@@ -206,6 +225,9 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     int H_kv, int H_q, int k, int splits, int chunk, int FZ, float scale, const float *__restrict__ heads, int hp, bool by_place)
 {
     static_assert(NGV % RG == 0, "a tile's groups of A^V start at ring entry 0");
+    static_assert(KEPT ? PARTS == 2 || PARTS == 3 : PARTS == 1, "");
+    constexpr bool FULL = PARTS == 3;
+    auto exponential = [](float x) __attribute__((always_inline)) { return FULL ? expf(x) : __expf(x); };
     constexpr int WAVES = kAbWaves, TILE = WAVES * 32;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     // workgroup id -> (KV head fastest: the heads of a sequence gather from the same rows' lines), split, sequence
@@ -435,23 +457,23 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
         }
         // ---- logits -> weights (bf16, as the operand); rescaling of U and of the running sum
         const float m_new = fmaxf(m_run, max_over_rows(m_loc));
-        const float alpha = (m_new == -INFINITY) ? 1.0f : __expf(m_run - m_new);
+        const float alpha = (m_new == -INFINITY) ? 1.0f : exponential(m_run - m_new);
         f32x8_t wv;
         float l_add = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            wv[e] = z8[e] == -INFINITY ? 0.0f : __expf(z8[e] - m_new);
+            wv[e] = z8[e] == -INFINITY ? 0.0f : exponential(z8[e] - m_new);
             l_add += wv[e];
         }
-        bf16x8_t wf = __builtin_convertvector(wv, bf16x8_t), wr;
-        if constexpr (KEPT) {
-            request_logits(tile + 1);
-            split_bf16(wv, wf, wr);
-        }
-        bf16x8_t wfc[QB == 0 ? CP : 1], wrc[QB == 0 ? CP : 1];
+        bf16x8_t wp[PARTS];
+        if constexpr (KEPT) request_logits(tile + 1);
+        split_bf16<PARTS>(wv, wp);
+        bf16x8_t wc[PARTS][QB == 0 ? CP : 1];
         if constexpr (KEPT && QB == 0) {
 #pragma unroll
-            for (int c = 0; c < CP; ++c) wfc[c] = only(wf, c), wrc[c] = only(wr, c);
+            for (int c = 0; c < CP; ++c)
+#pragma unroll
+                for (int p = 0; p < PARTS; ++p) wc[p][c] = only(wp[p], c);
         }
         l_run = l_run * alpha + l_add;
         m_run = m_new;
@@ -468,7 +490,7 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
             }
         }
         // ---- U += W A^V[rows]
-        [[maybe_unused]] bf16x8_t sf, sr, gf, gr;
+        [[maybe_unused]] bf16x8_t sp[PARTS], gp[PARTS];
 #pragma unroll
         for (int gv = 0; gv < NGV; ++gv) {
             const Request q = request_of();
@@ -476,7 +498,7 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
             int tk[NF];
             if constexpr (OCC == 1) rows_of(q, tk, 0, NF);
             if constexpr (KEPT && QB != 0)
-                codes_to_tile<QB>(ring[gv % RG], At, steps, offsets + gv * (kStepBytes / 4), lane);
+                codes_to_tile<QB, FULL>(ring[gv % RG], At, steps, offsets + gv * (kStepBytes / 4), lane);
             else
                 group_to_tile<QB, false>(ring[gv % RG], At, lane);
             __builtin_amdgcn_sched_barrier(0);
@@ -511,21 +533,22 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
                             f32x8_t ws;
 #pragma unroll
                             for (int e = 0; e < 8; ++e) ws[e] = wv[e] * pq[j / (2 * KEPT)][e / 4][e % 4];
-                            split_bf16(ws, sf, sr);
+                            split_bf16<PARTS>(ws, sp);
                         }
                         if (j % 2 == 0) {
-                            gf = only(sf, (h4 + j) / 2 % CP);
-                            gr = only(sr, (h4 + j) / 2 % CP);
+#pragma unroll
+                            for (int p = 0; p < PARTS; ++p) gp[p] = only(sp[p], (h4 + j) / 2 % CP);
                         }
                         f32x4_t &u = U[(gv * 4 + (h4 + j) / 2) / CP * 2 + j % 2];
-                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf, v8, u, 0, 0, 0);
-                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gr, v8, u, 0, 0, 0);
+#pragma unroll
+                        for (int p = 0; p < PARTS; ++p) u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gp[p], v8, u, 0, 0, 0);
                     } else if constexpr (KEPT) {
                         f32x4_t &u = U[(gv * 4 + (h4 + j) / 2) / CP * 2 + j % 2];
-                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wfc[(h4 + j) / 2 % CP], v8, u, 0, 0, 0);
-                        u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wrc[(h4 + j) / 2 % CP], v8, u, 0, 0, 0);
+#pragma unroll
+                        for (int p = 0; p < PARTS; ++p)
+                            u = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[p][(h4 + j) / 2 % CP], v8, u, 0, 0, 0);
                     } else {
-                        U[gv * 8 + h4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, v8, U[gv * 8 + h4 + j], 0, 0, 0);
+                        U[gv * 8 + h4 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[0], v8, U[gv * 8 + h4 + j], 0, 0, 0);
                     }
                 }
                 if (OCC == 2 || h4 + HS == 8) __builtin_amdgcn_sched_barrier(0);
@@ -537,11 +560,14 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
                 const int grp = 16 * c + l16 < NGV * 4 ? 16 * c + l16 : 0;  // (columns beyond the groups are not used)
                 const f32x4_t *ps = reinterpret_cast<const f32x4_t *>(offsets + 32 * grp + 8 * q4);
                 const f32x8_t o8 = __builtin_shufflevector(ps[0], ps[1], 0, 1, 2, 3, 4, 5, 6, 7);
-                bf16x8_t oh, ol;
-                split_bf16(o8, oh, ol);
-                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, oh, off_sum[c], 0, 0, 0);
-                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr, oh, off_sum[c], 0, 0, 0);
-                off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, ol, off_sum[c], 0, 0, 0);
+                constexpr int OP = FULL ? 1 : PARTS;  // (lo is a bf16 number)
+                bf16x8_t op[OP];
+                split_bf16<OP>(o8, op);
+#pragma unroll
+                for (int i = 0; i < OP; ++i)
+#pragma unroll
+                    for (int p = 0; p < PARTS - i; ++p)  // (remainder by remainder is left out)
+                        off_sum[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wp[p], op[i], off_sum[c], 0, 0, 0);
             }
         }
     }
@@ -569,10 +595,15 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
     for (int f = 0; f < NPF; ++f) bv[f] = pv[(size_t)f * 256];
 
     const float l_a = l_run + __shfl_xor(l_run, 16, kWave), l_tot = l_a + __shfl_xor(l_a, 32, kWave);
-    const int PG = slab_groups(n_rep, NGV, OCC), NQ = slab_quads(n_rep);
+    const int PG = slab_groups(n_rep, NGV, OCC, FULL && CP == 1), NQ = slab_quads(n_rep);
+    // Rows of an operand: the high parts of the slots, then their remainders.  Three parts fit it where there are eight slots; else the
+    // third is an operand of its own, Uf3, whose other rows repeat it.
+    constexpr bool THIRD = FULL && CP == 1;
+    constexpr int PROWS = FULL && !THIRD ? 8 : 16;
     uint16_t *Uf = reinterpret_cast<uint16_t *>(smem_raw);                         // [NGV * 8][64][8]
     float *ml = reinterpret_cast<float *>(smem_raw + NGV * 8 * 1024);               // [2][WAVES][16]
-    float *slab = ml + 2 * WAVES * 16;
+    uint16_t *Uf3 = reinterpret_cast<uint16_t *>(ml + 2 * WAVES * 16);              // THIRD: [NGV * 8][2][16][8]
+    float *slab = ml + 2 * WAVES * 16 + (THIRD ? NGV * 1024 : 0);
     __syncthreads();  // everybody is done with the operands
     if (lane < 16) {
         ml[w * 16 + lane] = m_run;
@@ -587,7 +618,7 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
 #pragma unroll
         for (int ww = 0; ww < WAVES; ++ww) M = fmaxf(M, ml[ww * 16 + hh]);
         const float mw = ml[w * 16 + hh];
-        f4[v] = mw == -INFINITY ? 0.0f : __expf(mw - M);
+        f4[v] = mw == -INFINITY ? 0.0f : exponential(mw - M);
     }
     for (int g0 = 0; g0 < NGV; g0 += PG) {
 #pragma unroll
@@ -612,30 +643,41 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
             for (int ww = 1; ww < WAVES; ++ww)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) sum[e] += src[(ww * PG * 128 + e) * NQ];
-            uint16_t *dst = Uf + (((g0 * 8 + (c >> 4)) * 64 + ((c >> 3) & 1) * 32 + 4 * hq) * 8 + (c & 7));
+            const int half = (g0 * 8 + (c >> 4)) * 2 + ((c >> 3) & 1);  // of the fragment
+            uint16_t *dst = Uf + ((half * 32 + 4 * hq) * 8 + (c & 7));
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const f32x4_t x = f32x4_t{sum[0][v], sum[1][v], sum[2][v], sum[3][v]};
-                const bf16x4_t hi = __builtin_convertvector(x, bf16x4_t);
-                *reinterpret_cast<bf16x4_t *>(dst + v * 8) = hi;
-                *reinterpret_cast<bf16x4_t *>(dst + (16 + v) * 8) =
-                    __builtin_convertvector(x - __builtin_convertvector(hi, f32x4_t), bf16x4_t);
+                f32x4_t x = f32x4_t{sum[0][v], sum[1][v], sum[2][v], sum[3][v]};
+#pragma unroll
+                for (int p = 0; p < (FULL ? 3 : 2); ++p) {
+                    const bf16x4_t part = __builtin_convertvector(x, bf16x4_t);
+                    uint16_t *to = THIRD && p == 2 ? Uf3 + ((half * 16 + 4 * hq + v) * 8 + (c & 7)) : dst + (PROWS * p + v) * 8;
+                    *reinterpret_cast<bf16x4_t *>(to) = part;
+                    x -= __builtin_convertvector(part, f32x4_t);
+                }
             }
         }
         __syncthreads();
     }
-    const u32x4_t *Uq = reinterpret_cast<const u32x4_t *>(Uf) + lane;
+    const u32x4_t *Uq = reinterpret_cast<const u32x4_t *>(Uf) + lane, *Uq3 = reinterpret_cast<const u32x4_t *>(Uf3) + 16 * hf + l16;
     float *po = slab;  // [16][kOutPitch]
-    f32x16_t o;
+    f32x16_t o, o3;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o[v] = 0.0f;
+    for (int v = 0; v < 16; ++v) o[v] = o3[v] = 0.0f;
 #pragma unroll
-    for (int f = 0; f < NFB; ++f)
-        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq[f * 64]),
-                                                    __builtin_bit_cast(bf16x8_t, f < NPF ? bv[f < NPF ? f : 0] : pv[(size_t)f * 256]), o, 0, 0, 0);
+    for (int f = 0; f < NFB; ++f) {
+        const bf16x8_t b8 = __builtin_bit_cast(bf16x8_t, f < NPF ? bv[f < NPF ? f : 0] : pv[(size_t)f * 256]);
+        o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq[f * 64]), b8, o, 0, 0, 0);
+        if constexpr (THIRD) o3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, Uq3[f * 32]), b8, o3, 0, 0, 0);
+    }
+    // register v is row 8 (v / 4) + 4 hf + v % 4
+    if constexpr (PROWS == 8) {
 #pragma unroll
-    for (int v = 0; v < 8; ++v)  // slot 8 (v / 4) + 4 hf + v % 4, its remainder's row eight registers on
-        po[(8 * (v / 4) + 4 * hf + (v % 4)) * kOutPitch + w * 32 + n] = o[v] + o[v + 8];
+        for (int v = 0; v < 4; ++v) po[(4 * hf + v) * kOutPitch + w * 32 + n] = o[v] + (o[v + 4] + o[v + 8]);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) po[(8 * (v / 4) + 4 * hf + (v % 4)) * kOutPitch + w * 32 + n] = THIRD ? o[v] + (o[v + 8] + o3[v]) : o[v] + o[v + 8];
+    }
     __syncthreads();
     for (int item = tid; item < n_rep * 128; item += WAVES * 64) {
         const int hh = item >> 7, dim = item & 127;
@@ -648,7 +690,7 @@ __global__ __launch_bounds__(kAbWaves * 64, OCC) void gather_absorb_kernel(
 #pragma unroll
             for (int ww = 0; ww < WAVES; ++ww) {
                 const float mw = ml[ww * 16 + hh];
-                den += (mw == -INFINITY ? 0.0f : __expf(mw - M)) * ml[(WAVES + ww) * 16 + hh];
+                den += (mw == -INFINITY ? 0.0f : exponential(mw - M)) * ml[(WAVES + ww) * 16 + hh];
             }
             part_ml[slot * 2 + 0] = M;
             part_ml[slot * 2 + 1] = den;
@@ -664,12 +706,13 @@ constexpr size_t kAbsorbLdsMax = 160 * 1024 - 512, kAbsorbLdsPair = 80 * 1024;  
 static constexpr int absorb_rg(int ngv, int occ, bool deep) { return ngv == 3 ? 3 : ngv == 4 && occ == 1 && deep ? 4 : 2; }
 static bool absorb_deep(int FZ) { return (FZ / 8 + 3) % 4 >= 2; }
 
-static size_t absorb_lds(int ngv, int occ, int n_rep, int FZ, int chunk, bool kept = false)
+static size_t absorb_lds(int ngv, int occ, int n_rep, int FZ, int chunk, int parts = 1)
 {
     const int rg = absorb_rg(ngv, occ, absorb_deep(FZ));
-    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)kAbWaves * (kTileBytes + 128 + (kept ? param_bytes(ngv) : 0)) + (size_t)chunk * 4;
-    const int slab = slab_bytes(n_rep, slab_groups(n_rep, ngv, occ)), out = 16 * kOutPitch * 4;
-    const size_t merge = (size_t)ngv * 8192 + (size_t)2 * kAbWaves * 16 * 4 + (size_t)(slab > out ? slab : out);
+    const size_t main = (size_t)(FZ / 8 + rg - 1) / rg * rg * 8192 + (size_t)kAbWaves * (kTileBytes + 128 + (parts > 1 ? param_bytes(ngv) : 0)) + (size_t)chunk * 4;
+    const bool third = parts == 3 && n_rep > 8;
+    const int slab = slab_bytes(n_rep, slab_groups(n_rep, ngv, occ, third)), out = 16 * kOutPitch * 4;
+    const size_t merge = (size_t)ngv * (third ? 8192 + 4096 : 8192) + (size_t)2 * kAbWaves * 16 * 4 + (size_t)(slab > out ? slab : out);
     return main > merge ? main : merge;
 }
 
@@ -748,18 +791,18 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
     const int ngv = absorb_ngv(s.r_v);
     const int hp = head_pitch_of(p.n_rep), FZ = heads ? 0 : pa.FZ;
     const int occ = p.ab_occ, splits = heads ? p.ak_splits : p.ab_splits, chunk = heads ? p.ak_chunk : p.ab_chunk;
-    const size_t lds = heads ? absorb_lds(ngv, p.n_rep <= 8 ? 2 : 1, p.n_rep, 0, chunk, true) : p.ab_lds;
+    const size_t lds = heads ? absorb_lds(ngv, p.n_rep <= 8 ? 2 : 1, p.n_rep, 0, chunk, by_place ? 2 : 3) : p.ab_lds;
     if (ngv == 0 || lds > kAbsorbLdsMax || splits > p.max_splits) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((long long)splits * s.H_kv * s.batch));
     const int stage = heads ? 4 : 1;
-#define XKV_AB(NV, OC, DP, QB, KP)                                                                                      \
+#define XKV_AB(NV, OC, DP, QB, KP, PT)                                                                                  \
     do {                                                                                                                \
         static DynamicLdsOnce attr;                                                                                     \
-        constexpr int RG = KP ? (NV == 3 ? 3 : NV == 4 ? 4 : 2) : absorb_rg(NV, OC, DP);                                                                       \
-        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<NV, RG, QB, OC, KP>, kAbsorbLdsMax);     \
+        constexpr int RG = KP ? (NV == 3 ? 3 : NV == 4 ? 4 : 2) : absorb_rg(NV, OC, DP);                                \
+        const hipError_t e = attr.ensure((const void *)gather_absorb_kernel<NV, RG, QB, OC, KP, PT>, kAbsorbLdsMax);    \
         if (e != hipSuccess) return e;                                                                                  \
         if (!by_place) profile_begin(stage, st);                                                                        \
-        hipLaunchKernelGGL((gather_absorb_kernel<NV, RG, QB, OC, KP>), grid, dim3(256), lds, st, A_k, A_v,           \
+        hipLaunchKernelGGL((gather_absorb_kernel<NV, RG, QB, OC, KP, PT>), grid, dim3(256), lds, st, A_k, A_v,          \
                            (const u32x4_t *)pa.Pz, pa.z_stride / 8, pv, seq_stride, per_head, idx, counts, part_o,      \
                            part_ml, s.L, s.r_k, s.r_v, s.H_kv, s.H_q, s.k, splits, chunk, FZ, p.scale,                  \
                            heads, hp, by_place);                                                                        \
@@ -768,20 +811,24 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
 #define XKV_AB_Q(NV, OC, DP)                  \
     do {                                      \
         if (qbits == 0)                       \
-            XKV_AB(NV, OC, DP, 0, 0);         \
+            XKV_AB(NV, OC, DP, 0, 0, 1);      \
         else if (qbits == 4)                  \
-            XKV_AB(NV, OC, DP, 4, 0);         \
+            XKV_AB(NV, OC, DP, 4, 0, 1);      \
         else                                  \
-            XKV_AB(NV, OC, DP, 3, 0);         \
+            XKV_AB(NV, OC, DP, 3, 0, 1);      \
     } while (0)
-#define XKV_AB_KC(NV, OC, CPS)              \
-    do {                                    \
-        if (qbits == 0)                     \
-            XKV_AB(NV, OC, true, 0, CPS);   \
-        else if (qbits == 4)                \
-            XKV_AB(NV, OC, true, 4, CPS);   \
-        else                                \
-            XKV_AB(NV, OC, true, 3, CPS);   \
+#define XKV_AB_KC(NV, OC, CPS)                 \
+    do {                                       \
+        if (by_place && qbits == 0)            \
+            XKV_AB(NV, OC, true, 0, CPS, 2);   \
+        else if (by_place && qbits == 4)       \
+            XKV_AB(NV, OC, true, 4, CPS, 2);   \
+        else if (by_place)                     \
+            XKV_AB(NV, OC, true, 3, CPS, 2);   \
+        else if (qbits == 0)                   \
+            XKV_AB(NV, OC, true, 0, CPS, 3);   \
+        else                                   \
+            XKV_AB(NV, OC, true, 4, CPS, 3);   \
     } while (0)
 #define XKV_AB_K(NV)                        \
     do {                                    \

@@ -67,6 +67,52 @@ def test_attention_from_kept_scores(n_rep, r_v, L, k, batch, bits):
             assert (got - ref).abs().max() <= (2.0 ** -8 + 2.0 ** -13) * ref.abs().max() + 1e-6, (b, h)
 
 
+@pytest.mark.parametrize("bits", [0, 4])
+@pytest.mark.parametrize("what", ["sums", "weights"])
+@pytest.mark.parametrize("n_rep,r_v,L,k,batch", [(1, 64, 300, 96, 2), (4, 96, 300, 96, 2), (8, 128, 400, 200, 1), (7, 384, 700, 300, 1),
+                                                 (12, 512, 300, 96, 1), (16, 768, 700, 300, 1)])
+def test_sums_keep_single_precision(n_rep, r_v, L, k, batch, what, bits):
+    """Outputs in which almost everything cancels, so that the rounding to bf16 at the end does not hide what came before it."""
+    torch = torch_mod()
+    H_kv = 2
+    shape = xb.Shape.of(workload(H_kv, n_rep, 64, r_v, L, k, batch))
+    g = torch.Generator(device="cuda").manual_seed(L + r_v + bits)
+    A_v = torch.randn((batch, L, r_v), generator=g, device="cuda").bfloat16()
+    pitch = 1 << (n_rep - 1).bit_length()
+    heads = torch.randn((batch, H_kv, L, pitch), generator=g, device="cuda")
+    B_v = torch.zeros((batch, 1, r_v, H_kv * 128), device="cuda")
+    B_v[:, 0, 0] = torch.rand((H_kv * 128,), generator=g, device="cuda") + 0.5
+    if what == "sums":  # of two columns that differ only in rows of little weight, the difference
+        A_v[:, :, 0] = (torch.rand((batch, L), generator=g, device="cuda") + 0.5).bfloat16()
+        A_v[:, :, 1] = A_v[:, :, 0]
+        A_v[:, ::10, 1] = 1 - A_v[:, ::10, 0]
+        heads[:, :, ::10] -= 9.0
+        B_v[:, 0, 1] = -B_v[:, 0, 0]
+        pick, group = L, 1
+    else:  # rows in pairs of opposite sign and nearly equal weight
+        A_v = A_v.clamp(-1, 1)
+        A_v[:, 0::2, 0], A_v[:, 1::2, 0] = 1, -1
+        heads[:, :, 1::2] = heads[:, :, 0::2] + 1e-4 * torch.randn((batch, H_kv, L // 2, pitch), generator=g, device="cuda")
+        pick, group = L // 2, 2
+    B_v = B_v.bfloat16()
+    idx = torch.stack([torch.randperm(pick, generator=g, device="cuda")[:k // group].sort().values for _ in range(batch * H_kv)])
+    idx = (group * idx[:, :, None] + torch.arange(group, device="cuda")).view(batch, H_kv, k).int().contiguous()
+    given, A64 = rows_of(torch, A_v, bits)
+    ws = torch.empty(xb.xkv_absorbed_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    out = torch.empty((batch, H_kv * n_rep, 128), dtype=torch.bfloat16, device="cuda")
+    (xb.xkv_attend_absorbed_q4 if bits else xb.xkv_attend_absorbed)(shape, 0, given, B_v, heads, idx, out, ws)
+    for b in range(batch):
+        for h in range(H_kv):
+            t = idx[b, h].long()
+            W = torch.softmax(heads[b, h, t, :n_rep].double(), 0)
+            B64 = B_v[b, 0, :, h * 128:(h + 1) * 128].double()
+            ref, size = (W.T @ A64[b, t]) @ B64, (W.T @ A64[b, t].abs()) @ B64.abs()
+            err = ((out[b, h * n_rep:(h + 1) * n_rep].double() - ref).abs() - 2.0 ** -8 * ref.abs()).clamp_min(0)
+            # sums of 300 products or fewer, each rounded to 24 bits of a partial sum: a few units of the last place of the whole
+            # (rounding errors that add up at random: sqrt(300) halves are 9); weights within two units, over rows that do not add up
+            assert (err / size).max() <= (8 if what == "sums" else 2) * 2.0 ** -24, (b, h)
+
+
 @pytest.mark.parametrize("bits", [0, 4, 3])
 @pytest.mark.parametrize("n_rep,r", [(4, 64), (7, 160), (1, 512)])
 def test_rotated_rows_in_two_halves(n_rep, r, bits):
