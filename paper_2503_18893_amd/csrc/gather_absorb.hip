@@ -730,6 +730,23 @@ bool gather_absorb_shape_ok(const xkv_shape &s)
     return s.L < (1 << 24) && s.L * widest * 2 < (1LL << 32) && s.r_k <= 1024 && absorb_ngv(s.r_v) != 0;
 }
 
+// What the matrix cores save grows with the query heads; what they cost is the packing of B^V (rows * r_v) and, per number
+// gathered, a little more than the general kernels need for rows of bf16.  Whole steps with 8 KV heads, budgets a sixteenth, us general
+// / matrix cores: 4 query heads each, ranks 512, 8 sequences x 4096 rows 198.8 / 198.8, 16 x 4096 363 / 399, ranks 256 221 / 230; in
+// 4 bits 16 x 4096 216 / 212, but 16 x 16384 (row sums alone) 234 / 247; ranks 768 (two groups in flight) 4 x 2048 102 / 101, 16 x 1024
+// 169 / 171, in 4 bits 110 / 112 and 170 / 176.  One query head: ranks 512, 1 x 4096 68 / 57, 4 x 512 40 / 42, 16 x 4096 340 / 366;
+// ranks 128, 16 x 512 41 / 44, 16 x 1024 the same, 16 x 4096 137 / 129; ranks 768, 1 x 512 38 / 40, 1 x 2048 52 / 50.  Two are like one;
+// from nine on the general row sums take 1.6 to 3.4 times as long.
+bool absorbed_mfma_pays(const xkv_shape &s, bool q4)
+{
+    const int n_rep = s.H_q / s.H_kv;
+    const long long rows = (long long)s.batch * s.H_kv, numbers = rows * s.k * s.r_v;
+    if (n_rep > 8) return true;
+    if (n_rep <= 2 && (s.k < (s.r_v > 512 ? 2048 : 1024) || (rows * s.r_v >= 16384 && s.r_v > (q4 ? 256 : 128)))) return false;
+    if (s.r_v > 512 && n_rep <= 4) return numbers < 1LL << 25;
+    return numbers < (q4 ? 1LL << 30 : 1LL << 27);
+}
+
 void gather_absorb_plan(const xkv_shape &s, Plan &p)
 {
     // Tiles are 128 rows.  Where every compute unit gets more than one, U fits 256 registers a lane and two workgroups fit the

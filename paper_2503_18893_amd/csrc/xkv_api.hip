@@ -714,9 +714,9 @@ static xkv_status prepare_absorbed(const xkv_shape *s, void *ws, size_t ws_bytes
 
 // Whether the row sums and the product with B^V run on the matrix cores (the selected-row kernel without its keys' half,
 // gather_absorb.hip) or in the general kernels of absorbed.hip; B^V_l is then packed in the projection's launch or one of its own.
-static bool absorbed_uses_mfma(const Plan &p, const void *A_v, const void *B_v, const void *pack_ws)
+static bool absorbed_uses_mfma(const xkv_shape &s, const Plan &p, const void *A_v, const void *B_v, const void *pack_ws, bool q4)
 {
-    return p.absorb && (((uintptr_t)A_v | (uintptr_t)B_v | (uintptr_t)pack_ws) & 15u) == 0;
+    return p.absorb && absorbed_mfma_pays(s, q4) && (((uintptr_t)A_v | (uintptr_t)B_v | (uintptr_t)pack_ws) & 15u) == 0;
 }
 static PackArgs absorbed_pack_args(const xkv_shape &s, int layer, const void *B_v, const void *q, void *pack_ws)
 {
@@ -771,7 +771,7 @@ static xkv_status attend_absorbed_impl(const xkv_shape *shape, int32_t layer, co
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
     void *pack_ws = at<void>(workspace, p.off_bpack);
-    if (absorbed_uses_mfma(p, A_v, B_v, pack_ws)) {
+    if (absorbed_uses_mfma(*shape, p, A_v, B_v, pack_ws, q4)) {
         const PackArgs pa = absorbed_pack_args(*shape, layer, B_v, nullptr, pack_ws);
         float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
         hipError_t e = launch_gather_prepare(pa, stream);
@@ -845,7 +845,7 @@ static xkv_status sr_decode_absorbed_impl(const xkv_shape *shape, int32_t layer,
     const bool tail_first = tail.mfma && (q4 || score_stage_uses_mfma(*shape, A_k, B_k, q, at<void>(workspace, p.off_p), heads));
     const DenseArgs *ta = tail_first ? &tail.args : nullptr;
     void *pack_ws = at<void>(workspace, p.off_bpack);
-    const bool mfma = absorbed_uses_mfma(p, A_v, B_v, pack_ws);
+    const bool mfma = absorbed_uses_mfma(*shape, p, A_v, B_v, pack_ws, q4);
     PackArgs pa{};
     if (mfma) pa = absorbed_pack_args(*shape, layer, B_v, q, pack_ws);
     bool packed = q4;

@@ -253,6 +253,8 @@ inline int gather_partials(const Plan &p, bool mfma, float rope_theta)
     return !mfma ? p.sr_splits * 4 : gather_uses_absorb(p, rope_theta) ? p.ab_splits : p.rope_kept ? p.ak_splits : p.sr_splits;
 }
 bool gather_absorb_shape_ok(const xkv_shape &s);
+// Whether the absorbed step of such a shape is faster there than in the general kernels of absorbed.hip (q4: 4-bit rows).
+bool absorbed_mfma_pays(const xkv_shape &s, bool q4);
 void gather_absorb_plan(const xkv_shape &s, Plan &p);
 hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *A_v,
                                 const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,

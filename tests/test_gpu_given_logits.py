@@ -37,12 +37,17 @@ def workload(H_kv, n_rep, r_k, r_v, L, k, batch):
                           dtype="bf16", a_scale=1.0, sigma_decay=0.5, q_scale=0.3)
 
 
+# query heads per KV head, r_v, L, k, batch of the absorbed step; the first two are summed by the general kernels
+CASES = [(1, 32, 300, 1, 1), (2, 96, 900, 127, 2), (3, 32, 300, 1, 1), (1, 32, 2500, 1025, 1), (2, 96, 1300, 1151, 2), (4, 512, 3000, 1000, 2),
+         (5, 384, 700, 129, 1), (7, 640, 2000, 600, 1), (8, 256, 1000, 1000, 3), (12, 768, 900, 400, 1), (16, 128, 5000, 4500, 1)]
+CASES_H_KV = 3
+
+
 @pytest.mark.parametrize("bits", [0, 4])
-@pytest.mark.parametrize("n_rep,r_v,L,k,batch", [(1, 32, 300, 1, 1), (2, 96, 900, 127, 2), (4, 512, 3000, 1000, 2), (5, 384, 700, 129, 1),
-                                                 (7, 640, 2000, 600, 1), (8, 256, 1000, 1000, 3), (12, 768, 900, 400, 1), (16, 128, 5000, 4500, 1)])
+@pytest.mark.parametrize("n_rep,r_v,L,k,batch", CASES)
 def test_attention_from_kept_scores(n_rep, r_v, L, k, batch, bits):
     torch = torch_mod()
-    H_kv = 3
+    H_kv = CASES_H_KV
     w = workload(H_kv, n_rep, 64, r_v, L, k, batch)
     g = torch.Generator(device="cuda").manual_seed(L + r_v + bits)
     A_v = torch.randn((batch, L, r_v), generator=g, device="cuda").bfloat16()
@@ -69,7 +74,7 @@ def test_attention_from_kept_scores(n_rep, r_v, L, k, batch, bits):
 
 @pytest.mark.parametrize("bits", [0, 4])
 @pytest.mark.parametrize("what", ["sums", "weights"])
-@pytest.mark.parametrize("n_rep,r_v,L,k,batch", [(1, 64, 300, 96, 2), (4, 96, 300, 96, 2), (8, 128, 400, 200, 1), (7, 384, 700, 300, 1),
+@pytest.mark.parametrize("n_rep,r_v,L,k,batch", [(1, 64, 300, 96, 2), (3, 64, 300, 96, 2), (4, 96, 300, 96, 2), (8, 128, 400, 200, 1), (7, 384, 700, 300, 1),
                                                  (12, 512, 300, 96, 1), (16, 768, 700, 300, 1)])
 def test_sums_keep_single_precision(n_rep, r_v, L, k, batch, what, bits):
     """Outputs in which almost everything cancels, so that the rounding to bf16 at the end does not hide what came before it."""

@@ -6,6 +6,7 @@ import pytest
 
 from paper_2503_18893_amd import build as xbuild
 from test_gpu_gather_absorb import CASES
+import test_gpu_given_logits as given
 
 
 @pytest.fixture(scope="module")
@@ -77,3 +78,17 @@ def test_the_kernels_tests_reach_the_tiles_they_name(plan_of):
     shapes = [dict(H_kv=h, H_q=h * n, r_k=rk, r_v=rv, batch=b, k=k) for h, n, rk, rv, b, k, _, _ in CASES]
     for case, p in zip(CASES, plan_of(shapes)):
         assert (p["occ"], p["chunk"] // 128) == case[6:] and p["absorb"] == (case[6] > 0), (case, p)
+
+
+def test_absorbed_step_takes_the_faster_kernels(plan_of):
+    """Both sides of each line at which the row sums of the absorbed step change over to the general kernels, bf16 and 4-bit rows."""
+    line = [  # n_rep, r, batch, k, matrix cores for bf16, for 4 bits
+        (4, 512, 8, 4095, 1, 1), (4, 512, 8, 4096, 0, 1), (4, 512, 16, 4096, 0, 1), (4, 512, 16, 16384, 0, 0), (4, 128, 16, 4096, 1, 1),
+        (4, 768, 4, 1024, 1, 1), (4, 768, 4, 2048, 0, 0), (8, 768, 4, 2048, 1, 1), (1, 512, 1, 1023, 0, 0), (1, 512, 1, 1024, 1, 1),
+        (1, 512, 4, 4096, 0, 0), (1, 128, 16, 1024, 1, 1), (2, 256, 8, 4096, 0, 1), (1, 768, 1, 1024, 0, 0), (1, 768, 1, 2048, 1, 1),
+        (9, 512, 16, 16384, 1, 1), (16, 768, 32, 4096, 1, 1)]
+    shapes = [dict(H_q=8 * n, r_k=r, r_v=r, batch=b, k=k) for n, r, b, k, _, _ in line]
+    for case, p in zip(line, plan_of(shapes)):
+        assert (p["absorbed"], p["absorbed_q4"]) == case[4:], case
+    shapes = [dict(H_kv=given.CASES_H_KV, H_q=given.CASES_H_KV * n, r_k=64, r_v=r, L=L, k=k, batch=b) for n, r, L, k, b in given.CASES]
+    assert [(p["absorbed"], p["absorbed_q4"]) for p in plan_of(shapes)] == [(0, 0)] * 2 + [(1, 1)] * (len(shapes) - 2)
