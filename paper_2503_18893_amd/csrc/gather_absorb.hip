@@ -836,13 +836,18 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
     } while (0)
 #define XKV_AB_KC(NV, OC, CPS)                 \
     do {                                       \
-        if (by_place && qbits == 0)            \
-            XKV_AB(NV, OC, true, 0, CPS, 2);   \
-        else if (by_place && qbits == 4)       \
-            XKV_AB(NV, OC, true, 4, CPS, 2);   \
-        else if (by_place)                     \
-            XKV_AB(NV, OC, true, 3, CPS, 2);   \
-        else if (qbits == 0)                   \
+        if (by_place) {                        \
+            if constexpr (CPS > 1 && NV <= 4) {      \
+                if (qbits == 0)                      \
+                    XKV_AB(NV, OC, true, 0, CPS, 2); \
+                else if (qbits == 4)                 \
+                    XKV_AB(NV, OC, true, 4, CPS, 2); \
+                else                                 \
+                    XKV_AB(NV, OC, true, 3, CPS, 2); \
+            } else {                           \
+                return hipErrorInvalidValue;   \
+            }                                  \
+        } else if (qbits == 0)                 \
             XKV_AB(NV, OC, true, 0, CPS, 3);   \
         else                                   \
             XKV_AB(NV, OC, true, 4, CPS, 3);   \

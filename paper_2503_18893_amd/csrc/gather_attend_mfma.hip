@@ -682,7 +682,7 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
     const u32x4_t *bsrc = B_packed ? (const u32x4_t *)B_packed + (size_t)layer * s.H_kv * per_head : (const u32x4_t *)pa.pack;
     const size_t seq_stride = (B_packed ? (size_t)s.G : 1) * s.H_kv * per_head;
     dim3 grid((unsigned)((long long)p.sr_splits * s.H_kv * s.batch));
-    const bool keys = use_rope && p.rope_kept && logits;
+    const bool keys = gather_keeps_logits(p, rope_theta, qbits) && logits;
     const int hp = head_pitch_of(p.n_rep);
 #define XKV_GA_LAUNCH(WV, RP, QB, KY)                                                                              \
     do {                                                                                                           \

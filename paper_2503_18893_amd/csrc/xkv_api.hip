@@ -29,6 +29,27 @@ static xkv_status validate(const xkv_shape *s)
     return XKV_OK;
 }
 
+// Whether rotated rows are faster in two halves, logits and then the values' sums from them.  That is a launch and a merge more (4 us);
+// what it saves are the values' products, whose ranks the one-launch kernel pads to 256 and takes per row.  Its time goes by `len`,
+// the rows that a compute unit takes one after the other (tiles of 256 in rounds of 256 workgroups).  One launch / two halves, us, 4
+// query heads on each of 8 KV heads: 4 bits, ranks 512: len 512 60 / 60, 768 77 / 74, 1024 104 / 96, 1536 136 / 112; ranks 384 len 512
+// 61 / 58; ranks 256 41 / 43, 51 / 51, 69 / 66; in 3 bits 38 / 40, 48 / 49, 65 / 62.  Eight heads, ranks 512 62 / 65, 78 / 78, 106 / 102; 64 in
+// 3 bits len 1024 61 / 62, 1536 84 / 75.  bf16, ranks 512: len 1024 117 / 125, 2048 in one round 207 / 212, in two full ones 227 / 229, in two
+// of which the second is a quarter full 196 / 183; ranks 384 at 1024 110 / 108; 448 114 / 121, at 1536 139 / 123.  Not with six groups of
+// values' ranks, whose kernel has two groups in flight instead of four (ranks 768 71 / 85), nor with more than eight query heads, where
+// one workgroup has a compute unit to itself (16 heads, len 512 65 / 78, 1024 in 4 bits 114 / 130).
+static bool rope_kept_pays(const xkv_shape &s, const Plan &p, int qbits)
+{
+    if (!p.absorb || s.r_v > 512 || p.n_rep > 8 || (long long)p.rows * s.k < 131072) return false;
+    const long long groups = (long long)p.rows * p.sr_splits, rounds = (groups + 255) / 256, len = rounds * p.sr_chunk;
+    if (qbits == 0) {
+        const int used = (s.r_v - 1) % 256 + 1;  // of the last 256 ranks
+        return used <= 128 ? len >= 1024 : len >= 1536 && (used < 256 || 4 * groups <= 3 * 256 * rounds);
+    }
+    if (p.n_rep > 4) return len >= (s.r_v > 256 ? 1024 : 1536);
+    return len >= (s.r_v > 256 ? 512 : 1024);
+}
+
 xkv_status make_plan(const xkv_shape &s, Plan &p)
 {
     std::memset(&p, 0, sizeof p);
@@ -91,12 +112,9 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     off = align_up(off + b * (size_t)(2 * s.H_q + 64) * (s.r_k + 128) * sizeof(float), 256);  // fp32 P or bf16 hi/lo fragments
     p.off_score = off;
     off = align_up(off + b * s.H_kv * (size_t)s.L * sizeof(float), 256);
-    // Rotated rows: logits first, into the room of the projected queries and the pooled scores, which are done with by then, and the
-    // values' sums from the given logits.  That is a launch and a merge more (4 us), which the sums make up for from four tiles of
-    // 128 rows per compute unit on (8 x 8 x 4128 rows of ranks 512, us: 4-bit 109 -> 96, bf16 123 -> 114), and not with
-    // six groups of values' ranks, whose kernel has two groups in flight instead of four (ranks 768 71 -> 85).
-    p.rope_kept = p.absorb && s.r_v <= 512 && (long long)rows * s.k >= 131072 && s.k < (1 << 24) &&
-                  b * s.H_kv * (size_t)s.k * head_pitch_of(p.n_rep) * sizeof(float) <= off - p.off_p;
+    // Rotated rows: logits first, into the room of the projected queries and the pooled scores, which are done with by then
+    const bool room = p.absorb && s.k < (1 << 24) && b * s.H_kv * (size_t)s.k * head_pitch_of(p.n_rep) * sizeof(float) <= off - p.off_p;
+    for (int i = 0; i < 3; ++i) p.rope_kept[i] = room && rope_kept_pays(s, p, i == 0 ? 0 : i == 1 ? 4 : 3);
     p.off_idx = off;
     off = align_up(off + b * s.H_kv * (size_t)s.k * sizeof(int32_t), 256);
     p.off_hist = off;
@@ -195,7 +213,7 @@ xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer, const void *
     const bool mfma = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_v, pack_ws);
     hipError_t e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
                                         stream);
-    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, 0.0f), part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, 0.0f, 0), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -273,7 +291,7 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
     // the merge is one softmax over the selected rows and the tail
     if (!tail_first && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, gather_partials(p, want_pack, 0.0f), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
+        e = launch_combine(*shape, gather_partials(p, want_pack, 0.0f, 0), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -603,7 +621,7 @@ static xkv_status sr_decode_landmark_impl(const xkv_shape *shape, int32_t layer,
                                  part_ml, stream, counts, rope_theta, qbits, at<float>(workspace, pa.off_p));
     if (!tail_first && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
+        e = launch_combine(*shape, gather_partials(pa, mfma, rope_theta, qbits), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 
@@ -670,7 +688,7 @@ xkv_status xkv_gather_attend_q(const xkv_shape *shape, int32_t layer, const void
     float *part_o = at<float>(workspace, p.off_part_o), *part_ml = at<float>(workspace, p.off_part_ml);
     hipError_t e = launch_gather_attend(*shape, p, layer, Aq_k, Aq_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o,
                                         part_ml, stream, counts, rope_theta, bits, at<float>(workspace, p.off_p));
-    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, true, rope_theta, bits), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -694,7 +712,7 @@ xkv_status xkv_gather_attend_ex(const xkv_shape *shape, int32_t layer, const voi
     const bool mfma = gather_attend_uses_mfma(p, A_k, A_v, B_k, B_v, pack_ws);
     hipError_t e = launch_gather_attend(*shape, p, layer, A_k, A_v, B_k, B_v, q, idx, pack_ws, nullptr, false, part_o, part_ml,
                                         stream, counts, rope_theta, 0, at<float>(workspace, p.off_p));
-    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, rope_theta), part_o, part_ml, out, stream);
+    if (e == hipSuccess) e = launch_combine(*shape, gather_partials(p, mfma, rope_theta, 0), part_o, part_ml, out, stream);
     return hip_status(e);
 }
 
@@ -922,7 +940,7 @@ xkv_status xkv_sr_decode_q4(const xkv_shape *shape, int32_t layer, const void *A
                                  stream, nullptr, rope_theta, 4, at<float>(workspace, p.off_p));
     if (!tail.mfma && e == hipSuccess) e = tail.run(stream);
     if (e == hipSuccess)
-        e = launch_combine(*shape, gather_partials(p, true, rope_theta), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
+        e = launch_combine(*shape, gather_partials(p, true, rope_theta, 4), part_o, part_ml, out, stream, tail.parts, tail.o, tail.ml);
     return hip_status(e);
 }
 

@@ -98,7 +98,7 @@ struct Plan {
     bool ga_mfma;      // shape fits the matrix-core gather-attend kernel
     int ga_waves;      // ... with this many wavefronts (32 selected tokens each) per workgroup
     bool absorb;       // ... and the one that keeps B_l out of the main loop (rows that are not rotated)
-    bool rope_kept;    // rotated rows: logits first (room for them from off_p on), then that kernel on the values
+    bool rope_kept[3]; // rotated rows in bf16, 4 and 3 bits: logits first (room for them from off_p on), then that kernel on the values
     int ab_occ, ab_splits, ab_chunk;  // its workgroups per compute unit, splits per (sequence, KV head), tokens per split
     size_t ab_lds;     // its LDS per workgroup
     int ak_splits, ak_chunk;  // ... where the logits are given (KEPT): one workgroup per compute unit
@@ -231,7 +231,7 @@ hipError_t launch_gather_attend(const xkv_shape &s, const Plan &p, int layer, co
                                 const void *B_packed, bool packed, float *part_o, float *part_ml, hipStream_t st,
                                 const int32_t *counts = nullptr, float rope_theta = 0.0f, int qbits = 0,
                                 float *logits = nullptr);
-// logits: room for the rotated rows' logits, needed where p.rope_kept
+// logits: room for the rotated rows' logits, needed where gather_keeps_logits
 // qbits 4 or 3: A_k and A_v are rows of 4-bit / 3-bit codes (quant.hip); matrix-core shapes with ranks that are
 // multiples of 32 only (gather_attend_quant_ok).
 bool gather_attend_quant_ok(const xkv_shape &s, const Plan &p, const void *Aq_k, const void *Aq_v, const void *B_k,
@@ -246,11 +246,17 @@ PackArgs gather_attend_pack_args(const xkv_shape &s, int layer, const void *B_k,
 hipError_t launch_gather_prepare(const PackArgs &a, hipStream_t st);
 // Which of the two matrix-core kernels takes a call (rope_theta as below).
 inline bool gather_uses_absorb(const Plan &p, float rope_theta) { return p.absorb && !(rope_theta > 0.0f); }
+inline bool gather_keeps_logits(const Plan &p, float rope_theta, int qbits)
+{
+    return rope_theta > 0.0f && p.rope_kept[qbits == 0 ? 0 : qbits == 4 ? 1 : 2];
+}
 // Partials per query head that launch_gather_attend leaves for launch_combine: one per split, or (general kernel, mfma =
 // false) one per wavefront.
-inline int gather_partials(const Plan &p, bool mfma, float rope_theta)
+inline int gather_partials(const Plan &p, bool mfma, float rope_theta, int qbits)
 {
-    return !mfma ? p.sr_splits * 4 : gather_uses_absorb(p, rope_theta) ? p.ab_splits : p.rope_kept ? p.ak_splits : p.sr_splits;
+    return !mfma ? p.sr_splits * 4
+         : gather_uses_absorb(p, rope_theta) ? p.ab_splits
+         : gather_keeps_logits(p, rope_theta, qbits) ? p.ak_splits : p.sr_splits;
 }
 bool gather_absorb_shape_ok(const xkv_shape &s);
 // Whether the absorbed step of such a shape is faster there than in the general kernels of absorbed.hip (q4: 4-bit rows).

@@ -92,3 +92,20 @@ def test_absorbed_step_takes_the_faster_kernels(plan_of):
         assert (p["absorbed"], p["absorbed_q4"]) == case[4:], case
     shapes = [dict(H_kv=given.CASES_H_KV, H_q=given.CASES_H_KV * n, r_k=64, r_v=r, L=L, k=k, batch=b) for n, r, L, k, b in given.CASES]
     assert [(p["absorbed"], p["absorbed_q4"]) for p in plan_of(shapes)] == [(0, 0)] * 2 + [(1, 1)] * (len(shapes) - 2)
+
+
+def test_rotated_rows_in_two_halves_where_that_is_faster(plan_of):
+    """Both sides of the lines, the room that the logits need, and that the kernel's test reaches it in every case."""
+    line = [  # n_rep, r, batch, k, two halves in bf16, 4 bits, 3 bits
+        (4, 512, 4, 4096, 0, 1, 1), (4, 512, 6, 4096, 1, 1, 1), (4, 512, 16, 4096, 0, 1, 1), (4, 512, 3, 4096, 0, 0, 0), (4, 256, 5, 4096, 0, 0, 0),
+        (4, 256, 8, 4096, 0, 1, 1), (4, 384, 5, 4096, 0, 1, 1), (4, 384, 8, 4096, 1, 1, 1), (4, 448, 8, 4096, 0, 1, 1), (8, 512, 5, 4096, 0, 0, 0),
+        (8, 512, 8, 4096, 0, 1, 1), (8, 64, 8, 4096, 1, 0, 0), (8, 64, 10, 4096, 1, 1, 1), (9, 512, 16, 4096, 0, 0, 0), (4, 528, 16, 4096, 0, 0, 0)]
+    shapes = [dict(H_q=8 * n, r_k=r, r_v=r, batch=b, k=k, L=16 * k) for n, r, b, k, _, _, _ in line]
+    for case, p in zip(line, plan_of(shapes)):
+        assert (p["kept_0"], p["kept_4"], p["kept_3"]) == case[4:], case
+    for (bits, *case), p in zip(given.ROTATED, plan_of([given.rotated_shape(*case) for _, *case in given.ROTATED])):
+        assert p[f"kept_{bits}"] == 1, (bits, case)
+    # 4 logits a row: 16 k <= 4 L + 4 (2 H_q + 64) (r_k + 128) / H_kv, all in bytes
+    room = (2 * 32 + 64) * (64 + 128) // 8
+    for L, kept in ((4 * 12288 - room, 1), (4 * 12288 - room - 64, 0)):
+        assert plan_of([dict(r_k=64, r_v=64, L=L, k=12288 + 0, batch=8)])[0]["kept_4"] == kept
