@@ -360,7 +360,7 @@ template <int NRP> __device__ __forceinline__ void store_head_row(float *dst, co
     }
 }
 
-// The same for ranks above 256 (up to 1024 tiles: a wavefront has one tile, of several steps).  What counts there is how soon
+// The same for ranks above 256 where a wavefront has one tile, of several steps, and a compute unit one workgroup.  What counts there is how soon
 // the rows are requested: the projected queries go straight to LDS, the first kScoreRing steps of rows (8 pieces of 16 B each) are
 // requested behind them before anything is waited for, and a step's registers are refilled as soon as it is multiplied.  (With the
 // projection, us: 9000 tokens of rank 512 12.0 -> 11.1, 32768 14.9 -> 14.3, 4096 of rank 768 14.0 -> 13.1.  With one or two steps, or several tiles per
@@ -1206,11 +1206,26 @@ static hipError_t launch_score_generic(const xkv_shape &s, const Plan &p, int la
     return hipGetLastError();
 }
 
+// Tiles per workgroup of the other kernels: about two workgroups of four wavefronts per compute unit in a single round, each streaming
+// one contiguous range of a sequence (staging P costs a fixed 2 KiB per rank-16 fragment, so fewer, longer workgroups win).
+static int score_tiles_per_wg(int pairs, int n_tiles)
+{
+    const int wgs_per_pair = pairs >= 512 ? 1 : 512 / pairs;
+    const int tiles = (n_tiles + wgs_per_pair - 1) / wgs_per_pair;
+    return tiles < 4 ? 4 : (tiles + 3) / 4 * 4;
+}
+
 // Whether a shape goes to the long-stream kernel, with how many 32-token tiles per workgroup, and whether its
 // LDS also has room for the top-digit histograms.  One 8-wavefront workgroup per compute unit in a single
-// round.  It pays from 1025 tiles on, where the others' wavefronts need a second one (us with the projection, this kernel against the other: ranks 512,
-// 1024 tiles 15.2 / 14.7, 1256 tiles 16.6 / 20.3, 2256 26.0 / 31.9, 3750 28.6 / 35.7; ranks 256 12.4 / 10.7, 13.0 / 13.8, 3750
-// tiles 19.2 / 21.6), with a single group of 128 ranks only where every wavefront has eight tiles of its own (5000 tiles 17.7 / 17.6).
+// round, a whole round of its wavefronts' tiles at a time (spread over all compute units instead, 3073 tiles of ranks 512 take 9 %
+// longer, 16385 of ranks 128 7 %: a workgroup is as long as its longest wavefront).
+// It pays in any case where every wavefront gets eight tiles of its own.  Below that it pays where the others' workgroups leave the
+// compute units with one or two each (us with the projection, rows in the caches / from memory, the others against this kernel:
+// 8 KV heads of 4, ranks 512: 1100 tiles 16.9 / 14.7 and 20.2 / 15.5, 2304 25.3 / 21.0 and 30.2 / 22.1, 4097 33.4 / 30.0 and 41.7 / 30.7;
+// ranks 192: 1100 12.0 / 11.7 and 14.4 / 12.5; ranks 320: 10000 42.8 / 46.4 and 55.7 / 47.5), and not where they get one each and a few over (1025 tiles, ranks 256 13.2 / 14.8), with
+// ranks that fill less than half of their last group of 128 (144: 1537 tiles 10.1 / 11.6 and 12.7 / 13.4) or have but one, with
+// sixteen query heads (ranks 256, 641 tiles of two pairs 15.8 / 17.7), or for many (sequence, heads) pairs of few tiles (350 of three,
+// ranks 256 50.7 / 56.7; 64 of 20 20.3 / 21.6, but ranks 512 32.4 / 31.0).
 bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, int *waves)
 {
     *tiles_per_wg = 0;
@@ -1223,7 +1238,10 @@ bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, i
     const int F8 = (s.r_k / 16 + 7) / 8 * 8;
     const int n_tiles = (s.L + 31) / 32;
     const int pairs = s.batch * mfma_blocks(s.H_kv, n_rep);
-    if ((long long)pairs * n_tiles < (s.r_k > 128 ? 1025 : 256 * kScoreWaves * 8)) return false;
+    if ((long long)pairs * n_tiles < 256 * kScoreWaves * 8) {
+        const int per = score_tiles_per_wg(pairs, n_tiles), others = pairs * ((n_tiles + per - 1) / per);
+        if (pairs > (s.r_k >= 512 ? 256 : 32) || n_rep > 8 || s.r_k < 192 || others <= 264) return false;
+    }
     const size_t lds_max = 160 * 1024 - 512, lds_p = (size_t)2 * F8 * 64 * 16;
     const size_t lds_hist = (size_t)2 * mfma_gph(n_rep) * kTopkBins * 4;
     int wv = kScoreWaves;
@@ -1231,7 +1249,7 @@ bool score_stream_plan(const xkv_shape &s, int *tiles_per_wg, bool *hist_fits, i
     if (lds_p + (size_t)wv * 512 * 16 > lds_max) return false;
     const int wgs = pairs >= 256 ? 1 : 256 / pairs;
     const int tpw = (n_tiles + wgs - 1) / wgs;
-    *tiles_per_wg = (tpw + kScoreWaves - 1) / kScoreWaves * kScoreWaves;
+    *tiles_per_wg = (tpw + wv - 1) / wv * wv;
     *hist_fits = lds_p + (size_t)wv * 512 * 16 + lds_hist <= lds_max;
     *waves = wv;
     return true;
@@ -1282,16 +1300,12 @@ static hipError_t launch_score_mfma_t(const xkv_shape &s, const Plan &p, const b
         if (hist_done) *hist_done = with_hist;
         return hipSuccess;
     }
-    // about two workgroups per compute unit in a single round, each streaming one contiguous range of a
-    // sequence (staging P costs a fixed 2 KiB per rank-16 fragment, so fewer, longer workgroups win)
-    const int pairs = s.batch * nblk;
-    const int wgs_per_pair = pairs >= 512 ? 1 : 512 / pairs;
-    int tiles_per_wg = (n_tiles + wgs_per_pair - 1) / wgs_per_pair;
-    tiles_per_wg = tiles_per_wg < 4 ? 4 : tiles_per_wg;
-    tiles_per_wg = (tiles_per_wg + 3) / 4 * 4;
+    const int tiles_per_wg = score_tiles_per_wg(s.batch * nblk, n_tiles);
     static DynamicLdsOnce attr_pooled, attr_heads, attr_ring, attr_ring_heads;
-    if (F8 > 16 && tiles_per_wg == 4) {  // a tile per wavefront, of several steps
-        const dim3 rgrid((n_tiles + 3) / 4, nblk, s.batch);
+    // a tile per wavefront, of several steps; where a second workgroup fits the compute units and some get one, its kernel has the
+    // loads in flight already (1025 tiles, ranks 512 13.0 us against 14.3, 640 15.3 / 18.3; 768 22.6 / 20.2: one per compute unit)
+    const dim3 rgrid((n_tiles + 3) / 4, nblk, s.batch);
+    if (F8 > 16 && tiles_per_wg == 4 && (2 * lds > 160 * 1024 || (long long)rgrid.x * nblk * s.batch <= 256)) {
         auto launch = [&](auto kernel, DynamicLdsOnce &attr) {
             if (hipError_t e0 = attr.ensure((const void *)kernel, 160 * 1024 - 512); e0 != hipSuccess) return e0;
             profile_begin(0, st);

@@ -67,8 +67,10 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     bool hist_fits = false;
     p.score_stream = score_stream_plan(s, &p.score_tpw, &hist_fits, &p.score_waves);
     p.topk_row = topk_row_shape_ok(s);  // then the selection needs no histogram from the score kernel
-    p.score_hist = !p.topk_row && p.score_stream && hist_fits && ceil_div(s.L, 32 * p.score_tpw) <= 128;
+    const int hist_tpw = (p.score_tpw + 7) / 8 * 8;  // (chunks are whole rounds of the selection's 256 threads)
+    p.score_hist = !p.topk_row && p.score_stream && hist_fits && ceil_div(s.L, 32 * hist_tpw) <= 128;
     if (p.score_hist) {
+        p.score_tpw = hist_tpw;
         p.topk_chunk = 32 * p.score_tpw;
         p.topk_chunks = ceil_div(s.L, p.topk_chunk);
     }

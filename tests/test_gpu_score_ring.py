@@ -1,5 +1,6 @@
 """The score kernel for ranks above 256 over up to 1024 token tiles: ragged last tiles and wavefronts without one, every number of
-rank steps, every number of heads per KV head, and both sides of the line to the long-stream kernel."""
+rank steps, every number of heads per KV head, and both sides of the line to the long-stream kernel, there with four and eight
+wavefronts."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("r_k,H_kv,n_rep,L,batch", [
     (272, 2, 1, 5, 1), (272, 3, 16, 33, 1), (288, 5, 2, 129, 2), (512, 8, 4, 1025, 3), (512, 2, 3, 4096, 1), (640, 4, 8, 97, 1), (768, 4, 5, 700, 1),
-    (768, 3, 6, 31, 1), (384, 2, 7, 1000, 1), (512, 2, 4, 32768, 1), (512, 2, 4, 32769, 1), (144, 2, 4, 33000, 1)])
+    (768, 3, 6, 31, 1), (384, 2, 7, 1000, 1), (512, 2, 4, 32768, 1), (512, 2, 4, 32769, 1), (144, 2, 4, 33000, 1),
+    (192, 8, 4, 36000, 1), (512, 2, 4, 41005, 1), (768, 3, 4, 33900, 1)])
 def test_score_ring(r_k, H_kv, n_rep, L, batch):
     import torch
     if not torch.cuda.is_available():

@@ -109,3 +109,22 @@ def test_rotated_rows_in_two_halves_where_that_is_faster(plan_of):
     room = (2 * 32 + 64) * (64 + 128) // 8
     for L, kept in ((4 * 12288 - room, 1), (4 * 12288 - room - 64, 0)):
         assert plan_of([dict(r_k=64, r_v=64, L=L, k=12288 + 0, batch=8)])[0]["kept_4"] == kept
+
+
+def test_which_scores_are_long_streams(plan_of):
+    """Which scores go to the long-stream kernel, a whole round of its wavefronts' tiles at a time; chunks of the selection's histograms
+    are multiples of 256."""
+    line = [  # tiles, r, batch, n_rep, taken
+        (1056, 512, 1, 4, 0), (1057, 512, 1, 4, 1), (1057, 176, 1, 4, 0), (1057, 192, 1, 4, 1), (2112, 256, 1, 4, 0), (2113, 256, 1, 4, 1),
+        (3, 512, 350, 4, 0), (20, 256, 64, 4, 0), (20, 512, 64, 4, 1), (1057, 512, 1, 16, 0), (3000, 512, 6, 4, 1), (16384, 64, 1, 4, 1),
+        (16383, 64, 1, 4, 0), (141, 768, 16, 4, 1), (60, 128, 300, 4, 1)]
+    shapes = [dict(H_q=8 * n, r_k=r, r_v=64, batch=b, L=32 * t, k=t) for t, r, b, n, _ in line]
+    for case, p in zip(line, plan_of(shapes)):
+        pairs = case[2] * (4 if case[3] == 16 else 1)
+        assert p["stream"] == case[4], case
+        if p["stream"] and not p["score_hist"]:
+            waves = 8 if case[1] <= 640 else 4
+            assert p["score_tpw"] == (-(-case[0] // max(256 // pairs, 1)) + waves - 1) // waves * waves, case
+    hist = plan_of([dict(L=L, k=8192, batch=b) for L in (131072, 100_001, 262_145) for b in (4, 5, 16)])
+    assert sum(p["score_hist"] for p in hist) > 3
+    assert all(p["topk_chunk"] % 256 == 0 for p in hist) and all(p["topk_chunk"] == 32 * p["score_tpw"] for p in hist if p["score_hist"])
