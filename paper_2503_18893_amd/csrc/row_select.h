@@ -31,7 +31,7 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x)
 }
 struct RowShared {
     uint32_t wave[3][kRowWaves], pick[2][4];
-    float lo[kRowWaves], hi[kRowWaves];
+    uint32_t lo[kRowWaves], hi[kRowWaves];
 };
 // Sum over the threads above this one of `mine`; *all: over all threads.  part: kRowWaves words that nobody reads any more.
 // One barrier.

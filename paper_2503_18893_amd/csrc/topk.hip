@@ -477,27 +477,31 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(const float *__re
 
 // ------------------------------------------------------------------------------------------
 // Long rows (kRowFloor to kRowMost scores, budgets that leave the lists below room): one launch that starts from a guess.  The
-// histogram of kRowSamples scores, 16 in a row at 256 places, over equal slices of their range gives a value that the k largest and
+// histogram of kRowSamples scores, 16 in a row at 256 places, over slices of their range gives a value that the k largest and
 // a margin reach.  Every wavefront compacts those of its scores that do into a list of its own in LDS, and the exact selection works
 // on these lists, ten scores a lane at most, on 11-bit digits of the keys' distance from the guess.  The selected ids set bits
-// of a bitmap, which is read off in order.  The guess only decides how much is left to do: where fewer than k scores
-// or more than the lists hold reach it (many equal scores, say), radix passes over the whole row follow.
+// of a bitmap, which is read off in order.  Where many scores are equal to the guess, the lists take those above it and a second bitmap
+// the equal ones, of which the lowest ids fill up the budget.  The guess only decides how much is left to do: where fewer than k
+// scores or more than the lists hold reach it (samples that miss what the row has), radix passes over the whole row follow.
 // The time is the instructions per score of four wavefronts per SIMD (a microsecond for two and a half of them at 65536 scores; a
 // workgroup reads such a row in three) and, in all that runs once, the fetching of the code: loops are kept rolled.  Scores
 // 1024 apart belong to one thread, so that neighbours, which are alike, spread over all lists.
-// Against the row in registers (below 20480 scores the same), 8 rows, k a sixteenth: 32768 scores 14.5 -> 12.7 us, 40001 22.9 ->
-// 15.0, 65536 22.4 -> 18.3; against the five launches 32 rows of 131072 38.5 -> 21.8, 128 rows 110 -> 22.  8 rows of 32768 equal
-// scores, the guess in vain: 42 -> 55.
+// Against the row in registers, 8 rows, k a sixteenth: 20480 scores 14.5 -> 10.7 us (the lists' length decides: k 5000 of 28000 15.0 -> 16.1,
+// hence half the lists at most up to 32768 scores), 32768 14.5 -> 12.4, 40001 22.9 -> 14.1, 65536 22.4 -> 18.1; against the five
+// launches 32 rows of 131072, k 1024, 38.9 -> 20.9, 128 rows 109 -> 22.  8 rows of 32768 equal scores 42 -> 11.5 (of 131072, where the five
+// launches use more compute units, 27 -> 29), five different values 19.8 -> 13.1; ninth powers of normal numbers, whose range has to be sliced
+// three times, 13.6 -> 18.6, 65536 of them 21.3 -> 23.9; radix passes 67 and 91.
 // ------------------------------------------------------------------------------------------
 constexpr int kRowFloor = 20480, kRowMost = 131072, kRowSamples = 4096;
 constexpr int kRowExpect = 8192;  // scores that may be expected to reach the guess
 constexpr float kRowSigmas = 4.5f;  // margin in standard deviations of the samples' rank
 
-template <int CTRL> __device__ __forceinline__ float max_step(float x)
+template <int CTRL> __device__ __forceinline__ uint32_t max_step(uint32_t x)
 {
-    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(x), __float_as_uint(x), CTRL, 0xF, 0xF, false)));
+    const uint32_t y = __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+    return x > y ? x : y;
 }
-__device__ __forceinline__ float wave_max_dpp(float x)  // the same in every lane
+__device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)  // the same in every lane
 {
     x = max_step<0x111>(x);
     x = max_step<0x112>(x);
@@ -505,59 +509,92 @@ __device__ __forceinline__ float wave_max_dpp(float x)  // the same in every lan
     x = max_step<0x118>(x);
     x = max_step<0x142>(x);
     x = max_step<0x143>(x);
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
+__device__ __forceinline__ float float_of_key(uint32_t key) { return __uint_as_float((int)key < 0 ? key ^ 0x80000000u : ~key); }
 
-// LDS of the guess: lists, bins, bitmap
+// LDS of the guess: bitmap, bins, lists, bitmap of the scores that equal the guess
 constexpr int kRowListWords = 2 * kRowWaves * kRowList, kRowMapWords = kRowMost / 32;
-constexpr int kRowWords = kRowListWords + kRowBins + kRowMapWords;
+constexpr int kRowWords = kRowListWords + kRowBins + kRowMapWords;  // ... without the last
 
-// Bounds (as floats' bits) from the samples: about r_lo of them reach lo_bits, about r_hi hi_bits.  bins: zero before and after.
-__device__ __forceinline__ void guess_bounds(const float (&x)[4], uint32_t r_lo, uint32_t r_hi, uint32_t *bins, RowShared &sh,
+// Bounds (as floats' bits) from the samples: at least r_lo and, where that can be had, at most r_max of them reach lo_bits; about r_hi
+// hi_bits.  Slices of the samples' range; where the one that holds the r_lo-th largest has too many (few large scores
+// stretch the range) or many that may be equal, slices of that one, and so on.  True: the samples in it are all equal, and lo_bits is
+// what they are.  bins: zero before and after.
+constexpr int kRowSlicings = 5;
+constexpr uint32_t kRowEqual = 64;  // samples in a slice that call for a closer look (half a dozen are usual; equal scores add up in one counter)
+__device__ __forceinline__ bool guess_bounds(const float (&x)[4], uint32_t r_lo, uint32_t r_hi, uint32_t r_max, uint32_t *bins, RowShared &sh,
                                              uint32_t &lo_bits, uint32_t &hi_bits)
 {
     static_assert(kRowSamples == 4 * kRowThreads && kRowBins == 2 * kRowThreads, "four samples and two bins per thread");
     const int w = wave_id(), tid = threadIdx.x;
-    // (scores that are not finite count as the nearest end of the others' range; NaN as the lower end)
-    float mn = INFINITY, mx = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (fabsf(x[u]) < INFINITY) {
-            mn = fminf(mn, x[u]);
-            mx = fmaxf(mx, x[u]);
-        }
-    mn = -wave_max_dpp(-mn);
-    mx = wave_max_dpp(mx);
-    if (lane_id() == 0) {
-        sh.lo[w] = mn;
-        sh.hi[w] = mx;
-    }
+    uint32_t in = 15u, above_all = 0;  // samples of this thread in the slice at hand, of all threads above it
     if (tid < 2) sh.pick[tid][0] = tid == 0 ? 0u : kRowBins - 1;
-    __syncthreads();
+    for (int level = 0;; ++level) {
+        // (scores that are not finite count as the nearest end of the others' range; NaN as the lower end)
+        uint32_t kmn = 0, kmx = 0;  // keys, the lower one turned over: zero where there is none
 #pragma unroll
-    for (int ww = 0; ww < kRowWaves; ++ww) {
-        mn = fminf(mn, sh.lo[ww]);
-        mx = fmaxf(mx, sh.hi[ww]);
+        for (int u = 0; u < 4; ++u)
+            if ((in >> u & 1u) && fabsf(x[u]) < INFINITY) {
+                const uint32_t key = order_key(x[u]);
+                kmn = kmn > ~key ? kmn : ~key;
+                kmx = kmx > key ? kmx : key;
+            }
+        kmn = wave_max_dpp(kmn);
+        kmx = wave_max_dpp(kmx);
+        if (lane_id() == 0) {
+            sh.lo[w] = kmn;
+            sh.hi[w] = kmx;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ww = 0; ww < kRowWaves; ++ww) {
+            kmn = kmn > sh.lo[ww] ? kmn : sh.lo[ww];
+            kmx = kmx > sh.hi[ww] ? kmx : sh.hi[ww];
+        }
+        kmn = (uint32_t)__builtin_amdgcn_readfirstlane((int)~kmn);
+        kmx = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmx);
+        const float mn = float_of_key(kmn), mx = float_of_key(kmx);
+        if (kmn == kmx) {
+            lo_bits = __float_as_uint(mn);
+            if (level == 0) hi_bits = lo_bits;
+            return true;
+        }
+        const float range = mx - mn, scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
+        uint32_t bin[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            bin[u] = range == 0.0f ? (__float_as_uint(x[u]) == 0u ? 1u : 0u)  // (zeros of both signs)
+                                   : (uint32_t)fminf(fmaxf((x[u] - mn) * scale, 0.0f), (float)(kRowBins - 1));
+            if (in >> u & 1u) atomicAdd(&bins[bin[u]], 1u);
+        }
+        __syncthreads();
+        const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
+        bins[2 * tid] = 0;
+        bins[2 * tid + 1] = 0;
+        const uint32_t above = sum_above(c0 + c1, sh.wave[level & 1]);
+        auto pick = [&](int which, uint32_t r) __attribute__((always_inline)) {
+            if (above < r && r <= above + c1 + c0) {
+                const bool odd = r <= above + c1;
+                sh.pick[which][0] = 2 * tid + (odd ? 1 : 0);
+                sh.pick[which][1] = above + (odd ? 0u : c1);
+                sh.pick[which][2] = odd ? c1 : c0;
+            }
+        };
+        const bool hi_in = level == 0 || r_hi > above_all;  // the r_hi-th largest is in the slice, too
+        pick(0, r_lo - above_all);
+        if (hi_in) pick(1, r_hi - above_all);
+        __syncthreads();
+        const uint32_t b_lo = sh.pick[0][0], in_bin = sh.pick[0][2];
+        const float width = range * (1.0f / kRowBins);
+        // (a thousandth of a slice lower: an edge rounded up, by 2^-12 at most, would leave out scores that the slice has)
+        lo_bits = __float_as_uint(fmaf((float)b_lo - 0.001f, width, mn));
+        if (hi_in) hi_bits = __float_as_uint(fmaf((float)sh.pick[1][0] + 1.0f, width, mn));
+        above_all += sh.pick[0][1];
+        if ((above_all + in_bin <= r_max && in_bin <= kRowEqual) || level == kRowSlicings - 1) return false;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) in &= ~((bin[u] == b_lo ? 0u : 1u) << u);
     }
-    const float range = mx - mn, scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) atomicAdd(&bins[(uint32_t)fminf(fmaxf((x[u] - mn) * scale, 0.0f), (float)(kRowBins - 1))], 1u);
-    __syncthreads();
-    const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
-    bins[2 * tid] = 0;
-    bins[2 * tid + 1] = 0;
-    const uint32_t above = sum_above(c0 + c1, sh.wave[0]);
-    auto pick = [&](int which, uint32_t r) __attribute__((always_inline)) {
-        if (above < r && r <= above + c1 + c0) sh.pick[which][0] = 2 * tid + (r <= above + c1 ? 1 : 0);
-    };
-    pick(0, r_lo);
-    pick(1, r_hi);
-    __syncthreads();
-    const uint32_t b_lo = sh.pick[0][0], b_hi = sh.pick[1][0];
-    const float width = range * (1.0f / kRowBins);
-    // (a hundredth of a slice lower: a rounded edge would leave out scores that the slice has)
-    lo_bits = __float_as_uint(scale == 0.0f || b_lo == 0 ? -INFINITY : fmaf((float)b_lo - 0.01f, width, mn));
-    hi_bits = __float_as_uint(fmaf((float)b_hi + 1.0f, width, mn));
 }
 
 // Calls f(bits, id, real) for every score of the row in groups of 8 x 1024, thread tid taking scores tid, tid + 1024, ..; the next two
@@ -660,11 +697,11 @@ __device__ __forceinline__ void select_by_radix(const float *__restrict__ Srow, 
     __syncthreads();
 }
 
-// r_lo, r_hi: ranks among the samples, see guess_bounds.  expand as above.
+// r_lo, r_hi, r_max: ranks among the samples, see guess_bounds.  expand as above.
 __global__ __launch_bounds__(kRowThreads) void topk_long_kernel(const float *__restrict__ S, int32_t *__restrict__ idx_out, int L, int k,
-                                                               uint32_t r_lo, uint32_t r_hi, ExpandArgs expand)
+                                                               uint32_t r_lo, uint32_t r_hi, uint32_t r_max, ExpandArgs expand)
 {
-    // bitmap, bins, lists (counters of the radix passes; at the end, with `expand`, the ids and what their union needs)
+    // bitmap, bins, lists (counters of the radix passes; at the end, with `expand`, the ids and what their union needs), equals
     extern __shared__ __attribute__((aligned(16))) uint32_t smem[];
     __shared__ RowShared sh;
     const int row = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -680,17 +717,19 @@ __global__ __launch_bounds__(kRowThreads) void topk_long_kernel(const float *__r
         bins[2 * tid] = 0;
         bins[2 * tid + 1] = 0;
         for (int i = tid; i < words; i += kRowThreads) map[i] = 0;
+        uint32_t *eq = lists + kRowListWords;
+        if (tid < 2) eq[words - 2 + tid] = 0;  // (all others are written)
         uint32_t lo_bits, hi_bits;
-        guess_bounds(sample, r_lo, r_hi, bins, sh, lo_bits, hi_bits);
+        const bool equal = guess_bounds(sample, r_lo, r_hi, r_max, bins, sh, lo_bits, hi_bits);  // (the same for all threads)
         lo_bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo_bits);
         // Scores that reach the bound.  Their bits as signed numbers are in order above zero; below a negative bound lie exactly
         // the larger unsigned numbers: turned over, they are in the same order.
         const uint32_t flip = (int)lo_bits < 0 ? 0x7FFFFFFFu : 0u;
         const int bound = (int)(lo_bits ^ flip);
         uint32_t *list = lists + w * 2 * kRowList, count = 0;  // scores, then ids: one store of two words; counted on where it is full
-        for_scores(Srow, L, [&](uint32_t bits, int t, auto real) __attribute__((always_inline)) {
-            const bool take = real && (int)(bits ^ flip) >= bound;
+        auto compact = [&](bool take, uint32_t bits, int t) __attribute__((always_inline)) {
             const uint64_t m = __ballot(take);
+            if (equal && m == 0) return;  // (few are taken then)
             const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, count));
             const uint32_t at = pos < kRowList ? pos : kRowList - 1;  // (a list that overflows is not used)
             if (take) {
@@ -698,8 +737,42 @@ __global__ __launch_bounds__(kRowThreads) void topk_long_kernel(const float *__r
                 list[at + kRowList] = (uint32_t)t;
             }
             count += (uint32_t)__popcll(m);
-        });
-        done = select_from_lists(lists, count, k, order_key(__uint_as_float(lo_bits)), order_key(__uint_as_float(hi_bits)), bins, map, words, sh);
+        };
+        const uint32_t lo_key = order_key(__uint_as_float(lo_bits)), hi_key = order_key(__uint_as_float(hi_bits));
+        if (!equal) {
+            for_scores(Srow, L, [&](uint32_t bits, int t, auto real) __attribute__((always_inline)) {
+                compact(real && (int)(bits ^ flip) >= bound, bits, t);
+            });
+            done = select_from_lists(lists, count, k, lo_key, hi_key, bins, map, words, sh);
+        } else {
+            // many scores are equal to the bound: those go to a bitmap, the lists take what is above
+            for_scores(Srow, L, [&](uint32_t bits, int t, auto real) __attribute__((always_inline)) {
+                compact(real && (int)(bits ^ flip) > bound, bits, t);
+                const uint64_t e = __ballot(real && bits == lo_bits);
+                if (lane < 2 && real) eq[(t >> 5) + lane] = (uint32_t)(e >> (32 * lane));  // (64 neighbours per wavefront)
+            });
+            if (lane == 0) sh.wave[2][w] = count;
+            __syncthreads();
+            uint32_t n = 0, most = 0;
+#pragma unroll
+            for (int ww = 0; ww < kRowWaves; ++ww) {
+                n += sh.wave[2][ww];
+                most = sh.wave[2][ww] > most ? sh.wave[2][ww] : most;
+            }
+            if (most > kRowList) {
+                done = false;
+            } else if (n >= (uint32_t)k) {
+                done = select_from_lists(lists, count, k, lo_key, hi_key, bins, map, words, sh);
+            } else {  // all of those, and the lowest ids of the equal ones
+                for (uint32_t i = lane; i < count; i += 64) atomicOr(&map[list[kRowList + i] >> 5], 1u << (list[kRowList + i] & 31));
+                __syncthreads();
+                lowest_bits(eq, map, words, (uint32_t)k - n, sh);
+#pragma unroll
+                for (int ww = 0; ww < kRowWaves; ++ww) n += sh.wave[0][ww];
+                done = n >= (uint32_t)k;
+                __syncthreads();
+            }
+        }
     }
     if (!done) select_by_radix(Srow, L, k, lists, map, words, sh);
     if (expand.rows) {
@@ -713,21 +786,22 @@ __global__ __launch_bounds__(kRowThreads) void topk_long_kernel(const float *__r
 
 // Ranks among the samples for a row's guess (0: none).  Margin: kRowSigmas standard deviations of the number of samples that the k
 // largest scores have, and an eighth of k for scores that come in clusters.
-static uint32_t row_guess(int L, int k, uint32_t *r_hi)
+static uint32_t row_guess(int L, int k, uint32_t *r_hi, uint32_t *r_max)
 {
-    *r_hi = 0;
+    *r_hi = *r_max = 0;
     if (L < kRowFloor || L > kRowMost) return 0;
     const double share = (double)k / L, mean = share * kRowSamples, dev = kRowSigmas * std::sqrt(mean * (1.0 - share)) + mean / 8 + 4.0;
     const double reach = (mean + 2 * dev) * L / kRowSamples;
-    if ((reach < L ? reach : L) > kRowExpect) return 0;
+    if ((reach < L ? reach : L) > (L <= kRowThreads * 32 ? kRowExpect / 2 : kRowExpect)) return 0;
+    *r_max = (uint32_t)((double)kRowExpect * kRowSamples / L);
     *r_hi = mean > dev ? (uint32_t)(mean - dev) : 0u;
     return (uint32_t)(mean + dev) + 1u;
 }
 
 bool topk_row_shape_ok(const xkv_shape &s)
 {
-    uint32_t r_hi;
-    return s.L <= kRowThreads * 64 || row_guess(s.L, s.k, &r_hi) > 0;
+    uint32_t r_hi, r_max;
+    return s.L <= kRowThreads * 64 || row_guess(s.L, s.k, &r_hi, &r_max) > 0;
 }
 
 // Whether the rows of the chunks fit `most` words of LDS behind `before`; then *ex is set and *words is raised to what they need.
@@ -762,15 +836,15 @@ static hipError_t launch_topk_row_t(const xkv_shape &s, const Plan &p, const flo
 }
 
 static hipError_t launch_topk_long(const xkv_shape &s, const Plan &p, const float *S, int32_t *idx, uint32_t r_lo, uint32_t r_hi,
-                                   const ExpandArgs *expand, bool *expanded, hipStream_t st)
+                                   uint32_t r_max, const ExpandArgs *expand, bool *expanded, hipStream_t st)
 {
     static DynamicLdsOnce attr;
-    const hipError_t e = attr.ensure((const void *)topk_long_kernel, (size_t)kRowWords * 4);
+    size_t words = kRowWords + kRowMapWords;
+    const hipError_t e = attr.ensure((const void *)topk_long_kernel, words * 4);
     if (e != hipSuccess) return e;
-    size_t words = kRowWords;
     ExpandArgs ex{};
     with_expansion(s, expand, expanded, kRowMapWords, kRowWords, &ex, &words);
-    hipLaunchKernelGGL(topk_long_kernel, dim3(p.rows), dim3(kRowThreads), 4 * words, st, S, idx, s.L, s.k, r_lo, r_hi, ex);
+    hipLaunchKernelGGL(topk_long_kernel, dim3(p.rows), dim3(kRowThreads), 4 * words, st, S, idx, s.L, s.k, r_lo, r_hi, r_max, ex);
     return hipGetLastError();
 }
 
@@ -786,9 +860,9 @@ hipError_t launch_topk(const xkv_shape &s, const Plan &p, const float *S, int32_
 {
     if (expanded) *expanded = false;
     if (p.topk_row) {
-        uint32_t r_hi;
-        const uint32_t r_lo = row_guess(s.L, s.k, &r_hi);
-        if (r_lo > 0) return launch_topk_long(s, p, S, idx, r_lo, r_hi, expand, expanded, st);
+        uint32_t r_hi, r_max;
+        const uint32_t r_lo = row_guess(s.L, s.k, &r_hi, &r_max);
+        if (r_lo > 0) return launch_topk_long(s, p, S, idx, r_lo, r_hi, r_max, expand, expanded, st);
         const int per_thread = (s.L + kRowThreads - 1) / kRowThreads;
         if (per_thread <= 8) return launch_topk_row_t<8>(s, p, S, idx, expand, expanded, st);
         if (per_thread <= 16) return launch_topk_row_t<16>(s, p, S, idx, expand, expanded, st);

@@ -1,4 +1,4 @@
-"""The selection that starts from a guess out of samples: every length at which its way changes, values for which the guess
+"""The selection that starts from a guess out of samples: every length at which its way changes, values for which the first guess
 does not help (few distinct ones, all equal, outliers that are not finite) and scores whose place is not random."""
 import numpy as np
 import pytest
@@ -19,6 +19,12 @@ VALUES = {
     "rising": lambda g, L: np.linspace(-3.0, 5.0, L),
     "cluster": lambda g, L: g.standard_normal(L) + 9.0 * (np.abs(np.arange(L) - 0.7 * L) < 0.04 * L),
     "periodic": lambda g, L: np.cos(2 * np.pi * np.arange(L) * 2048 / L) + 1e-3 * g.standard_normal(L),
+    "levels": lambda g, L: g.integers(0, 64, L).astype(np.float64),
+    "one_large": lambda g, L: np.where(np.arange(L) == L // 3, 1e30, g.standard_normal(L)),
+    "zeros_of_both_signs": lambda g, L: np.where(g.random(L) < 0.5, 0.0, -0.0),
+    "equal_but_a_few": lambda g, L: np.where(g.random(L) < 0.002, g.standard_normal(L), 0.25),
+    "equal_negative": lambda g, L: np.minimum(-1.0, g.standard_normal(L)),
+    "all_minus_inf": lambda g, L: np.full(L, -np.inf),
     "not_finite": lambda g, L: np.where(g.random(L) < 0.3, -np.inf, np.where(g.random(L) < 0.001, np.inf, g.standard_normal(L))),
 }
 
