@@ -345,3 +345,50 @@ def test_landmark_step_with_rope_and_uncompressed_tail(T):
         no_tail = oracle.gather_attend_rows(case["A_k"][b], case["A_v"][b], case["B_k"][b, 0], case["B_v"][b, 0], qh[b],
                                             row_lists, rope_theta=theta)
         assert np.abs(no_tail - ref).max() > 1e-3 * np.abs(ref).max()      # the tail does matter in this case
+
+
+@pytest.mark.parametrize("scores", ["random", "pairs", "equal"])
+@pytest.mark.parametrize("L,c,o,k", [
+    (3001, 1, 3, 333),       # a row in registers
+    (24005, 8, 5, 1201),
+    (20000, 1, 2, 9000),     # lists that do not fit beside the selection: a launch of their own
+    (41001, 2, 8, 3001),     # more chunks than a row in registers is taken for, a short last one
+    (20480, 1, 0, 1),
+    (65601, 1, 40, 2001),
+    (131072, 1, 64, 901)])
+def test_chunks_to_rows(L, c, o, k, scores):
+    """The rows that the step attends to, where the selection of the chunks expands them itself and where it does not, with chunks
+    whose scores tie across the budget (landmarks that occur twice, a query of zeros)."""
+    torch = torch_mod()
+    w = workload(dict(G=1, H_kv=2, H_q=4, d_h=128, r_k=16, r_v=16, L=L, k=k, batch=2, dtype="bf16"))
+    shape = xb.Shape.of(w)
+    n_c = -(-L // c)
+    k_ch = oracle.chunk_budget(k, c, n_c)
+    cap = (k_ch + o) * c
+    g = torch.Generator(device="cuda").manual_seed(L + o)
+    draw = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    A = [draw(w.batch, L, 16) for _ in "kv"]
+    B = [draw(w.batch, 1, 16, w.H_kv * 128) for _ in "kv"]
+    Lm, q = draw(w.batch, w.H_kv, n_c, 128), draw(w.batch, w.H_q, 128)
+    if scores == "pairs":
+        Lm[:, :, n_c // 2:2 * (n_c // 2)] = Lm[:, :, :n_c // 2]
+    if scores == "equal":
+        q.zero_()
+    outl = torch.stack([torch.randperm(n_c, generator=g, device="cuda")[:o].sort().values for _ in range(w.batch * w.H_kv)])
+    outl = outl.view(w.batch, w.H_kv, o).int().contiguous()
+    if o:
+        outl[1, :, -1] = n_c - 1                              # the short chunk among them
+    ws = torch.empty(xb.xkv_landmark_workspace_bytes(shape, c, o), dtype=torch.uint8, device="cuda")
+    out = torch.zeros((w.batch, w.H_q, 128), dtype=torch.bfloat16, device="cuda")
+    rows = torch.full((w.batch, w.H_kv, cap), -7, dtype=torch.int32, device="cuda")
+    cnt = torch.zeros((w.batch, w.H_kv), dtype=torch.int32, device="cuda")
+    S = torch.zeros((w.batch, w.H_kv, n_c), dtype=torch.float32, device="cuda")
+    xb.xkv_sr_decode_landmark(shape, 0, A[0], A[1], B[0], B[1], q, Lm, outl if o else None, c, o, out, rows, cnt, S, ws)
+    S_h, rows_h, cnt_h, outl_h = S.cpu().numpy(), rows.cpu().numpy(), cnt.cpu().numpy(), outl.cpu().numpy()
+    for b in range(w.batch):
+        for h in range(w.H_kv):
+            if scores == "equal":
+                assert not S_h[b, h].any()
+            want = oracle.expand_chunks(oracle.select(S_h[b, h], k_ch), outl_h[b, h], c, L)
+            assert cnt_h[b, h] == len(want) and np.array_equal(rows_h[b, h, :len(want)], want), (b, h)
+            assert not rows_h[b, h, len(want):].any()
