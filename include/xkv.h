@@ -379,7 +379,10 @@ XKV_API xkv_status xkv_sr_decode_absorbed_q4(const xkv_shape *shape, int32_t lay
  * Not part of the method.  For stage = 0 (low-rank score kernel), 1 (gather-reconstruct + sparse
  * attention kernel), 2 (dense decode kernel), 3 (the Gram-matrix product X_cat^T X_cat of xkv_factorize, all
  * sequences of a chunk in one launch) or 4 (the row-sum kernel of xkv_attend_absorbed), every later call that launches that kernel records
- * start_event on the call's stream right before the launch and stop_event right after it.  Both are
+ * start_event on the call's stream right before the launch and stop_event right after it.  Which kernels a call launches does not
+ * depend on it: a small fp32 step is one launch, around which both stage 0 and stage 1 record; stage 1 on many rotated rows is two
+ * kernels (logits, then the values' sums) between the events; a tail that is attended in another stage's launch is not recorded
+ * as stage 2.  Both are
  * hipEvent_t created by the caller with timing enabled (HOST handles, passed as void*); NULL for
  * either switches the recording off.  The setting belongs to the calling host thread: only that thread's later calls
  * record, other threads are not affected. */

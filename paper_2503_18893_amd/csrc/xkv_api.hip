@@ -207,7 +207,7 @@ xkv_status xkv_gather_attend(const xkv_shape *shape, int32_t layer, const void *
         return XKV_ERR_INVALID_ARG;
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
-    if (small_step_ok(*shape, 0) && !g_profile[1].start)
+    if (small_step_ok(*shape, 0))
         return hip_status(launch_small_step(*shape, layer, A_k, A_v, B_k, B_v, q, nullptr, nullptr, 0, out, nullptr, nullptr, p.scale, idx, stream));
     float *part_o = at<float>(workspace, p.off_part_o);
     float *part_ml = at<float>(workspace, p.off_part_ml);
@@ -264,10 +264,20 @@ static xkv_status sr_decode_impl(const xkv_shape *shape, int32_t layer, const vo
         return XKV_ERR_UNSUPPORTED;  // the packed form belongs to the matrix-core kernel
     if (shape->batch == 0) return XKV_OK;
     hipStream_t stream = (hipStream_t)hip_stream;
-    if (small_step_ok(*shape, T) && !g_profile[0].start && !g_profile[1].start)  // (a caller that times the stages gets the stages)
-        return hip_status(launch_small_step(*shape, layer, A_k, A_v, B_k, B_v, q, K_tail, V_tail, T, out, idx_out, score_out, p.scale, nullptr, stream));
     float *S = score_out ? score_out : at<float>(workspace, p.off_score);
     int32_t *idx = idx_out ? idx_out : at<int32_t>(workspace, p.off_idx);
+    if (small_step_ok(*shape, T)) {
+        const bool whole = small_step_whole(*shape);
+        hipError_t e = hipSuccess;
+        if (!whole)
+            e = launch_score_stage(*shape, p, layer, A_k, B_k, q, at<void>(workspace, p.off_p), S, nullptr, nullptr, nullptr, nullptr, nullptr, stream);
+        if (!whole && e == hipSuccess)
+            e = launch_topk(*shape, p, S, idx, at<uint32_t>(workspace, p.off_hist), at<uint32_t>(workspace, p.off_state), false, stream);
+        if (e == hipSuccess)
+            e = launch_small_step(*shape, layer, A_k, A_v, B_k, B_v, q, K_tail, V_tail, T, out, whole ? idx_out : nullptr, whole ? score_out : nullptr,
+                                  p.scale, whole ? nullptr : idx, stream);
+        return hip_status(e);
+    }
     float *part_o = at<float>(workspace, p.off_part_o);
     float *part_ml = at<float>(workspace, p.off_part_ml);
     uint32_t *hist = at<uint32_t>(workspace, p.off_hist), *state = at<uint32_t>(workspace, p.off_state);

@@ -287,6 +287,7 @@ bool dense_uses_mfma(const Plan &p, const void *K, const void *V, const void *q)
 // A whole step of a small single-precision problem in one launch, or (idx) its attention over given rows (small_step.hip);
 // idx_out and score_out may be NULL.
 bool small_step_ok(const xkv_shape &s, int T);
+bool small_step_whole(const xkv_shape &s);  // ... whether scores and selection are faster in that launch, too
 hipError_t launch_small_step(const xkv_shape &s, int layer, const void *A_k, const void *A_v, const void *B_k, const void *B_v, const void *q,
                              const void *K_tail, const void *V_tail, int T, void *out, int32_t *idx_out, float *score_out, float scale,
                              const int32_t *idx, hipStream_t st);

@@ -13,7 +13,11 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("H_kv,n_rep,d_h,r_k,r_v,L,k,T,batch,shift", [
     (1, 4, 64, 32, 32, 512, 32, 0, 1, 0), (1, 1, 1, 1, 1, 1, 1, 0, 1, 0), (2, 5, 100, 33, 47, 63, 63, 1, 2, 0), (1, 16, 96, 64, 96, 1023, 100, 64, 1, 0),
     (2, 3, 256, 48, 32, 1025, 1, 0, 1, 0), (1, 4, 64, 48, 32, 4096, 1024, 10, 1, 0), (1, 4, 64, 64, 64, 4096, 300, 0, 1, 0),
-    (8, 2, 128, 32, 1024, 200, 50, 0, 1, 0), (3, 7, 65, 40, 24, 900, 450, 33, 2, 1), (1, 4, 64, 63, 63, 4097, 64, 0, 1, 0)])
+    (8, 2, 128, 32, 1024, 200, 50, 0, 1, 0), (3, 7, 65, 40, 24, 900, 450, 33, 2, 1), (1, 4, 64, 63, 63, 4097, 64, 0, 1, 0),
+    # scores and selection launched before it
+    (1, 1, 64, 64, 40, 2050, 77, 5, 1, 0), (4, 3, 64, 64, 64, 2600, 100, 0, 2, 0),
+    # more pairs than compute units: four wavefronts each for given rows, more parts of a sum than threads; sixteen for more work
+    (8, 2, 32, 16, 16, 64, 16, 0, 40, 0), (3, 5, 64, 24, 7, 100, 33, 0, 90, 0), (8, 4, 64, 32, 48, 90, 30, 3, 70, 0), (8, 4, 128, 96, 64, 70, 40, 0, 33, 0)])
 def test_small_step(H_kv, n_rep, d_h, r_k, r_v, L, k, T, batch, shift):
     import torch
     if not torch.cuda.is_available():
@@ -50,3 +54,38 @@ def test_small_step(H_kv, n_rep, d_h, r_k, r_v, L, k, T, batch, shift):
     if T == 0:
         xb.xkv_gather_attend(shape, 1, A_k, dev["A_v"], dev["B_k"], dev["B_v"], q, idx, staged, ws)
         assert torch.equal(out, staged)
+
+
+@pytest.mark.parametrize("L,H_kv", [(512, 1), (4096, 1)])   # one launch; scores and selection on their own
+def test_kernel_timing_does_not_change_the_step(L, H_kv):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    w = synth.Workload("small_step", G=1, H_kv=H_kv, H_q=4, d_h=64, r_k=48, r_v=32, L=L, k=40, batch=1, dtype="f32", a_scale=1.0,
+                       sigma_decay=0.3, q_scale=0.3)
+    dev = synth.to_device(synth.make_case(w, seed=L), "f32")
+    shape, q = xb.Shape.of(w), dev["q"][0].contiguous()
+    ws = xb.alloc_workspace(shape)
+    idx = torch.empty((1, H_kv, w.k), dtype=torch.int32, device="cuda")
+
+    def outputs():
+        step, rows = torch.empty_like(q), torch.empty_like(q)
+        xb.xkv_sr_decode(shape, 0, dev["A_k"], dev["A_v"], dev["B_k"], dev["B_v"], q, step, idx, None, ws)
+        xb.xkv_gather_attend(shape, 0, dev["A_k"], dev["A_v"], dev["B_k"], dev["B_v"], q, idx, rows, ws)
+        return step, rows
+
+    plain = outputs()
+    for stage in (xb.STAGE_SCORE, xb.STAGE_GATHER_ATTEND):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        for e in ev:
+            e.record()
+        torch.cuda.synchronize()
+        assert 0.0 <= ev[0].elapsed_time(ev[1])
+        xb.xkv_profile_kernel(stage, ev[0].cuda_event, ev[1].cuda_event)
+        try:
+            timed = outputs()
+        finally:
+            xb.xkv_profile_kernel(stage, None, None)
+        torch.cuda.synchronize()
+        assert ev[0].elapsed_time(ev[1]) > 0.0
+        assert all(torch.equal(a, b) for a, b in zip(plain, timed)), stage
