@@ -239,8 +239,10 @@ static Tail make_tail(const xkv_shape &shape, const Plan &p, const void *K, cons
     t.shape.L = T;
     t.mfma = dense_uses_mfma(p, K, V, q);
     // (a workgroup of the matrix-core kernel takes 128 tokens a round, 5 us for the first: 333 tokens 9 us in one workgroup per
-    // head.  The general kernel leaves a partial per wavefront.)
-    const int splits = t.mfma ? clampi(ceil_div(T, 128), 1, kTailParts / 2) : clampi(ceil_div(T, 512), 1, kTailParts / 4);
+    // head.  Cut as finely as that fills the chip, two workgroups per compute unit, and no finer than 512 tokens beyond it: a step of 64 sequences
+    // with 8 heads and 2048 tokens takes 139 us, 161 with 128 tokens a workgroup.  The general kernel leaves a partial per wavefront.)
+    int splits = clampi(ceil_div(T, 512), 1, kTailParts / 4);
+    if (t.mfma) splits = clampi(512 / (p.rows > 0 ? p.rows : 1), splits, clampi(ceil_div(T, 128), 1, kTailParts / 2));
     t.plan.dense_chunk = ceil_div(ceil_div(T, splits), 128) * 128;
     t.plan.dense_splits = ceil_div(T, t.plan.dense_chunk);
     t.parts = t.mfma ? t.plan.dense_splits : t.plan.dense_splits * 4;

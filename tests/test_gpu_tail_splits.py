@@ -11,12 +11,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shift", [0, 1])
-@pytest.mark.parametrize("T", [1, 128, 129, 333, 2048, 2049, 5000])
-def test_tail_of_a_step(T, shift):
+@pytest.mark.parametrize("T,batch", [(1, 2), (128, 2), (129, 2), (333, 2), (2048, 2), (2049, 2), (5000, 2), (700, 12), (513, 40)])  # (fewer splits each)
+def test_tail_of_a_step(T, batch, shift):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    w = synth.LLAMA_GROUP.with_(L=700, k=90, r_k=64, r_v=96, batch=2, G=1)
+    w = synth.LLAMA_GROUP.with_(L=700, k=90, r_k=64, r_v=96, batch=batch, G=1)
     case = synth.make_case(w, seed=T)
     dev = synth.to_device(case, "bf16")
     rng = np.random.default_rng(T)
