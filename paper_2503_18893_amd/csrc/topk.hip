@@ -486,13 +486,13 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(const float *__re
 // The time is the instructions per score of four wavefronts per SIMD (a microsecond for two and a half of them at 65536 scores; a
 // workgroup reads such a row in three) and, in all that runs once, the fetching of the code: loops are kept rolled.  Scores
 // 1024 apart belong to one thread, so that neighbours, which are alike, spread over all lists.
-// Against the row in registers, 8 rows, k a sixteenth: 20480 scores 14.5 -> 10.7 us (the lists' length decides: k 5000 of 28000 15.0 -> 16.1,
-// hence half the lists at most up to 32768 scores), 32768 14.5 -> 12.4, 40001 22.9 -> 14.1, 65536 22.4 -> 18.1; against the five
+// Against the row in registers, 8 rows, k a sixteenth: 16384 scores 10.1 -> 10.2 us, 16385, twice the registers, 14.4 -> 11.6 (the lists'
+// length decides: k 5000 of 28000 15.0 -> 16.1, hence half the lists at most up to 32768 scores), 32768 14.5 -> 12.4, 40001 22.9 -> 14.1, 65536 22.4 -> 18.1; against the five
 // launches 32 rows of 131072, k 1024, 38.9 -> 20.9, 128 rows 109 -> 22.  8 rows of 32768 equal scores 42 -> 11.5 (of 131072, where the five
 // launches use more compute units, 27 -> 29), five different values 19.8 -> 13.1; ninth powers of normal numbers, whose range has to be sliced
 // three times, 13.6 -> 18.6, 65536 of them 21.3 -> 23.9; radix passes 67 and 91.
 // ------------------------------------------------------------------------------------------
-constexpr int kRowFloor = 20480, kRowMost = 131072, kRowSamples = 4096;
+constexpr int kRowFloor = 16 * kRowThreads + 1, kRowMost = 131072, kRowSamples = 4096;
 constexpr int kRowExpect = 8192;  // scores that may be expected to reach the guess
 constexpr float kRowSigmas = 4.5f;  // margin in standard deviations of the samples' rank
 
