@@ -14,8 +14,6 @@
 // multiple of 16 (none when r is a multiple of 128), so that every row and every group is 16-byte aligned.
 //   lo = min of the group, step = bf16((max - lo) / 15) (1 if that is 0), code = clip(rint((x - lo) * (1 / step)), 0, 15),
 // each a single fp32 operation (the same sequence as the CPU oracle: the codes agree bit for bit);  x^ = step * code + lo.
-#include <type_traits>
-
 #include "xkv_common.h"
 
 namespace xkv {
@@ -23,8 +21,7 @@ namespace xkv {
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
 constexpr int kQuantPieces = 4;         // 16-byte pieces per thread (1 where the call is small)
-constexpr int kQuantSmall = 1536 * 1024;          // pieces
-constexpr int kQuantCached = 16 * 1024 * 1024;  // pieces of 256 MiB
+constexpr int kQuantSmall = 1536 * 1024;  // pieces
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -55,8 +52,7 @@ __device__ __forceinline__ float max3(float a, float b, float c)
 // 24 bits of b are ones, and a step has 8 (Markstein, IBM J. Res. Dev. 34, 1990).  Outside the range where r is exact the
 // ordinary division is used.  50001 rows of 512: 17.6 -> 15.2 us (67 MB; reading and writing as many bytes alone 11.5; with a
 // store of a word per lane and one for the parameters 16.3: rows of 320 bytes leave most lines in parts).
-// PAST: the rows are read past the caches.
-template <int BITS, bool STAGED, int U, bool PAST>
+template <int BITS, bool STAGED, int U>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out,
                                                             long long pieces, int r)
 {
@@ -84,7 +80,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__rest
     for (int u = 0; u < U; ++u) {
         const uint32_t i = u * 256 + threadIdx.x;
         const q_u32x4_t *src = Xb + (i < left ? i : left - 1);
-        raw[u] = PAST ? __builtin_nontemporal_load(src) : *src;
+        raw[u] = U == 1 ? *src : __builtin_nontemporal_load(src);  // (a small call's rows may still be in the caches)
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -171,21 +167,12 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, pieces, r);
     };
-    // Rows that the last-level cache holds may be there already (100000 rows of 512 25.2 -> 23.4 us with ordinary loads); more than that are
-    // read past it (300000: 69 instead of 73).
-    const bool past = pieces > kQuantCached;
-    auto launch_bits = [&](auto b) {
-        constexpr int B = decltype(b)::value;
-        small             ? launch(quantize_rows_kernel<B, false, 1, false>)
-        : staged && past ? launch(quantize_rows_kernel<B, true, kQuantPieces, true>)
-        : staged         ? launch(quantize_rows_kernel<B, true, kQuantPieces, false>)
-        : past           ? launch(quantize_rows_kernel<B, false, kQuantPieces, true>)
-                         : launch(quantize_rows_kernel<B, false, kQuantPieces, false>);
-    };
     if (bits == 3)
-        launch_bits(std::integral_constant<int, 3>());
+        small ? launch(quantize_rows_kernel<3, false, 1>)
+              : staged ? launch(quantize_rows_kernel<3, true, kQuantPieces>) : launch(quantize_rows_kernel<3, false, kQuantPieces>);
     else
-        launch_bits(std::integral_constant<int, 4>());
+        small ? launch(quantize_rows_kernel<4, false, 1>)
+              : staged ? launch(quantize_rows_kernel<4, true, kQuantPieces>) : launch(quantize_rows_kernel<4, false, kQuantPieces>);
     return hipGetLastError();
 }
 
