@@ -486,11 +486,12 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(const float *__re
 // The time is the instructions per score of four wavefronts per SIMD (a microsecond for two and a half of them at 65536 scores; a
 // workgroup reads such a row in three) and, in all that runs once, the fetching of the code: loops are kept rolled.  Scores
 // 1024 apart belong to one thread, so that neighbours, which are alike, spread over all lists.
-// Against the row in registers, 8 rows, k a sixteenth: 16384 scores 10.1 -> 10.2 us, 16385, twice the registers, 14.4 -> 11.6 (the lists'
-// length decides: k 5000 of 28000 15.0 -> 16.1, hence half the lists at most up to 32768 scores), 32768 14.5 -> 12.4, 40001 22.9 -> 14.1, 65536 22.4 -> 18.1; against the five
-// launches 32 rows of 131072, k 1024, 38.9 -> 20.9, 128 rows 109 -> 22.  8 rows of 32768 equal scores 42 -> 11.5 (of 131072, where the five
-// launches use more compute units, 27 -> 29), five different values 19.8 -> 13.1; ninth powers of normal numbers, whose range has to be sliced
-// three times, 13.6 -> 18.6, 65536 of them 21.3 -> 23.9; radix passes 67 and 91.
+// Against the row in registers, 8 rows, k a sixteenth: 16384 scores 10.1 -> 10.2 us, 20480, twice the registers, 14.5 -> 10.6 (the lists'
+// length decides: k 3000 of 32768 14.6 -> 13.5, rectified 14.6 -> 16.2, hence half of it at most up to 32768 scores), 32768 14.5 -> 12.3,
+// 40001 22.9 -> 14.1, 65536 22.4 -> 18.1; against the five launches 32 rows of 131072, k 1024, 38.6 -> 20.5, 128 rows 110 -> 21.
+// 8 rows of 32768 equal scores 42 -> 11.9, five different values 19.9 -> 13.1; ninth powers of normal numbers, whose range has to be sliced
+// again, 14.7 -> 19.9, 65536 of them 21.4 -> 24.1; radix passes 67 and 91.  Of 131072 scores, where the five launches use more compute units
+// than 8 rows have here, equal ones 27 -> 30, rising ones 24 -> 27, normal ones 27 -> 20.
 // ------------------------------------------------------------------------------------------
 constexpr int kRowFloor = 16 * kRowThreads + 1, kRowMost = 131072, kRowSamples = 4096;
 constexpr int kRowExpect = 8192;  // scores that may be expected to reach the guess
@@ -511,6 +512,20 @@ __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t x)  // the same in eve
     x = max_step<0x143>(x);
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
+template <int CTRL> __device__ __forceinline__ float max_step(float x)
+{
+    return fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(__float_as_uint(x), __float_as_uint(x), CTRL, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float x)
+{
+    x = max_step<0x111>(x);
+    x = max_step<0x112>(x);
+    x = max_step<0x114>(x);
+    x = max_step<0x118>(x);
+    x = max_step<0x142>(x);
+    x = max_step<0x143>(x);
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), 63));
+}
 __device__ __forceinline__ float float_of_key(uint32_t key) { return __uint_as_float((int)key < 0 ? key ^ 0x80000000u : ~key); }
 
 // LDS of the guess: bitmap, bins, lists, bitmap of the scores that equal the guess
@@ -522,16 +537,80 @@ constexpr int kRowWords = kRowListWords + kRowBins + kRowMapWords;  // ... witho
 // stretch the range) or many that may be equal, slices of that one, and so on.  True: the samples in it are all equal, and lo_bits is
 // what they are.  bins: zero before and after.
 constexpr int kRowSlicings = 5;
-constexpr uint32_t kRowEqual = 64;  // samples in a slice that call for a closer look (half a dozen are usual; equal scores add up in one counter)
+constexpr uint32_t kRowEqual = 384;  // samples in a slice that call for a closer look (equal scores add up in one counter; a slicing takes 0.7 us)
 __device__ __forceinline__ bool guess_bounds(const float (&x)[4], uint32_t r_lo, uint32_t r_hi, uint32_t r_max, uint32_t *bins, RowShared &sh,
                                              uint32_t &lo_bits, uint32_t &hi_bits)
 {
     static_assert(kRowSamples == 4 * kRowThreads && kRowBins == 2 * kRowThreads, "four samples and two bins per thread");
     const int w = wave_id(), tid = threadIdx.x;
-    uint32_t in = 15u, above_all = 0;  // samples of this thread in the slice at hand, of all threads above it
+    uint32_t bin[4], in = 15u, above_all = 0;  // slices of this thread's samples, which are in the one at hand; samples of all threads above it
     if (tid < 2) sh.pick[tid][0] = tid == 0 ? 0u : kRowBins - 1;
-    for (int level = 0;; ++level) {
-        // (scores that are not finite count as the nearest end of the others' range; NaN as the lower end)
+    // one slicing of the samples `in`: finds the slices of the r_lo-th and, where it is in it, the r_hi-th largest; true: that will do
+    auto slice = [&](float mn, float range, int level) __attribute__((always_inline)) {
+        __syncthreads();
+        const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
+        bins[2 * tid] = 0;
+        bins[2 * tid + 1] = 0;
+        const uint32_t above = sum_above(c0 + c1, sh.wave[level & 1]);
+        auto pick = [&](int which, uint32_t r) __attribute__((always_inline)) {
+            if (above < r && r <= above + c1 + c0) {
+                const bool odd = r <= above + c1;
+                sh.pick[which][0] = 2 * tid + (odd ? 1 : 0);
+                sh.pick[which][1] = above + (odd ? 0u : c1);
+                sh.pick[which][2] = odd ? c1 : c0;
+            }
+        };
+        const bool hi_in = level == 0 || r_hi > above_all;
+        pick(0, r_lo - above_all);
+        if (hi_in) pick(1, r_hi - above_all);
+        __syncthreads();
+        const uint32_t b_lo = sh.pick[0][0], in_bin = sh.pick[0][2];
+        const float width = range * (1.0f / kRowBins);
+        // (a thousandth of a slice lower: an edge rounded up, by 2^-12 at most, would leave out scores that the slice has)
+        lo_bits = __float_as_uint(fmaf((float)b_lo - 0.001f, width, mn));
+        if (hi_in) hi_bits = __float_as_uint(fmaf((float)sh.pick[1][0] + 1.0f, width, mn));
+        above_all += sh.pick[0][1];
+        if (above_all + in_bin <= r_max && in_bin <= kRowEqual) return true;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) in &= ~((bin[u] == b_lo ? 0u : 1u) << u);
+        return false;
+    };
+    // (scores that are not finite count as the nearest end of the others' range; NaN as the lower end)
+    float mn = INFINITY, mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (fabsf(x[u]) < INFINITY) {
+            mn = fminf(mn, x[u]);
+            mx = fmaxf(mx, x[u]);
+        }
+    mn = -wave_max_dpp(-mn);
+    mx = wave_max_dpp(mx);
+    if (lane_id() == 0) {
+        sh.lo[w] = __float_as_uint(mn);
+        sh.hi[w] = __float_as_uint(mx);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ww = 0; ww < kRowWaves; ++ww) {
+        mn = fminf(mn, __uint_as_float(sh.lo[ww]));
+        mx = fmaxf(mx, __uint_as_float(sh.hi[ww]));
+    }
+    float range = mx - mn, scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
+    auto bin_of = [&](float v) __attribute__((always_inline)) {
+        return (uint32_t)fminf(fmaxf((v - mn) * scale, 0.0f), (float)(kRowBins - 1));
+    };
+    if (__builtin_expect(range == 0.0f, 0)) {  // (zeros of both signs are looked at below)
+        hi_bits = __float_as_uint(mx + 0.0f);
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            bin[u] = bin_of(x[u]);
+            atomicAdd(&bins[bin[u]], 1u);
+        }
+        if (__builtin_expect(slice(mn, range, 0), 1)) return false;
+    }
+    for (int level = 1; level < kRowSlicings; ++level) {
         uint32_t kmn = 0, kmx = 0;  // keys, the lower one turned over: zero where there is none
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -554,47 +633,21 @@ __device__ __forceinline__ bool guess_bounds(const float (&x)[4], uint32_t r_lo,
         }
         kmn = (uint32_t)__builtin_amdgcn_readfirstlane((int)~kmn);
         kmx = (uint32_t)__builtin_amdgcn_readfirstlane((int)kmx);
-        const float mn = float_of_key(kmn), mx = float_of_key(kmx);
+        mn = float_of_key(kmn);
         if (kmn == kmx) {
             lo_bits = __float_as_uint(mn);
-            if (level == 0) hi_bits = lo_bits;
             return true;
         }
-        const float range = mx - mn, scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
-        uint32_t bin[4];
+        range = float_of_key(kmx) - mn;
+        scale = range > 0.0f && range < INFINITY ? (float)kRowBins / range : 0.0f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            bin[u] = range == 0.0f ? (__float_as_uint(x[u]) == 0u ? 1u : 0u)  // (zeros of both signs)
-                                   : (uint32_t)fminf(fmaxf((x[u] - mn) * scale, 0.0f), (float)(kRowBins - 1));
+            bin[u] = range == 0.0f ? (__float_as_uint(x[u]) == 0u ? 1u : 0u) : bin_of(x[u]);  // (zeros of both signs)
             if (in >> u & 1u) atomicAdd(&bins[bin[u]], 1u);
         }
-        __syncthreads();
-        const uint32_t c0 = bins[2 * tid], c1 = bins[2 * tid + 1];
-        bins[2 * tid] = 0;
-        bins[2 * tid + 1] = 0;
-        const uint32_t above = sum_above(c0 + c1, sh.wave[level & 1]);
-        auto pick = [&](int which, uint32_t r) __attribute__((always_inline)) {
-            if (above < r && r <= above + c1 + c0) {
-                const bool odd = r <= above + c1;
-                sh.pick[which][0] = 2 * tid + (odd ? 1 : 0);
-                sh.pick[which][1] = above + (odd ? 0u : c1);
-                sh.pick[which][2] = odd ? c1 : c0;
-            }
-        };
-        const bool hi_in = level == 0 || r_hi > above_all;  // the r_hi-th largest is in the slice, too
-        pick(0, r_lo - above_all);
-        if (hi_in) pick(1, r_hi - above_all);
-        __syncthreads();
-        const uint32_t b_lo = sh.pick[0][0], in_bin = sh.pick[0][2];
-        const float width = range * (1.0f / kRowBins);
-        // (a thousandth of a slice lower: an edge rounded up, by 2^-12 at most, would leave out scores that the slice has)
-        lo_bits = __float_as_uint(fmaf((float)b_lo - 0.001f, width, mn));
-        if (hi_in) hi_bits = __float_as_uint(fmaf((float)sh.pick[1][0] + 1.0f, width, mn));
-        above_all += sh.pick[0][1];
-        if ((above_all + in_bin <= r_max && in_bin <= kRowEqual) || level == kRowSlicings - 1) return false;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) in &= ~((bin[u] == b_lo ? 0u : 1u) << u);
+        if (slice(mn, range, level)) return false;
     }
+    return false;
 }
 
 // Calls f(bits, id, real) for every score of the row in groups of 8 x 1024, thread tid taking scores tid, tid + 1024, ..; the next two
