@@ -310,14 +310,13 @@ bool small_step_ok(const xkv_shape &s, int T)
            s.r_v <= kRowThreads && n_rep * d_h <= kSmPart && s.k + n_rep * (s.k + T) <= kSmLists;
 }
 
-// Scores and selection on one compute unit against two launches and a selection over all of them (staged / whole, us, one KV head: 2048 tokens
-// of rank 32 23.5 / 21.0, 3000 23.5 / 24.5, 4096 23.4 / 28.5, 2048 of rank 48 30.9 / 26.8, of rank 64 27.4 / 30.5, 3000 27.1 / 37.5, 1000 of rank
-// 128 43.7 / 42.3, 512 of rank 256 102 / 97).  The score kernel takes the KV heads of a sequence one after the other: four heads, 3000 of rank 64, one query head each
-// 12 % longer as a whole, four the same; with eight a whole step is 1.1 to 1.7 times as fast.
+// Scores and selection on one compute unit against two launches and a selection over all of them (staged / whole, in a graph, us, one KV head:
+// 2048 tokens of rank 32 23.5 / 21.0, 4096 23.4 / 28.5, 2048 of rank 64 27.4 / 30.5, 1000 of rank 128 43.7 / 42.3, 512 of rank 256 102 / 97, 3000 of
+// rank 64 27.1 / 37.5; launched one by one, three launches more cost 3 to 5 us more).  The score kernel takes the KV heads of a sequence one
+// after the other: with two 3000 of rank 64 31 / 38, with four about the same, with eight a whole step is 1.1 to 1.7 times as fast.
 bool small_step_whole(const xkv_shape &s)
 {
-    const long long numbers = (long long)s.L * s.r_k;
-    return (long long)s.batch * s.H_kv > 32 || s.H_kv > 4 || numbers <= (s.H_kv > 2 || s.r_k > 96 ? 163840 : 130000);
+    return (long long)s.batch * s.H_kv > 32 || s.H_kv > 2 || (long long)s.L * s.r_k <= 163840;
 }
 
 // idx (nullable): attend over these rows only, nothing is scored or selected

@@ -14,8 +14,9 @@ pytestmark = pytest.mark.gpu
     (1, 4, 64, 32, 32, 512, 32, 0, 1, 0), (1, 1, 1, 1, 1, 1, 1, 0, 1, 0), (2, 5, 100, 33, 47, 63, 63, 1, 2, 0), (1, 16, 96, 64, 96, 1023, 100, 64, 1, 0),
     (2, 3, 256, 48, 32, 1025, 1, 0, 1, 0), (1, 4, 64, 48, 32, 4096, 1024, 10, 1, 0), (1, 4, 64, 64, 64, 4096, 300, 0, 1, 0),
     (8, 2, 128, 32, 1024, 200, 50, 0, 1, 0), (3, 7, 65, 40, 24, 900, 450, 33, 2, 1), (1, 4, 64, 63, 63, 4097, 64, 0, 1, 0),
-    # scores and selection launched before it
-    (1, 1, 64, 64, 40, 2050, 77, 5, 1, 0), (4, 3, 64, 64, 64, 2600, 100, 0, 2, 0),
+    # scores and selection launched before it (from 163840 numbers of A^K on, up to two KV heads), and beside that line
+    (1, 1, 64, 64, 40, 2050, 77, 5, 1, 0), (4, 3, 64, 64, 64, 2600, 100, 0, 2, 0), (1, 1, 64, 64, 40, 2600, 77, 5, 1, 0),
+    (2, 3, 64, 64, 64, 2700, 100, 0, 2, 0), (2, 1, 64, 64, 40, 2560, 77, 5, 1, 0),
     # more pairs than compute units: four wavefronts each for given rows, more parts of a sum than threads; sixteen for more work
     (8, 2, 32, 16, 16, 64, 16, 0, 40, 0), (3, 5, 64, 24, 7, 100, 33, 0, 90, 0), (8, 4, 64, 32, 48, 90, 30, 3, 70, 0), (8, 4, 128, 96, 64, 70, 40, 0, 33, 0)])
 def test_small_step(H_kv, n_rep, d_h, r_k, r_v, L, k, T, batch, shift):
