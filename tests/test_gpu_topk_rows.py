@@ -24,13 +24,15 @@ VALUES = {
     "zeros_of_both_signs": lambda g, L: np.where(g.random(L) < 0.5, 0.0, -0.0),
     "equal_but_a_few": lambda g, L: np.where(g.random(L) < 0.002, g.standard_normal(L), 0.25),
     "equal_negative": lambda g, L: np.minimum(-1.0, g.standard_normal(L)),
+    "equal_not_zero": lambda g, L: np.full(L, -0.7),
+    "ends_of_the_type": lambda g, L: np.where(g.random(L) < 0.5, 3e38, -3e38) * (1.0 - 0.1 * g.random(L)),
     "all_minus_inf": lambda g, L: np.full(L, -np.inf),
     "not_finite": lambda g, L: np.where(g.random(L) < 0.3, -np.inf, np.where(g.random(L) < 0.001, np.inf, g.standard_normal(L))),
 }
 
 
-@pytest.mark.parametrize("L,k", [(2047, 100), (2048, 1), (2048, 2047), (4096, 256), (8192, 4000), (8193, 512), (16385, 1024),
-                                 (20000, 6000), (32768, 2048), (32769, 7000), (40001, 1777), (65535, 4096), (65536, 9000),
+@pytest.mark.parametrize("L,k", [(2047, 100), (2048, 1), (2048, 2047), (4096, 256), (8192, 4000), (8193, 512), (16384, 1000), (16385, 1024),
+                                 (20000, 6000), (32768, 2048), (32768, 2300), (32768, 2600), (32769, 7000), (40001, 1777), (65535, 4096), (65536, 9000),
                                  (65537, 4096), (100001, 300), (131072, 4096), (131072, 9000), (131073, 4096)])
 def test_selected_ids_are_the_largest_in_order(L, k):
     import torch
