@@ -12,7 +12,7 @@
 // n_rep * r_v instead of (r_k + r_v) * d_h multiply-adds per token, so it is bound by the row gather alone.
 // It is only valid where the keys need no per-token treatment after reconstruction (no rotary embedding).
 // The kernels here are the general form; bf16 and quantised rows whose shape and alignment gather_absorb_kernel takes are
-// summed there, on the matrix cores.
+// summed there, on the matrix cores, where that is faster (absorbed_mfma_pays).
 #include "xkv_common.h"
 
 namespace xkv {

@@ -17,7 +17,7 @@
 //           here, so the operand comes out of the tile through the transposing LDS read (4 rows x 16 ranks a time).
 // The 16 result lanes of a logit tile hold, slot by slot, exactly the rows that the weights operand wants in that lane, so
 // logits become weights without leaving the registers (online softmax, U rescaled once per tile).  At the end the wavefronts' U are added in LDS,
-// split into a bf16 high part and remainder (again 16 + 16 rows of one operand) and multiplied with B^V.
+// split into a bf16 high part and remainder (again 16 + 16 rows of one operand; KEPT with three parts: see there) and multiplied with B^V.
 //
 // KEPT: the logits are there already, so that the keys' half falls away and a row costs its values alone: from the score stage
 // (the absorbed step: every query head's score of every token) or, for rotated keys, from the KEYS form of
