@@ -30,21 +30,23 @@ static xkv_status validate(const xkv_shape *s)
 }
 
 // Whether rotated rows are faster in two halves, logits and then the values' sums from them.  That is a launch and a merge more (4 us);
-// what it saves are the values' products, whose ranks the one-launch kernel pads to 256 and takes per row.  Its time goes by `len`,
-// the rows that a compute unit takes one after the other (tiles of 256 in rounds of 256 workgroups).  One launch / two halves, us, 4
-// query heads on each of 8 KV heads: 4 bits, ranks 512: len 512 60 / 60, 768 77 / 74, 1024 104 / 96, 1536 136 / 112; ranks 384 len 512
-// 61 / 58; ranks 256 41 / 43, 51 / 51, 69 / 66; in 3 bits 38 / 40, 48 / 49, 65 / 62.  Eight heads, ranks 512 62 / 65, 78 / 78, 106 / 102; 64 in
-// 3 bits len 1024 61 / 62, 1536 84 / 75.  bf16, ranks 512: len 1024 117 / 125, 2048 in one round 207 / 212, in two full ones 227 / 229, in two
-// of which the second is a quarter full 196 / 183; ranks 384 at 1024 110 / 108; 448 114 / 121, at 1536 139 / 123.  Not with six groups of
-// values' ranks, whose kernel has two groups in flight instead of four (ranks 768 71 / 85), nor with more than eight query heads, where
-// one workgroup has a compute unit to itself (16 heads, len 512 65 / 78, 1024 in 4 bits 114 / 130).
+// what it saves are the values' products, whose ranks the one-launch kernel pads to 256 and takes per row.  Its time goes by `len`, the
+// rows that a compute unit takes one after the other (tiles of 256 in rounds of 256 workgroups).  One launch / two halves, us, 4 query
+// heads on each of 8 KV heads: 4 bits, ranks 512: len 512 60 / 60, 768 77 / 74, 1024 104 / 96, 1536 136 / 112; ranks 384 len 512 61 /
+// 58; ranks 256 41 / 43, 51 / 51, 69 / 66; in 3 bits 38 / 40, 48 / 49, 65 / 62.  Eight heads, ranks 512 62 / 65, 78 / 78, 106 / 102; 64
+// in 3 bits len 1024 61 / 62, 1536 84 / 75.  bf16, ranks 512: len 1024 117 / 125, 2048 in one round 207 / 212, in two full ones 227 /
+// 229, in two of which the second is a quarter full 196 / 183; from 65536 tokens in memory len 2048 247 / 248, 2304 229 / 230, 2560 265
+// / 262 (one query head 267 / 259, eight 272 / 266), 4608 445 / 434, 5120 521 / 496; ranks 256 len 2048 141 / 147, 2560 159 / 157, 4608
+// 264 / 257; ranks 384 at 1024 110 / 108; 448 114 / 121, at 1536 139 / 123.  Not with six groups of values' ranks, whose kernel has two
+// groups in flight instead of four (ranks 768 71 / 85), nor with more than eight query heads, where one workgroup has a compute unit to
+// itself (16 heads, len 512 65 / 78, 1024 in 4 bits 114 / 130).
 static bool rope_kept_pays(const xkv_shape &s, const Plan &p, int qbits)
 {
     if (!p.absorb || s.r_v > 512 || p.n_rep > 8 || (long long)p.rows * s.k < 131072) return false;
     const long long groups = (long long)p.rows * p.sr_splits, rounds = (groups + 255) / 256, len = rounds * p.sr_chunk;
     if (qbits == 0) {
         const int used = (s.r_v - 1) % 256 + 1;  // of the last 256 ranks
-        return used <= 128 ? len >= 1024 : len >= 1536 && (used < 256 || 4 * groups <= 3 * 256 * rounds);
+        return len >= 2560 || (used <= 128 ? len >= 1024 : len >= 1536 && (used < 256 || 4 * groups <= 3 * 256 * rounds));
     }
     if (p.n_rep > 4) return len >= (s.r_v > 256 ? 1024 : 1536);
     return len >= (s.r_v > 256 ? 512 : 1024);

@@ -120,7 +120,7 @@ def test_sums_keep_single_precision(n_rep, r_v, L, k, batch, what, bits):
 
 # bits, query heads per KV head (8 of them), ranks, k, batch: all in two halves.  The logits take the room of the projected queries and
 # the scores, so the context is as long as they are.
-ROTATED = [(0, 4, 64, 12300, 2), (0, 7, 96, 12300, 2), (0, 8, 320, 12300, 2), (0, 1, 512, 4100, 6), (0, 3, 448, 4100, 6),
+ROTATED = [(0, 4, 64, 12300, 2), (0, 7, 96, 12300, 2), (0, 8, 320, 12300, 2), (0, 1, 512, 4100, 6), (0, 3, 448, 4100, 6), (0, 4, 256, 9300, 8),
            (4, 4, 64, 12300, 2), (4, 7, 160, 20500, 2), (4, 1, 512, 8200, 2), (4, 3, 288, 8200, 2), (4, 8, 384, 12300, 2),
            (3, 4, 64, 12300, 2), (3, 2, 512, 8200, 2), (3, 6, 512, 12300, 2)]
 

@@ -99,7 +99,7 @@ def test_rotated_rows_in_two_halves_where_that_is_faster(plan_of):
     line = [  # n_rep, r, batch, k, two halves in bf16, 4 bits, 3 bits
         (4, 512, 4, 4096, 0, 1, 1), (4, 512, 6, 4096, 1, 1, 1), (4, 512, 16, 4096, 0, 1, 1), (4, 512, 3, 4096, 0, 0, 0), (4, 256, 5, 4096, 0, 0, 0),
         (4, 256, 8, 4096, 0, 1, 1), (4, 384, 5, 4096, 0, 1, 1), (4, 384, 8, 4096, 1, 1, 1), (4, 448, 8, 4096, 0, 1, 1), (8, 512, 5, 4096, 0, 0, 0),
-        (8, 512, 8, 4096, 0, 1, 1), (8, 64, 8, 4096, 1, 0, 0), (8, 64, 10, 4096, 1, 1, 1), (9, 512, 16, 4096, 0, 0, 0), (4, 528, 16, 4096, 0, 0, 0)]
+        (8, 512, 8, 4096, 0, 1, 1), (8, 64, 8, 4096, 1, 0, 0), (8, 64, 10, 4096, 1, 1, 1), (4, 512, 16, 4128, 1, 1, 1), (1, 256, 16, 4128, 1, 1, 1), (9, 512, 16, 4096, 0, 0, 0), (4, 528, 16, 4096, 0, 0, 0)]
     shapes = [dict(H_q=8 * n, r_k=r, r_v=r, batch=b, k=k, L=16 * k) for n, r, b, k, _, _, _ in line]
     for case, p in zip(line, plan_of(shapes)):
         assert (p["kept_0"], p["kept_4"], p["kept_3"]) == case[4:], case
