@@ -33,3 +33,10 @@ def test_tiles_against_fp64(H_kv, r, batch, L):
     want = np.matmul(A64, B64).reshape(batch, L, H_kv, d_h).transpose(0, 2, 1, 3)
     size = np.matmul(np.abs(A64), np.abs(B64)).reshape(batch, L, H_kv, d_h).transpose(0, 2, 1, 3)
     assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + (1 + 2.0 ** -8) * r * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("r", [128, 256, 384, 512, 640, 768])
+@pytest.mark.parametrize("H_kv,batch,L", [(1, 1, 1), (2, 2, 31), (3, 1, 33), (2, 3, 64), (5, 2, 97), (8, 1, 161), (1, 17, 130), (8, 3, 4133), (3, 130, 70)])
+def test_factor_in_registers(H_kv, batch, L, r):
+    """The ranks whose B_l is kept: 32 tokens a tile, runs of one to many tiles, odd numbers of KV heads, more groups than compute units."""
+    test_tiles_against_fp64(H_kv, r, batch, L)
