@@ -12,7 +12,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libxkv.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["xkv_api.hip", "score.hip", "topk.hip", "gather_attend.hip", "gather_attend_mfma.hip", "gather_absorb.hip", "dense.hip", "reconstruct.hip",
+SOURCES = ["xkv_api.hip", "score.hip", "topk.hip", "gather_attend.hip", "gather_attend_mfma.hip", "gather_absorb.hip", "rope_keys.hip", "dense.hip", "reconstruct.hip",
            "factorize.hip", "landmark.hip", "absorbed.hip", "quant.hip", "small_step.hip"]
 
 # packed-fp32 instructions are switched off on purpose (they have produced wrong results on the test machines)

@@ -708,7 +708,10 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
         else                                                                                                       \
             XKV_GA_LAUNCH(WV, RP, 0, KY);                                                                          \
     } while (0)
-    if (p.ga_waves == 8) {
+    if (keys && p.rope_regs[qbits == 0 ? 0 : qbits == 4 ? 1 : 2]) {
+        profile_begin(1, st);
+        e = launch_rope_keys(s, p, pa, A_k, B_packed, layer, idx, counts, rope_theta, qbits, logits, st);
+    } else if (p.ga_waves == 8) {
         if (keys)
             XKV_GA_LAUNCH_Q(8, true, true);
         else if (use_rope)
@@ -725,7 +728,7 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
     }
 #undef XKV_GA_LAUNCH_Q
 #undef XKV_GA_LAUNCH
-    e = hipGetLastError();
+    if (e == hipSuccess) e = hipGetLastError();
     if (!keys || e != hipSuccess) return e;
     e = launch_gather_absorb(s, p, pa, nullptr, A_v, B_packed, layer, idx, counts, part_o, part_ml, qbits, st, logits, true);
     profile_end(1, st);

@@ -29,7 +29,8 @@ static xkv_status validate(const xkv_shape *s)
     return XKV_OK;
 }
 
-// Whether rotated rows are faster in two halves, logits and then the values' sums from them.  That is a launch and a merge more (4 us);
+// Whether rotated rows are faster in two halves, logits (by gather_attend_mfma_kernel's KEYS form; see rope_keys_pays for the other)
+// and then the values' sums from them.  That is a launch and a merge more (4 us);
 // what it saves are the values' products, whose ranks the one-launch kernel pads to 256 and takes per row.  Its time goes by `len`, the
 // rows that a compute unit takes one after the other (tiles of 256 in rounds of 256 workgroups).  One launch / two halves, us, 4 query
 // heads on each of 8 KV heads: 4 bits, ranks 512: len 512 60 / 60, 768 77 / 74, 1024 104 / 96, 1536 136 / 112; ranks 384 len 512 61 /
@@ -118,7 +119,10 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     off = align_up(off + b * s.H_kv * (size_t)s.L * sizeof(float), 256);
     // Rotated rows: logits first, into the room of the projected queries and the pooled scores, which are done with by then
     const bool room = p.absorb && s.k < (1 << 24) && b * s.H_kv * (size_t)s.k * head_pitch_of(p.n_rep) * sizeof(float) <= off - p.off_p;
-    for (int i = 0; i < 3; ++i) p.rope_kept[i] = room && rope_kept_pays(s, p, i == 0 ? 0 : i == 1 ? 4 : 3);
+    for (int i = 0; i < 3; ++i) {
+        p.rope_kept[i] = room && rope_kept_pays(s, p, i == 0 ? 0 : i == 1 ? 4 : 3);
+        p.rope_regs[i] = room && rope_keys_ok(s) && (p.rope_kept[i] || rope_keys_pays(s, p));
+    }
     p.off_idx = off;
     off = align_up(off + b * s.H_kv * (size_t)s.k * sizeof(int32_t), 256);
     p.off_hist = off;

@@ -98,6 +98,7 @@ struct Plan {
     bool ga_mfma;      // shape fits the matrix-core gather-attend kernel
     int ga_waves;      // ... with this many wavefronts (32 selected tokens each) per workgroup
     bool absorb;       // ... and the one that keeps B_l out of the main loop (rows that are not rotated)
+    bool rope_regs[3]; // rotated rows whose logits come from rope_keys.hip (bf16, 4 and 3 bits)
     bool rope_kept[3]; // rotated rows in bf16, 4 and 3 bits: logits first (room for them from off_p on), then that kernel on the values
     int ab_occ, ab_splits, ab_chunk;  // its workgroups per compute unit, splits per (sequence, KV head), tokens per split
     size_t ab_lds;     // its LDS per workgroup
@@ -248,7 +249,8 @@ hipError_t launch_gather_prepare(const PackArgs &a, hipStream_t st);
 inline bool gather_uses_absorb(const Plan &p, float rope_theta) { return p.absorb && !(rope_theta > 0.0f); }
 inline bool gather_keeps_logits(const Plan &p, float rope_theta, int qbits)
 {
-    return rope_theta > 0.0f && p.rope_kept[qbits == 0 ? 0 : qbits == 4 ? 1 : 2];
+    const int form = qbits == 0 ? 0 : qbits == 4 ? 1 : 2;
+    return rope_theta > 0.0f && (p.rope_kept[form] || p.rope_regs[form]);
 }
 // Partials per query head that launch_gather_attend leaves for launch_combine: one per split, or (general kernel, mfma =
 // false) one per wavefront.
@@ -266,6 +268,11 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
                                 const void *B_packed, int layer, const int32_t *idx, const int32_t *counts, float *part_o,
                                 float *part_ml, int qbits, hipStream_t st, const float *heads = nullptr,
                                 bool by_place = false);
+// The logits of rotated rows alone (rope_keys.hip), [batch][H_kv][k][head_pitch].
+bool rope_keys_ok(const xkv_shape &s);
+bool rope_keys_pays(const xkv_shape &s, const Plan &p);
+hipError_t launch_rope_keys(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *B_packed, int layer,
+                            const int32_t *idx, const int32_t *counts, float rope_theta, int qbits, float *logits, hipStream_t st);
 bool gather_attend_mfma_shape_ok(const xkv_shape &s);
 int gather_attend_mfma_waves(const xkv_shape &s);
 size_t gather_attend_pack_bytes(const xkv_shape &s);        // Q^T fragments + one layer's packed B (workspace)
