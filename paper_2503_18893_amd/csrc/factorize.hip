@@ -459,34 +459,31 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
 
 // (3c) Cholesky factor Lc of G + shift I, right-looking in panels of PB columns, and beside it the inverses of the
 // diagonal blocks.  A launch has two kinds of workgroups:
-//   * workgroup j >= 1 owns the 32 rows from c0 + PB + 32 (j - 1) of G and touches nothing else.  The panel entries
-//     Lc[j'][c0 .. c0 + PB) of all rows below the diagonal block down to its own last row are G[j'][panel] times the
-//     transposed inverse of the diagonal block's factor (fp64 matrix cores, 16 rows a step) and stay in LDS; it subtracts
-//     the panel's outer product from its own rows of the trailing matrix, G[i][j'] -= Lc[i] . Lc[j'].  Own rows of the
-//     panel are written to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a later substitution
-//     needs is a contiguous row;
+//   * the others own a 32 x 32 block of the trailing matrix each, on or below the diagonal.  The panel entries Lc[j'][c0 .. c0 + PB)
+//     of its rows and of its columns are G[j'][panel] times the transposed inverse of the diagonal block's factor (fp64 matrix
+//     cores, 16 rows a step) and stay in LDS; their product is subtracted.  The first block of a row also writes the panel's rows
+//     to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a later substitution needs is a contiguous row;
 //   * workgroup 0 prepares the next panel: it brings the next diagonal block up to date by itself (its 32 panel rows and one
 //     outer product), factors and inverts it, and leaves the inverse in LI for the next launch (two places in turn, the
 //     other workgroups of this launch still read theirs), the factor's columns in Lt and the inverses of the 16 x 16
 //     diagonal blocks in Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity).  The first launch, c0 = -PB,
 //     has only this workgroup.
-// The elimination runs in one wavefront without a barrier: lane i holds row i of the block and lane 32 + i column i of an
+// The elimination runs in one wavefront without a barrier, 16 columns at a time: a lane holds a row of the block or a column of an
 // identity, and step c is the same for both: t = x[c] / sqrt(pivot), x[j] -= (t of lane j) t for j > c.  What t leaves in
-// the lanes are column c of the factor and row c of its inverse.  The elements move one register down at each step, so
-// that the steps are a loop.
+// the lanes are column c of the factor and row c of its inverse.  Between the two halves of a block of 32 the lower right quarter and
+// the start of the inverse's lower left quarter are brought up to date with eight matrix instructions.
 // shift = 1e-13 * max diagonal of the original G (diag0) keeps the factor defined when the r vectors are
 // numerically dependent (an X_cat of rank below r): such directions come out short instead of normalised and
 // contribute nothing to A B.
-// What bounds it: the chain of its 16 launches at r = 512, and in each the elimination (PB dependent steps, 9 us), which
-// here runs beside the trailing update of the same launch.  Every workgroup eliminating the block before its update
-// took 29 us per launch on average, now 21.6 us.
+// What bounds it: the chain of its 16 launches at r = 512, each of which is workgroup 0: 9.8 us without a panel before it, 12
+// with it.  32 steps on rows of 32 elements with scalar broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with
+// workgroups of 32 whole rows, 25 us in the first launches and 14 in the last; blocks of 32 x 32 12 in all of them.
 constexpr int kCholRB = 32, kCholThreads = 512, kSolveIB = 16;
 constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
-constexpr size_t chol_lds(int pb, int rows)  // panel rows below the diagonal block; workgroup 0: its rows and two blocks
+constexpr size_t chol_lds(int pb)  // 64 rows of the panel; workgroup 0: its rows and three blocks
 {
-    const size_t all = (size_t)((rows + 15) / 16 * 16) * chol_pitch(pb);
-    const size_t head = (size_t)pb * chol_pitch(pb) + 3 * (size_t)pb * (pb + 1);
-    return (all > head ? all : head) * 8;
+    const size_t rows = 2 * (size_t)kCholRB * chol_pitch(pb), head = (size_t)pb * chol_pitch(pb) + 3 * (size_t)pb * (pb + 1);
+    return (rows > head ? rows : head) * 8;
 }
 
 // 1 / sqrt(x): the hardware's estimate y (better than 2^-20) and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with
@@ -497,9 +494,19 @@ __device__ __forceinline__ double fz_rsqrt(double x)
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-__device__ __forceinline__ double fz_readlane(double x, int l)
+// The value of lane N of the same 16.
+template <int N> __device__ __forceinline__ double fz_lane_of_16(double x)
 {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + N, 0xF, 0xF, false);  // row_newbcast
+}
+
+// f(I), f(I + 1) .. with the index as a type
+template <int I, int END, typename F> __device__ __forceinline__ void fz_for(F f)
+{
+    if constexpr (I < END) {
+        f(std::integral_constant<int, I>{});
+        fz_for<I + 1, END>(f);
+    }
 }
 
 template <int PB>
@@ -508,7 +515,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
                                                                   double *LI_next, long long li_seq,
                                                                   const double *__restrict__ diag0, int r, int c0)
 {
-    constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64, NB = 4;
+    constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64;
     G += (size_t)blockIdx.z * r * r;
     Lt += (size_t)blockIdx.z * r * r;
     Minv += (size_t)blockIdx.z * ((r + kSolveIB - 1) / kSolveIB) * (kSolveIB * kSolveIB);
@@ -519,31 +526,20 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), l16 = lane & 15, kk = lane >> 4;
     const int d0 = c0 + PB;  // first row below the diagonal block
 
-    // the inverse as the second operand of the product with the panel (rows of the inverse = columns of the result)
-    double lb[CT][KS];
+    // Sixteen rows of the panel, from `row0` on, times columns 16 ct .. of the transposed inverse -> rows `at` .. of P
+    auto panel_tile = [&](int row0, int ct, int at) __attribute__((always_inline)) {
+        double ga[KS], lb[KS];
+        const int row = row0 + l16;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) lb[ct][ks] = c0 >= 0 ? LI_now[(16 * ct + l16) * PB + 4 * ks + kk] : 0.0;
-    double ga[NB][KS];
-    auto fetch = [&](int q0, int n_q, int end) __attribute__((always_inline)) {  // 16 rows each, blocks q0, q0 + WAVES, ..
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int row = d0 + 16 * (q0 + WAVES * u) + l16;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                ga[u][ks] = (q0 + WAVES * u < n_q && row < end) ? G[(size_t)row * r + c0 + 4 * ks + kk] : 0.0;
+        for (int ks = 0; ks < KS; ++ks) {
+            ga[ks] = row < r ? G[(size_t)row * r + c0 + 4 * ks + kk] : 0.0;
+            lb[ks] = LI_now[(16 * ct + l16) * PB + 4 * ks + kk];
         }
-    };
-    auto panel_rows = [&](int q, const double (&g)[KS]) __attribute__((always_inline)) {
+        fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+        for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[ks], lb[ks], acc, 0, 0, 0);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(g[ks], lb[ct][ks], acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) P[(16 * q + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
-        }
+        for (int v = 0; v < 4; ++v) P[(at + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
     };
     auto outer = [&](int rs, int cs) __attribute__((always_inline)) {  // tile of 16 x 16 of the panel's outer product
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
@@ -554,40 +550,33 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     };
 
     if (blockIdx.x > 0) {
-        const int i0 = d0 + ((int)blockIdx.x - 1) * kCholRB;
-        const int own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
-        const int n_q = (own_end - d0 + 15) / 16;
-        for (int q0 = w; q0 < n_q; q0 += WAVES * NB) {
-            fetch(q0, n_q, own_end);
+        int bi, bj;
+        fz_lower_pair((int)blockIdx.x - 1, bi, bj);
+        const int i0 = d0 + kCholRB * bi, j0 = d0 + kCholRB * bj, own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
+        // tile (w / 2 % 2, w % 2) of the block for wavefronts 0 .. 3, requested first
+        const int rt = (w >> 1) & 1, ctile = w & 1, jc = j0 + 16 * ctile + l16;
+        double old[4];
 #pragma unroll
-            for (int u = 0; u < NB; ++u)
-                if (q0 + WAVES * u < n_q) panel_rows(q0 + WAVES * u, ga[u]);
+        for (int v = 0; v < 4; ++v) {
+            const int irow = i0 + 16 * rt + kk + 4 * v;
+            old[v] = (w < 4 && irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
+        }
+        // rows of the panel: 32 of the block's rows, 32 of its columns
+        for (int item = w; item < (bi == bj ? 2 : 4) * CT; item += WAVES) {
+            const int half = item / (2 * CT), rest = item % (2 * CT);
+            panel_tile((half ? j0 : i0) + 16 * (rest / CT), rest % CT, kCholRB * half + 16 * (rest / CT));
         }
         __syncthreads();
-        for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
-            const int c = t / kCholRB, row = i0 + t % kCholRB;
-            if (row < own_end) Lt[(size_t)(c0 + c) * r + row] = P[(row - d0) * PITCH + c];
-        }
-        // own rows of the trailing matrix: tiles on or below the diagonal
-        const int own_t = (i0 - d0) / 16, n_rt = (own_end - i0 + 15) / 16;  // row tile rt has own_t + rt + 1 column tiles
-        for (int item = w;; item += WAVES) {
-            int rt = 0, ctile = item;
-            while (rt < n_rt && ctile > own_t + rt) {
-                ctile -= own_t + rt + 1;
-                ++rt;
+        if (bj == 0)
+            for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
+                const int c = t / kCholRB, row = i0 + t % kCholRB;
+                if (row < own_end) Lt[(size_t)(c0 + c) * r + row] = P[(row - i0) * PITCH + c];
             }
-            if (rt >= n_rt) break;
-            const int rs = i0 - d0 + 16 * rt, cs = 16 * ctile;
-            double old[4];
+        if (w < 4 && !(bi == bj && ctile > rt)) {
+            const fz_f64x4_t acc = outer(16 * rt, (bi == bj ? 0 : kCholRB) + 16 * ctile);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int irow = d0 + rs + kk + 4 * v, jc = d0 + cs + l16;
-                old[v] = (irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
-            }
-            const fz_f64x4_t acc = outer(rs, cs);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int irow = d0 + rs + kk + 4 * v, jc = d0 + cs + l16;
+                const int irow = i0 + 16 * rt + kk + 4 * v;
                 // (the next diagonal block is workgroup 0's: it reads what this launch began with)
                 if (irow < own_end && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
             }
@@ -608,10 +597,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
         const int i = 16 * tr + kk + 4 * v, j = 16 * tc + l16;
         g0[0][v] = (w < CT * CT && i < pwc && j <= i) ? G[(size_t)(d0 + i) * r + d0 + j] : 0.0;
     }
-    if (c0 >= 0 && w < CT) {
-        fetch(w, CT, d0 + pwc);
-        panel_rows(w, ga[0]);
-    }
+    if (c0 >= 0 && w < CT * CT) panel_tile(d0 + 16 * tr, tc, 16 * tr);  // (rows beyond the matrix are zero)
     for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
     if (lane == 0) red[w] = mx;
     __syncthreads();
@@ -630,30 +616,59 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     }
     __syncthreads();
     if (w == 0) {
-        const int i = lane & 31;
-        const bool lower = lane < 32;
-        double x[PB];  // x[j]: element c + j of row i of the block, or of column i of the identity, at step c
+        // 16 columns at a time.  Every 16 lanes hold the block's lower triangle, lane l16 row l16 (x), and beside it (y) the lanes kk = 1
+        // column l16 of an identity, kk = 2 row l16 of the block's lower left quarter, then column l16 of what the inverse's lower left
+        // quarter comes from
+        double x[16], y[16];
 #pragma unroll
-        for (int j = 0; j < PB; ++j) x[j] = i >= PB ? 0.0 : lower ? D[i * LP + j] : (i == j ? 1.0 : 0.0);
-        double *out = lower ? LF + i * LP : LI + i;
-        const int step = lower ? 1 : LP;
-        auto steps = [&](auto first) __attribute__((always_inline)) {  // eight steps of at most PB - 1 - C0 elements
-            constexpr int C0 = decltype(first)::value, W = PB - 1 - C0;
+        for (int j = 0; j < 16; ++j) {
+            x[j] = D[l16 * LP + j];
+            y[j] = kk == 1 ? (l16 == j ? 1.0 : 0.0) : PB == 32 && kk == 2 ? D[(PB - 16 + l16) * LP + j] : 0.0;
+        }
+        double *out = kk == 0 ? LF + l16 * LP : kk == 1 ? LI + l16 : kk == 2 ? LF + (PB - 16 + l16) * LP : LI + PB - 16 + l16;
+        int step = kk & 1 ? LP : 1;
+        bool store = PB == 32 || kk < 2;
 #pragma unroll 1
-            for (int c = C0; c < C0 + 8; ++c) {
-                double piv = fz_readlane(x[0], c);
+        for (int half = 0; half < CT; ++half) {
+            fz_for<0, 16>([&](auto cc) __attribute__((always_inline)) {
+                constexpr int c = decltype(cc)::value;
+                double piv = fz_lane_of_16<c>(x[c]);
                 piv = piv > shift * 1e-3 ? piv : shift * 1e-3;
-                const double t = lane < c ? 0.0 : x[0] * fz_rsqrt(piv);
-                if (i < PB) out[c * step] = t;
+                const double rs = fz_rsqrt(piv), t = l16 < c ? 0.0 : x[c] * rs, ty = y[c] * rs;
+                if (store) out[c * step] = kk == 0 ? t : ty;
+                fz_for<c + 1, 16>([&](auto jj) __attribute__((always_inline)) {
+                    constexpr int j = decltype(jj)::value;
+                    const double tj = fz_lane_of_16<j>(t);
+                    x[j] = fma(tj, -t, x[j]);
+                    y[j] = fma(tj, -ty, y[j]);
+                });
+            });
+            if (half + 1 == CT) break;
+            // lower right quarter minus the product of the lower left quarter of the factor with itself; and minus its product with the
+            // inverse of the upper left one
+            __builtin_amdgcn_wave_barrier();
+            double *F = LF + 16 * LP, *Q = D + 16 * LP;  // (Q: the quarters of D that were read above)
+            fz_f64x4_t s0 = fz_f64x4_t{0.0, 0.0, 0.0, 0.0}, s1 = s0;
 #pragma unroll
-                for (int j = 1; j <= W; ++j) x[j - 1] = fma(-fz_readlane(t, c + j), t, x[j]);
+            for (int ks = 0; ks < 4; ++ks) {
+                const double f = F[l16 * LP + 4 * ks + kk], v = LI[(4 * ks + kk) * LP + l16];
+                s0 = __builtin_amdgcn_mfma_f64_16x16x4f64(f, f, s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f64_16x16x4f64(f, v, s1, 0, 0, 0);
             }
-        };
-        steps(std::integral_constant<int, 0>{});
-        steps(std::integral_constant<int, 8>{});
-        if constexpr (PB == 32) {
-            steps(std::integral_constant<int, 16>{});
-            steps(std::integral_constant<int, 24>{});
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                Q[(kk + 4 * v) * LP + 16 + l16] -= s0[v];
+                Q[(kk + 4 * v) * LP + l16] = -s1[v];
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                x[j] = Q[l16 * LP + 16 + j];
+                y[j] = kk == 1 ? (l16 == j ? 1.0 : 0.0) : kk == 2 ? Q[j * LP + l16] : 0.0;
+            }
+            out = kk == 0 ? LF + (16 + l16) * LP + 16 : LI + 16 * LP + (kk == 1 ? 16 : 0) + l16;
+            step = kk == 0 ? 1 : LP;
+            store = kk < 3;
         }
     }
     __syncthreads();
@@ -1341,10 +1356,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
     double *Minv = reinterpret_cast<double *>(ws + f.off_minv);
     int *rotations = reinterpret_cast<int *>(ws + f.off_rot);
     static_assert(kJacobiSweeps <= 16, "the rotation counters have 16 slots per sequence");
-    static DynamicLdsOnce attr_c32, attr_c16;
-    static_assert(chol_lds(32, 512) <= 160 * 1024 - 256 && chol_lds(16, 1024) <= 160 * 1024 - 256, "the panel fits the LDS");
-    if (hipError_t e0 = attr_c32.ensure((const void *)chol_panel_kernel<32>, 160 * 1024 - 256); e0 != hipSuccess) return e0;
-    if (hipError_t e0 = attr_c16.ensure((const void *)chol_panel_kernel<16>, 160 * 1024 - 256); e0 != hipSuccess) return e0;
+    static_assert(chol_lds(32) <= 64 * 1024 - 256 && chol_lds(16) <= 64 * 1024 - 256, "no raised LDS limit needed");
     hipError_t e = hipSuccess;
     const long long vcount = (long long)r * n, x_seq = (long long)n * s.L;
     for (int b0 = 0; b0 < s.batch && e == hipSuccess; b0 += f.bc) {
@@ -1380,8 +1392,9 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
             const int pb = f.chol_pb;
             const long long li_seq = (long long)f.g_splits * r * r;
             for (int c0 = -pb; c0 + pb < r; c0 += pb) {
-                const dim3 grid(1 + std::max(0, c0 < 0 ? 0 : (r - c0 - pb + kCholRB - 1) / kCholRB), 1, nb);
-                const size_t lds = chol_lds(pb, c0 < 0 ? 0 : r - c0 - pb);
+                const int blocks = c0 < 0 ? 0 : (r - c0 - pb + kCholRB - 1) / kCholRB;
+                const dim3 grid(1 + blocks * (blocks + 1) / 2, 1, nb);
+                const size_t lds = chol_lds(pb);
                 double *now = planes + ((c0 / pb) & 1) * pb * pb, *next = planes + ((c0 / pb + 1) & 1) * pb * pb;
                 if (c0 + 2 * pb >= r) next = nullptr;
                 if (pb == 32)
