@@ -457,17 +457,18 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
     if (i == j) diag0[i] = v;
 }
 
-// (3c) Cholesky factor Lc of G + shift I, right-looking in panels of PB columns, and beside it the inverses of the
-// diagonal blocks.  A launch has two kinds of workgroups:
-//   * the others own a 32 x 32 block of the trailing matrix each, on or below the diagonal.  The panel entries Lc[j'][c0 .. c0 + PB)
-//     of its rows and of its columns are G[j'][panel] times the transposed inverse of the diagonal block's factor (fp64 matrix
-//     cores, 16 rows a step) and stay in LDS; their product is subtracted.  The first block of a row also writes the panel's rows
-//     to Lt transposed (Lt[k][i] = Lc[i][k], i >= k), so that the column of Lc a later substitution needs is a contiguous row;
+// (3c) The inverse Li of the Cholesky factor Lc of G + shift I, right-looking in panels of PB columns: the factor's columns are eliminated from
+// the trailing matrix and, the same way, from the rows of an identity that becomes the inverse.  A launch has three kinds of
+// workgroups, for the panel c0 .. c0 + PB - 1, whose diagonal block of Li is there:
+//   * 32 x 32 blocks of the trailing matrix, on or below the diagonal.  The panel entries Lc[j'][c0 .. c0 + PB) of its rows and of its
+//     columns are G[j'][panel] times the transposed diagonal block of Li (fp64 matrix cores, 16 rows a step) and stay in LDS; their
+//     product is subtracted;
+//   * 32 x 32 blocks of the unfinished inverse X: rows below the panel, columns up to its end.  The panel's rows of X times the diagonal
+//     block of Li are the final rows of Li (written by the first block of each column); with the panel entries of the block's rows
+//     they are subtracted.  X lies transposed above the diagonal of G, which the factorization does not use;
 //   * workgroup 0 prepares the next panel: it brings the next diagonal block up to date by itself (its 32 panel rows and one
-//     outer product), factors and inverts it, and leaves the inverse in LI for the next launch (two places in turn, the
-//     other workgroups of this launch still read theirs), the factor's columns in Lt and the inverses of the 16 x 16
-//     diagonal blocks in Minv[b][ii][jj] = (Lc_bb^-1)[ii][jj] (rows beyond r: identity).  The first launch, c0 = -PB,
-//     has only this workgroup.
+//     outer product), factors and inverts it and leaves the inverse in Li.  The first launch, c0 = -PB, has only this
+//     workgroup; in the last, the last panel's, it has nothing to do.
 // The elimination runs in one wavefront without a barrier, 16 columns at a time: a lane holds a row of the block or a column of an
 // identity, and step c is the same for both: t = x[c] / sqrt(pivot), x[j] -= (t of lane j) t for j > c.  What t leaves in
 // the lanes are column c of the factor and row c of its inverse.  Between the two halves of a block of 32 the lower right quarter and
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
 // What bounds it: the chain of its 16 launches at r = 512, each of which is workgroup 0: 9.8 us without a panel before it, 12
 // with it.  32 steps on rows of 32 elements with scalar broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with
 // workgroups of 32 whole rows, 25 us in the first launches and 14 in the last; blocks of 32 x 32 12 in all of them.
-constexpr int kCholRB = 32, kCholThreads = 512, kSolveIB = 16;
+constexpr int kCholRB = 32, kCholThreads = 512;
 constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
 constexpr size_t chol_lds(int pb)  // 64 rows of the panel; workgroup 0: its rows and three blocks
 {
@@ -510,36 +511,43 @@ template <int I, int END, typename F> __device__ __forceinline__ void fz_for(F f
 }
 
 template <int PB>
-__global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Lt,
-                                                                  double *__restrict__ Minv, const double *LI_now,
-                                                                  double *LI_next, long long li_seq,
+__global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Li,
                                                                   const double *__restrict__ diag0, int r, int c0)
 {
     constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64;
     G += (size_t)blockIdx.z * r * r;
-    Lt += (size_t)blockIdx.z * r * r;
-    Minv += (size_t)blockIdx.z * ((r + kSolveIB - 1) / kSolveIB) * (kSolveIB * kSolveIB);
-    LI_now += blockIdx.z * li_seq;
+    Li += (size_t)blockIdx.z * r * r;
     diag0 += (size_t)blockIdx.z * r;
     extern __shared__ __attribute__((aligned(16))) unsigned char fz_smem[];
     double *P = reinterpret_cast<double *>(fz_smem);  // [rows][PITCH] panel entries of Lc
     const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), l16 = lane & 15, kk = lane >> 4;
     const int d0 = c0 + PB;  // first row below the diagonal block
 
-    // Sixteen rows of the panel, from `row0` on, times columns 16 ct .. of the transposed inverse -> rows `at` .. of P
-    auto panel_tile = [&](int row0, int ct, int at) __attribute__((always_inline)) {
+    // Sixteen rows (value(row, k): row l16, column k of PB) times columns 16 ct .. of the transposed inverse of the panel's diagonal block
+    // -> rows `at` .. of P
+    auto times_inverse = [&](auto value, int ct, int at) __attribute__((always_inline)) {
         double ga[KS], lb[KS];
-        const int row = row0 + l16;
+        const int ir = c0 + 16 * ct + l16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            ga[ks] = row < r ? G[(size_t)row * r + c0 + 4 * ks + kk] : 0.0;
-            lb[ks] = LI_now[(16 * ct + l16) * PB + 4 * ks + kk];
+            ga[ks] = value(4 * ks + kk);
+            lb[ks] = (ir < r && c0 + 4 * ks + kk < r) ? Li[(size_t)ir * r + c0 + 4 * ks + kk] : 0.0;
         }
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[ks], lb[ks], acc, 0, 0, 0);
 #pragma unroll
         for (int v = 0; v < 4; ++v) P[(at + kk + 4 * v) * PITCH + 16 * ct + l16] = acc[v];
+    };
+    auto panel_tile = [&](int row0, int ct, int at) __attribute__((always_inline)) {  // rows of the factor
+        const int row = row0 + l16;
+        times_inverse([&](int k) __attribute__((always_inline)) { return row < r ? G[(size_t)row * r + c0 + k] : 0.0; }, ct, at);
+    };
+    auto inverse_tile = [&](int col0, int ct, int at) __attribute__((always_inline)) {  // columns of the panel's rows of the inverse
+        const int col = col0 + l16;
+        times_inverse([&](int k) __attribute__((always_inline)) {
+            return col < c0 ? (c0 + k < r ? G[(size_t)col * r + c0 + k] : 0.0) : col == c0 + k ? 1.0 : 0.0;
+        }, ct, at);
     };
     auto outer = [&](int rs, int cs) __attribute__((always_inline)) {  // tile of 16 x 16 of the panel's outer product
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
@@ -550,39 +558,70 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     };
 
     if (blockIdx.x > 0) {
+        const int nb = (r - d0 + kCholRB - 1) / kCholRB, n_tri = nb > 0 ? nb * (nb + 1) / 2 : 0;
+        const bool inverse = (int)blockIdx.x - 1 >= n_tri;
         int bi, bj;
-        fz_lower_pair((int)blockIdx.x - 1, bi, bj);
-        const int i0 = d0 + kCholRB * bi, j0 = d0 + kCholRB * bj, own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
-        // tile (w / 2 % 2, w % 2) of the block for wavefronts 0 .. 3, requested first
+        if (inverse) {
+            const int x = (int)blockIdx.x - 1 - n_tri, n_cb = (d0 + kCholRB - 1) / kCholRB;
+            bi = x / n_cb;
+            bj = x % n_cb;
+        } else {
+            fz_lower_pair((int)blockIdx.x - 1, bi, bj);
+        }
+        const int i0 = d0 + kCholRB * bi, j0 = (inverse ? 0 : d0) + kCholRB * bj, own_end = (i0 + kCholRB) < r ? (i0 + kCholRB) : r;
+        // tile (w / 2 % 2, w % 2) of the block for wavefronts 0 .. 3, requested first: rows i0 .., columns j0 .. of the trailing matrix, or
+        // columns j0 .., rows i0 .. of the inverse, which lies transposed above the diagonal
         const int rt = (w >> 1) & 1, ctile = w & 1, jc = j0 + 16 * ctile + l16;
         double old[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int irow = i0 + 16 * rt + kk + 4 * v;
-            old[v] = (w < 4 && irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
+            if (inverse) {
+                const int col = j0 + 16 * ctile + kk + 4 * v, irow = i0 + 16 * rt + l16;
+                old[v] = (w < 4 && irow < own_end && col < c0) ? G[(size_t)col * r + irow] : 0.0;
+            } else {
+                const int irow = i0 + 16 * rt + kk + 4 * v;
+                old[v] = (w < 4 && irow < own_end && jc <= irow) ? G[(size_t)irow * r + jc] : 0.0;
+            }
         }
-        // rows of the panel: 32 of the block's rows, 32 of its columns
-        for (int item = w; item < (bi == bj ? 2 : 4) * CT; item += WAVES) {
-            const int half = item / (2 * CT), rest = item % (2 * CT);
-            panel_tile((half ? j0 : i0) + 16 * (rest / CT), rest % CT, kCholRB * half + 16 * (rest / CT));
+        // panel entries of the block's 32 rows; of its 32 columns
+        const bool square = !inverse && bi == bj;
+        for (int item = w; item < (square ? 2 : 4) * CT; item += WAVES) {
+            const int half = item / (2 * CT), rest = item % (2 * CT), ct = rest % CT, at = 16 * (rest / CT);
+            if (half == 0)
+                panel_tile(i0 + at, ct, at);
+            else if (inverse)
+                inverse_tile(j0 + at, ct, kCholRB + at);
+            else
+                panel_tile(j0 + at, ct, kCholRB + at);
         }
         __syncthreads();
-        if (bj == 0)
+        if (inverse && bi == 0)  // the panel's rows of the inverse are final (its diagonal block is there already)
             for (int t = tid; t < PB * kCholRB; t += kCholThreads) {
-                const int c = t / kCholRB, row = i0 + t % kCholRB;
-                if (row < own_end) Lt[(size_t)(c0 + c) * r + row] = P[(row - i0) * PITCH + c];
+                const int row = c0 + t / kCholRB, col = j0 + t % kCholRB;
+                if (row < r && col < c0) Li[(size_t)row * r + col] = P[(kCholRB + col - j0) * PITCH + row - c0];
             }
-        if (w < 4 && !(bi == bj && ctile > rt)) {
-            const fz_f64x4_t acc = outer(16 * rt, (bi == bj ? 0 : kCholRB) + 16 * ctile);
+        if (w < 4 && !(square && ctile > rt)) {
+            if (inverse) {
+                const fz_f64x4_t acc = outer(kCholRB + 16 * ctile, 16 * rt);
+                const int irow = i0 + 16 * rt + l16;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int irow = i0 + 16 * rt + kk + 4 * v;
-                // (the next diagonal block is workgroup 0's: it reads what this launch began with)
-                if (irow < own_end && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
+                for (int v = 0; v < 4; ++v) {
+                    const int col = j0 + 16 * ctile + kk + 4 * v;
+                    if (irow < own_end && col < d0) G[(size_t)col * r + irow] = old[v] - acc[v];
+                }
+            } else {
+                const fz_f64x4_t acc = outer(16 * rt, (square ? 0 : kCholRB) + 16 * ctile);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int irow = i0 + 16 * rt + kk + 4 * v;
+                    // (the next diagonal block is workgroup 0's: it reads what this launch began with)
+                    if (irow < own_end && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
+                }
             }
         }
         return;
     }
+    if (d0 >= r) return;  // (the last launch: the last panel's rows of the inverse)
 
     // ---- workgroup 0: the next diagonal block, rows and columns d0 .. d0 + pwc - 1
     double *D = P + PB * PITCH, *LF = D + PB * LP, *LI = LF + PB * LP;  // [PB][LP] block, its factor, the inverse
@@ -673,95 +712,92 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     }
     __syncthreads();
     for (int t = tid; t < PB * PB; t += kCholThreads) {
-        const int c = t / PB, i = t % PB;
-        if (i < pwc && c <= i) Lt[(size_t)(d0 + c) * r + d0 + i] = LF[i * LP + c];
-        if (LI_next) (LI_next + blockIdx.z * li_seq)[t] = LI[c * LP + i];
-        const int ii = c & 15, jj = i & 15;
-        if (c / 16 == i / 16 && d0 + (c & ~15) < r) Minv[(size_t)((d0 + c) / 16) * 256 + ii * 16 + jj] = LI[c * LP + i];
+        const int row = t / PB, col = t % PB;
+        if (row < pwc && col < pwc) Li[(size_t)(d0 + row) * r + d0 + col] = LI[row * LP + col];
+        // (what reads the inverse goes by blocks of 32 columns)
+        if (PB == 16 && d0 % 32 == 0 && row < pwc && d0 + PB + col < r) Li[(size_t)(d0 + row) * r + d0 + PB + col] = 0.0;
     }
 }
 
-// (3d) V = Lc^-1 W by blocked forward substitution on the fp64 matrix cores.  Rows of W^T (Wn [n][r]) are
-// independent; a workgroup of 4 wavefronts takes 16 RT of them and keeps them in registers as 16 x 16 accumulator
-// tiles (tile t = columns 16 t .. 16 t + 15, owned by wavefront t % 4).  For tile I in turn: its owner hands the
-// values to LDS, the threads multiply them by the inverse of the diagonal block (the final rows 16 I .. 16 I + 15
-// of V for these n, written out as fp32), and every wavefront subtracts V_I Lc[16 t .., 16 I ..]^T from its tiles
-// t > I (four matrix-core steps per tile and row group; the Lc operands come straight from global memory and are
-// requested before the block inverse is applied, the block inverse itself one block ahead).
-template <int MAXT, int RT>  // tiles per wavefront (r <= 64 MAXT), groups of 16 rows per workgroup
-__global__ __launch_bounds__(256) void orth_solve_kernel(const float *__restrict__ Wn, const double *__restrict__ Lt,
-                                                         const double *__restrict__ Minv, float *__restrict__ Vt, int n, int r)
+// (3d) V = Lc^-1 W: Vt[i][n] = sum over c <= i of Li[i][c] Wn[n][c] on the fp64 matrix cores, written as fp32.  A wavefront makes tiles of 32
+// x 32, the four of a workgroup next to each other in n; it takes a block of 32 rows of Vt from the bottom, whose sums are long, and
+// one from the top, so that all are equally long.  Of 16 values of c a lane asks for four in a row, two such steps ahead.
+// What bounds it: the matrix cores (16 us of products at r = 512, n = 4096).  Forward substitution in blocks of 16, the factor instead of
+// its inverse, took 121 us: 32 dependent steps of two barriers.
+template <bool VEC>  // r a multiple of four
+__global__ __launch_bounds__(256) void orth_apply_kernel(const float *__restrict__ Wn, const double *__restrict__ Li, float *__restrict__ Vt,
+                                                         int n, int r)
 {
     Wn += (size_t)blockIdx.z * n * r;
-    Lt += (size_t)blockIdx.z * r * r;
-    Minv += (size_t)blockIdx.z * ((r + 15) / 16) * 256;
+    Li += (size_t)blockIdx.z * r * r;
     Vt += (size_t)blockIdx.z * n * r;
-    __shared__ double wt[16 * RT][17], vblk[16 * RT][17], minv_s[16][17];
-    const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), col = lane & 15, kk = lane >> 4;
-    const int n0 = blockIdx.x * (16 * RT), n_tiles = (r + 15) / 16;
-    fz_f64x4_t acc[RT][MAXT];
+    const int lane = lane_id(), w = wave_id(), l16 = lane & 15, kk = lane >> 4;
+    const int n0 = blockIdx.x * 128 + 32 * w, n_blocks = (r + 31) / 32;
+    if (n0 >= n) return;
+    struct Step {
+        double a[2][4];
+        float b[2][4];
+    };
+    for (int turn = 0; turn < 2; ++turn) {
+        const int blk = turn == 0 ? n_blocks - 1 - (int)blockIdx.y : (int)blockIdx.y;
+        if (turn == 1 && blk == n_blocks - 1 - (int)blockIdx.y) break;
+        const int i0 = 32 * blk, c_end = i0 + 32 < r ? i0 + 32 : r, steps = (c_end + 15) / 16;
+        auto fetch = [&](Step &x, int step) __attribute__((always_inline)) {
+            const int c = 16 * step + 4 * kk;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+            for (int u = 0; u < 2; ++u) {
+                const int i = i0 + 16 * u + l16;
+                const double *pa = Li + (size_t)(i < r ? i : 0) * r + c;
+                const float *pb = Wn + (size_t)(n0 + 16 * u + l16) * r + c;
+                if constexpr (VEC) {
+                    const bool in = c < c_end;  // (whole quads)
+                    const fz_f64x2_t lo = in && i < r ? *reinterpret_cast<const fz_f64x2_t *>(pa) : fz_f64x2_t{0.0, 0.0};
+                    const fz_f64x2_t hi = in && i < r ? *reinterpret_cast<const fz_f64x2_t *>(pa + 2) : fz_f64x2_t{0.0, 0.0};
+                    const fz_f32x4_t v = in ? *reinterpret_cast<const fz_f32x4_t *>(pb) : fz_f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                    x.a[u][0] = lo[0], x.a[u][1] = lo[1], x.a[u][2] = hi[0], x.a[u][3] = hi[1];
 #pragma unroll
-        for (int u = 0; u < MAXT; ++u) {
-            const int c = 16 * (w + 4 * u) + col;
+                    for (int q = 0; q < 4; ++q) x.b[u][q] = v[q];
+                } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = n0 + 16 * rt + kk + 4 * e;
-                acc[rt][u][e] = (c < r && row < n) ? (double)Wn[(size_t)row * r + c] : 0.0;
-            }
-        }
-    const int s_row = tid >> 4, s_ii = tid & 15;  // role when the block inverse is applied: outputs (s_row + 16 rt, ii)
-    double mi = Minv[tid];
-    for (int I = 0; I < n_tiles; ++I) {
-        // operands of the update for this wavefront's tiles behind I: Lc[16 t + col][16 I + 4 g + kk]
-        double bop[MAXT][4];
-#pragma unroll
-        for (int u = 0; u < MAXT; ++u) {
-            const int t = w + 4 * u, c = 16 * t + col;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int lrow = 16 * I + 4 * g + kk;
-                bop[u][g] = (t > I && c < r && lrow < r) ? Lt[(size_t)lrow * r + c] : 0.0;
-            }
-        }
-        if ((I & 3) == w) {
-#pragma unroll
-            for (int u = 0; u < MAXT; ++u)
-                if (u == (I >> 2)) {
-#pragma unroll
-                    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) wt[16 * rt + kk + 4 * e][col] = acc[rt][u][e];
-                }
-        }
-        minv_s[tid >> 4][tid & 15] = mi;
-        if (I + 1 < n_tiles) mi = Minv[(size_t)(I + 1) * 256 + tid];
-        __syncthreads();
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            double v = 0.0;
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) v += minv_s[s_ii][jj] * wt[16 * rt + s_row][jj];  // entries jj > ii of the inverse are zero
-            vblk[16 * rt + s_row][s_ii] = v;
-            const int row = n0 + 16 * rt + s_row;
-            if (16 * I + s_ii < r && row < n) Vt[(size_t)(16 * I + s_ii) * n + row] = (float)v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            double aop[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) aop[g] = -vblk[16 * rt + col][4 * g + kk];
-#pragma unroll
-            for (int u = 0; u < MAXT; ++u) {
-                if (w + 4 * u > I && w + 4 * u < n_tiles) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        acc[rt][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(aop[g], bop[u][g], acc[rt][u], 0, 0, 0);
+                    for (int q = 0; q < 4; ++q) {
+                        x.a[u][q] = c + q < c_end && i < r ? pa[q] : 0.0;
+                        x.b[u][q] = c + q < c_end ? pb[q] : 0.0f;
+                    }
                 }
             }
+        };
+        fz_f64x4_t acc[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) acc[u][v] = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+        auto multiply = [&](const Step &x) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int v = 0; v < 2; ++v)
+                        acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a[u][q], (double)x.b[v][q], acc[u][v], 0, 0, 0);
+        };
+        Step s0, s1;
+        fetch(s0, 0);
+        fetch(s1, steps > 1 ? 1 : 0);
+        for (int step = 0; step < steps; step += 2) {
+            multiply(s0);
+            if (step + 2 < steps) fetch(s0, step + 2);
+            if (step + 1 < steps) multiply(s1);
+            if (step + 3 < steps) fetch(s1, step + 3);
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = i0 + 16 * u + kk + 4 * e;
+                    if (i < r) Vt[(size_t)i * n + n0 + 16 * v + l16] = (float)acc[u][v][e];
+                }
     }
 }
 
@@ -1387,27 +1423,21 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                                planes, n, r, f.g_splits, pairs);
             hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                f.g_splits);
-            // the inverse of a panel's diagonal block goes from one launch to the next through `planes`, which has been
-            // added up; where no further launch reads it (two panels at most, r^2 may be less than two blocks), nowhere
             const int pb = f.chol_pb;
-            const long long li_seq = (long long)f.g_splits * r * r;
-            for (int c0 = -pb; c0 + pb < r; c0 += pb) {
-                const int blocks = c0 < 0 ? 0 : (r - c0 - pb + kCholRB - 1) / kCholRB;
-                const dim3 grid(1 + blocks * (blocks + 1) / 2, 1, nb);
-                const size_t lds = chol_lds(pb);
-                double *now = planes + ((c0 / pb) & 1) * pb * pb, *next = planes + ((c0 / pb + 1) & 1) * pb * pb;
-                if (c0 + 2 * pb >= r) next = nullptr;
+            for (int c0 = -pb; c0 < r; c0 += pb) {
+                const int blocks = c0 < 0 ? 0 : std::max(0, (r - c0 - pb + kCholRB - 1) / kCholRB);
+                const int columns = c0 < 0 ? 0 : std::max(1, blocks) * ((c0 + pb + kCholRB - 1) / kCholRB);
+                const dim3 grid(1 + blocks * (blocks + 1) / 2 + columns, 1, nb);
                 if (pb == 32)
-                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, now, next, li_seq,
-                                       diag0, r, c0);
+                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
                 else
-                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), lds, st, Gm, Lt, Minv, now, next, li_seq,
-                                       diag0, r, c0);
+                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), chol_lds(16), st, Gm, Lt, diag0, r, c0);
             }
-            if (r <= 512)
-                hipLaunchKernelGGL((orth_solve_kernel<8, 2>), dim3((n + 31) / 32, 1, nb), dim3(256), 0, st, Wn, Lt, Minv, Vt, n, r);
+            const dim3 grid((n + 127) / 128, ((r + 31) / 32 + 1) / 2, nb);
+            if (r % 4 == 0)
+                hipLaunchKernelGGL(orth_apply_kernel<true>, grid, dim3(256), 0, st, Wn, Lt, Vt, n, r);
             else
-                hipLaunchKernelGGL((orth_solve_kernel<16, 1>), dim3((n + 15) / 16, 1, nb), dim3(256), 0, st, Wn, Lt, Minv, Vt, n, r);
+                hipLaunchKernelGGL(orth_apply_kernel<false>, grid, dim3(256), 0, st, Wn, Lt, Vt, n, r);
         };
         for (int it = 0; it < iters; ++it) {
             GemmArgs a{};  // Wn [n][r] = C Vt^T
