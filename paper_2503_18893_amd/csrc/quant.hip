@@ -20,8 +20,7 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
-constexpr int kQuantPieces = 4;         // 16-byte pieces per thread (1 where the call is small)
-constexpr int kQuantSmall = 1536 * 1024;  // pieces
+constexpr int kQuantSmall = 256 * 1024;  // pieces of 16 bytes
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -41,32 +40,78 @@ __device__ __forceinline__ float max3(float a, float b, float c)
     return d;
 }
 
-// One lane per 16-byte piece (8 ranks); the four lanes of a group share min and max through two exchanges.  A
-// workgroup takes whole rows, as many as 256 U pieces hold, collects the quantised rows in LDS and writes them as
-// one run of 16-byte pieces; with rows longer than that (STAGED false) every lane stores its own word.
-// The row stream and the vector ALU take about the same time, so: a thread of a large call has kQuantPieces requests in flight; rows and
-// offsets are 32-bit numbers from the workgroup's first row (a 64-bit division per piece took longer than the
-// quantisation), exchanges are lane permutations on the ALU, clamping is one median, two codes meet in a multiply-add before they
-// become a byte.  The two quotients take a product and a correction each: with y the rounded reciprocal of b, q = a y and
-// r = a - b q (exact), q + r y is the rounded a / b; a reciprocal one unit off is corrected the same way unless all
-// 24 bits of b are ones, and a step has 8 (Markstein, IBM J. Res. Dev. 34, 1990).  Outside the range where r is exact the
-// ordinary division is used.  50001 rows of 512: 17.6 -> 15.2 us (67 MB; reading and writing as many bytes alone 11.5; with a
-// store of a word per lane and one for the parameters 16.3: rows of 320 bytes leave most lines in parts).
-template <int BITS, bool STAGED, int U>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out,
-                                                            long long pieces, int r)
+// (lo, hi) of a group -> its step and the reciprocal.  The two quotients take a product and a correction each: with y the rounded
+// reciprocal of b, q = a y and r = a - b q (exact), q + r y is the rounded a / b; a reciprocal one unit off is corrected the same way
+// unless all 24 bits of b are ones, and a step has 8 (Markstein, IBM J. Res. Dev. 34, 1990).  Outside the range where r is exact the
+// ordinary division is used.
+template <int BITS> __device__ __forceinline__ void group_scale(float lo, float hi, float &step, float &inv)
 {
-    constexpr int kBlock = 256 * U;  // pieces of a workgroup: kBlock / (r / 8) rows of at most 5 r / 8 + 12 bytes
-    __shared__ __attribute__((aligned(16))) unsigned char stage[STAGED ? 8 * kBlock : 16];
     constexpr float kQmax = (float)((1 << BITS) - 1), kQinv = 1.0f / kQmax;
     constexpr uint32_t kSmall = 0x20000000u, kLarge = 0x5F000000u;  // 2^-63, 2^63
-    const uint32_t ppr = (uint32_t)r >> 3;  // pieces per row
-    const uint32_t most = STAGED ? kBlock / ppr * ppr : kBlock;  // pieces of this workgroup
-    const long long first = (long long)blockIdx.x * most, row0 = first / ppr;
-    const uint32_t pc0 = STAGED ? 0u : (uint32_t)(first - row0 * ppr);
-    const uint32_t left = pieces - first < most ? (uint32_t)(pieces - first) : most;
-    const uint32_t pitch = BITS == 3 ? (uint32_t)r >> 1 : (uint32_t)quant_row_bytes(r);
-    const q_u32x4_t *Xb = reinterpret_cast<const q_u32x4_t *>(X) + first;
+    const float range = hi - lo;
+    float q = range * kQinv;
+    q = fmaf(fmaf(-kQmax, q, range), kQinv, q);
+    if (__float_as_uint(range) - kSmall > kLarge - kSmall && range != 0.0f) q = range / kQmax;
+    step = bf16_to_f32(f32_to_bf16(q));
+    step = step > 0.0f ? step : 1.0f;
+    inv = __builtin_amdgcn_rcpf(step);
+    inv = fmaf(fmaf(-step, inv, 1.0f), inv, inv);
+    if (__float_as_uint(step) - kSmall > kLarge - kSmall) inv = 1.0f / step;
+}
+
+// Eight ranks (four words of two) -> their codes: even ranks in the low half, odd ranks in the high half (16 bits up for 4-bit codes, 12
+// for 3-bit codes).
+template <int BITS> __device__ __forceinline__ uint32_t eight_codes(const float (&x)[8], float lo, float inv)
+{
+    constexpr float kQmax = (float)((1 << BITS) - 1);
+    float c[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) c[e] = __builtin_amdgcn_fmed3f(rintf((x[e] - lo) * inv), 0.0f, kQmax);
+    uint32_t word = 0;
+    if constexpr (BITS == 4) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {  // byte h: ranks 4 (h % 2) + h / 2 and two further
+            const int e = 4 * (h & 1) + (h >> 1);
+            word = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(c[e + 2], 16.0f, c[e]), h, word);
+        }
+    } else {
+        // (a half of four codes is a number below 4096: exact in single precision)
+        const float even = fmaf(fmaf(c[6], 8.0f, c[4]), 64.0f, fmaf(c[2], 8.0f, c[0]));
+        const float odd = fmaf(fmaf(c[7], 8.0f, c[5]), 64.0f, fmaf(c[3], 8.0f, c[1]));
+        word = (uint32_t)fmaf(odd, 4096.0f, even);
+    }
+    return word;
+}
+
+__device__ __forceinline__ void unpack8(const q_u32x4_t &raw, float (&x)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        x[2 * e] = __uint_as_float(raw[e] << 16);
+        x[2 * e + 1] = __uint_as_float(raw[e] & 0xFFFF0000u);
+    }
+}
+
+__device__ __forceinline__ uint32_t group_params(float step, float lo)
+{
+    return (__float_as_uint(step) >> 16) | __float_as_uint(lo);  // (both have empty low halves)
+}
+
+// Large calls: a lane per group of 32 ranks, four 16-byte pieces, so that what a group needs is done once.  A workgroup takes whole rows,
+// as many as 256 groups make, collects the quantised rows in LDS and writes them as one run of 16-byte pieces; with rows longer
+// than that (STAGED false) every lane stores its own.
+// What bounds it: the stream, then about 75 vector instructions per piece; 140 with a lane per piece, where the two took the same time.
+// 50001 rows of 512 in 4 bits 14.2 us (67 MB; reading and writing as many bytes alone 11.5), a lane per piece 16.6; 3 bits 13.6 and
+// 15.9; 20000 rows of 640 7.5 and 9.5.  The four requests of a lane share lines, so they must go through the cache: non-temporal 19 us.
+template <int BITS, bool STAGED>
+__global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out, long long groups, int r)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char stage[STAGED ? 256 * 32 : 16];
+    const uint32_t gpr = (uint32_t)r >> 5, most = STAGED ? 256 / gpr * gpr : 256;  // groups per row, of this workgroup
+    const long long first = (long long)blockIdx.x * most, row0 = first / gpr;
+    const uint32_t g0 = STAGED ? 0u : (uint32_t)(first - row0 * gpr);
+    const uint32_t left = groups - first < most ? (uint32_t)(groups - first) : most;
+    const uint32_t pitch = (uint32_t)quant_row_bytes(r, BITS);
     unsigned char *og = out + row0 * (long long)pitch;
     auto put = [&](uint32_t o, auto v) __attribute__((always_inline)) {
         if constexpr (STAGED)
@@ -74,105 +119,106 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const bf16_t *__rest
         else
             *reinterpret_cast<decltype(v) *>(og + o) = v;
     };
-    // pieces is a multiple of 4 (r % 32 == 0), so a group's four lanes are all inside or all outside
-    q_u32x4_t raw[U];
+    const uint32_t i = threadIdx.x;
+    if (i < left) {
+        const q_u32x4_t *src = reinterpret_cast<const q_u32x4_t *>(X) + 4 * (first + i);
+        q_u32x4_t raw[4];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t i = u * 256 + threadIdx.x;
-        const q_u32x4_t *src = Xb + (i < left ? i : left - 1);
-        raw[u] = U == 1 ? *src : __builtin_nontemporal_load(src);  // (a small call's rows may still be in the caches)
-    }
+        for (int u = 0; u < 4; ++u) raw[u] = src[u];
+        float lo, hi;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint32_t i = u * 256 + threadIdx.x, lrow = (pc0 + i) / ppr, pc = pc0 + i - lrow * ppr;
-        const bool in = i < left;
-        float x[8];
+        for (int u = 0; u < 4; ++u) {
+            float x[8];
+            unpack8(raw[u], x);
+            lo = u == 0 ? min3(x[0], x[1], x[1]) : min3(lo, x[0], x[1]);
+            hi = u == 0 ? max3(x[0], x[1], x[1]) : max3(hi, x[0], x[1]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            x[2 * e] = __uint_as_float(raw[u][e] << 16);
-            x[2 * e + 1] = __uint_as_float(raw[u][e] & 0xFFFF0000u);
+            for (int e = 2; e < 8; e += 2) lo = min3(lo, x[e], x[e + 1]), hi = max3(hi, x[e], x[e + 1]);
         }
-        float mn = min3(min3(x[0], x[1], x[2]), min3(x[3], x[4], x[5]), min3(x[6], x[7], x[7]));
-        float mx = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7]));
-        // the group's other three lanes: 1 0 3 2, 2 3 0 1, 3 2 1 0
-        const float mn1 = __uint_as_float(quad_perm<0xB1>(__float_as_uint(mn))), mx1 = __uint_as_float(quad_perm<0xB1>(__float_as_uint(mx)));
-        const float lo0 = min3(mn, mn1, mn1), hi0 = max3(mx, mx1, mx1);
-        const float mn2 = __uint_as_float(quad_perm<0x4E>(__float_as_uint(lo0))), mx2 = __uint_as_float(quad_perm<0x4E>(__float_as_uint(hi0)));
-        const float lo = min3(lo0, mn2, mn2), hi = max3(hi0, mx2, mx2);  // bf16 values
-        const float range = hi - lo;
-        float q = range * kQinv;
-        q = fmaf(fmaf(-kQmax, q, range), kQinv, q);
-        if (__float_as_uint(range) - kSmall > kLarge - kSmall && range != 0.0f) q = range / kQmax;
-        float step = bf16_to_f32(f32_to_bf16(q));
-        step = step > 0.0f ? step : 1.0f;
-        float inv = __builtin_amdgcn_rcpf(step);
-        inv = fmaf(fmaf(-step, inv, 1.0f), inv, inv);
-        if (__float_as_uint(step) - kSmall > kLarge - kSmall) inv = 1.0f / step;
-        float c[8];
+        float step, inv;
+        group_scale<BITS>(lo, hi, step, inv);
+        uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) c[e] = __builtin_amdgcn_fmed3f(rintf((x[e] - lo) * inv), 0.0f, kQmax);
-        // even ranks in the low half, odd ranks in the high half (16 bits up for 4-bit codes, 12 for 3-bit codes)
-        uint32_t word = 0;
-        if constexpr (BITS == 4) {
-#pragma unroll
-            for (int h = 0; h < 4; ++h) {  // byte h: ranks 4 (h % 2) + h / 2 and two further
-                const int e = 4 * (h & 1) + (h >> 1);
-                word = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(c[e + 2], 16.0f, c[e]), h, word);
-            }
+        for (int u = 0; u < 4; ++u) {
+            float x[8];
+            unpack8(raw[u], x);
+            w[u] = eight_codes<BITS>(x, lo, inv);
+        }
+        const uint32_t row = (g0 + i) / gpr, g = g0 + i - row * gpr, at = row * pitch, par = group_params(step, lo);
+        if constexpr (BITS == 3) {  // four units of 24 bits, then the parameters
+            put(at + 16 * g, q_u32x4_t{w[0] | (w[1] << 24), (w[1] >> 8) | (w[2] << 16), (w[2] >> 16) | (w[3] << 8), par});
         } else {
-            // (a half of four codes is a number below 4096: exact in single precision)
-            const float even = fmaf(fmaf(c[6], 8.0f, c[4]), 64.0f, fmaf(c[2], 8.0f, c[0]));
-            const float odd = fmaf(fmaf(c[7], 8.0f, c[5]), 64.0f, fmaf(c[3], 8.0f, c[1]));
-            word = (uint32_t)fmaf(odd, 4096.0f, even);
-        }
-        const uint32_t par = (__float_as_uint(step) >> 16) | __float_as_uint(lo);  // (both have empty low halves)
-        const uint32_t orow = lrow * pitch;
-        if constexpr (BITS == 3) {
-            // the group's four 24-bit units into three words; the group's first lane writes the 16-byte piece
-            const uint32_t u1 = quad_perm<0x55>(word), u2 = quad_perm<0xAA>(word), u3 = quad_perm<0xFF>(word);
-            q_u32x4_t piece;
-            piece[0] = word | (u1 << 24);
-            piece[1] = (u1 >> 8) | (u2 << 16);
-            piece[2] = (u2 >> 16) | (u3 << 8);
-            piece[3] = par;
-            if (in && (pc & 3) == 0) put(orow + 4 * pc, piece);
-        } else if (in) {
-            put(orow + 4 * pc, word);
-            if ((pc & 3) == 0) put(orow + ((uint32_t)r >> 1) + pc, par);
-            if (pc == 0)  // the row's padding
-                for (uint32_t o = ((uint32_t)r >> 1) + ((uint32_t)r >> 3); o < pitch; o += 4) put(orow + o, 0u);
+            put(at + 16 * g, q_u32x4_t{w[0], w[1], w[2], w[3]});
+            put(at + ((uint32_t)r >> 1) + 4 * g, par);
+            if (g == 0)  // the row's padding
+                for (uint32_t o = ((uint32_t)r >> 1) + ((uint32_t)r >> 3); o < pitch; o += 4) put(at + o, 0u);
         }
     }
     if constexpr (STAGED) {
         __syncthreads();
-        const uint32_t n16 = left / ppr * pitch / 16;
-        for (uint32_t i = threadIdx.x; i < n16; i += 256)
-            reinterpret_cast<q_u32x4_t *>(og)[i] = reinterpret_cast<const q_u32x4_t *>(stage)[i];
+        const uint32_t n16 = left / gpr * pitch / 16;
+        for (uint32_t j = threadIdx.x; j < n16; j += 256)
+            reinterpret_cast<q_u32x4_t *>(og)[j] = reinterpret_cast<const q_u32x4_t *>(stage)[j];
+    }
+}
+
+// Small calls: a lane per 16-byte piece (8 ranks); the four lanes of a group share min and max through two exchanges, and every lane
+// stores its own word.
+template <int BITS>
+__global__ __launch_bounds__(256) void quantize_pieces_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out, long long pieces, int r)
+{
+    const uint32_t ppr = (uint32_t)r >> 3;  // pieces per row
+    const long long first = (long long)blockIdx.x * 256, row0 = first / ppr;
+    const uint32_t pc0 = (uint32_t)(first - row0 * ppr);
+    const uint32_t left = pieces - first < 256 ? (uint32_t)(pieces - first) : 256u;
+    const uint32_t pitch = (uint32_t)quant_row_bytes(r, BITS);
+    // pieces is a multiple of 4 (r % 32 == 0), so a group's four lanes are all inside or all outside
+    const uint32_t i = threadIdx.x, lrow = (pc0 + i) / ppr, pc = pc0 + i - lrow * ppr;
+    const q_u32x4_t raw = reinterpret_cast<const q_u32x4_t *>(X)[first + (i < left ? i : left - 1)];  // (may still be in the caches)
+    float x[8];
+    unpack8(raw, x);
+    const float mn = min3(min3(x[0], x[1], x[2]), min3(x[3], x[4], x[5]), min3(x[6], x[7], x[7]));
+    const float mx = max3(max3(x[0], x[1], x[2]), max3(x[3], x[4], x[5]), max3(x[6], x[7], x[7]));
+    // the group's other three lanes: 1 0 3 2, 2 3 0 1, 3 2 1 0
+    const float mn1 = __uint_as_float(quad_perm<0xB1>(__float_as_uint(mn))), mx1 = __uint_as_float(quad_perm<0xB1>(__float_as_uint(mx)));
+    const float lo0 = min3(mn, mn1, mn1), hi0 = max3(mx, mx1, mx1);
+    const float mn2 = __uint_as_float(quad_perm<0x4E>(__float_as_uint(lo0))), mx2 = __uint_as_float(quad_perm<0x4E>(__float_as_uint(hi0)));
+    const float lo = min3(lo0, mn2, mn2), hi = max3(hi0, mx2, mx2);  // bf16 values
+    float step, inv;
+    group_scale<BITS>(lo, hi, step, inv);
+    const uint32_t word = eight_codes<BITS>(x, lo, inv), par = group_params(step, lo);
+    unsigned char *orow = out + row0 * (long long)pitch + lrow * pitch;
+    if constexpr (BITS == 3) {
+        // the group's four 24-bit units into three words; the group's first lane writes the 16-byte piece
+        const uint32_t u1 = quad_perm<0x55>(word), u2 = quad_perm<0xAA>(word), u3 = quad_perm<0xFF>(word);
+        if (i < left && (pc & 3) == 0)
+            *reinterpret_cast<q_u32x4_t *>(orow + 4 * pc) = q_u32x4_t{word | (u1 << 24), (u1 >> 8) | (u2 << 16), (u2 >> 16) | (u3 << 8), par};
+    } else if (i < left) {
+        *reinterpret_cast<uint32_t *>(orow + 4 * pc) = word;
+        if ((pc & 3) == 0) *reinterpret_cast<uint32_t *>(orow + ((uint32_t)r >> 1) + pc) = par;
+        if (pc == 0)  // the row's padding
+            for (uint32_t o = ((uint32_t)r >> 1) + ((uint32_t)r >> 3); o < pitch; o += 4) *reinterpret_cast<uint32_t *>(orow + o) = 0u;
     }
 }
 
 hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, void *out, hipStream_t st)
 {
-    const int ppr = r >> 3;
-    const long long pieces = rows * (long long)ppr;
-    if (pieces == 0) return hipSuccess;
-    // A small call is one round of loads and stores: its pieces are spread over as many workgroups as there are, and stored as they
-    // come (two calls, their landmarks and selection, us: 4100 rows of 512, four pieces a thread 26.8, one 25.3; 12000 of 768 28.2
-    // and 27.0; 20000 of 640 37.0 with four and 39.4 with one and 64-bit row numbers).
-    const bool small = pieces <= kQuantSmall;
-    const int block = 256 * (small ? 1 : kQuantPieces);
-    const bool staged = !small && ppr <= block;
-    const long long most = staged ? block / ppr * ppr : block, blocks = (pieces + most - 1) / most;
+    const long long groups = rows * (long long)(r >> 5), pieces = 4 * groups;
+    if (groups == 0) return hipSuccess;
+    // A small call is one round of loads: its pieces are spread over four times as many lanes.  Lane per piece / per group, us: 1000 rows
+    // of 512 2.1 / 2.6, 4100 (262400 pieces) 3.05 / 3.05, 16000 6.6 / 5.7, 12000 of 768 7.2 / 6.2.
+    const bool small = pieces <= kQuantSmall, staged = (r >> 5) <= 256;
+    const long long most = small ? 256 : staged ? 256 / (r >> 5) * (r >> 5) : 256, blocks = ((small ? pieces : groups) + most - 1) / most;
     if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, pieces, r);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, small ? pieces : groups, r);
     };
-    if (bits == 3)
-        small ? launch(quantize_rows_kernel<3, false, 1>)
-              : staged ? launch(quantize_rows_kernel<3, true, kQuantPieces>) : launch(quantize_rows_kernel<3, false, kQuantPieces>);
+    if (small)
+        bits == 3 ? launch(quantize_pieces_kernel<3>) : launch(quantize_pieces_kernel<4>);
+    else if (bits == 3)
+        staged ? launch(quantize_groups_kernel<3, true>) : launch(quantize_groups_kernel<3, false>);
     else
-        small ? launch(quantize_rows_kernel<4, false, 1>)
-              : staged ? launch(quantize_rows_kernel<4, true, kQuantPieces>) : launch(quantize_rows_kernel<4, false, kQuantPieces>);
+        staged ? launch(quantize_groups_kernel<4, true>) : launch(quantize_groups_kernel<4, false>);
     return hipGetLastError();
 }
 

@@ -38,6 +38,13 @@ def test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits):
     assert (got[rows] == 0xAB).all()     # nothing behind the last row
 
 
+@pytest.mark.parametrize("bits", [4, 3])
+@pytest.mark.parametrize("rows,r", [(4096, 512), (4097, 512), (260, 8192), (259, 8224), (9363, 224), (21846, 96), (65537, 32)])
+def test_quantised_rows_a_lane_per_group(rows, r, bits):
+    """Both sides of 2^18 pieces; 256 groups a row, one more, and numbers of groups that do not divide a workgroup."""
+    test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits)
+
+
 @pytest.mark.parametrize("c", [4, 8, 12, 16])
 @pytest.mark.parametrize("chunks,rest", [(1, 0), (15, 1), (16, 0), (17, 3), (64, 2)])
 def test_landmarks_at_the_edges_of_a_wavefront(c, chunks, rest):
