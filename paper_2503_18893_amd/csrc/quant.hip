@@ -20,7 +20,7 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
-constexpr int kQuantSmall = 256 * 1024;  // pieces of 16 bytes
+constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 256 * 1024;  // pieces of 16 bytes
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -101,12 +101,15 @@ __device__ __forceinline__ uint32_t group_params(float step, float lo)
 // as many as 256 groups make, collects the quantised rows in LDS and writes them as one run of 16-byte pieces; with rows longer
 // than that (STAGED false) every lane stores its own.
 // What bounds it: the stream, then about 75 vector instructions per piece; 140 with a lane per piece, where the two took the same time.
-// 50001 rows of 512 in 4 bits 14.2 us (67 MB; reading and writing as many bytes alone 11.5), a lane per piece 16.6; 3 bits 13.6 and
-// 15.9; 20000 rows of 640 7.5 and 9.5.  The four requests of a lane share lines, so they must go through the cache: non-temporal 19 us.
-template <int BITS, bool STAGED>
+// 50001 rows of 512 in 4 bits 13.5 us (67 MB; reading and writing as many bytes alone 11.5), a lane per piece 16.6; 3 bits 12.5 and
+// 16.1; 262144 rows 60.9 and 63.4, in 3 bits 58.0 and 66.1; 20000 rows of 640 7.6 and 9.7.  STREAM: calls of more than 2^21 pieces (32
+// MiB), whose rows are hardly in the caches.  Others ask for a group's four pieces per lane, which share lines, so through the
+// cache: 20000 rows of 640 8.4 us the other way; 262144 rows of 512 this way 63.6, non-temporal 80.
+template <int BITS, bool STAGED, bool STREAM>
 __global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out, long long groups, int r)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char stage[STAGED ? 256 * 32 : 16];
+    __shared__ q_u32x4_t pieces[STREAM ? 1024 : STAGED ? 512 : 1];
+    unsigned char *stage = reinterpret_cast<unsigned char *>(pieces);  // STAGED
     const uint32_t gpr = (uint32_t)r >> 5, most = STAGED ? 256 / gpr * gpr : 256;  // groups per row, of this workgroup
     const long long first = (long long)blockIdx.x * most, row0 = first / gpr;
     const uint32_t g0 = STAGED ? 0u : (uint32_t)(first - row0 * gpr);
@@ -120,11 +123,30 @@ __global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__re
             *reinterpret_cast<decltype(v) *>(og + o) = v;
     };
     const uint32_t i = threadIdx.x;
-    if (i < left) {
-        const q_u32x4_t *src = reinterpret_cast<const q_u32x4_t *>(X) + 4 * (first + i);
-        q_u32x4_t raw[4];
+    const q_u32x4_t *src = reinterpret_cast<const q_u32x4_t *>(X) + 4 * first;
+    q_u32x4_t raw[4];
+    if constexpr (STREAM) {
+        // the rows come in as they lie, 16 bytes a lane and past the caches, and change hands in LDS: piece p of group g in place 4 g +
+        // (p ^ (g / 4 % 4)), which neither side finds on a busy bank
 #pragma unroll
-        for (int u = 0; u < 4; ++u) raw[u] = src[u];
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t p = 256 * u + i;
+            raw[u] = __builtin_nontemporal_load(src + (p < 4 * left ? p : 0u));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t p = 256 * u + i, g = p >> 2;
+            pieces[4 * g + ((p & 3) ^ ((g >> 2) & 3))] = raw[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) raw[u] = pieces[4 * i + (u ^ ((i >> 2) & 3))];
+        if constexpr (STAGED) __syncthreads();  // (the same room for what leaves)
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) raw[u] = src[4 * (i < left ? i : 0u) + u];
+    }
+    if (i < left) {
         float lo, hi;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -215,10 +237,15 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
     };
     if (small)
         bits == 3 ? launch(quantize_pieces_kernel<3>) : launch(quantize_pieces_kernel<4>);
+    else if (pieces <= kQuantCached)
+        if (bits == 3)
+            staged ? launch(quantize_groups_kernel<3, true, false>) : launch(quantize_groups_kernel<3, false, false>);
+        else
+            staged ? launch(quantize_groups_kernel<4, true, false>) : launch(quantize_groups_kernel<4, false, false>);
     else if (bits == 3)
-        staged ? launch(quantize_groups_kernel<3, true>) : launch(quantize_groups_kernel<3, false>);
+        staged ? launch(quantize_groups_kernel<3, true, true>) : launch(quantize_groups_kernel<3, false, true>);
     else
-        staged ? launch(quantize_groups_kernel<4, true>) : launch(quantize_groups_kernel<4, false>);
+        staged ? launch(quantize_groups_kernel<4, true, true>) : launch(quantize_groups_kernel<4, false, true>);
     return hipGetLastError();
 }
 
