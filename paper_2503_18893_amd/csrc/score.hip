@@ -758,11 +758,12 @@ __global__ __launch_bounds__(WAVES * 64) void score_stream_kernel(const bf16_t *
 // Lane (n, hf) loads the 16 bytes of each of token n's groups (both halves load the same pieces) and the parameter
 // words.  Always writes the per-head scores as well as the pooled ones.
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ bf16x8_t q4_fragment(uint32_t w)
+// (above: 0x43004300, in a register: an and-or instruction takes one constant)
+__device__ __forceinline__ bf16x8_t q4_fragment(uint32_t w, uint32_t above = 0x43004300u)
 {
     u32x4_t o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = ((w >> (4 * i)) & 0x000F000Fu) | 0x43004300u;
+    for (int i = 0; i < 4; ++i) o[i] = ((w >> (4 * i)) & 0x000F000Fu) | above;
     return __builtin_bit_cast(bf16x8_t, o);
 }
 
@@ -927,6 +928,12 @@ __global__ __launch_bounds__(WAVES * 64) void score_q4_kernel(const unsigned cha
 // 81 of 175 us).  Rows sit in the tile at a pitch of an odd number of 16-byte units, so the per-row reads are free
 // of bank conflicts.  The next tile waits in registers while the current one is multiplied; nothing needs a
 // barrier (P is read-only, the tiles are private).
+// What bounds it: vector instructions (900 per tile of 32 tokens at ranks 512, of which 450 are the codes' conversion and the groups'
+// multiply-adds) and matrix instructions (70), which two wavefronts per SIMD overlap only in part, and the stores, 20 bytes per
+// token and KV head.  Two groups of 32 ranks go side by side, so that neither waits for the other's products; the first tile is
+// requested with the operands, awaited after them; a tile's results are stored as they come (held back for bursts of four tiles
+// they cost registers, and at the end of a short range nothing was left to hide them behind).  4 x 65536 tokens of ranks 512
+// 37.4 -> 34.2 us, 16 x 65536 with the projection 134 -> 121, 7 query heads 4 x 131072 of 384 61 -> 53.
 constexpr int kQ4TileWaves = 8;
 constexpr int kQ4MaxLoads = 10;  // 16-byte requests per lane and tile: 32 rows * 5r/8 bytes <= 10 KiB, r <= 512
 
@@ -956,19 +963,44 @@ __global__ __launch_bounds__(kQ4TileWaves * 64) void score_q4_tile_kernel(const 
     const int n_pass = (n_groups + 15) >> 4;  // passes of 16 groups of the offset term
     u32x4_t *PsF = reinterpret_cast<u32x4_t *>(Ps + (F8 / 2) * 32);  // [n_pass][3 parts][64]: Ps as operand fragments
     unsigned char *tile_lds = reinterpret_cast<unsigned char *>(PsF + n_pass * 3 * 64) + (size_t)w * (32 * tpitch + kQ4TileSlack);
+    const int pitch = r_k * 5 / 8;
+    const int ppr = pitch >> 4;            // 16-byte pieces per row
+    const int pieces = 32 * ppr;           // per tile
+    const unsigned char *Ab = Aq + (size_t)b * L * pitch;
+    const size_t seq_last = (size_t)L * pitch - 16;  // last piece of the sequence: requests beyond it are redirected
+    const int n_tiles = (L + 31) / 32;
+    const int tile_begin = blockIdx.x * tiles_per_wg;
+    const int tile_end = tile_begin + tiles_per_wg < n_tiles ? tile_begin + tiles_per_wg : n_tiles;
+    int tile = tile_begin + w;
+    u32x4_t stage[kQ4MaxLoads];
+    // (a tile whose requests all lie within the sequence, all but the last ones: one address and constant offsets)
+    auto request = [&](int tl) __attribute__((always_inline)) {
+        const size_t at = (size_t)tl * 32 * pitch;
+        if (at + kQ4MaxLoads * 1024 <= seq_last + 16) {
+            const unsigned char *from = Ab + at;
+#pragma unroll
+            for (int i = 0; i < kQ4MaxLoads; ++i)
+                stage[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(from + (uint32_t)(lane * 16) + i * 1024));
+        } else {
+#pragma unroll
+            for (int i = 0; i < kQ4MaxLoads; ++i) {
+                const size_t off = at + (size_t)(i * 64 + lane) * 16;
+                stage[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Ab + (off < seq_last ? off : seq_last)));
+            }
+        }
+    };
     {
         const u32x4_t *src = reinterpret_cast<const u32x4_t *>(Pfrag) + ((size_t)b * nblk + blk) * 2 * F8 * 64;
-        const int total = 2 * F8 * 64;  // a multiple of 1024
-        for (int e0 = threadIdx.x; e0 < total; e0 += 4 * WAVES * 64) {
-            u32x4_t tmp[4];
+        const int total = 2 * F8 * 64;  // a multiple of 1024, and no more than 4096 (r <= 512)
+        u32x4_t tmp[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) tmp[j] = src[e0 + j * WAVES * 64 < total ? e0 + j * WAVES * 64 : e0];
+        for (int j = 0; j < 8; ++j) tmp[j] = src[(int)threadIdx.x + j * WAVES * 64 < total ? threadIdx.x + j * WAVES * 64 : threadIdx.x];
+        request(tile);  // (behind the operands, which are awaited first; a wavefront without a tile asks for the sequence's last bytes)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (e0 + j * WAVES * 64 < total) Pl[e0 + j * WAVES * 64] = tmp[j];
-        }
+        for (int j = 0; j < 8; ++j)
+            if ((int)threadIdx.x + j * WAVES * 64 < total) Pl[threadIdx.x + j * WAVES * 64] = tmp[j];
     }
-    __syncthreads();
+    lds_barrier();
     for (int g = w; g < F8 / 2; g += WAVES) {
         float sum = 0.0f;
 #pragma unroll
@@ -982,7 +1014,7 @@ __global__ __launch_bounds__(kQ4TileWaves * 64) void score_q4_tile_kernel(const 
         sum += __shfl_xor(sum, 32, kWave);
         if (hf == 0) Ps[g * 32 + n] = sum;
     }
-    __syncthreads();
+    lds_barrier();
     // The offset term sum_g (lo_tg - 128 step_tg) Ps_g[slot] is a product [slots x groups] . [groups x tokens] and
     // runs on the matrix cores, 16 groups per instruction.  Because 128 step Ps cancels against the first term it
     // needs full fp32 accuracy: both factors are split *exactly* into three bf16 numbers (8 + 8 + 8 mantissa bits,
@@ -1009,17 +1041,8 @@ __global__ __launch_bounds__(kQ4TileWaves * 64) void score_q4_tile_kernel(const 
 #pragma unroll
         for (int q3 = 0; q3 < 3; ++q3) PsF[(ps * 3 + q3) * 64 + lane] = f3[q3];
     }
-    __syncthreads();
+    lds_barrier();
 
-    const int pitch = r_k * 5 / 8;
-    const int ppr = pitch >> 4;            // 16-byte pieces per row
-    const int pieces = 32 * ppr;           // per tile
-    const unsigned char *Ab = Aq + (size_t)b * L * pitch;
-    const size_t seq_last = (size_t)L * pitch - 16;  // last piece of the sequence: requests beyond it are redirected
-    const int n_tiles = (L + 31) / 32;
-    const int tile_begin = blockIdx.x * tiles_per_wg;
-    const int tile_end = tile_begin + tiles_per_wg < n_tiles ? tile_begin + tiles_per_wg : n_tiles;
-    int tile = tile_begin + w;
     if (tile >= tile_end) return;
     // where this lane's pieces go in the LDS tile (the same for every tile); -1: no such piece
     int dst_off[kQ4MaxLoads];
@@ -1028,32 +1051,19 @@ __global__ __launch_bounds__(kQ4TileWaves * 64) void score_q4_tile_kernel(const 
         const int pc = i * 64 + lane;
         dst_off[i] = pc < pieces ? (pc / ppr) * tpitch + (pc % ppr) * 16 : -1;
     }
-    u32x4_t stage[kQ4MaxLoads];
-#define XKV_Q4_REQUEST(TL)                                                                              \
-    _Pragma("unroll") for (int i = 0; i < kQ4MaxLoads; ++i)                                             \
-    {                                                                                                   \
-        const size_t off = (size_t)(TL) * 32 * pitch + (size_t)(i * 64 + lane) * 16;                    \
-        stage[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Ab + (off < seq_last ? off : seq_last))); \
-    }
-    XKV_Q4_REQUEST(tile);
     f32x16_t tot;
 #pragma unroll
     for (int v = 0; v < 16; ++v) tot[v] = 0.0f;
     const f32x16_t zero = tot;
     const unsigned char *my_row = tile_lds + n * tpitch;
-    constexpr int kQ4Burst = 4;
-    float res[kQ4Burst][16];
-#pragma unroll
-    for (int i = 0; i < kQ4Burst; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) res[i][v] = 0.0f;
-    int ti = 0, tile0 = tile;  // tiles held in res, first of them
+    uint32_t above = 0x43004300u;
+    asm("" : "+v"(above));
     while (true) {
 #pragma unroll
         for (int i = 0; i < kQ4MaxLoads; ++i)
-            if (dst_off[i] >= 0) *reinterpret_cast<u32x4_t *>(tile_lds + dst_off[i]) = stage[i];
+            if (64 * (i + 1) <= pieces || dst_off[i] >= 0) *reinterpret_cast<u32x4_t *>(tile_lds + dst_off[i]) = stage[i];
         const int tile_n = tile + WAVES;
-        XKV_Q4_REQUEST(tile_n < tile_end ? tile_n : tile);
+        request(tile_n < tile_end ? tile_n : tile);
         for (int ps = 0; ps < n_pass; ++ps) {
             // (lo - 128 step) of this half's eight groups of the pass, split like Ps
             const u32x4_t *par = reinterpret_cast<const u32x4_t *>(my_row + (r_k >> 1) + 64 * ps + 32 * hf);
@@ -1090,70 +1100,81 @@ __global__ __launch_bounds__(kQ4TileWaves * 64) void score_q4_tile_kernel(const 
             tot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p0, c1, tot, 0, 0, 0);
             tot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p0, c0, tot, 0, 0, 0);
         }
-        for (int g = 0; g < n_groups; ++g) {
-            const u32x4_t cw = *reinterpret_cast<const u32x4_t *>(my_row + 16 * g);
-            const uint32_t pword = *reinterpret_cast<const uint32_t *>(my_row + (r_k >> 1) + 4 * g);
-            f32x16_t acc = zero;
+        // Four groups a round (a row's groups are a multiple of that), two at a time: their products do not wait for each other.  The codes of
+        // the next two are on their way.
+        u32x4_t codes[2];
 #pragma unroll
-            for (int ff = 0; ff < 2; ++ff) {
-                const uint32_t word = hf ? (ff ? cw[3] : cw[1]) : (ff ? cw[2] : cw[0]);
-                const bf16x8_t bop = q4_fragment(word);
-                const u32x4_t ph = Pl[(2 * g + ff) * 64 + lane];
-                const u32x4_t pl = Pl[(F8 + 2 * g + ff) * 64 + lane];
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ph), bop, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pl), bop, acc, 0, 0, 0);
+        for (int j = 0; j < 2; ++j) codes[j] = *reinterpret_cast<const u32x4_t *>(my_row + 16 * j);
+        for (int g4 = 0; g4 < n_groups; g4 += 4) {
+            const u32x4_t par = *reinterpret_cast<const u32x4_t *>(my_row + (r_k >> 1) + 4 * g4);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int g = g4 + 2 * h;
+                f32x16_t acc[2];
+                u32x4_t ph[2][2], pl[2][2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int ff = 0; ff < 2; ++ff) {
+                        ph[j][ff] = Pl[(2 * (g + j) + ff) * 64 + lane];
+                        pl[j][ff] = Pl[(F8 + 2 * (g + j) + ff) * 64 + lane];
+                    }
+                uint32_t now[2][2];
+                const int gn = g + 2 < n_groups ? g + 2 : 0;
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                    for (int ff = 0; ff < 2; ++ff) now[j][ff] = hf ? codes[j][2 * ff + 1] : codes[j][2 * ff];
+                    codes[j] = *reinterpret_cast<const u32x4_t *>(my_row + 16 * (gn + j));
+                }
+#pragma unroll
+                for (int ff = 0; ff < 2; ++ff) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const bf16x8_t c8 = q4_fragment(now[j][ff], above);
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, ph[j][ff]), c8, ff == 0 ? zero : acc[j], 0, 0, 0);
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pl[j][ff]), c8, acc[j], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const float step = __uint_as_float(par[2 * h + j] << 16);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) tot[v] = fmaf(step, acc[j][v], tot[v]);
+                }
             }
-            const float step = __uint_as_float(pword << 16);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) tot[v] = fmaf(step, acc[v], tot[v]);
         }
-        // results wait in registers and are written in bursts of kQ4Burst tiles (as in the bf16 stream kernel:
-        // stores dribbled out between the reads cost the memory system more than their bytes)
+        const int t = tile * 32 + n;
+        if (t < L) {
 #pragma unroll
-        for (int i = 0; i < kQ4Burst; ++i)
+            for (int u = 0; u < GPH; ++u) {
+                const int g = blk * 2 * GPH + hf * GPH + u;
+                if (g < H_kv) {
+                    float hv[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) res[i][v] = (i == ti) ? scale * tot[v] : res[i][v];
-        ++ti;
+                    for (int hh = 0; hh < 16; ++hh) hv[hh] = hh < N_REP ? scale * tot[(u * N_REP + hh) & 15] : 0.0f;
+                    float best = hv[0];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) tot[v] = 0.0f;
-        const bool done = tile_n >= tile_end;
-        if (ti == kQ4Burst || done) {
+                    for (int hh = 1; hh < N_REP; ++hh) best = fmaxf(best, hv[hh]);
+                    S[((size_t)b * H_kv + g) * L + t] = best;
+                    float *dst = S_heads + (((size_t)b * H_kv + g) * L + t) * NRP;
+                    if constexpr (NRP >= 4) {
 #pragma unroll
-            for (int i = 0; i < kQ4Burst; ++i) {
-                const int t = (tile0 + i * WAVES) * 32 + n;
-                if (i < ti && t < L) {
+                        for (int c = 0; c < NRP / 4; ++c)
+                            *reinterpret_cast<float4 *>(dst + 4 * c) =
+                                make_float4(hv[4 * c], hv[4 * c + 1], hv[4 * c + 2], hv[4 * c + 3]);
+                    } else {
 #pragma unroll
-                    for (int u = 0; u < GPH; ++u) {
-                        const int g = blk * 2 * GPH + hf * GPH + u;
-                        if (g < H_kv) {
-                            float hv[16];
-#pragma unroll
-                            for (int hh = 0; hh < 16; ++hh) hv[hh] = hh < N_REP ? res[i][(u * N_REP + hh) & 15] : 0.0f;
-                            float best = hv[0];
-#pragma unroll
-                            for (int hh = 1; hh < N_REP; ++hh) best = fmaxf(best, hv[hh]);
-                            S[((size_t)b * H_kv + g) * L + t] = best;
-                            float *dst = S_heads + (((size_t)b * H_kv + g) * L + t) * NRP;
-                            if constexpr (NRP >= 4) {
-#pragma unroll
-                                for (int c = 0; c < NRP / 4; ++c)
-                                    *reinterpret_cast<float4 *>(dst + 4 * c) =
-                                        make_float4(hv[4 * c], hv[4 * c + 1], hv[4 * c + 2], hv[4 * c + 3]);
-                            } else {
-#pragma unroll
-                                for (int hh = 0; hh < NRP; ++hh) dst[hh] = hv[hh];
-                            }
-                        }
+                        for (int hh = 0; hh < NRP; ++hh) dst[hh] = hv[hh];
                     }
                 }
             }
-            tile0 += ti * WAVES;
-            ti = 0;
         }
-        if (done) break;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) tot[v] = 0.0f;
+        if (tile_n >= tile_end) break;
         tile = tile_n;
     }
-#undef XKV_Q4_REQUEST
 }
 
 static bool score_mfma_ok(const xkv_shape &s, const void *A_k)
