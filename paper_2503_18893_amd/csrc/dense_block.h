@@ -13,15 +13,21 @@ namespace dense {
 //   Z^T [tokens x head slots] = K block (loaded line-wise, operand fragments through an LDS tile)  x  Q^T (registers)
 //   O [head slots x dims]    += W = exp(Z^T - max) (the result registers of Z^T, packed)   x  V block
 // The contraction of the second product runs over tokens, so each lane needs eight token rows of one
-// column of V: the V block goes through a wavefront-private LDS tile (row pitch 272 B, conflict-free)
-// and is read back transposed.  The four wavefronts merge their partials in LDS before writing.
+// column of V: the V block goes through a wavefront-private LDS tile, which the transposing LDS read (4 rows x 16 columns a time) turns.
+// The rows of the next block are requested as soon as those of this one have left the registers for LDS.
+// The four wavefronts merge their partials in LDS before writing.
+// What bounds it: the stream where it is long, 4 x 8 x 65536 tokens 165 us (6.5 TB/s; 167 with V read back two bytes at a time and the rows
+// requested at the start of their block), latencies where it is short: 8 x 4096 with the merge 10.5 us (11.6), 8 x 32768 29.8 (31.0).
 // ==========================================================================================
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) float f32x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
-constexpr int kVPitch = 272;  // bytes per token row of the LDS tile of V (256 + 16: rows 4 apart land 64 B apart)
+typedef __attribute__((ext_vector_type(4))) short s16x4_t;
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+
+constexpr int kVPitch = 288;  // bytes per token row of the LDS tile of V (256 + 32: the 32 B of eight rows lie on different banks)
 
 __device__ __forceinline__ bf16x8_t pack8_bf16(const f32x16_t &c, int j)
 {
@@ -31,7 +37,7 @@ __device__ __forceinline__ bf16x8_t pack8_bf16(const f32x16_t &c, int j)
     return __builtin_convertvector(x, bf16x8_t);
 }
 
-// LDS: per wavefront a V tile (32 x 272 B) and a K tile (32 x 256 B), 66 KiB; the V part is reused for the merge
+// LDS: per wavefront a V tile (32 x 288 B) and a K tile (32 x 256 B), 68 KiB; the V part is reused for the merge
 constexpr int kLdsBytes = 4 * 32 * kVPitch + 4 * 32 * 256;
 
 // A workgroup of 256 threads: tokens [split chunk, (split + 1) chunk) of one (sequence b, KV head g), one partial per query head.
@@ -77,17 +83,23 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
 #pragma unroll
         for (int v = 0; v < 8; ++v) O[db][v] = 0.0f;
 
-    for (int t0 = t_begin + w * 32; t0 < t_end; t0 += 128) {
-        // K and V rows, whole lines per instruction: 16 lanes cover one 256 B row, the wavefront 4 rows per load
-        // (with one lane per row four instructions would share every 128 B line, which streams measurably slower)
-        u32x4_t kr[8], vr[8];
+    // K and V rows, whole lines per instruction: 16 lanes cover one 256 B row, the wavefront 4 rows per load
+    // (with one lane per row four instructions would share every 128 B line, which streams measurably slower)
+    u32x4_t kr[8], vr[8];
+    auto request = [&](u32x4_t (&to)[8], const bf16_t *from, int t0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int row = i * 4 + (lane >> 4);
-            const int tv = t0 + row < t_end ? t0 + row : t_end - 1;
-            kr[i] = __builtin_nontemporal_load(&reinterpret_cast<const u32x4_t *>(Kg + (size_t)tv * 128)[lane & 15]);
-            vr[i] = __builtin_nontemporal_load(&reinterpret_cast<const u32x4_t *>(Vg + (size_t)tv * 128)[lane & 15]);
+            const int row = t0 + i * 4 + (lane >> 4), tv = row < t_end ? row : t_end - 1;
+            to[i] = __builtin_nontemporal_load(&reinterpret_cast<const u32x4_t *>(from + (size_t)tv * 128)[lane & 15]);
         }
+    };
+    // this lane's place in the tile of V for the transposing read: row 4 hf + l16 / 4, columns 16 (lane / 16 % 2) + 4 (l16 % 4) ..
+    const unsigned char *vrd = vt + (4 * hf + ((lane & 15) >> 2)) * kVPitch + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    if (t_begin + w * 32 < t_end) {
+        request(kr, Kg, t_begin + w * 32);
+        request(vr, Vg, t_begin + w * 32);
+    }
+    for (int t0 = t_begin + w * 32; t0 < t_end; t0 += 128) {
         // K through its LDS tile: written row-wise, read back as the operand fragment of each 16 head dims
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -95,6 +107,7 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
             const int row = i * 4 + kw_row;
             kt[16 * row + ((kw_piece + row) & 15)] = kr[i];
         }
+        if (t0 + 128 < t_end) request(kr, Kg, t0 + 128);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -135,6 +148,7 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
             const int row = i * 4 + (lane >> 4);
             *reinterpret_cast<u32x4_t *>(vt + row * kVPitch + (lane & 15) * 16) = vr[i];
         }
+        if (t0 + 128 < t_end) request(vr, Vg, t0 + 128);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -151,18 +165,13 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
             for (int v = 0; v < 16; ++v) ot[v] = 0.0f;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                u32x4_t raw;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int e = 2 * e2;
-                    const int tok = 8 * (2 * j + e / 4) + 4 * hf + (e % 4);  // e, e+1 are adjacent tokens
-                    const uint32_t lo = *reinterpret_cast<const uint16_t *>(vt + tok * kVPitch + (db * 32 + n) * 2);
-                    const uint32_t hi =
-                        *reinterpret_cast<const uint16_t *>(vt + (tok + 1) * kVPitch + (db * 32 + n) * 2);
-                    raw[e2] = lo | (hi << 16);
-                }
-                ot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j == 0 ? W0 : W1, __builtin_bit_cast(bf16x8_t, raw), ot, 0,
-                                                             0, 0);
+                // position e of lane (column n, hf): token 16 j + 8 (e / 4) + 4 hf + e % 4
+                const unsigned char *from = vrd + 16 * j * kVPitch + 64 * db;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)from);
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t *)(from + 8 * kVPitch));
+                ot = __builtin_amdgcn_mfma_f32_32x32x16_bf16(j == 0 ? W0 : W1,
+                                                             __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)),
+                                                             ot, 0, 0, 0);
             }
 #pragma unroll
             for (int v = 0; v < 8; ++v) O[db][v] += ot[v];
