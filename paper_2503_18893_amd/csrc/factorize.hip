@@ -817,8 +817,11 @@ __global__ __launch_bounds__(256) void orth_apply_kernel(const float *__restrict
 // launch: it applies its rotations and finds those of the next round, for which each pair of blocks brings its diagonal
 // block up to date by itself.  Launch boundaries are the only synchronisation.
 // What bounds it: the chain of launches, and in a launch the 16 dependent inner rounds of the rotations.  One launch takes
-// 16 us (13.3 us over all that are enqueued, r = 512), eight sweeps run.  One-sided Jacobi on whole columns of 512, three dot
-// products of columns per rotation, took 63 us per launch: 13.9 against 4.1 ms; every workgroup finding the rotations
+// 12.4 us (r = 512; 5.2 us the inner rounds, 1.6 us one that returns at once), eight sweeps run: 3.25 ms.  The rest is instructions of one
+// wavefront per SIMD, so there are few of them: no division in the tournament's schedule, 16-byte requests, and no bounds checks where
+// every block lies inside the matrix (15.8 -> 13.2 us); and no compute unit of a finding workgroup is shared while 256 are
+// enough (J^T in 128 instead of 64 positions: 216 workgroups instead of 280 at r = 512, 12.9 -> 12.4 us).  One-sided Jacobi on whole columns of 512, three dot
+// products of columns per rotation, took 63 us per launch; every workgroup finding the rotations
 // of its own two pairs 16 us with one sequence, but all 200 workgroups of a sequence then hold a compute unit for the 16
 // inner rounds; two launches per round 18 us.
 // The launches of kJacobiSweeps sweeps are all enqueued up front (no value is read back by the host); a sequence is
@@ -900,34 +903,67 @@ __device__ __forceinline__ void fz_rotation(double alpha, double beta, double ga
 
 // (5c) round k of the tournament: M' = T M T^T and J^T' = T J^T with the rotations T that the launch before found, and
 // beside them the rotations of round k + 1.  Workgroups x < pairs find rotations; the next pairs (pairs + 1) / 2 make block
-// (p, q), p >= q, of M' and its mirror image, in the other buffer; the others the rows of J^T of one pair, 64 positions.
+// (p, q), p >= q, of M' and its mirror image, in the other buffer; the others the rows of J^T of one pair, 128 positions.
 // The first launch, k = -1, only finds the rotations of round 0.
 constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34, kJacTile = kJacNC * kJacLP;
 constexpr int kJacLds = 2 * kJacTile + 2 * 256 * 2 + 2 * 16 * 4;  // doubles
 
-// First columns of the two blocks of pair number x in a round of the round-robin tournament of m = n_blocks players:
-// the last player meets t = round % (m - 1), and t + x meets t - x modulo m - 1.
-__device__ __forceinline__ void fz_pair_of_blocks(int x, int round, int n_blocks, int (&b)[2])
+// The products run over the 32 positions of a pair in steps of 4: in step s, lane group kk takes position fz_jac_k(s, kk), so that what
+// a lane needs of a row are two runs of four.
+__device__ __forceinline__ constexpr int fz_jac_k(int s, int kk) { return 16 * (s >> 2) + 4 * kk + (s & 3); }
+
+// The elements fz_jac_k(0 .. 7, kk) of a row of T.
+__device__ __forceinline__ void fz_jac_t_row(const double *row, int kk, double (&v)[8])
 {
-    const int m1 = n_blocks - 1, t = round % m1, u = (t + x) % m1, v = x == 0 ? m1 : (t - x + m1) % m1;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const fz_f64x2_t t = *reinterpret_cast<const fz_f64x2_t *>(row + 16 * (h >> 1) + 4 * kk + 2 * (h & 1));
+        v[2 * h] = t[0];
+        v[2 * h + 1] = t[1];
+    }
+}
+
+// The same of row `row` of M in the columns of a pair of blocks; FULL: every block lies inside the matrix, otherwise zeros beyond it.
+template <bool FULL>
+__device__ __forceinline__ void fz_jac_m_row(const double *M, int row, const int (&b)[2], int kk, int r, double (&v)[8])
+{
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const int col = b[h >> 1] + 4 * kk + 2 * (h & 1);
+        if constexpr (FULL) {
+            const fz_f64x2_t t = *reinterpret_cast<const fz_f64x2_t *>(M + (size_t)row * r + col);
+            v[2 * h] = t[0];
+            v[2 * h + 1] = t[1];
+        } else {
+            v[2 * h] = (row < r && col < r) ? M[(size_t)row * r + col] : 0.0;
+            v[2 * h + 1] = (row < r && col + 1 < r) ? M[(size_t)row * r + col + 1] : 0.0;
+        }
+    }
+}
+
+// First columns of the two blocks of pair number x in round t, 0 <= t < m - 1, of the round-robin tournament of m = n_blocks players:
+// the last player meets t, and t + x meets t - x modulo m - 1.
+__device__ __forceinline__ void fz_pair_of_blocks(int x, int t, int n_blocks, int (&b)[2])
+{
+    const int m1 = n_blocks - 1, u = t + x >= m1 ? t + x - m1 : t + x, v = x == 0 ? m1 : t < x ? t - x + m1 : t - x;
     b[0] = (u < v ? u : v) * kJacBS;
     b[1] = (u < v ? v : u) * kJacBS;
 }
 
 __device__ __forceinline__ int fz_pair_column(const int (&b)[2], int c) { return (c < kJacBS ? b[0] : b[1]) + (c & 15); }
 
-// Which pair of round `round` a block is in, and as which half (inverse of fz_pair_of_blocks).
-__device__ __forceinline__ void fz_pair_of_block(int b, int round, int n_blocks, int &x, int &half)
+// Which pair of round t a block is in, and as which half (inverse of fz_pair_of_blocks).
+__device__ __forceinline__ void fz_pair_of_block(int b, int t, int n_blocks, int &x, int &half)
 {
-    const int m1 = n_blocks - 1, t = round % m1;
+    const int m1 = n_blocks - 1;
     int other;
     if (b == m1 || b == t) {
         x = 0;
         other = b == t ? m1 : t;
     } else {
-        const int up = (b - t + m1) % m1, down = (t - b + m1) % m1;
-        x = up < down ? up : down;
-        other = (2 * t - b + 2 * m1) % m1;
+        const int up = b < t ? b - t + m1 : b - t, o = 2 * t - b;  // -m1 < o < 2 m1
+        x = up < m1 - up ? up : m1 - up;
+        other = o < 0 ? o + m1 : o >= m1 ? o - m1 : o;
     }
     half = b > other ? 1 : 0;
 }
@@ -938,6 +974,7 @@ __device__ __forceinline__ void fz_pair_of_block(int b, int round, int n_blocks,
 // a = w meets b = 16 + (w + t) % 16.  A thread keeps the elements of its pairs in registers; from one inner round to the
 // next the b side moves on by one pair, along the columns with a lane permutation, along the rows through LDS.  One
 // barrier per inner round.  Rows and columns beyond the matrix are zero and are not rotated.
+template <bool FULL>
 __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, const double *T_old, double *T, int *count, int r,
                                                   int n_blocks, int round, int x, double *sm)
 {
@@ -955,7 +992,7 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
         constexpr int KS = kJacNC / 4, YP = 18;
         auto Y = reinterpret_cast<double (*)[kJacNC * YP]>(Ts);  // [3]
         static_assert(3 * kJacNC * YP <= kJacLds - kJacTile, "in the place of what comes later");
-        const int w = wave_id(), l16 = lane & 15, kk = lane >> 4, before = round + n_blocks - 2;  // the round before, modulo n_blocks - 1
+        const int w = wave_id(), l16 = lane & 15, kk = lane >> 4, before = round == 0 ? n_blocks - 2 : round - 1;
         int px[2], half[2], pb[2][2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -969,17 +1006,15 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
             const int item = w + 4 * u, part = item >> 1, mt = item & 1, a = part == 1 ? 1 : 0, c = part == 0 ? 0 : 1;
             const int row = (mt ? (a ? pb[1][1] : pb[0][1]) : (a ? pb[1][0] : pb[0][0])) + l16;
             const double *Tc = T_old + (size_t)(c ? px[1] : px[0]) * kJacNC * kJacNC + (16 * (c ? half[1] : half[0]) + l16) * kJacNC;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int i = 4 * ks + kk, col = (i < kJacBS ? (c ? pb[1][0] : pb[0][0]) : (c ? pb[1][1] : pb[0][1])) + (i & 15);
-                ma[u][ks] = (item < 6 && row < r && col < r) ? M[(size_t)row * r + col] : 0.0;
-                tc[u][ks] = Tc[i];
+            const int pbc[2] = {c ? pb[1][0] : pb[0][0], c ? pb[1][1] : pb[0][1]};
+            if (u == 0 || w < 2) {
+                fz_jac_m_row<FULL>(M, row, pbc, kk, r, ma[u]);
+                fz_jac_t_row(Tc, kk, tc[u]);
             }
         }
         const int sa = w == 1 ? 1 : 0, sc0 = w == 0 ? 0 : 1;  // wavefronts 0 .. 2: the part they finish
         const double *Ta = T_old + (size_t)(sa ? px[1] : px[0]) * kJacNC * kJacNC + (16 * (sa ? half[1] : half[0]) + l16) * kJacNC;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) ta0[ks] = Ta[4 * ks + kk];
+        fz_jac_t_row(Ta, kk, ta0);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int item = w + 4 * u;
@@ -991,12 +1026,12 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
                 for (int v = 0; v < 4; ++v) Y[item >> 1][(16 * (item & 1) + kk + 4 * v) * YP + l16] = acc[v];
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (w < 3) {
             fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta0[ks], Y[w][(4 * ks + kk) * YP + l16], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta0[ks], Y[w][fz_jac_k(ks, kk) * YP + l16], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 G[(16 * sa + kk + 4 * v) * kJacLP + 16 * sc0 + l16] = acc[v];
@@ -1009,13 +1044,13 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int ri = fz_pair_column(blk, li + 8 * u);
-            g[u] = (ri < r && cj < r) ? M[(size_t)ri * r + cj] : 0.0;
+            g[u] = FULL || (ri < r && cj < r) ? M[(size_t)ri * r + cj] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) G[(li + 8 * u) * kJacLP + lj] = g[u];
     }
     if (tid == 0) big_rotations = 0;
-    __syncthreads();
+    lds_barrier();
 
     int big = 0;
     auto note = [&](double al, double be, double ga) __attribute__((always_inline)) {
@@ -1039,7 +1074,7 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
             for (int t = 0; t < h; ++t) {
                 const int ar = pr / h * 2 * h + pr % h, br = pr / h * 2 * h + h + (pr + t) % h;
                 const int ac = pc / h * 2 * h + pc % h, bc = pc / h * 2 * h + h + (pc + t) % h;
-                __syncthreads();
+                lds_barrier();
                 double cc, sc;
                 fz_rotation(G[ac * kJacLP + bc], G[ac * kJacLP + ac], G[bc * kJacLP + bc], cc, sc);
                 const double cr = fz_from_lane(cc, (lane & 48) | pr), sr = fz_from_lane(sc, (lane & 48) | pr);
@@ -1052,13 +1087,13 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
                     Ts[ac * kJacLP + 2 * pr + u] = cc * x - sc * y;
                     Ts[bc * kJacLP + 2 * pr + u] = sc * x + cc * y;
                 }
-                __syncthreads();
+                lds_barrier();
                 G[ar * kJacLP + ac] = cc * x0 - sc * x1;
                 G[ar * kJacLP + bc] = pr == pc ? 0.0 : sc * x0 + cc * x1;
                 G[br * kJacLP + ac] = pr == pc ? 0.0 : cc * y0 - sc * y1;
                 G[br * kJacLP + bc] = sc * y0 + cc * y1;
             }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             ta[u] = Ts[pc * kJacLP + 2 * pr + u];
@@ -1074,11 +1109,11 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
         // (every 16 lanes compute the rotations of all pairs, for their columns; the one of their row is among them)
         const double cr = fz_from_lane(cc, (lane & 48) | pr), sr = fz_from_lane(sc, (lane & 48) | pr);
         note(al, be, ga);
-        const double x0 = cr * aa - sr * ba, x1 = cr * ab - sr * bb, y0 = sr * aa + cr * ba, y1 = sr * ab + cr * bb;
-        aa = cc * x0 - sc * x1;
-        ab = fz_next_of_16(pr == pc ? 0.0 : sc * x0 + cc * x1);
-        ba = pr == pc ? 0.0 : cc * y0 - sc * y1;
-        bb = fz_next_of_16(sc * y0 + cc * y1);
+        const double x0 = cc * aa - sc * ab, x1 = sc * aa + cc * ab, y0 = cc * ba - sc * bb, y1 = sc * ba + cc * bb;
+        aa = cr * x0 - sr * y0;
+        ab = fz_next_of_16(pr == pc ? 0.0 : cr * x1 - sr * y1);
+        ba = pr == pc ? 0.0 : sr * x0 + cr * y0;
+        bb = fz_next_of_16(sr * x1 + cr * y1);
         mv[par][pr][pc] = fz_f64x2_t{ba, bb};
         if (pr == pc) *reinterpret_cast<fz_f64x2_t *>(dg[par][pc]) = fz_f64x2_t{ab, aa};
         if (pr == ((pc + 1) & 15)) dg[par][pc][2] = bb;
@@ -1088,7 +1123,7 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
             ta[u] = cc * x - sc * y;
             tb[u] = fz_next_of_16(sc * x + cc * y);
         }
-        __syncthreads();
+        lds_barrier();
         const fz_f64x2_t m = mv[par][(pr + 1) & 15][pc], c2 = *reinterpret_cast<const fz_f64x2_t *>(dg[par][pc]);
         ba = m[0];
         bb = m[1];
@@ -1099,14 +1134,15 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
     *reinterpret_cast<fz_f64x2_t *>(T + pc * kJacNC + 2 * pr) = fz_f64x2_t{ta[0], ta[1]};
     *reinterpret_cast<fz_f64x2_t *>(T + (16 + pc) * kJacNC + 2 * pr) = fz_f64x2_t{tb[0], tb[1]};
     if (big > 0) atomicAdd(&big_rotations, big);
-    __syncthreads();
+    lds_barrier();
     if (tid == 0 && big_rotations > 0) atomicAdd(count, big_rotations);
 }
 
+template <bool FULL>
 __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restrict__ Ma, double *__restrict__ Mb,
                                                            double *__restrict__ Jt, const double *__restrict__ T,
                                                            double *__restrict__ T_next, long long t_seq, int *rotations, int r,
-                                                           int n_blocks, int k)
+                                                           int n_blocks, int sweep, int round)
 {
     // rotations[sequence][sweep]: written by the workgroups that find the rotations of that sweep; final before a launch
     // that applies the sweep's last ones, and a sweep without any ends the work of all later launches
@@ -1117,43 +1153,48 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     const int n_pairs = n_blocks / 2, n_tri = n_pairs * (n_pairs + 1) / 2, m1 = n_blocks - 1;
     int x = (int)blockIdx.x;
     if (x < n_pairs) {
-        const int sweep = (k + 1) / m1;
-        if (sweep == kJacobiSweeps || (sweep > 0 && rotations[sweep - 1] == 0)) return;  // same for the whole workgroup
-        fz_find_rotations(Ma, k < 0 ? nullptr : T, T_next + (size_t)blockIdx.z * t_seq, rotations + sweep, r, n_blocks, (k + 1) % m1, x, sm);
+        const bool next = round + 1 == m1;
+        const int s = sweep + next;
+        if (s == kJacobiSweeps || (s > 0 && rotations[s - 1] == 0)) return;  // same for the whole workgroup
+        fz_find_rotations<FULL>(Ma, round < 0 ? nullptr : T, T_next + (size_t)blockIdx.z * t_seq, rotations + s, r, n_blocks,
+                                next ? 0 : round + 1, x, sm);
         return;
     }
     x -= n_pairs;
-    const int round = k % m1;
-    if (k >= m1 && rotations[k / m1 - 1] == 0) return;
+    if (sweep > 0 && rotations[sweep - 1] == 0) return;
     double *Y = sm;
     Mb += (size_t)blockIdx.z * r * r;
     Jt += (size_t)blockIdx.z * r * r;
     constexpr int KS = kJacNC / 4;
     const int tid = threadIdx.x, lane = lane_id(), w = wave_id(), l16 = lane & 15, kk = lane >> 4;
-    if (x >= n_tri) {  // wavefront = 16 positions
-        const int p = (x - n_tri) % n_pairs, i = (x - n_tri) / n_pairs * 64 + 16 * w + l16;
+    if (x >= n_tri) {  // wavefront = two times 16 positions
+        const int p = (x - n_tri) % n_pairs, i0 = (x - n_tri) / n_pairs * 128 + 32 * w + l16;
         int blk[2];
         fz_pair_of_blocks(p, round, n_blocks, blk);
         const double *Tp = T + (size_t)p * kJacNC * kJacNC;
-        double tv[KS], ta[2][KS];
+        double tv[2][KS], ta[2][KS];
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int c = fz_pair_column(blk, 4 * ks + kk);
-            tv[ks] = (c < r && i < r) ? Jt[(size_t)c * r + i] : 0.0;
+        for (int g = 0; g < 2; ++g)
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) ta[mt][ks] = Tp[(16 * mt + l16) * kJacNC + 4 * ks + kk];
-        }
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[mt][ks], tv[ks], acc, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int c = fz_pair_column(blk, 16 * mt + kk + 4 * v);
-                if (c < r && i < r) Jt[(size_t)c * r + i] = acc[v];
+            for (int ks = 0; ks < KS; ++ks) {
+                const int c = fz_pair_column(blk, fz_jac_k(ks, kk)), i = i0 + 16 * g;
+                tv[g][ks] = (FULL || c < r) && i < r ? Jt[(size_t)c * r + i] : 0.0;
             }
-        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) fz_jac_t_row(Tp + (16 * mt + l16) * kJacNC, kk, ta[mt]);
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[mt][ks], tv[g][ks], acc, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int c = fz_pair_column(blk, 16 * mt + kk + 4 * v), i = i0 + 16 * g;
+                    if ((FULL || c < r) && i < r) Jt[(size_t)c * r + i] = acc[v];
+                }
+            }
         return;
     }
     int p, q, bp[2], bq[2];
@@ -1163,13 +1204,9 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     const double *Tp = T + (size_t)p * kJacNC * kJacNC, *Tq = T + (size_t)q * kJacNC * kJacNC;
     const int mt = w >> 1, nt = w & 1;  // wavefront = one tile of 16 x 16
     double xa[KS], tq[KS], tp[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const int ra = fz_pair_column(bp, 16 * mt + l16), cb = fz_pair_column(bq, 4 * ks + kk);
-        xa[ks] = (ra < r && cb < r) ? Ma[(size_t)ra * r + cb] : 0.0;
-        tq[ks] = Tq[(16 * nt + l16) * kJacNC + 4 * ks + kk];
-        tp[ks] = Tp[(16 * mt + l16) * kJacNC + 4 * ks + kk];
-    }
+    fz_jac_m_row<FULL>(Ma, bp[mt] + l16, bq, kk, r, xa);
+    fz_jac_t_row(Tq + (16 * nt + l16) * kJacNC, kk, tq);
+    fz_jac_t_row(Tp + (16 * mt + l16) * kJacNC, kk, tp);
     fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[ks], tq[ks], acc, 0, 0, 0);
@@ -1179,19 +1216,26 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[ks], Y[(4 * ks + kk) * kJacLP + 16 * nt + l16], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[ks], Y[fz_jac_k(ks, kk) * kJacLP + 16 * nt + l16], acc, 0, 0, 0);
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < 4; ++v) Y[(16 * mt + kk + 4 * v) * kJacLP + 16 * nt + l16] = acc[v];
     __syncthreads();
-    const int lj = tid & 31, li = tid >> 5;
+    const int j = 2 * l16, li = tid >> 4;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {  // M' stays symmetric to the last bit
-        const int i = li + 8 * u, ra = fz_pair_column(bp, i), cb = fz_pair_column(bq, lj);
-        const bool swap = p == q && i > lj;
-        if (ra < r && cb < r) Mb[(size_t)ra * r + cb] = Y[(swap ? lj : i) * kJacLP + (swap ? i : lj)];
-        const int rb = fz_pair_column(bq, i), ca = fz_pair_column(bp, lj);
-        if (p != q && rb < r && ca < r) Mb[(size_t)rb * r + ca] = Y[lj * kJacLP + i];
+    for (int u = 0; u < 2; ++u) {  // rows li + 16 u, columns j and j + 1; M' stays symmetric to the last bit
+        const int i = li + 16 * u, ra = bp[u] + li, cb = fz_pair_column(bq, j), rb = bq[u] + li, ca = fz_pair_column(bp, j);
+        const double v0 = p == q && i > j ? Y[j * kJacLP + i] : Y[i * kJacLP + j];
+        const double v1 = p == q && i > j + 1 ? Y[(j + 1) * kJacLP + i] : Y[i * kJacLP + j + 1];
+        if constexpr (FULL) {
+            *reinterpret_cast<fz_f64x2_t *>(Mb + (size_t)ra * r + cb) = fz_f64x2_t{v0, v1};
+            if (p != q) *reinterpret_cast<fz_f64x2_t *>(Mb + (size_t)rb * r + ca) = fz_f64x2_t{Y[j * kJacLP + i], Y[(j + 1) * kJacLP + i]};
+        } else {
+            if (ra < r && cb < r) Mb[(size_t)ra * r + cb] = v0;
+            if (ra < r && cb + 1 < r) Mb[(size_t)ra * r + cb + 1] = v1;
+            if (p != q && rb < r && ca < r) Mb[(size_t)rb * r + ca] = Y[j * kJacLP + i];
+            if (p != q && rb < r && ca + 1 < r) Mb[(size_t)rb * r + ca + 1] = Y[(j + 1) * kJacLP + i];
+        }
     }
 }
 
@@ -1486,11 +1530,14 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                            rotations, r, f.g_splits);
         {
             const int n_blocks = std::max(2, ((r + kJacBS - 1) / kJacBS + 1) / 2 * 2);  // an even number of column blocks
-            const int n_pairs = n_blocks / 2, grid = n_pairs * (n_pairs + 1) / 2 + n_pairs * ((r + 63) / 64);
+            const int n_pairs = n_blocks / 2, grid = n_pairs * (n_pairs + 1) / 2 + n_pairs * ((r + 127) / 128);
+            const auto round_kernel = r == n_blocks * kJacBS ? jacobi_round_kernel<true> : jacobi_round_kernel<false>;
             for (int k = -1; k < kJacobiSweeps * (n_blocks - 1); ++k) {
                 const bool odd = k & 1;
-                hipLaunchKernelGGL(jacobi_round_kernel, dim3(k < 0 ? n_pairs : n_pairs + grid, 1, nb), dim3(256), 0, st,
-                                   k >= 0 && odd ? Mb : Ma, odd ? Ma : Mb, Jt, Tj[odd], Tj[!odd], tj_seq, rotations, r, n_blocks, k);
+                const int sweep = k < 0 ? 0 : k / (n_blocks - 1), round = k < 0 ? -1 : k % (n_blocks - 1);
+                hipLaunchKernelGGL(round_kernel, dim3(k < 0 ? n_pairs : n_pairs + grid, 1, nb), dim3(256), 0, st,
+                                   k >= 0 && odd ? Mb : Ma, odd ? Ma : Mb, Jt, Tj[odd], Tj[!odd], tj_seq, rotations, r, n_blocks, sweep,
+                                   round);
             }
         }
         hipLaunchKernelGGL(ritz_order_kernel, dim3(nb), dim3(1024), 0, st, Ma, Mb, rotations, order,

@@ -80,3 +80,9 @@ def test_a_nan_in_the_input_stays_a_value():
     flat = X[1].astype(np.float64).transpose(2, 0, 1, 3).reshape(L, n)
     ref_A = flat @ B[1].T
     assert np.abs(A[1] - ref_A).max() <= 1e-5 * np.abs(ref_A).max()
+
+
+@pytest.mark.parametrize("r,batch", [(64, 3), (96, 1), (128, 1), (130, 1), (160, 2), (256, 1)])
+def test_ranks_of_whole_pairs_of_blocks(r, batch):
+    """The eigen-solver leaves its bounds checks out where r is a multiple of 32; 128 positions of J^T per workgroup."""
+    test_ranks_around_the_block_sizes(r, batch, None)
