@@ -1368,6 +1368,16 @@ struct FzLayout {
         off_rot, total;
 };
 
+// Of at most `most` splits of `tiles` output tiles the number with which the rounds of 256 workgroups take least, in shares of a tile:
+// ceil(tiles splits / 256) / splits (136 tiles: 2 / 3 with three, 3 / 4 with four).  Fewer, where that is the same: less to add up.
+int gram_splits_of(int tiles, int most)
+{
+    int best = 1;
+    for (int s = 2; s <= most; ++s)
+        if ((tiles * s + 255) / 256 * best < (tiles * best + 255) / 256 * s) best = s;
+    return best;
+}
+
 FzLayout fz_layout(const xkv_shape &s, int r)
 {
     FzLayout f{};
@@ -1448,14 +1458,14 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
             GemmArgs a{};
             a.P = GemmOperand{Xt, f.Lp, 0, f.Lp, n, (long long)f.xt_seq};
             a.Q = a.P;
-            a.n_slabs = f.Lp / E; a.splits = f.gram_splits; a.lower_only = 1; a.tiles_n = tn;
+            a.n_slabs = f.Lp / E; a.splits = gram_splits_of(f.gram_tiles * nb, f.gram_splits); a.lower_only = 1; a.tiles_n = tn;
             a.out_f32 = part; a.out_bf16 = nullptr; a.ldo = n; a.plane = (long long)n * n; a.out_seq = (long long)f.part_seq;
             profile_begin(3, st);
             e = launch_gemm<T>(a, f.gram_tiles, nb, st);
             profile_end(3, st);
             if (e != hipSuccess) break;
             const int n64 = (n + 63) / 64;
-            hipLaunchKernelGGL(gram_finish_kernel, dim3(n64, n64, nb), dim3(256), 0, st, part, C, n, f.gram_splits, a.plane,
+            hipLaunchKernelGGL(gram_finish_kernel, dim3(n64, n64, nb), dim3(256), 0, st, part, C, n, a.splits, a.plane,
                                (long long)f.part_seq);
         }
         hipLaunchKernelGGL(init_v_kernel, dim3(blocks256(vcount), 1, nb), dim3(256), 0, st, Vt, vcount,
