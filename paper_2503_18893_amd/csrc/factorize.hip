@@ -476,9 +476,11 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
 // shift = 1e-13 * max diagonal of the original G (diag0) keeps the factor defined when the r vectors are
 // numerically dependent (an X_cat of rank below r): such directions come out short instead of normalised and
 // contribute nothing to A B.
-// What bounds it: the chain of its 16 launches at r = 512, each of which is workgroup 0: 9.8 us without a panel before it, 12
-// with it.  32 steps on rows of 32 elements with scalar broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with
-// workgroups of 32 whole rows, 25 us in the first launches and 14 in the last; blocks of 32 x 32 12 in all of them.
+// What bounds it: the chain of its 16 launches at r = 512, each of which is workgroup 0: 12 us
+// in general, 9.3 where r is a multiple of 32: few wavefronts do all the work, so instructions count, and there every row comes in 16-byte
+// runs and without bounds checks; the maximum of the diagonal is found once (11.4 -> 9.3 us).  32 steps on rows of 32 elements with scalar
+// broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with workgroups of 32 whole rows, 25 us in the first
+// launches and 14 in the last; blocks of 32 x 32 12 in all of them.
 constexpr int kCholRB = 32, kCholThreads = 512;
 constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
 constexpr size_t chol_lds(int pb)  // 64 rows of the panel; workgroup 0: its rows and three blocks
@@ -510,10 +512,26 @@ template <int I, int END, typename F> __device__ __forceinline__ void fz_for(F f
     }
 }
 
-template <int PB>
-__global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Li,
-                                                                  const double *__restrict__ diag0, int r, int c0)
+// Products over 16 or 32 positions in steps of 4: in step s, lane group kk takes position fz_run_k(s, kk), so that what a lane needs of
+// a row are runs of four.
+__device__ __forceinline__ constexpr int fz_run_k(int s, int kk) { return 16 * (s >> 2) + 4 * kk + (s & 3); }
+
+// The elements fz_run_k(0 .. N - 1, kk) of a row.
+template <int N> __device__ __forceinline__ void fz_run_row(const double *row, int kk, double (&v)[N])
 {
+#pragma unroll
+    for (int h = 0; h < N / 2; ++h) {
+        const fz_f64x2_t t = *reinterpret_cast<const fz_f64x2_t *>(row + 16 * (h >> 1) + 4 * kk + 2 * (h & 1));
+        v[2 * h] = t[0];
+        v[2 * h + 1] = t[1];
+    }
+}
+
+template <int PB, bool FULL>  // FULL: r a multiple of the panel, which is as wide as a block
+__global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Li,
+                                                                  double *__restrict__ diag0, int r, int c0)
+{
+    static_assert(!FULL || PB == kCholRB, "panels begin where blocks do");
     constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64;
     G += (size_t)blockIdx.z * r * r;
     Li += (size_t)blockIdx.z * r * r;
@@ -523,15 +541,17 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     const int tid = threadIdx.x, lane = tid & 63, w = wave_id(), l16 = lane & 15, kk = lane >> 4;
     const int d0 = c0 + PB;  // first row below the diagonal block
 
-    // Sixteen rows (value(row, k): row l16, column k of PB) times columns 16 ct .. of the transposed inverse of the panel's diagonal block
-    // -> rows `at` .. of P
-    auto times_inverse = [&](auto value, int ct, int at) __attribute__((always_inline)) {
-        double ga[KS], lb[KS];
+    // Sixteen rows (lane l16 holds fz_run_k(.., kk) of row l16) times columns 16 ct .. of the transposed inverse of the panel's diagonal
+    // block -> rows `at` .. of P
+    auto times_inverse = [&](const double (&ga)[KS], int ct, int at) __attribute__((always_inline)) {
+        double lb[KS];
         const int ir = c0 + 16 * ct + l16;
+        if constexpr (FULL) {
+            fz_run_row(Li + (size_t)ir * r + c0, kk, lb);
+        } else {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            ga[ks] = value(4 * ks + kk);
-            lb[ks] = (ir < r && c0 + 4 * ks + kk < r) ? Li[(size_t)ir * r + c0 + 4 * ks + kk] : 0.0;
+            for (int ks = 0; ks < KS; ++ks)
+                lb[ks] = (ir < r && c0 + fz_run_k(ks, kk) < r) ? Li[(size_t)ir * r + c0 + fz_run_k(ks, kk)] : 0.0;
         }
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -541,19 +561,36 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     };
     auto panel_tile = [&](int row0, int ct, int at) __attribute__((always_inline)) {  // rows of the factor
         const int row = row0 + l16;
-        times_inverse([&](int k) __attribute__((always_inline)) { return row < r ? G[(size_t)row * r + c0 + k] : 0.0; }, ct, at);
+        double ga[KS];
+        if constexpr (FULL) {
+            fz_run_row(G + (size_t)row * r + c0, kk, ga);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) ga[ks] = row < r ? G[(size_t)row * r + c0 + fz_run_k(ks, kk)] : 0.0;
+        }
+        times_inverse(ga, ct, at);
     };
     auto inverse_tile = [&](int col0, int ct, int at) __attribute__((always_inline)) {  // columns of the panel's rows of the inverse
         const int col = col0 + l16;
-        times_inverse([&](int k) __attribute__((always_inline)) {
-            return col < c0 ? (c0 + k < r ? G[(size_t)col * r + c0 + k] : 0.0) : col == c0 + k ? 1.0 : 0.0;
-        }, ct, at);
+        double ga[KS];
+        if (FULL && col0 < c0) {
+            fz_run_row(G + (size_t)col * r + c0, kk, ga);
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const int k = fz_run_k(ks, kk);
+                ga[ks] = !FULL && col < c0 ? (c0 + k < r ? G[(size_t)col * r + c0 + k] : 0.0) : col == c0 + k ? 1.0 : 0.0;
+            }
+        }
+        times_inverse(ga, ct, at);
     };
     auto outer = [&](int rs, int cs) __attribute__((always_inline)) {  // tile of 16 x 16 of the panel's outer product
+        double a[KS], b[KS];
+        fz_run_row(P + (rs + l16) * PITCH, kk, a);
+        fz_run_row(P + (cs + l16) * PITCH, kk, b);
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(rs + l16) * PITCH + 4 * ks + kk], P[(cs + l16) * PITCH + 4 * ks + kk], acc, 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ks], b[ks], acc, 0, 0, 0);
         return acc;
     };
 
@@ -572,10 +609,18 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
         // tile (w / 2 % 2, w % 2) of the block for wavefronts 0 .. 3, requested first: rows i0 .., columns j0 .. of the trailing matrix, or
         // columns j0 .., rows i0 .. of the inverse, which lies transposed above the diagonal
         const int rt = (w >> 1) & 1, ctile = w & 1, jc = j0 + 16 * ctile + l16;
+        const bool rows = !FULL || i0 < r;  // (the last launch has rows of the inverse to write, and no blocks below them)
         double old[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            if (inverse) {
+            if constexpr (FULL) {
+                if (!rows || w >= 4 || (inverse && j0 >= c0))
+                    old[v] = 0.0;
+                else if (inverse)
+                    old[v] = G[(size_t)(j0 + 16 * ctile + kk + 4 * v) * r + i0 + 16 * rt + l16];
+                else
+                    old[v] = G[(size_t)(i0 + 16 * rt + kk + 4 * v) * r + jc];
+            } else if (inverse) {
                 const int col = j0 + 16 * ctile + kk + 4 * v, irow = i0 + 16 * rt + l16;
                 old[v] = (w < 4 && irow < own_end && col < c0) ? G[(size_t)col * r + irow] : 0.0;
             } else {
@@ -587,9 +632,9 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
         const bool square = !inverse && bi == bj;
         for (int item = w; item < (square ? 2 : 4) * CT; item += WAVES) {
             const int half = item / (2 * CT), rest = item % (2 * CT), ct = rest % CT, at = 16 * (rest / CT);
-            if (half == 0)
-                panel_tile(i0 + at, ct, at);
-            else if (inverse)
+            if (half == 0) {
+                if (rows) panel_tile(i0 + at, ct, at);
+            } else if (inverse)
                 inverse_tile(j0 + at, ct, kCholRB + at);
             else
                 panel_tile(j0 + at, ct, kCholRB + at);
@@ -600,14 +645,14 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
                 const int row = c0 + t / kCholRB, col = j0 + t % kCholRB;
                 if (row < r && col < c0) Li[(size_t)row * r + col] = P[(kCholRB + col - j0) * PITCH + row - c0];
             }
-        if (w < 4 && !(square && ctile > rt)) {
+        if (w < 4 && rows && !(square && ctile > rt)) {
             if (inverse) {
                 const fz_f64x4_t acc = outer(kCholRB + 16 * ctile, 16 * rt);
                 const int irow = i0 + 16 * rt + l16;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int col = j0 + 16 * ctile + kk + 4 * v;
-                    if (irow < own_end && col < d0) G[(size_t)col * r + irow] = old[v] - acc[v];
+                    if (FULL || (irow < own_end && col < d0)) G[(size_t)col * r + irow] = old[v] - acc[v];
                 }
             } else {
                 const fz_f64x4_t acc = outer(16 * rt, (square ? 0 : kCholRB) + 16 * ctile);
@@ -615,7 +660,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
                 for (int v = 0; v < 4; ++v) {
                     const int irow = i0 + 16 * rt + kk + 4 * v;
                     // (the next diagonal block is workgroup 0's: it reads what this launch began with)
-                    if (irow < own_end && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
+                    if ((FULL || irow < own_end) && jc <= irow && irow >= d0 + PB) G[(size_t)irow * r + jc] = old[v] - acc[v];
                 }
             }
         }
@@ -626,23 +671,29 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     // ---- workgroup 0: the next diagonal block, rows and columns d0 .. d0 + pwc - 1
     double *D = P + PB * PITCH, *LF = D + PB * LP, *LI = LF + PB * LP;  // [PB][LP] block, its factor, the inverse
     __shared__ double red[WAVES];
-    const int pwc = (r - d0) < PB ? (r - d0) : PB;
-    double mx = 0.0;
-    for (int i = tid; i < r; i += kCholThreads) mx = fmax(mx, diag0[i]);
-    double g0[CT][4];  // this wavefront's tile (w / CT, w % CT) of the block
+    const int pwc = FULL || (r - d0) >= PB ? PB : r - d0;
+    double mx = c0 < 0 ? 0.0 : diag0[0];  // the first launch leaves the largest element of the diagonal there
+    double g0[4];  // this wavefront's tile (w / CT, w % CT) of the block
     const int tr = w / CT, tc = w % CT;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int i = 16 * tr + kk + 4 * v, j = 16 * tc + l16;
-        g0[0][v] = (w < CT * CT && i < pwc && j <= i) ? G[(size_t)(d0 + i) * r + d0 + j] : 0.0;
+        g0[v] = (w < CT * CT && (FULL || (i < pwc && j <= i))) ? G[(size_t)(d0 + i) * r + d0 + j] : 0.0;
     }
-    if (c0 >= 0 && w < CT * CT) panel_tile(d0 + 16 * tr, tc, 16 * tr);  // (rows beyond the matrix are zero)
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
-    if (lane == 0) red[w] = mx;
+    if (c0 < 0) {
+        for (int i = tid; i < r; i += kCholThreads) mx = fmax(mx, diag0[i]);
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        if (lane == 0) red[w] = mx;
+    } else if (w < CT * CT) {
+        panel_tile(d0 + 16 * tr, tc, 16 * tr);  // (rows beyond the matrix are zero)
+    }
     __syncthreads();
-    mx = red[0];
+    if (c0 < 0) {
+        mx = red[0];
 #pragma unroll
-    for (int ww = 1; ww < WAVES; ++ww) mx = fmax(mx, red[ww]);
+        for (int ww = 1; ww < WAVES; ++ww) mx = fmax(mx, red[ww]);
+        if (tid == 0) diag0[0] = mx;
+    }
     const double shift = fmax(1e-13 * mx, 1e-300);
     if (w < CT * CT) {
         fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
@@ -650,7 +701,7 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
 #pragma unroll
         for (int v = 0; v < 4; ++v) {  // (rows beyond the matrix are identity rows)
             const int i = 16 * tr + kk + 4 * v, j = 16 * tc + l16;
-            D[i * LP + j] = (i < pwc && j <= i) ? g0[0][v] - acc[v] + (i == j ? shift : 0.0) : i == j ? 1.0 : 0.0;
+            D[i * LP + j] = (i < pwc && j <= i) ? g0[v] - acc[v] + (i == j ? shift : 0.0) : i == j ? 1.0 : 0.0;
         }
     }
     __syncthreads();
@@ -711,6 +762,12 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
         }
     }
     __syncthreads();
+    if constexpr (FULL) {
+        const int row = tid / (PB / 2), col = tid % (PB / 2) * 2;
+        static_assert(!FULL || kCholThreads == PB * PB / 2, "two elements each");
+        *reinterpret_cast<fz_f64x2_t *>(Li + (size_t)(d0 + row) * r + d0 + col) = fz_f64x2_t{LI[row * LP + col], LI[row * LP + col + 1]};
+        return;
+    }
     for (int t = tid; t < PB * PB; t += kCholThreads) {
         const int row = t / PB, col = t % PB;
         if (row < pwc && col < pwc) Li[(size_t)(d0 + row) * r + d0 + col] = LI[row * LP + col];
@@ -908,22 +965,7 @@ __device__ __forceinline__ void fz_rotation(double alpha, double beta, double ga
 constexpr int kJacNC = 32, kJacBS = 16, kJacLP = 34, kJacTile = kJacNC * kJacLP;
 constexpr int kJacLds = 2 * kJacTile + 2 * 256 * 2 + 2 * 16 * 4;  // doubles
 
-// The products run over the 32 positions of a pair in steps of 4: in step s, lane group kk takes position fz_jac_k(s, kk), so that what
-// a lane needs of a row are two runs of four.
-__device__ __forceinline__ constexpr int fz_jac_k(int s, int kk) { return 16 * (s >> 2) + 4 * kk + (s & 3); }
-
-// The elements fz_jac_k(0 .. 7, kk) of a row of T.
-__device__ __forceinline__ void fz_jac_t_row(const double *row, int kk, double (&v)[8])
-{
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        const fz_f64x2_t t = *reinterpret_cast<const fz_f64x2_t *>(row + 16 * (h >> 1) + 4 * kk + 2 * (h & 1));
-        v[2 * h] = t[0];
-        v[2 * h + 1] = t[1];
-    }
-}
-
-// The same of row `row` of M in the columns of a pair of blocks; FULL: every block lies inside the matrix, otherwise zeros beyond it.
+// Row `row` of M in the columns of a pair of blocks, in that order; FULL: every block lies inside the matrix, otherwise zeros beyond it.
 template <bool FULL>
 __device__ __forceinline__ void fz_jac_m_row(const double *M, int row, const int (&b)[2], int kk, int r, double (&v)[8])
 {
@@ -1009,12 +1051,12 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
             const int pbc[2] = {c ? pb[1][0] : pb[0][0], c ? pb[1][1] : pb[0][1]};
             if (u == 0 || w < 2) {
                 fz_jac_m_row<FULL>(M, row, pbc, kk, r, ma[u]);
-                fz_jac_t_row(Tc, kk, tc[u]);
+                fz_run_row(Tc, kk, tc[u]);
             }
         }
         const int sa = w == 1 ? 1 : 0, sc0 = w == 0 ? 0 : 1;  // wavefronts 0 .. 2: the part they finish
         const double *Ta = T_old + (size_t)(sa ? px[1] : px[0]) * kJacNC * kJacNC + (16 * (sa ? half[1] : half[0]) + l16) * kJacNC;
-        fz_jac_t_row(Ta, kk, ta0);
+        fz_run_row(Ta, kk, ta0);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int item = w + 4 * u;
@@ -1031,7 +1073,7 @@ __device__ __forceinline__ void fz_find_rotations(const double *__restrict__ M, 
             fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta0[ks], Y[w][fz_jac_k(ks, kk) * YP + l16], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ta0[ks], Y[w][fz_run_k(ks, kk) * YP + l16], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 G[(16 * sa + kk + 4 * v) * kJacLP + 16 * sc0 + l16] = acc[v];
@@ -1177,11 +1219,11 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
         for (int g = 0; g < 2; ++g)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const int c = fz_pair_column(blk, fz_jac_k(ks, kk)), i = i0 + 16 * g;
+                const int c = fz_pair_column(blk, fz_run_k(ks, kk)), i = i0 + 16 * g;
                 tv[g][ks] = (FULL || c < r) && i < r ? Jt[(size_t)c * r + i] : 0.0;
             }
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) fz_jac_t_row(Tp + (16 * mt + l16) * kJacNC, kk, ta[mt]);
+        for (int mt = 0; mt < 2; ++mt) fz_run_row(Tp + (16 * mt + l16) * kJacNC, kk, ta[mt]);
 #pragma unroll
         for (int g = 0; g < 2; ++g)
 #pragma unroll
@@ -1205,8 +1247,8 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     const int mt = w >> 1, nt = w & 1;  // wavefront = one tile of 16 x 16
     double xa[KS], tq[KS], tp[KS];
     fz_jac_m_row<FULL>(Ma, bp[mt] + l16, bq, kk, r, xa);
-    fz_jac_t_row(Tq + (16 * nt + l16) * kJacNC, kk, tq);
-    fz_jac_t_row(Tp + (16 * mt + l16) * kJacNC, kk, tp);
+    fz_run_row(Tq + (16 * nt + l16) * kJacNC, kk, tq);
+    fz_run_row(Tp + (16 * mt + l16) * kJacNC, kk, tp);
     fz_f64x4_t acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[ks], tq[ks], acc, 0, 0, 0);
@@ -1216,7 +1258,7 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double *__restr
     acc = fz_f64x4_t{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[ks], Y[fz_jac_k(ks, kk) * kJacLP + 16 * nt + l16], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(tp[ks], Y[fz_run_k(ks, kk) * kJacLP + 16 * nt + l16], acc, 0, 0, 0);
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < 4; ++v) Y[(16 * mt + kk + 4 * v) * kJacLP + 16 * nt + l16] = acc[v];
@@ -1482,10 +1524,12 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                 const int blocks = c0 < 0 ? 0 : std::max(0, (r - c0 - pb + kCholRB - 1) / kCholRB);
                 const int columns = c0 < 0 ? 0 : std::max(1, blocks) * ((c0 + pb + kCholRB - 1) / kCholRB);
                 const dim3 grid(1 + blocks * (blocks + 1) / 2 + columns, 1, nb);
-                if (pb == 32)
-                    hipLaunchKernelGGL(chol_panel_kernel<32>, grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
+                if (pb == 32 && r % 32 == 0)
+                    hipLaunchKernelGGL((chol_panel_kernel<32, true>), grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
+                else if (pb == 32)
+                    hipLaunchKernelGGL((chol_panel_kernel<32, false>), grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
                 else
-                    hipLaunchKernelGGL(chol_panel_kernel<16>, grid, dim3(kCholThreads), chol_lds(16), st, Gm, Lt, diag0, r, c0);
+                    hipLaunchKernelGGL((chol_panel_kernel<16, false>), grid, dim3(kCholThreads), chol_lds(16), st, Gm, Lt, diag0, r, c0);
             }
             const dim3 grid((n + 127) / 128, ((r + 31) / 32 + 1) / 2, nb);
             if (r % 4 == 0)
