@@ -457,17 +457,17 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
     if (i == j) diag0[i] = v;
 }
 
-// (3c) The inverse Li of the Cholesky factor Lc of G + shift I, right-looking in panels of PB columns: the factor's columns are eliminated from
+// (3c) The inverse Li of the Cholesky factor Lc of G + shift I, right-looking in panels of 32 columns: the factor's columns are eliminated from
 // the trailing matrix and, the same way, from the rows of an identity that becomes the inverse.  A launch has three kinds of
-// workgroups, for the panel c0 .. c0 + PB - 1, whose diagonal block of Li is there:
-//   * 32 x 32 blocks of the trailing matrix, on or below the diagonal.  The panel entries Lc[j'][c0 .. c0 + PB) of its rows and of its
+// workgroups, for the panel c0 .. c0 + 31, whose diagonal block of Li is there:
+//   * 32 x 32 blocks of the trailing matrix, on or below the diagonal.  The panel entries Lc[j'][c0 .. c0 + 32) of its rows and of its
 //     columns are G[j'][panel] times the transposed diagonal block of Li (fp64 matrix cores, 16 rows a step) and stay in LDS; their
 //     product is subtracted;
 //   * 32 x 32 blocks of the unfinished inverse X: rows below the panel, columns up to its end.  The panel's rows of X times the diagonal
 //     block of Li are the final rows of Li (written by the first block of each column); with the panel entries of the block's rows
 //     they are subtracted.  X lies transposed above the diagonal of G, which the factorization does not use;
 //   * workgroup 0 prepares the next panel: it brings the next diagonal block up to date by itself (its 32 panel rows and one
-//     outer product), factors and inverts it and leaves the inverse in Li.  The first launch, c0 = -PB, has only this
+//     outer product), factors and inverts it and leaves the inverse in Li.  The first launch, c0 = -32, has only this
 //     workgroup; in the last, the last panel's, it has nothing to do.
 // The elimination runs in one wavefront without a barrier, 16 columns at a time: a lane holds a row of the block or a column of an
 // identity, and step c is the same for both: t = x[c] / sqrt(pivot), x[j] -= (t of lane j) t for j > c.  What t leaves in
@@ -480,14 +480,11 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
 // in general, 9.3 where r is a multiple of 32: few wavefronts do all the work, so instructions count, and there every row comes in 16-byte
 // runs and without bounds checks; the maximum of the diagonal is found once (11.4 -> 9.3 us).  32 steps on rows of 32 elements with scalar
 // broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with workgroups of 32 whole rows, 25 us in the first
-// launches and 14 in the last; blocks of 32 x 32 12 in all of them.
-constexpr int kCholRB = 32, kCholThreads = 512;
-constexpr int chol_pitch(int pb) { return pb == 32 ? 36 : 18; }  // doubles per row of the panel in LDS
-constexpr size_t chol_lds(int pb)  // 64 rows of the panel; workgroup 0: its rows and three blocks
-{
-    const size_t rows = 2 * (size_t)kCholRB * chol_pitch(pb), head = (size_t)pb * chol_pitch(pb) + 3 * (size_t)pb * (pb + 1);
-    return (rows > head ? rows : head) * 8;
-}
+// launches and 14 in the last; blocks of 32 x 32 12 in all of them.  Panels of 16 columns, twice as many launches, take longer at every
+// rank (factorisation at r = 1024, one and four sequences: 14.3 and 29.2 ms, with 32 columns 13.7 and 26.9).
+constexpr int kCholRB = 32, kCholThreads = 512, kCholPitch = 36;  // panels and blocks; doubles per row of the panel in LDS
+// 64 rows of the panel; workgroup 0: its rows and three blocks
+constexpr size_t kCholLds = 8 * std::max<size_t>(2 * kCholRB * kCholPitch, kCholRB * kCholPitch + 3 * kCholRB * (kCholRB + 1));
 
 // 1 / sqrt(x): the hardware's estimate y (better than 2^-20) and one third-order step, y (1 + e / 2 + 3 e^2 / 8) with
 // e = 1 - x y^2: a chain of four dependent operations where two Newton steps are eight.
@@ -527,12 +524,11 @@ template <int N> __device__ __forceinline__ void fz_run_row(const double *row, i
     }
 }
 
-template <int PB, bool FULL>  // FULL: r a multiple of the panel, which is as wide as a block
+template <bool FULL>  // FULL: r a multiple of 32
 __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__restrict__ G, double *__restrict__ Li,
                                                                   double *__restrict__ diag0, int r, int c0)
 {
-    static_assert(!FULL || PB == kCholRB, "panels begin where blocks do");
-    constexpr int KS = PB / 4, CT = PB / 16, PITCH = chol_pitch(PB), LP = PB + 1, WAVES = kCholThreads / 64;
+    constexpr int PB = kCholRB, KS = PB / 4, CT = PB / 16, PITCH = kCholPitch, LP = PB + 1, WAVES = kCholThreads / 64;
     G += (size_t)blockIdx.z * r * r;
     Li += (size_t)blockIdx.z * r * r;
     diag0 += (size_t)blockIdx.z * r;
@@ -713,11 +709,11 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             x[j] = D[l16 * LP + j];
-            y[j] = kk == 1 ? (l16 == j ? 1.0 : 0.0) : PB == 32 && kk == 2 ? D[(PB - 16 + l16) * LP + j] : 0.0;
+            y[j] = kk == 1 ? (l16 == j ? 1.0 : 0.0) : kk == 2 ? D[(PB - 16 + l16) * LP + j] : 0.0;
         }
         double *out = kk == 0 ? LF + l16 * LP : kk == 1 ? LI + l16 : kk == 2 ? LF + (PB - 16 + l16) * LP : LI + PB - 16 + l16;
         int step = kk & 1 ? LP : 1;
-        bool store = PB == 32 || kk < 2;
+        bool store = true;
 #pragma unroll 1
         for (int half = 0; half < CT; ++half) {
             fz_for<0, 16>([&](auto cc) __attribute__((always_inline)) {
@@ -764,15 +760,13 @@ __global__ __launch_bounds__(kCholThreads) void chol_panel_kernel(double *__rest
     __syncthreads();
     if constexpr (FULL) {
         const int row = tid / (PB / 2), col = tid % (PB / 2) * 2;
-        static_assert(!FULL || kCholThreads == PB * PB / 2, "two elements each");
+        static_assert(kCholThreads == PB * PB / 2, "two elements each");
         *reinterpret_cast<fz_f64x2_t *>(Li + (size_t)(d0 + row) * r + d0 + col) = fz_f64x2_t{LI[row * LP + col], LI[row * LP + col + 1]};
         return;
     }
     for (int t = tid; t < PB * PB; t += kCholThreads) {
         const int row = t / PB, col = t % PB;
         if (row < pwc && col < pwc) Li[(size_t)(d0 + row) * r + d0 + col] = LI[row * LP + col];
-        // (what reads the inverse goes by blocks of 32 columns)
-        if (PB == 16 && d0 % 32 == 0 && row < pwc && d0 + PB + col < r) Li[(size_t)(d0 + row) * r + d0 + PB + col] = 0.0;
     }
 }
 
@@ -1405,7 +1399,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 constexpr int kFzChunk = 16;
 
 struct FzLayout {
-    int n, Lp, bc, gram_tiles, gram_splits, w_splits, g_splits, chol_pb;
+    int n, Lp, bc, gram_tiles, gram_splits, w_splits, g_splits;
     size_t esz, xt_seq, part_seq, off_xt, off_part, off_c, off_vt, off_wn, off_g, off_lt, off_planes, off_diag, off_minv,
         off_rot, total;
 };
@@ -1441,7 +1435,6 @@ FzLayout fz_layout(const xkv_shape &s, int r)
     f.w_splits = splits_for(t * ((r + kGemmTile - 1) / kGemmTile), 256, f.n / 32);
     const int gb = (r + 31) / 32;
     f.g_splits = splits_for((gb * (gb + 1) / 2 + 3) / 4, 1024, f.n / 64);
-    f.chol_pb = r <= 512 ? 32 : 16;
     f.xt_seq = (size_t)f.n * f.Lp;
     f.part_seq = std::max((size_t)f.gram_splits * f.n * f.n, (size_t)f.w_splits * f.n * r);
     const size_t bc = (size_t)f.bc;
@@ -1488,7 +1481,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
     double *Minv = reinterpret_cast<double *>(ws + f.off_minv);
     int *rotations = reinterpret_cast<int *>(ws + f.off_rot);
     static_assert(kJacobiSweeps <= 16, "the rotation counters have 16 slots per sequence");
-    static_assert(chol_lds(32) <= 64 * 1024 - 256 && chol_lds(16) <= 64 * 1024 - 256, "no raised LDS limit needed");
+    static_assert(kCholLds <= 64 * 1024 - 256, "no raised LDS limit needed");
     hipError_t e = hipSuccess;
     const long long vcount = (long long)r * n, x_seq = (long long)n * s.L;
     for (int b0 = 0; b0 < s.batch && e == hipSuccess; b0 += f.bc) {
@@ -1519,17 +1512,12 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
                                planes, n, r, f.g_splits, pairs);
             hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                f.g_splits);
-            const int pb = f.chol_pb;
-            for (int c0 = -pb; c0 < r; c0 += pb) {
-                const int blocks = c0 < 0 ? 0 : std::max(0, (r - c0 - pb + kCholRB - 1) / kCholRB);
-                const int columns = c0 < 0 ? 0 : std::max(1, blocks) * ((c0 + pb + kCholRB - 1) / kCholRB);
-                const dim3 grid(1 + blocks * (blocks + 1) / 2 + columns, 1, nb);
-                if (pb == 32 && r % 32 == 0)
-                    hipLaunchKernelGGL((chol_panel_kernel<32, true>), grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
-                else if (pb == 32)
-                    hipLaunchKernelGGL((chol_panel_kernel<32, false>), grid, dim3(kCholThreads), chol_lds(32), st, Gm, Lt, diag0, r, c0);
-                else
-                    hipLaunchKernelGGL((chol_panel_kernel<16, false>), grid, dim3(kCholThreads), chol_lds(16), st, Gm, Lt, diag0, r, c0);
+            const auto panel_kernel = r % kCholRB == 0 ? chol_panel_kernel<true> : chol_panel_kernel<false>;
+            for (int c0 = -kCholRB; c0 < r; c0 += kCholRB) {
+                const int blocks = c0 < 0 ? 0 : std::max(0, (r - c0 - 1) / kCholRB);
+                const int columns = c0 < 0 ? 0 : std::max(1, blocks) * (c0 / kCholRB + 1);
+                hipLaunchKernelGGL(panel_kernel, dim3(1 + blocks * (blocks + 1) / 2 + columns, 1, nb), dim3(kCholThreads), kCholLds, st, Gm,
+                                   Lt, diag0, r, c0);
             }
             const dim3 grid((n + 127) / 128, ((r + 31) / 32 + 1) / 2, nb);
             if (r % 4 == 0)

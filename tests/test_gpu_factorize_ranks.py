@@ -1,4 +1,4 @@
-"""xkv_factorize_svd at ranks on both sides of its block sizes: the Cholesky panels (16 / 32 columns, r <= 512 / more), their
+"""xkv_factorize_svd at ranks on both sides of its block sizes: the Cholesky panels (32 columns, with and without bounds checks), their
 row tiles of 16 and the column blocks of 16 of the eigen-solver; several sequences, rank-deficient input.
 
 Checked on what holds for every spectrum, converged or not: B B^T = I, A = X B^T, A^T A diagonal and descending with the
