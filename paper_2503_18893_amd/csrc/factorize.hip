@@ -297,7 +297,8 @@ __global__ __launch_bounds__(kGemmThreads) void gemm_nt_kernel(const GemmArgs a)
         }
 }
 
-// (2b) C = sum of the split planes of the lower 64 x 64 blocks, mirrored into the upper triangle.
+// (2b) C = sum of the split planes of the lower 64 x 64 blocks, mirrored into the upper triangle.  Memory bound: n = 4096, three planes,
+// 164 MB in 34 us (64 with four bytes per request and one plane's value after the other).
 __global__ __launch_bounds__(256) void gram_finish_kernel(const float *__restrict__ part, float *__restrict__ C, int n,
                                                           int splits, long long plane, long long part_seq)
 {
@@ -306,20 +307,26 @@ __global__ __launch_bounds__(256) void gram_finish_kernel(const float *__restric
     const int bm = blockIdx.y, bn = blockIdx.x;
     if (bn > bm) return;
     __shared__ float tile[64][65];
-    for (int i = threadIdx.x; i < 4096; i += 256) {
-        const int rr = i >> 6, cc = i & 63, m = bm * 64 + rr, c = bn * 64 + cc;
-        float v = 0.0f;
-        if (m < n && c < n) {
-            for (int s = 0; s < splits; ++s) v += part[(size_t)s * plane + (size_t)m * n + c];
-            C[(size_t)m * n + c] = v;
-        }
-        tile[rr][cc] = v;
+    const int c4 = (threadIdx.x & 15) * 4, r0 = threadIdx.x >> 4;  // (n is a multiple of 64)
+    fz_f32x4_t v[4] = {};
+    for (int s = 0; s < splits; ++s)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] += *reinterpret_cast<const fz_f32x4_t *>(part + (size_t)s * plane + (size_t)(bm * 64 + r0 + 16 * u) * n + bn * 64 + c4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        *reinterpret_cast<fz_f32x4_t *>(C + (size_t)(bm * 64 + r0 + 16 * u) * n + bn * 64 + c4) = v[u];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[r0 + 16 * u][c4 + e] = v[u][e];
     }
     __syncthreads();
     if (bn == bm) return;
-    for (int i = threadIdx.x; i < 4096; i += 256) {
-        const int rr = i >> 6, cc = i & 63, m = bn * 64 + rr, c = bm * 64 + cc;  // element (m, c) of the upper block
-        if (m < n && c < n) C[(size_t)m * n + c] = tile[cc][rr];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {  // rows of the upper block
+        fz_f32x4_t x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = tile[c4 + e][r0 + 16 * u];
+        *reinterpret_cast<fz_f32x4_t *>(C + (size_t)(bn * 64 + r0 + 16 * u) * n + bm * 64 + c4) = x;
     }
 }
 
@@ -447,11 +454,11 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
     planes += (size_t)blockIdx.z * splits * r * r;
     G += (size_t)blockIdx.z * r * r;
     diag0 += (size_t)blockIdx.z * r;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long long)r * r) return;
-    const int i = (int)(idx / r), j = (int)(idx % r);
-    if ((j >> 5) > (i >> 5)) return;
+    const int i = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= r || (j >> 5) > (i >> 5)) return;
+    const size_t idx = (size_t)i * r + j;
     double v = 0.0;
+#pragma unroll 8
     for (int s = 0; s < splits; ++s) v += planes[(size_t)s * r * r + idx];
     G[idx] = v;
     if (i == j) diag0[i] = v;
@@ -905,7 +912,8 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const float *__restric
 constexpr int kJacobiSweeps = 10;        // most sweeps of the block Jacobi eigen-solver (each: every pair of column blocks once)
 constexpr double kJacobiSettled = 1e-7;  // a sweep whose elements all stayed below this cosine was the last one needed
 
-// (5b) M = (S + S^T) / 2 with S the sum of its planes, Jt = identity, rotation counts zero.
+// (5b) M = (S + S^T) / 2 with S the sum of its planes, Jt = identity, rotation counts zero.  A workgroup makes a block of 32 x 32 and its
+// mirror image, so that the transposed one is read in rows too (r = 512, 16 planes: 36 -> 12 us).
 __global__ __launch_bounds__(256) void jacobi_init_kernel(const double *__restrict__ planes, double *__restrict__ M,
                                                           double *__restrict__ Jt, int *__restrict__ rotations, int r,
                                                           int splits)
@@ -914,16 +922,39 @@ __global__ __launch_bounds__(256) void jacobi_init_kernel(const double *__restri
     planes += (size_t)blockIdx.z * splits * r * r;
     M += (size_t)blockIdx.z * r * r;
     Jt += (size_t)blockIdx.z * r * r;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (long long)r * r) return;
-    const int i = (int)(idx / r), j = (int)(idx % r);
-    double x = 0.0, y = 0.0;
+    // block (bi, bj), bi >= bj, of 32 x 32 and its mirror image
+    __shared__ double low[32][33], up[32][33];
+    int bi, bj;
+    fz_lower_pair((int)blockIdx.x, bi, bj);
+    const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    double x[4] = {}, y[4] = {};
     for (int s = 0; s < splits; ++s) {
-        x += planes[(size_t)s * r * r + idx];
-        y += planes[(size_t)s * r * r + (size_t)j * r + i];
+        const double *p = planes + (size_t)s * r * r;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = r0 + 8 * u;
+            x[u] += (32 * bi + k < r && 32 * bj + c < r) ? p[(size_t)(32 * bi + k) * r + 32 * bj + c] : 0.0;
+            y[u] += (32 * bj + k < r && 32 * bi + c < r) ? p[(size_t)(32 * bj + k) * r + 32 * bi + c] : 0.0;
+        }
     }
-    M[idx] = 0.5 * (x + y);
-    Jt[idx] = i == j ? 1.0 : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        low[r0 + 8 * u][c] = x[u];
+        up[r0 + 8 * u][c] = y[u];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = r0 + 8 * u, i = 32 * bi + k, j = 32 * bj + c, it = 32 * bj + k, jt = 32 * bi + c;
+        if (i < r && j < r) {
+            M[(size_t)i * r + j] = 0.5 * (x[u] + up[c][k]);
+            Jt[(size_t)i * r + j] = i == j ? 1.0 : 0.0;
+        }
+        if (bi != bj && it < r && jt < r) {
+            M[(size_t)it * r + jt] = 0.5 * (low[c][k] + y[u]);
+            Jt[(size_t)it * r + jt] = 0.0;
+        }
+    }
 }
 
 // The value of the next lane of the same 16 (the last lane takes the first one's).
@@ -1520,7 +1551,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
             const int gb = (r + 31) / 32, pairs = gb * (gb + 1) / 2, g_splits = g_splits_of((pairs + 3) / 4 * nb, f.g_splits);
             hipLaunchKernelGGL(gram_f64_kernel<true>, dim3((pairs + 3) / 4, g_splits, nb), dim3(256), 0, st, Wn, vcount, Wn,
                                planes, n, r, g_splits, pairs);
-            hipLaunchKernelGGL(gram_sum_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Gm, diag0, r,
+            hipLaunchKernelGGL(gram_sum_kernel, dim3((r + 255) / 256, r, nb), dim3(256), 0, st, planes, Gm, diag0, r,
                                g_splits);
             const auto panel_kernel = r % kCholRB == 0 ? chol_panel_kernel<true> : chol_panel_kernel<false>;
             for (int c0 = -kCholRB; c0 < r; c0 += kCholRB) {
@@ -1578,7 +1609,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
         hipLaunchKernelGGL(transpose_v_kernel, dim3((n + 31) / 32, gb, nb), dim3(256), 0, st, Vt, part, (long long)f.part_seq, n, r);
         hipLaunchKernelGGL(gram_f64_kernel<false>, dim3((gb * gb + 3) / 4, f.g_splits, nb), dim3(256), 0, st, part,
                            (long long)f.part_seq, Wn, planes, n, r, f.g_splits, gb * gb);
-        hipLaunchKernelGGL(jacobi_init_kernel, dim3(blocks256((long long)r * r), 1, nb), dim3(256), 0, st, planes, Ma, Jt,
+        hipLaunchKernelGGL(jacobi_init_kernel, dim3(gb * (gb + 1) / 2, 1, nb), dim3(256), 0, st, planes, Ma, Jt,
                            rotations, r, f.g_splits);
         {
             const int n_blocks = std::max(2, ((r + kJacBS - 1) / kJacBS + 1) / 2 * 2);  // an even number of column blocks
