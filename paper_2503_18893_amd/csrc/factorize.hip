@@ -11,7 +11,7 @@
 //   2. C = Xt Xt^T (lower tiles, split over the tokens, fp32 accumulation), mirrored to the full matrix;
 //   3. block power iteration on C: V <- orth(C V) for a random start V [r][n], `iters` times.  The product
 //      runs on the fp32 matrix cores; orth() is a Cholesky-QR in fp64 (Gram matrix of the r vectors,
-//      Cholesky factor, forward substitution), which keeps r directions apart whose lengths differ by many
+//      inverse of its Cholesky factor, product with it), which keeps r directions apart whose lengths differ by many
 //      orders of magnitude after the multiplication by C;
 //   4. B = V rounded to the storage type (rows of B are an orthonormal basis of the dominant right singular
 //      subspace), A = X_cat B^T (matrix cores again).
@@ -1546,7 +1546,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
         }
         hipLaunchKernelGGL(init_v_kernel, dim3(blocks256(vcount), 1, nb), dim3(256), 0, st, Vt, vcount,
                            seed + 0x9E37u * (uint32_t)b0);
-        // Vt <- orthonormal basis of the columns of Wn (Cholesky-QR: r x r Gram matrix, Cholesky factor, solve; fp64)
+        // Vt <- orthonormal basis of the columns of Wn (Cholesky-QR: r x r Gram matrix, inverse of its Cholesky factor, product; fp64)
         auto orthonormalise = [&]() {
             const int gb = (r + 31) / 32, pairs = gb * (gb + 1) / 2, g_splits = g_splits_of((pairs + 3) / 4 * nb, f.g_splits);
             hipLaunchKernelGGL(gram_f64_kernel<true>, dim3((pairs + 3) / 4, g_splits, nb), dim3(256), 0, st, Wn, vcount, Wn,

@@ -20,8 +20,8 @@
 // split into a bf16 high part and remainder (again 16 + 16 rows of one operand; KEPT with three parts: see there) and multiplied with B^V.
 //
 // KEPT: the logits are there already, so that the keys' half falls away and a row costs its values alone: from the score stage
-// (the absorbed step: every query head's score of every token) or, for rotated keys, from the KEYS form of
-// gather_attend_mfma_kernel (of every selected row).  The weights meet the rows in parts of 8 bits, a matrix instruction each: in
+// (the absorbed step: every query head's score of every token) or, for rotated keys, from rope_keys_kernel
+// or the KEYS form of gather_attend_mfma_kernel (of every selected row).  The weights meet the rows in parts of 8 bits, a matrix instruction each: in
 // the absorbed step three, all 24 bits of them, as the general kernels have them (with two, 16 bits, and their exponentials short of a
 // unit or two, sums that cancel showed it: test_sums_keep_single_precision); with rotated keys two, where the weights of the other form are
 // rounded to 8.  Quantised rows are not rounded to bf16 either: the operand is the code itself (exact; with two parts 16 + c, which
