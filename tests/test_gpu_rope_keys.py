@@ -7,10 +7,23 @@ from paper_2503_18893_amd import binding as xb
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("bits,n_rep,r_k,r_v,k,batch", [
+CASES = [
     (0, 4, 128, 128, 1025, 32), (0, 8, 512, 64, 1057, 32), (0, 1, 80, 48, 2049, 16), (0, 4, 384, 512, 1031, 32), (0, 2, 640, 256, 8200, 6),
-    (4, 8, 512, 512, 1025, 32), (4, 4, 32, 64, 1056, 32), (4, 5, 352, 384, 1023, 33), (4, 4, 640, 512, 8200, 2), (3, 4, 256, 256, 1025, 32), (3, 8, 480, 96, 1025, 32)])
+    (4, 8, 512, 512, 1025, 32), (4, 4, 32, 64, 1056, 32), (4, 5, 352, 384, 1023, 33), (4, 4, 640, 512, 8200, 2), (3, 4, 256, 256, 1025, 32), (3, 8, 480, 96, 1025, 32)]
+
+
+@pytest.mark.parametrize("bits,n_rep,r_k,r_v,k,batch", CASES)
 def test_rotated_rows(bits, n_rep, r_k, r_v, k, batch):
+    check(bits, n_rep, r_k, r_v, k, batch)
+
+
+@pytest.mark.parametrize("bits,r_k", [(4, 512), (4, 96), (3, 352)])
+def test_steps_up_to_the_end_of_the_range(bits, r_k):
+    """Groups of 32 ranks whose steps (0.2 to 0.7 of the powers) lie on both sides of 2^104, up to 2^120; the factor's rows are as much smaller."""
+    check(bits, 4, r_k, 64, 1025, 32, powers=[0, 106, 121, 104, 105, 1, 110, 118, 102])
+
+
+def check(bits, n_rep, r_k, r_v, k, batch, powers=None):
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -19,6 +32,11 @@ def test_rotated_rows(bits, n_rep, r_k, r_v, k, batch):
     g = torch.Generator(device="cuda").manual_seed(r_k + bits)
     A = [torch.randn((batch, L, r), generator=g, device="cuda").bfloat16() for r in (r_k, r_v)]
     B = [(torch.randn((batch, 1, r, H_kv * 128), generator=g, device="cuda") / r ** 0.5).bfloat16() for r in (r_k, r_v)]
+    if powers:  # (no element of the factor below the normal numbers)
+        e = torch.tensor([powers[j // 32 % len(powers)] for j in range(r_k)], device="cuda", dtype=torch.float64)
+        A[0] = (A[0].double() * 2.0 ** e).bfloat16()
+        sign = 2.0 * torch.randint(0, 2, B[0].shape, generator=g, device="cuda") - 1
+        B[0] = (sign * (0.5 + 0.5 * torch.rand(B[0].shape, generator=g, device="cuda")) * 2.0 ** -(e[:, None] + 4)).bfloat16()
     q = torch.randn((batch, H_kv * n_rep, 128), generator=g, device="cuda").bfloat16()
     idx = torch.argsort(torch.rand((batch, H_kv, L), generator=g, device="cuda"), dim=-1)[..., :k].sort(-1).values.int().contiguous()
     counts = torch.full((batch, H_kv), k, dtype=torch.int32, device="cuda")
