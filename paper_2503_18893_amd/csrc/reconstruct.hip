@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(const T *__restrict__ 
 // in turn, the column tiles of a token tile to the same die (its rows of A are read once from memory).  (With every
 // sequence beginning at the first die 16 of 256 tokens kept two of the eight busy: 23.4 us, now 14.6; 64 of 100 tokens,
 // rank 128, 33.5 us, now 8.0.)
-// Takes the ranks that reconstruct_kept_kernel does not.  What bounds it: the copies into LDS (24 KiB per slab and workgroup, at ranks
+// Takes the calls that reconstruct_kept_kernel does not (reconstruct_keeps_factor).  What bounds it: the copies into LDS (24 KiB per slab and workgroup, at ranks
 // 512 403 MB from L2 at 8.5 TB/s) before the products: 47 us there at L = 32768, H_kv = 8 (34 GFLOP, 0.73 PFLOP/s).  Eight wavefronts
 // of 32 tokens x 128 dims, every wavefront reading all of B_l's fragments for its 32 tokens and B_l transposed by 2 B
 // stores, took 64 us, bound by LDS and by A read once per head.
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const b
 }
 
 // ==========================================================================================
-// Multiples of 128 ranks up to 768: the factor B_l stays in registers.  A wavefront holds 64 dims of all ranks as operands (256
+// Multiples of 128 ranks up to 768, few or long sequences: the factor B_l stays in registers.  A wavefront holds 64 dims of all ranks as operands (256
 // registers at 512 ranks) and walks a run of tokens, 32 at a time; four wavefronts, 256 dims, share the rows of A, which go global -> LDS
 // directly, whole rows.  Four tiles are live: the one that is multiplied, the next (landed, so that its first operands are read ahead of
 // the barrier) and two on their way; above 512 ranks, where the LDS holds three, one.  An operand read of A feeds two
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kRcThreads, 2) void reconstruct_mfma_kernel(const b
 // What bounds it: the matrix cores at the clock that they run at under load, then the stores.  L = 32768, H_kv = 8, ranks 512: 37 us (0.93
 // PFLOP/s; 47 before), of which start and B_l take 5; all numbers zero 30 us, without stores 35; four sequences 131 us (201; 1.05
 // PFLOP/s, a large library product 1.25).  Ranks 128: 17.7 us (22.1), 256 22 (30), 384 30 (39), 640 49 (56), 768 54 (64); 64 tokens of
-// ranks 512 6.1 (12.4).  The slabs of the kernel above were nowhere faster at these ranks.
+// ranks 512 6.1 (12.4).  Many short sequences: see reconstruct_keeps_factor.
 // ==========================================================================================
 constexpr int kRkTok = 32;
 constexpr int rk_stages(int nf) { return nf <= 32 ? 4 : 3; }
@@ -452,6 +452,30 @@ static void reconstruct_cut(int tiles, long long groups, int slots, int start, i
     }
 }
 
+// Whether B_l in registers pays (r = 128, 256 .. 768).  With two workgroups on a compute unit, ranks up to 256, always (64 to 128
+// sequences of 8 KV heads x 128 tokens are 0 to 5 % slower).  Otherwise nothing goes on beside a workgroup's start, and many short
+// sequences are mostly starts, each with a factor of its own from memory; the slabs' copies are bound by the same bytes there, but
+// go on beside products.  Both times in tiles of 32 tokens x 256 dims (0.35 us per 128 ranks), fitted to 2250 shapes: the slower kernel is
+// taken by 12 % at most, 0.14 % on average.  B_l kept / slabs, us, ranks 768: 64 sequences x 8 KV heads x 128 tokens 27.2 / 21.4, 128 of
+// them 60 / 45, 300 x 1 x 384 77 / 67, 128 x 2 x 200 21.9 / 25.8, 33 x 2 x 1000 21 / 37, 33 x 8 x 384 38 / 33; ranks 384: 200 x 8 x 128 59
+// / 46, 300 x 1 x 96 18.0 / 16.9, 33 x 2 x 1000 13.7 / 22.2.
+bool reconstruct_keeps_factor(const xkv_shape &s, int r)
+{
+    if (r % 128 != 0 || r > 768) return false;
+    if (r <= 256) return true;
+    const int col_groups = (s.H_kv * 128 + kRcDims - 1) / kRcDims, tiles = (s.L + kRkTok - 1) / kRkTok, tok_tiles = (s.L + kRcTok - 1) / kRcTok;
+    const long long groups = (long long)s.batch * col_groups;
+    int runs = 1, run_tiles = tiles;
+    reconstruct_cut(tiles, groups, 256, 4, &runs, &run_tiles);
+    // (rounds of the chip: the last one is done earlier where it is not full)
+    auto rounds = [](long long n) { return 0.75 * (double)((n + 255) / 256) + 0.25 * (double)n / 256; };
+    const double factors = (double)s.batch * s.H_kv;  // read once, or by the token tiles on every die
+    const double kept = 3.85 * rounds(groups * runs) + (double)((groups * runs + 255) / 256) * run_tiles + factors / 123;
+    const double products = 7.0 * rounds(groups * tok_tiles);
+    const double bytes = factors * std::min(tok_tiles, 8) / 132 + (double)s.batch * s.L * (1.0 + 128.0 * s.H_kv / r) / 9500;
+    return kept <= std::max(products, bytes) + 1900.0 / r;
+}
+
 template <int NF>
 static hipError_t launch_reconstruct_kept(const xkv_shape &s, int layer, const bf16_t *A, const bf16_t *B, bf16_t *X, hipStream_t st)
 {
@@ -479,13 +503,14 @@ hipError_t launch_reconstruct(const xkv_shape &s, int layer, const void *A, cons
 {
     if (reconstruct_mfma_ok(s, r, A, B, X)) {
         const bf16_t *Ab = (const bf16_t *)A, *Bb = (const bf16_t *)B;
-        // (whole swizzle groups of A's rows, and B_l within the registers)
-        if (r == 128) return launch_reconstruct_kept<8>(s, layer, Ab, Bb, (bf16_t *)X, st);
-        if (r == 256) return launch_reconstruct_kept<16>(s, layer, Ab, Bb, (bf16_t *)X, st);
-        if (r == 384) return launch_reconstruct_kept<24>(s, layer, Ab, Bb, (bf16_t *)X, st);
-        if (r == 512) return launch_reconstruct_kept<32>(s, layer, Ab, Bb, (bf16_t *)X, st);
-        if (r == 640) return launch_reconstruct_kept<40>(s, layer, Ab, Bb, (bf16_t *)X, st);
-        if (r == 768) return launch_reconstruct_kept<48>(s, layer, Ab, Bb, (bf16_t *)X, st);
+        if (reconstruct_keeps_factor(s, r)) switch (r / 128) {
+            case 1: return launch_reconstruct_kept<8>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            case 2: return launch_reconstruct_kept<16>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            case 3: return launch_reconstruct_kept<24>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            case 4: return launch_reconstruct_kept<32>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            case 5: return launch_reconstruct_kept<40>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            case 6: return launch_reconstruct_kept<48>(s, layer, Ab, Bb, (bf16_t *)X, st);
+            }
         static DynamicLdsOnce attr;
         if (hipError_t e0 = attr.ensure((const void *)reconstruct_mfma_kernel, kRcLds); e0 != hipSuccess) return e0;
         const int tok_tiles = (s.L + kRcTok - 1) / kRcTok, col_tiles = (s.H_kv * 128 + kRcDims - 1) / kRcDims;

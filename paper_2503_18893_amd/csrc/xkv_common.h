@@ -298,6 +298,7 @@ bool small_step_whole(const xkv_shape &s);  // ... whether scores and selection 
 hipError_t launch_small_step(const xkv_shape &s, int layer, const void *A_k, const void *A_v, const void *B_k, const void *B_v, const void *q,
                              const void *K_tail, const void *V_tail, int T, void *out, int32_t *idx_out, float *score_out, float scale,
                              const int32_t *idx, hipStream_t st);
+bool reconstruct_keeps_factor(const xkv_shape &s, int r);  // which of its matrix-core kernels
 hipError_t launch_reconstruct(const xkv_shape &s, int layer, const void *A, const void *B, int r, void *X,
                               hipStream_t st);
 // Attention over selected tokens in the absorbed form (see absorbed.hip): extra workspace laid out behind the

@@ -35,8 +35,12 @@ def test_tiles_against_fp64(H_kv, r, batch, L):
     assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want) + (1 + 2.0 ** -8) * r * 2.0 ** -24 * size).all()
 
 
-@pytest.mark.parametrize("r", [128, 256, 384, 512, 640, 768])
-@pytest.mark.parametrize("H_kv,batch,L", [(1, 1, 1), (2, 2, 31), (3, 1, 33), (2, 3, 64), (5, 2, 97), (8, 1, 161), (1, 17, 130), (8, 3, 4133), (3, 130, 70)])
+KEPT_RANKS = [128, 256, 384, 512, 640, 768]
+KEPT = [(1, 1, 1), (2, 2, 31), (3, 1, 33), (2, 3, 64), (5, 2, 97), (8, 1, 161), (1, 17, 130), (8, 3, 4133), (1, 300, 33)]
+
+
+@pytest.mark.parametrize("r", KEPT_RANKS)
+@pytest.mark.parametrize("H_kv,batch,L", KEPT + [(3, 130, 70)])  # (the last: from 640 ranks on in slabs)
 def test_factor_in_registers(H_kv, batch, L, r):
     """The ranks whose B_l is kept: 32 tokens a tile, runs of one to many tiles, odd numbers of KV heads, more groups than compute units."""
     test_tiles_against_fp64(H_kv, r, batch, L)

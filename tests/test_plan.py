@@ -7,6 +7,7 @@ import pytest
 from paper_2503_18893_amd import build as xbuild
 from test_gpu_gather_absorb import CASES
 import test_gpu_given_logits as given
+import test_gpu_reconstruct_tiles as tiles
 
 
 @pytest.fixture(scope="module")
@@ -128,3 +129,19 @@ def test_which_scores_are_long_streams(plan_of):
     hist = plan_of([dict(L=L, k=8192, batch=b) for L in (131072, 100_001, 262_145) for b in (4, 5, 16)])
     assert sum(p["score_hist"] for p in hist) > 3
     assert all(p["topk_chunk"] % 256 == 0 for p in hist) and all(p["topk_chunk"] == 32 * p["score_tpw"] for p in hist if p["score_hist"])
+
+
+def test_reconstruction_keeps_the_factor_where_that_is_faster(plan_of):
+    """Few long runs and every call of one sequence keep B_l in registers; many short sequences, each with a factor of its own, do not,
+    above 256 ranks."""
+    line = [  # KV heads, r, batch, L, kept
+        (8, 512, 1, 32768, 1), (8, 768, 1, 64, 1), (8, 384, 4, 65536, 1), (8, 768, 64, 128, 0), (8, 512, 200, 128, 0), (8, 384, 200, 96, 0),
+        (8, 256, 200, 128, 1), (8, 128, 300, 96, 1), (1, 768, 300, 384, 0), (2, 768, 128, 200, 1), (2, 640, 33, 1000, 1), (8, 768, 33, 384, 0),
+        (1, 640, 300, 20, 1), (8, 768, 16, 4096, 1), (8, 496, 1, 32768, 0), (8, 896, 1, 32768, 0)]
+    shapes = [dict(H_kv=h, H_q=h, r_k=r, L=L, batch=b) for h, r, b, L, _ in line]
+    for case, p in zip(line, plan_of(shapes)):
+        assert p["factor_kept"] == case[4], case
+    cases = [dict(H_kv=h, H_q=h, r_k=r, L=L, batch=b) for h, b, L in tiles.KEPT for r in tiles.KEPT_RANKS]
+    assert all(p["factor_kept"] for p in plan_of(cases))
+    # nothing is divided by zero or wraps around at the ends of what the call takes
+    plan_of([dict(H_kv=h, H_q=h, r_k=512, L=L, batch=b) for h, b in ((1, 1), (1, 65535), (255, 257)) for L in (1, 1 << 24)])
