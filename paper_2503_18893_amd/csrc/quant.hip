@@ -20,7 +20,7 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
-constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 256 * 1024;  // pieces of 16 bytes
+constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 320 * 1024;  // pieces of 16 bytes
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -195,8 +195,12 @@ __global__ __launch_bounds__(256) void quantize_pieces_kernel(const bf16_t *__re
     const uint32_t left = pieces - first < 256 ? (uint32_t)(pieces - first) : 256u;
     const uint32_t pitch = (uint32_t)quant_row_bytes(r, BITS);
     // pieces is a multiple of 4 (r % 32 == 0), so a group's four lanes are all inside or all outside
-    const uint32_t i = threadIdx.x, lrow = (pc0 + i) / ppr, pc = pc0 + i - lrow * ppr;
+    const uint32_t i = threadIdx.x, lrow = (pc0 + i) / ppr;
     const q_u32x4_t raw = reinterpret_cast<const q_u32x4_t *>(X)[first + (i < left ? i : left - 1)];  // (may still be in the caches)
+    unsigned char *og = out + row0 * (long long)pitch;
+    uint32_t pc = pc0 + i - lrow * ppr, orow = lrow * pitch;
+    asm volatile("" : "+v"(pc), "+v"(orow));  // (while the piece is on its way, not before the store)
+    __builtin_amdgcn_sched_barrier(0);
     float x[8];
     unpack8(raw, x);
     const float mn = min3(min3(x[0], x[1], x[2]), min3(x[3], x[4], x[5]), min3(x[6], x[7], x[7]));
@@ -209,17 +213,16 @@ __global__ __launch_bounds__(256) void quantize_pieces_kernel(const bf16_t *__re
     float step, inv;
     group_scale<BITS>(lo, hi, step, inv);
     const uint32_t word = eight_codes<BITS>(x, lo, inv), par = group_params(step, lo);
-    unsigned char *orow = out + row0 * (long long)pitch + lrow * pitch;
     if constexpr (BITS == 3) {
         // the group's four 24-bit units into three words; the group's first lane writes the 16-byte piece
         const uint32_t u1 = quad_perm<0x55>(word), u2 = quad_perm<0xAA>(word), u3 = quad_perm<0xFF>(word);
         if (i < left && (pc & 3) == 0)
-            *reinterpret_cast<q_u32x4_t *>(orow + 4 * pc) = q_u32x4_t{word | (u1 << 24), (u1 >> 8) | (u2 << 16), (u2 >> 16) | (u3 << 8), par};
+            *reinterpret_cast<q_u32x4_t *>(og + (orow + 4 * pc)) = q_u32x4_t{word | (u1 << 24), (u1 >> 8) | (u2 << 16), (u2 >> 16) | (u3 << 8), par};
     } else if (i < left) {
-        *reinterpret_cast<uint32_t *>(orow + 4 * pc) = word;
-        if ((pc & 3) == 0) *reinterpret_cast<uint32_t *>(orow + ((uint32_t)r >> 1) + pc) = par;
+        *reinterpret_cast<uint32_t *>(og + (orow + 4 * pc)) = word;
+        if ((pc & 3) == 0) *reinterpret_cast<uint32_t *>(og + (orow + ((uint32_t)r >> 1) + pc)) = par;
         if (pc == 0)  // the row's padding
-            for (uint32_t o = ((uint32_t)r >> 1) + ((uint32_t)r >> 3); o < pitch; o += 4) *reinterpret_cast<uint32_t *>(orow + o) = 0u;
+            for (uint32_t o = ((uint32_t)r >> 1) + ((uint32_t)r >> 3); o < pitch; o += 4) *reinterpret_cast<uint32_t *>(og + (orow + o)) = 0u;
     }
 }
 
@@ -228,7 +231,7 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
     const long long groups = rows * (long long)(r >> 5), pieces = 4 * groups;
     if (groups == 0) return hipSuccess;
     // A small call is one round of loads: its pieces are spread over four times as many lanes.  Lane per piece / per group, us: 1000 rows
-    // of 512 2.1 / 2.6, 4100 (262400 pieces) 3.05 / 3.05, 16000 6.6 / 5.7, 12000 of 768 7.2 / 6.2.
+    // of 512 2.1 / 2.6, 4218 (270000 pieces) 3.08 / 3.25, 4800 3.2 / 3.4, 5300 3.2 / 3.3, 6250 3.7 / 3.5, 16000 6.6 / 5.7.
     const bool small = pieces <= kQuantSmall, staged = (r >> 5) <= 256;
     const long long most = small ? 256 : staged ? 256 / (r >> 5) * (r >> 5) : 256, blocks = ((small ? pieces : groups) + most - 1) / most;
     if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
