@@ -240,7 +240,8 @@ struct RopeTable {
 // QB: 0 = rows of A in bf16; 4 or 3 = rows given as 4-bit / 3-bit codes (A_k, A_v then point to quantised rows).
 // KEYS: products (1) and (2) only; the scaled logits go to logits [batch][H_kv][k][hp], and the values are summed by
 // gather_absorb_kernel, where B^V meets one vector per query head instead of every row (8 x 8 x 4128 rows of ranks 512 in 4 bits:
-// 60 us and 36, against 109 for all four products).
+// 60 us and 36, against 109 for all four products).  Eight wavefronts; it runs for 528 to 1024 of the keys' ranks only, fewer are
+// rope_keys_kernel's.
 template <int WAVES, bool ROPE, int QB, bool KEYS>
 __global__ __launch_bounds__(WAVES * 64, 2) void gather_attend_mfma_kernel(
     const bf16_t *__restrict__ A_k, const bf16_t *__restrict__ A_v, const u32x4_t *__restrict__ pack,
@@ -718,10 +719,8 @@ hipError_t launch_gather_attend_mfma(const xkv_shape &s, const Plan &p, int laye
             XKV_GA_LAUNCH_Q(8, true, false);
         else
             XKV_GA_LAUNCH_Q(8, false, false);
-    } else {
-        if (keys)
-            XKV_GA_LAUNCH_Q(4, true, true);
-        else if (use_rope)
+    } else {  // (never the keys alone: they have 131072 rows at least, which eight wavefronts take)
+        if (use_rope)
             XKV_GA_LAUNCH_Q(4, true, false);
         else
             XKV_GA_LAUNCH_Q(4, false, false);
