@@ -8,6 +8,7 @@ from paper_2503_18893_amd import build as xbuild
 from test_gpu_gather_absorb import CASES
 import test_gpu_given_logits as given
 import test_gpu_reconstruct_tiles as tiles
+import test_gpu_rope_keys as rope
 
 
 @pytest.fixture(scope="module")
@@ -110,6 +111,25 @@ def test_rotated_rows_in_two_halves_where_that_is_faster(plan_of):
     room = (2 * 32 + 64) * (64 + 128) // 8
     for L, kept in ((4 * 12288 - room, 1), (4 * 12288 - room - 64, 0)):
         assert plan_of([dict(r_k=64, r_v=64, L=L, k=12288 + 0, batch=8)])[0]["kept_4"] == kept
+
+
+def test_rotated_rows_whose_logits_come_from_the_factor_in_registers(plan_of):
+    """Both sides of the limits of ranks, heads and rows."""
+    line = [  # n_rep, r_k, r_v, batch, k, that kernel in bf16, 4 bits, 3 bits
+        (4, 256, 256, 8, 4096, 1, 1, 1), (4, 256, 256, 8, 4095, 0, 1, 1), (8, 256, 256, 8, 4096, 1, 1, 1), (8, 256, 256, 8, 4095, 0, 0, 0),
+        (4, 512, 512, 8, 4096, 1, 1, 1), (4, 528, 512, 8, 4096, 0, 0, 0), (4, 512, 512, 8, 4095, 0, 1, 1), (9, 256, 256, 16, 4096, 0, 0, 0),
+        (4, 512, 528, 16, 4096, 0, 0, 0), (4, 512, 512, 6, 4096, 1, 1, 1), (4, 544, 512, 6, 4096, 0, 0, 0)]
+    shapes = [dict(H_q=8 * n, r_k=rk, r_v=rv, batch=b, k=k, L=16 * k) for n, rk, rv, b, k, _, _, _ in line]
+    for case, p in zip(line, plan_of(shapes)):
+        assert (p["regs_0"], p["regs_4"], p["regs_3"]) == case[5:], case
+    for (bits, _, r_k, *_), p in zip(rope.CASES, plan_of([rope.shape_of(*case) for _, *case in rope.CASES])):
+        assert (p[f"regs_{bits}"], p[f"kept_{bits}"] or p[f"regs_{bits}"]) == (int(r_k <= 512), 1), (bits, r_k)
+    p = plan_of([{**rope.LAYERS, "k": 1032}])[0]
+    assert p["regs_0"] and p["regs_4"]
+    # the other kernel that leaves logits has eight wavefronts
+    some = [dict(H_q=8 * n, r_k=rk, r_v=rv, batch=b, k=k, L=16 * k) for n in (1, 4, 8) for rk in (64, 512, 640) for rv in (64, 256, 512)
+            for b in (1, 2, 8) for k in (1024, 8191, 8192, 16384, 20000)]
+    assert all(p["waves"] == 8 for p in plan_of(some) if p["kept_0"] or p["kept_4"] or p["kept_3"])
 
 
 def test_which_scores_are_long_streams(plan_of):
