@@ -355,10 +355,14 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
 // (B^K in 128 registers at most; eight slots of partial logits in LDS)
 bool rope_keys_ok(const xkv_shape &s) { return s.r_k <= 512 && s.H_q / s.H_kv <= 8; }
 
-// Where two halves pay with these keys beyond what they did before (rope_kept_pays): from 2^18 rows on.  One launch / two halves, us, 8
-// sequences with 8 KV heads, four query heads each, bf16: 4096 rows of ranks 512 127.6 / 127.0, 16 sequences 240 / 223, 4128 rows 138 / 129;
-// 3000 100.5 / 104.5 of ranks 512, 93 / 84 of 384; ranks 256, 4096 rows 77 / 74; four sequences 66 / 72 (ranks 512), 59 / 58 (384), 40.6 /
-// 42.5 (256).  Eight query heads in 4 bits: 4128 rows of ranks 256 81 / 72, four sequences of ranks 512 59 / 63.
+// Where two halves pay with these keys beyond where they do with the KEYS form (rope_kept_pays; below 2^18 rows that line is kept for
+// both: where it says two halves they are 0.99 to 1.9 times as fast with these keys): from 2^18 rows on.  One launch / two halves, us, 8 KV
+// heads, bf16, four query heads: ranks 512, 8 sequences x 4096 rows 129 / 122 (from 32768 tokens), 132 / 127 (65536), 135 / 134
+// (131072), with eight heads 130 / 125, 132 / 132, 134 / 137; 8 x 4128 136 / 128, 16 x 4096 240 / 223, 4 x 8192 124 / 116; ranks 384, 8 x
+// 4096 116 / 101; ranks 256 80 / 73; ranks 128 65 / 51.  (8 x 4096 is where the one launch has nothing to pad and its rounds are
+// full; there its time varies by 10 % from one card to another, and ranks 512 were 0.91 to 1.09 times as fast in two halves on different ones.)
+// Quantised, 8 x 4096 from 131072 tokens: ranks 256 62.8 / 60.0 in 4 bits, 62.1 / 60.5 in 3, with eight heads 64.7 / 64.2 and 63.2 /
+// 63.3; ranks 512 113.8 / 98.9.  Below: 4 x 4096 in bf16 71 / 74 (ranks 512), 42.5 / 44.4 (256), but 65 / 60 (384).
 bool rope_keys_pays(const xkv_shape &s, const Plan &p)
 {
     return p.absorb && s.r_v <= 512 && p.n_rep <= 8 && (long long)p.rows * s.k >= 1 << 18;

@@ -29,8 +29,9 @@ static xkv_status validate(const xkv_shape *s)
     return XKV_OK;
 }
 
-// Whether rotated rows are faster in two halves, logits (by gather_attend_mfma_kernel's KEYS form; see rope_keys_pays for the other)
-// and then the values' sums from them.  That is a launch and a merge more (4 us);
+// Whether rotated rows are faster in two halves, logits and then the values' sums from them, with the logits from
+// gather_attend_mfma_kernel's KEYS form, whose figures these are (with rope_keys_kernel's: here and where rope_keys_pays says so).  That is
+// a launch and a merge more (4 us);
 // what it saves are the values' products, whose ranks the one-launch kernel pads to 256 and takes per row.  Its time goes by `len`, the
 // rows that a compute unit takes one after the other (tiles of 256 in rounds of 256 workgroups).  One launch / two halves, us, 4 query
 // heads on each of 8 KV heads: 4 bits, ranks 512: len 512 60 / 60, 768 77 / 74, 1024 104 / 96, 1536 136 / 112; ranks 384 len 512 61 /
