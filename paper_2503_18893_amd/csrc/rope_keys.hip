@@ -131,9 +131,9 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
         }
     };
 
-    // From a step of 2^104 on step' is infinite, and 0 step' no number.  Pieces of a wavefront that holds one (hardly ever there) are
-    // written a second time, their codes converted one by one.  (The look at the steps costs 1 % at ranks 512, where the registers are
-    // full: both halves at 8 x 8 x 4128 rows in 4 bits 101.8 -> 103.1 us, in 3 bits 98.1 -> 99.5; nothing at fewer ranks.)
+    // From a step of 2^104 on step' is infinite, and 0 step' no number.  A tile in which a wavefront has one (hardly ever) is read once
+    // more and written by it a second time, the codes converted one by one.  (Behind the tile's products: a look at each piece between
+    // them cost 1.3 % at ranks 512, both halves at 8 x 8 x 4128 rows in 4 bits 101.8 -> 103.1 us; this costs nothing that shows.)
     auto has_large_step = [&](const Codes &c) __attribute__((always_inline)) {
         uint32_t most = 0;
 #pragma unroll
@@ -143,26 +143,32 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
         }
         return __ballot(most >= 0x7380u) != 0;
     };
-    auto large_steps = [&](const Codes &c, int tile, int i, int thread) __attribute__((always_inline)) {
-        u32x4_t p = c.piece[i];
-        const uint32_t par = QB == 4 ? c.param[i] : p[3];
-        const float step = __uint_as_float(par << 16), lo = __uint_as_float(par & 0xFFFF0000u);
-        const int e = 256 * i + thread, t = e / GR, q = e - t * GR;
+    auto large_steps = [&](int tile, int thread) __attribute__((always_inline)) {
 #pragma unroll 1
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t wd = QB == 4 ? p[0] : (p[0] & 0xFFFu) | ((p[0] << 4) & 0x0FFF0000u);
-            u32x4_t x;
+        for (int i = 0; i < NQ; ++i) {
+            const int e = 256 * i + thread, t = e / GR, q = e - t * GR;
+            if (t >= kRows) break;
+            const unsigned char *row = Ak + __umul24((uint32_t)toks[(tile < n_tiles ? tile : n_tiles - 1) * kRows + t], pitch);
+            const int qr = q < (r_k >> 5) ? q : 0;
+            u32x4_t p = *reinterpret_cast<const u32x4_t *>(row + 16 * qr);
+            const uint32_t par = QB == 4 ? *reinterpret_cast<const uint32_t *>(row + (r_k >> 1) + 4 * qr) : p[3];
+            const float step = __uint_as_float(par << 16), lo = __uint_as_float(par & 0xFFFF0000u);
+#pragma unroll 1
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t wd = QB == 4 ? p[0] : (p[0] & 0xFFFu) | ((p[0] << 4) & 0x0FFF0000u);
+                u32x4_t x;
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                const uint32_t c0 = (wd >> (QB * h)) & ((1u << QB) - 1), c1 = (wd >> (16 + QB * h)) & ((1u << QB) - 1);
-                const f32x2_t y = f32x2_t{__builtin_fmaf(step, (float)c0, lo), __builtin_fmaf(step, (float)c1, lo)};
-                x[h] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, bf16x2_t));
+                for (int h = 0; h < 4; ++h) {
+                    const uint32_t c0 = (wd >> (QB * h)) & ((1u << QB) - 1), c1 = (wd >> (16 + QB * h)) & ((1u << QB) - 1);
+                    const f32x2_t y = f32x2_t{__builtin_fmaf(step, (float)c0, lo), __builtin_fmaf(step, (float)c1, lo)};
+                    x[h] = __builtin_bit_cast(uint32_t, __builtin_convertvector(y, bf16x2_t));
+                }
+                *reinterpret_cast<u32x4_t *>(smem_raw + (tile & 1) * kImage + t * (NF * 32) + (((GR * u + q) ^ (t & 15)) << 4)) = x;
+                if constexpr (QB == 4)
+                    p = u32x4_t{p[1], p[2], p[3], 0};
+                else
+                    p = u32x4_t{(p[0] >> 24) | (p[1] << 8), (p[1] >> 24) | (p[2] << 8), p[2] >> 24, 0};
             }
-            if (256 * (i + 1) <= kRows * GR || t < kRows) *reinterpret_cast<u32x4_t *>(smem_raw + (tile & 1) * kImage + t * (NF * 32) + (((GR * u + q) ^ (t & 15)) << 4)) = x;
-            if constexpr (QB == 4)
-                p = u32x4_t{p[1], p[2], p[3], 0};
-            else
-                p = u32x4_t{(p[0] >> 24) | (p[1] << 8), (p[1] >> 24) | (p[2] << 8), p[2] >> 24, 0};
         }
     };
 
@@ -193,9 +199,7 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
                 value_word(odd, 0, i, u, 0, x, tid);
                 value_word(odd, 0, i, u, 1, x, tid);
             }
-        if (has_large_step(odd))
-#pragma unroll
-            for (int i = 0; i < NQ; ++i) large_steps(odd, 0, i, tid);
+        if (__builtin_expect(has_large_step(odd), 0)) large_steps(0, tid);
 #pragma unroll
         for (int i = 0; i < NQ; ++i) fetch(odd, 2, i, tid);
     }
@@ -299,10 +303,7 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
 #pragma unroll
                     for (int u = (f - H) * 8 * NQ / H; u < (f - H + 1) * 8 * NQ / H; ++u) {  // half u % 2 of word u / 2 % 4 of piece u / 8
                         value_word(codes, i + 1, u / 8, u / 2 % 4, u % 2, x, 64 * w + l);
-                        if (u % 8 == 7) {
-                            if (__builtin_expect(large, 0)) large_steps(codes, i + 1, u / 8, 64 * w + l);
-                            fetch(codes, i + 3, u / 8, 64 * w + l);
-                        }
+                        if (u % 8 == 7) fetch(codes, i + 3, u / 8, 64 * w + l);
                     }
                 }
                 if (f - H < 2) meets_q(last, f - H);
@@ -310,6 +311,8 @@ __global__ __launch_bounds__(256, 2) void rope_keys_kernel(const void *__restric
             __builtin_amdgcn_sched_barrier(0);
         }
         if (i > 0) leave(i - 1);
+        if constexpr (QB != 0)
+            if (__builtin_expect(large, 0)) large_steps(i + 1, 64 * w + l);
     };
     auto meet = [&]() __attribute__((always_inline)) {  // the next image is there, this one is no longer read
         if constexpr (QB == 0) XKV_WAIT_VMCNT(0);
