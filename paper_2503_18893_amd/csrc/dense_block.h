@@ -14,10 +14,13 @@ namespace dense {
 //   O [head slots x dims]    += W = exp(Z^T - max) (the result registers of Z^T, packed)   x  V block
 // The contraction of the second product runs over tokens, so each lane needs eight token rows of one
 // column of V: the V block goes through a wavefront-private LDS tile, which the transposing LDS read (4 rows x 16 columns a time) turns.
-// The rows of the next block are requested as soon as those of this one have left the registers for LDS.
+// The rows of the next block, K and V together, are requested once this one's have left the registers for LDS.
 // The four wavefronts merge their partials in LDS before writing.
-// What bounds it: the stream where it is long, 4 x 8 x 65536 tokens 165 us (6.5 TB/s; 167 with V read back two bytes at a time and the rows
-// requested at the start of their block), latencies where it is short: 8 x 4096 with the merge 10.5 us (11.6), 8 x 32768 29.8 (31.0).
+// What bounds it: the stream where it is long, 4 x 8 x 65536 tokens 164 us (6.5 TB/s; 167 with V read back two bytes at a time and the rows
+// requested at the start of their block), latencies where it is short: 8 x 4096 with the merge 10.0 us (11.3), 8 x 32768 29.3 (30.3).
+// Where a compute unit has two workgroups of two blocks each, the next rows of K requested ahead of those of V, before the logits,
+// were slower than no early request: 18 x 8 x 684 tokens, 16 query heads each, 17.5 us, at the start of their block 17.0, as it is 16.9; 32 x 8
+// x 400, four heads, 14.0, 13.6 and 13.2.
 // ==========================================================================================
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) float f32x8_t;
@@ -107,7 +110,6 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
             const int row = i * 4 + kw_row;
             kt[16 * row + ((kw_piece + row) & 15)] = kr[i];
         }
-        if (t0 + 128 < t_end) request(kr, Kg, t0 + 128);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -148,7 +150,10 @@ __device__ __forceinline__ void mfma_block(const DenseArgs &a, int split, int g,
             const int row = i * 4 + (lane >> 4);
             *reinterpret_cast<u32x4_t *>(vt + row * kVPitch + (lane & 15) * 16) = vr[i];
         }
-        if (t0 + 128 < t_end) request(vr, Vg, t0 + 128);
+        if (t0 + 128 < t_end) {
+            request(kr, Kg, t0 + 128);
+            request(vr, Vg, t0 + 128);
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
