@@ -20,7 +20,7 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
-constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 320 * 1024;  // pieces of 16 bytes
+constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 416 * 1024;  // pieces of 16 bytes
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
 {
@@ -230,8 +230,11 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
 {
     const long long groups = rows * (long long)(r >> 5), pieces = 4 * groups;
     if (groups == 0) return hipSuccess;
-    // A small call is one round of loads: its pieces are spread over four times as many lanes.  Lane per piece / per group, us: 1000 rows
-    // of 512 2.1 / 2.6, 4218 (270000 pieces) 3.08 / 3.25, 4800 3.2 / 3.4, 5300 3.2 / 3.3, 6250 3.7 / 3.5, 16000 6.6 / 5.7.
+    // A small call is one round of loads: its pieces are spread over four times as many lanes, which is the faster where the rows come from
+    // memory (a lane per group then waits for four requests of parts of lines) and the slower where they are in the caches.  The line is where
+    // the sums of both are the same.  Lane per piece / per group, us, rows of 512 in 4 bits: 4200 in the caches 2.87 / 2.96, from
+    // memory 3.5 / 4.0; 5700 3.14 / 3.07 and 3.89 / 4.29; 6700 (418 K pieces) 3.40 / 3.11 and 4.14 / 4.42; 8200 3.64 / 3.28 and 4.56 / 4.66;
+    // 9000 3.85 / 3.53 and 5.35 / 5.04.
     const bool small = pieces <= kQuantSmall, staged = (r >> 5) <= 256;
     const long long most = small ? 256 : staged ? 256 / (r >> 5) * (r >> 5) : 256, blocks = ((small ? pieces : groups) + most - 1) / most;
     if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;

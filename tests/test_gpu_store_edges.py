@@ -41,9 +41,9 @@ def test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits):
 @pytest.mark.parametrize("bits", [4, 3])
 @pytest.mark.parametrize("rows,r", [(4096, 512), (4097, 512), (260, 8192), (259, 8224), (9363, 224), (21846, 96), (65537, 32),
                                     (65537, 256), (4081, 4128), (2041, 8224), (5120, 512), (5121, 512), (321, 8192), (319, 8224),
-                                    (11703, 224), (27307, 96), (81921, 32)])
+                                    (11703, 224), (27307, 96), (81921, 32), (6656, 512), (6657, 512), (417, 8192), (15213, 224), (15214, 224)])
 def test_quantised_rows_a_lane_per_group(rows, r, bits):
-    """Both sides of 320 x 1024 pieces; 256 groups a row, one more, and numbers of groups that do not divide a workgroup; more than 2^21
+    """Both sides of 416 x 1024 pieces; 256 groups a row, one more, and numbers of groups that do not divide a workgroup; more than 2^21
     pieces."""
     test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits)
 
