@@ -20,6 +20,7 @@ namespace xkv {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t q_u32x4_t;
 
+constexpr long long kQuantFar = 160 * 1024 * 1024;  // bytes
 constexpr int kQuantCached = 2048 * 1024, kQuantSmall = 416 * 1024;  // pieces of 16 bytes
 
 template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t x)  // lane exchange within groups of four
@@ -101,12 +102,15 @@ __device__ __forceinline__ uint32_t group_params(float step, float lo)
 // as many as 256 groups make, collects the quantised rows in LDS and writes them as one run of 16-byte pieces; with rows longer
 // than that (STAGED false) every lane stores its own.
 // What bounds it: the stream, then about 75 vector instructions per piece; 140 with a lane per piece, where the two took the same time.
-// 50001 rows of 512 in 4 bits 13.5 us (67 MB; reading and writing as many bytes alone 11.5), a lane per piece 16.6; 3 bits 12.5 and
-// 16.1; 262144 rows 60.9 and 63.4, in 3 bits 58.0 and 66.1; 20000 rows of 640 7.6 and 9.7.  STREAM: calls of more than 2^21 pieces (32
+// 50001 rows of 512 in 4 bits 13.5 us (67 MB; reading and writing as many bytes alone 11.5), a lane per piece 16.6; 3 bits 12.4 and
+// 15.9; 262144 rows 60.4 and 68.6, in 3 bits 56.0 and 67.8; 20000 rows of 640 7.6 and 9.7.  STREAM: calls of more than 2^21 pieces (32
 // MiB), whose rows are hardly in the caches.  Others ask for a group's four pieces per lane, which share lines, so through the
 // cache: 20000 rows of 640 8.4 us the other way; 262144 rows of 512 this way 63.6, non-temporal 80.
+// far: more than 160 MiB of packed rows, which do not stay in the last level either, pass by the caches too: 1048576 rows of 512 in 4 bits
+// 247 -> 237 us (a lane per piece 239), 524288 the same either way, 300000 66 -> 69; in 3 bits 600000 rows of 768 206 -> 198, 550000 of 512 (134 MiB)
+// 113 -> 120.
 template <int BITS, bool STAGED, bool STREAM>
-__global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out, long long groups, int r)
+__global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__restrict__ X, unsigned char *__restrict__ out, long long groups, int r, int far)
 {
     __shared__ q_u32x4_t pieces[STREAM ? 1024 : STAGED ? 512 : 1];
     unsigned char *stage = reinterpret_cast<unsigned char *>(pieces);  // STAGED
@@ -179,8 +183,11 @@ __global__ __launch_bounds__(256) void quantize_groups_kernel(const bf16_t *__re
     if constexpr (STAGED) {
         __syncthreads();
         const uint32_t n16 = left / gpr * pitch / 16;
-        for (uint32_t j = threadIdx.x; j < n16; j += 256)
-            reinterpret_cast<q_u32x4_t *>(og)[j] = reinterpret_cast<const q_u32x4_t *>(stage)[j];
+        q_u32x4_t *to = reinterpret_cast<q_u32x4_t *>(og);
+        if (STREAM && far)
+            for (uint32_t j = threadIdx.x; j < n16; j += 256) __builtin_nontemporal_store(reinterpret_cast<const q_u32x4_t *>(stage)[j], to + j);
+        else
+            for (uint32_t j = threadIdx.x; j < n16; j += 256) to[j] = reinterpret_cast<const q_u32x4_t *>(stage)[j];
     }
 }
 
@@ -238,11 +245,10 @@ hipError_t launch_quantize_rows(const void *X, long long rows, int r, int bits, 
     const bool small = pieces <= kQuantSmall, staged = (r >> 5) <= 256;
     const long long most = small ? 256 : staged ? 256 / (r >> 5) * (r >> 5) : 256, blocks = ((small ? pieces : groups) + most - 1) / most;
     if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, small ? pieces : groups, r);
-    };
+    auto launch_with = [&](auto kernel, auto... args) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t *)X, (unsigned char *)out, args...); };
+    auto launch = [&](auto kernel) { launch_with(kernel, groups, r, (int)(rows * (long long)quant_row_bytes(r, bits) > kQuantFar)); };
     if (small)
-        bits == 3 ? launch(quantize_pieces_kernel<3>) : launch(quantize_pieces_kernel<4>);
+        bits == 3 ? launch_with(quantize_pieces_kernel<3>, pieces, r) : launch_with(quantize_pieces_kernel<4>, pieces, r);
     else if (pieces <= kQuantCached)
         if (bits == 3)
             staged ? launch(quantize_groups_kernel<3, true, false>) : launch(quantize_groups_kernel<3, false, false>);

@@ -48,6 +48,24 @@ def test_quantised_rows_a_lane_per_group(rows, r, bits):
     test_quantised_rows_at_the_edges_of_a_workgroup(rows, r, bits)
 
 
+@pytest.mark.parametrize("bits,rows,r", [(4, 524289, 512), (3, 655361, 512), (4, 163900, 1632)])
+def test_packed_rows_beyond_the_caches(bits, rows, r):
+    """More than 160 MiB of packed rows, the last workgroup not full: the same bytes as from calls of a tenth."""
+    torch = torch_mod()
+    X = torch.randn((rows, r), generator=torch.Generator(device="cuda").manual_seed(rows), device="cuda", dtype=torch.bfloat16)
+    pitch = xb.xkv_quantized_row_bytes(r, bits)
+    out = torch.full((rows + 1, pitch), 0xAB, dtype=torch.uint8, device="cuda")
+    xb.xkv_quantize_rows(X, rows, r, out, bits)
+    assert rows * pitch > 160 << 20
+    step = rows // 10
+    for first in range(0, rows, step):
+        n = min(step, rows - first)
+        part = torch.empty((n, pitch), dtype=torch.uint8, device="cuda")
+        xb.xkv_quantize_rows(X[first:], n, r, part, bits)
+        assert torch.equal(out[first:first + n], part), first
+    assert bool((out[rows] == 0xAB).all())
+
+
 @pytest.mark.parametrize("c", [4, 8, 12, 16])
 @pytest.mark.parametrize("chunks,rest", [(1, 0), (15, 1), (16, 0), (17, 3), (64, 2)])
 def test_landmarks_at_the_edges_of_a_wavefront(c, chunks, rest):
