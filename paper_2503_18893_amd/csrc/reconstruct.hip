@@ -452,8 +452,11 @@ static void reconstruct_cut(int tiles, long long groups, int slots, int start, i
     }
 }
 
-// Whether B_l in registers pays (r = 128, 256 .. 768).  With two workgroups on a compute unit, ranks up to 256, always (64 to 128
-// sequences of 8 KV heads x 128 tokens are 0 to 5 % slower).  Otherwise nothing goes on beside a workgroup's start, and many short
+// Whether B_l in registers pays (r = 128, 256 .. 768).  With two workgroups on a compute unit, ranks up to 256, one multiplies while the
+// other starts, and it does, but for factors that have one slab tile of 128 tokens each (more than 96, so that little of it is padding)
+// and fill the chip with slab workgroups once: B_l kept / slabs, us, ranks 256, 64 sequences x 8 KV heads x 128 tokens 12.2 / 12.0, 128 of them
+// 20.0 / 18.8, with 97 tokens 19.3 / 17.9, 129 x 4 x 128 16.5 / 14.8; but 56 x 8 x 128, 128 x 8 x 96 and x 129 the same or less, 130 x 8 x 97
+// 22.4 / 22.2; ranks 128, 128 x 8 x 128 14.7 / 14.2, 112 of them 0.99.  Above, nothing goes on beside a workgroup's start, and many short
 // sequences are mostly starts, each with a factor of its own from memory; the slabs' copies are bound by the same bytes there, but
 // go on beside products.  Both times in tiles of 32 tokens x 256 dims (0.35 us per 128 ranks), fitted to 2250 shapes: the slower kernel is
 // taken by 12 % at most, 0.14 % on average.  B_l kept / slabs, us, ranks 768: 64 sequences x 8 KV heads x 128 tokens 27.2 / 21.4, 128 of
@@ -462,9 +465,9 @@ static void reconstruct_cut(int tiles, long long groups, int slots, int start, i
 bool reconstruct_keeps_factor(const xkv_shape &s, int r)
 {
     if (r % 128 != 0 || r > 768) return false;
-    if (r <= 256) return true;
     const int col_groups = (s.H_kv * 128 + kRcDims - 1) / kRcDims, tiles = (s.L + kRkTok - 1) / kRkTok, tok_tiles = (s.L + kRcTok - 1) / kRcTok;
     const long long groups = (long long)s.batch * col_groups;
+    if (r <= 256) return tok_tiles > 1 || tiles < kRcTok / kRkTok || groups < (r == 256 ? 256 : 480) || groups > 512;
     int runs = 1, run_tiles = tiles;
     reconstruct_cut(tiles, groups, 256, 4, &runs, &run_tiles);
     // (rounds of the chip: the last one is done earlier where it is not full)

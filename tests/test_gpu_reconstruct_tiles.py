@@ -44,3 +44,9 @@ KEPT = [(1, 1, 1), (2, 2, 31), (3, 1, 33), (2, 3, 64), (5, 2, 97), (8, 1, 161), 
 def test_factor_in_registers(H_kv, batch, L, r):
     """The ranks whose B_l is kept: 32 tokens a tile, runs of one to many tiles, odd numbers of KV heads, more groups than compute units."""
     test_tiles_against_fp64(H_kv, r, batch, L)
+
+
+@pytest.mark.parametrize("r,batch,L", [(256, 129, 101), (128, 245, 128)])
+def test_one_slab_tile_a_factor(r, batch, L):
+    """Ranks up to 256 whose B_l is not kept: 97 to 128 tokens each of as many factors as fill the chip once."""
+    test_tiles_against_fp64(4, r, batch, L)

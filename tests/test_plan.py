@@ -157,7 +157,9 @@ def test_reconstruction_keeps_the_factor_where_that_is_faster(plan_of):
     line = [  # KV heads, r, batch, L, kept
         (8, 512, 1, 32768, 1), (8, 768, 1, 64, 1), (8, 384, 4, 65536, 1), (8, 768, 64, 128, 0), (8, 512, 200, 128, 0), (8, 384, 200, 96, 0),
         (8, 256, 200, 128, 1), (8, 128, 300, 96, 1), (1, 768, 300, 384, 0), (2, 768, 128, 200, 1), (2, 640, 33, 1000, 1), (8, 768, 33, 384, 0),
-        (1, 640, 300, 20, 1), (8, 768, 16, 4096, 1), (8, 496, 1, 32768, 0), (8, 896, 1, 32768, 0)]
+        (1, 640, 300, 20, 1), (8, 768, 16, 4096, 1), (8, 496, 1, 32768, 0), (8, 896, 1, 32768, 0),
+        (8, 256, 64, 97, 0), (8, 256, 128, 128, 0), (8, 256, 63, 128, 1), (8, 256, 129, 128, 1), (8, 256, 128, 96, 1), (8, 256, 128, 129, 1),
+        (8, 128, 128, 128, 0), (8, 128, 120, 128, 0), (8, 128, 119, 128, 1)]
     shapes = [dict(H_kv=h, H_q=h, r_k=r, L=L, batch=b) for h, r, b, L, _ in line]
     for case, p in zip(line, plan_of(shapes)):
         assert p["factor_kept"] == case[4], case
