@@ -483,7 +483,7 @@ __global__ __launch_bounds__(256) void gram_sum_kernel(const double *__restrict_
 // shift = 1e-13 * max diagonal of the original G (diag0) keeps the factor defined when the r vectors are
 // numerically dependent (an X_cat of rank below r): such directions come out short instead of normalised and
 // contribute nothing to A B.
-// What bounds it: the chain of its 16 launches at r = 512, each of which is workgroup 0: 12 us
+// What bounds it: the chain of its launches, 17 at r = 512, each of which takes as long as its workgroup 0 (the last has none): 12 us
 // in general, 9.3 where r is a multiple of 32: few wavefronts do all the work, so instructions count, and there every row comes in 16-byte
 // runs and without bounds checks; the maximum of the diagonal is found once (11.4 -> 9.3 us).  32 steps on rows of 32 elements with scalar
 // broadcasts of t took 21.5 us per launch (13 of them the steps); 16 + 16 steps 17, with workgroups of 32 whole rows, 25 us in the first
@@ -1431,7 +1431,7 @@ constexpr int kFzChunk = 16;
 
 struct FzLayout {
     int n, Lp, bc, gram_tiles, gram_splits, w_splits, g_splits;
-    size_t esz, xt_seq, part_seq, off_xt, off_part, off_c, off_vt, off_wn, off_g, off_lt, off_planes, off_diag, off_minv,
+    size_t esz, xt_seq, part_seq, off_xt, off_part, off_c, off_vt, off_wn, off_g, off_lt, off_planes, off_diag, off_order,
         off_rot, total;
 };
 
@@ -1489,7 +1489,7 @@ FzLayout fz_layout(const xkv_shape &s, int r)
     f.off_lt = o;     o += align256(bc * r * r * 8);
     f.off_planes = o; o += align256(bc * f.g_splits * r * r * 8);
     f.off_diag = o;   o += align256(bc * r * 8);
-    f.off_minv = o;   o += align256(bc * ((r + 15) / 16) * 256 * 8);
+    f.off_order = o;  o += align256(bc * ((r + 15) / 16) * 256 * 8);
     f.off_rot = o;    o += align256(bc * 16 * 4);
     f.total = o;
     return f;
@@ -1519,7 +1519,7 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
     float *Vt = reinterpret_cast<float *>(ws + f.off_vt), *Wn = reinterpret_cast<float *>(ws + f.off_wn);
     double *Gm = reinterpret_cast<double *>(ws + f.off_g), *Lt = reinterpret_cast<double *>(ws + f.off_lt);
     double *planes = reinterpret_cast<double *>(ws + f.off_planes), *diag0 = reinterpret_cast<double *>(ws + f.off_diag);
-    double *Minv = reinterpret_cast<double *>(ws + f.off_minv);
+    int *order = reinterpret_cast<int *>(ws + f.off_order);
     int *rotations = reinterpret_cast<int *>(ws + f.off_rot);
     static_assert(kJacobiSweeps <= 16, "the rotation counters have 16 slots per sequence");
     static_assert(kCholLds <= 64 * 1024 - 256, "no raised LDS limit needed");
@@ -1604,7 +1604,6 @@ hipError_t factorize_typed(const xkv_shape &s, const FzLayout &f, const void *X,
         // most (r + 31) / 32 pairs, and n^2 / 2 doubles are 1024 for each of n / 32 pairs or more, n a multiple of 64, n >= r
         const long long tj_seq = (long long)n * n / 2;
         double *Tj[2] = {reinterpret_cast<double *>(part), reinterpret_cast<double *>(C)};
-        int *order = reinterpret_cast<int *>(Minv);
         const int gb = (r + 31) / 32;
         hipLaunchKernelGGL(transpose_v_kernel, dim3((n + 31) / 32, gb, nb), dim3(256), 0, st, Vt, part, (long long)f.part_seq, n, r);
         hipLaunchKernelGGL(gram_f64_kernel<false>, dim3((gb * gb + 3) / 4, f.g_splits, nb), dim3(256), 0, st, part,

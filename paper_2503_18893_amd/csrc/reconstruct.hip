@@ -242,6 +242,7 @@ constexpr int rk_stages(int nf) { return nf <= 32 ? 4 : 3; }
 constexpr bool rk_pair(int nf) { return nf <= 16; }  // two workgroups per compute unit
 
 // All but the youngest `left` copies have landed.  (left: even, known once the loop around it is unrolled)
+// (Any access more behind them, a register stored to scratch memory for instance, makes this wait longer, never too short.)
 __device__ __forceinline__ void wait_copies(int left)
 {
     switch (left) {
