@@ -366,9 +366,17 @@ bool rope_keys_ok(const xkv_shape &s) { return s.r_k <= 512 && s.H_q / s.H_kv <=
 // full; there its time varies by 10 % from one card to another, and ranks 512 were 0.91 to 1.09 times as fast in two halves on different ones.)
 // Quantised, 8 x 4096 from 131072 tokens: ranks 256 62.8 / 60.0 in 4 bits, 62.1 / 60.5 in 3, with eight heads 64.7 / 64.2 and 63.2 /
 // 63.3; ranks 512 113.8 / 98.9.  Below: 4 x 4096 in bf16 71 / 74 (ranks 512), 42.5 / 44.4 (256), but 65 / 60 (384).
-bool rope_keys_pays(const xkv_shape &s, const Plan &p)
+// But not bf16 rows of more than 384 and 512 ranks where the one launch is a single round of workgroups with at least 9 of 10 places filled
+// and the rows are few of the tokens, so that the heads share little of what the caches hold, which the second pass over the list
+// feels: 8 x 4096 rows of ranks 512 from 32768 tokens 120 / 115, 65536 123 / 124, 98304 127 / 128, 131072 127 / 130, 196608 126 / 133; eight
+// heads 120 / 118, 125 / 128, 126 / 131, 127 / 133 and 128 / 137; 4 x 8192 from 131072 118 / 118, eight heads 118 / 122; 8 x 5000 149 / 150 and
+// 153 / 156, 8 x 4128 (8 of 10 places) 142 / 136 and 143 / 140; 8 x 4096 of ranks 448 121 / 118.
+bool rope_keys_pays(const xkv_shape &s, const Plan &p, int qbits)
 {
-    return p.absorb && s.r_v <= 512 && p.n_rep <= 8 && (long long)p.rows * s.k >= 1 << 18;
+    if (!p.absorb || s.r_v > 512 || p.n_rep > 8 || (long long)p.rows * s.k < 1 << 18) return false;
+    const long long places = (long long)p.rows * p.sr_splits * p.sr_chunk;
+    const bool one_round = p.rows * p.sr_splits <= 256 && 10LL * p.rows * s.k >= 9 * places;
+    return qbits != 0 || s.r_k <= 384 || s.r_v != 512 || !one_round || (p.n_rep > 4 ? 16LL : 24LL) * s.k > s.L;
 }
 
 hipError_t launch_rope_keys(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *B_packed, int layer,

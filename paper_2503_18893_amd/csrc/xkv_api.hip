@@ -121,8 +121,9 @@ xkv_status make_plan(const xkv_shape &s, Plan &p)
     // Rotated rows: logits first, into the room of the projected queries and the pooled scores, which are done with by then
     const bool room = p.absorb && s.k < (1 << 24) && b * s.H_kv * (size_t)s.k * head_pitch_of(p.n_rep) * sizeof(float) <= off - p.off_p;
     for (int i = 0; i < 3; ++i) {
-        p.rope_kept[i] = room && rope_kept_pays(s, p, i == 0 ? 0 : i == 1 ? 4 : 3);
-        p.rope_regs[i] = room && rope_keys_ok(s) && (p.rope_kept[i] || rope_keys_pays(s, p));
+        const int qbits = i == 0 ? 0 : i == 1 ? 4 : 3;
+        p.rope_kept[i] = room && rope_kept_pays(s, p, qbits);
+        p.rope_regs[i] = room && rope_keys_ok(s) && (p.rope_kept[i] || rope_keys_pays(s, p, qbits));
     }
     p.off_idx = off;
     off = align_up(off + b * s.H_kv * (size_t)s.k * sizeof(int32_t), 256);

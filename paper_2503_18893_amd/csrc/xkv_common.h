@@ -270,7 +270,7 @@ hipError_t launch_gather_absorb(const xkv_shape &s, const Plan &p, const PackArg
                                 bool by_place = false);
 // The logits of rotated rows alone (rope_keys.hip), [batch][H_kv][k][head_pitch].
 bool rope_keys_ok(const xkv_shape &s);
-bool rope_keys_pays(const xkv_shape &s, const Plan &p);
+bool rope_keys_pays(const xkv_shape &s, const Plan &p, int qbits);
 hipError_t launch_rope_keys(const xkv_shape &s, const Plan &p, const PackArgs &pa, const void *A_k, const void *B_packed, int layer,
                             const int32_t *idx, const int32_t *counts, float rope_theta, int qbits, float *logits, hipStream_t st);
 bool gather_attend_mfma_shape_ok(const xkv_shape &s);

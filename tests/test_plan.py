@@ -122,6 +122,12 @@ def test_rotated_rows_whose_logits_come_from_the_factor_in_registers(plan_of):
     shapes = [dict(H_q=8 * n, r_k=rk, r_v=rv, batch=b, k=k, L=16 * k) for n, rk, rv, b, k, _, _, _ in line]
     for case, p in zip(line, plan_of(shapes)):
         assert (p["regs_0"], p["regs_4"], p["regs_3"]) == case[5:], case
+    # bf16 rows of ranks 512 in one full round, few of the tokens: heads, rows, batch, tokens, that kernel
+    few = [(4, 4096, 8, 98303, 1), (4, 4096, 8, 98304, 0), (8, 4096, 8, 65535, 1), (8, 4096, 8, 65536, 0), (4, 4128, 8, 131072, 1),
+           (4, 5000, 8, 131072, 0), (4, 4096, 16, 131072, 1), (4, 4096, 10, 131072, 1), (8, 8192, 4, 131072, 0), (4, 8192, 4, 131072, 1)]
+    for case, p in zip(few, plan_of([dict(H_q=8 * n, r_k=512, r_v=512, batch=b, k=k, L=L) for n, k, b, L, _ in few])):
+        assert (p["regs_0"], p["regs_4"], p["regs_3"]) == (case[4], 1, 1), case
+    assert all(p["regs_0"] for p in plan_of([dict(r_k=rk, r_v=rv, batch=8, k=4096, L=131072) for rk, rv in ((384, 512), (512, 496))]))
     for (bits, _, r_k, *_), p in zip(rope.CASES, plan_of([rope.shape_of(*case) for _, *case in rope.CASES])):
         assert (p[f"regs_{bits}"], p[f"kept_{bits}"] or p[f"regs_{bits}"]) == (int(r_k <= 512), 1), (bits, r_k)
     p = plan_of([{**rope.LAYERS, "k": 1032}])[0]
